@@ -84,7 +84,8 @@ fs_status fs_destroy(fs_ctx *ctx);
  * init_mode and the correspondence-grid shape are fixed at creation). */
 fs_status fs_set_params(fs_ctx *ctx, const fs_params *params);
 
-/* Launch-shape knobs of the solve kernel; results never depend on them.  chunk = lanes a wave draws
+/* Launch-shape knobs of the solve kernel for large batches (small ones, up to about 200,000 pairs, run in kernels that
+ * have no queue and ask lds_grid only); results never depend on them.  chunk = lanes a wave draws
  * from the work cursor at a time (8..4096; every draw is one atomic on a single counter, which serves about
  * 1e8 of them per second, so small chunks make the counter the bottleneck), refill_min = idle SIMD lanes that trigger a refill
  * (1..64; until it is set: 8, 24 for grids of more than 32 MiB, 32 for a grid held in LDS),

@@ -248,6 +248,32 @@ constexpr size_t FS_LDS_GRID_MAX = 60 * 1024;
 constexpr int FS_LDS_BIG_WAVES = 12;
 constexpr size_t FS_LDS_GRID_MAX_BIG = 148 * 1024;
 
+// the counts of converged lanes per grid cell that a solve with slots keeps, cleared; the work cursor is reset on the way
+fs_status clear_solve_counts(fs_ctx *c, int ncell, unsigned drawers, unsigned chunk)
+{
+    const long long ncp = (long long)c->G.P * ncell;
+    if (ncp + 1 >= (1ll << 31)) return fail(c, FS_E_SHAPE, "fs_solve: too many grid cells for d_slot");
+    if (!c->gcount_solve && !dev_alloc(&c->gcount_solve, (size_t)ncp + 1)) return fail(c, FS_E_ALLOC, "fs_solve: out of device memory");
+    k_fill_zero_i32<<<(int)std::min<long long>(grid1d(ncp + 1, 256), 4096), 256, 0, c->stream>>>(ncp + 1, c->gcount_solve, c->cursor, drawers, chunk);
+    return FS_OK;
+}
+
+// Kernels of the solve by the size of a batch (pairs = K * N; all three give the same bits).  What bounds a small batch is
+// max_iters times the latency of a step, and a step is half as long with four lanes per pair (0.45 instead of 1.0 us);
+// what bounds a large one is instruction issue and the vector cache, where one lane per pair and refilled waves win.
+// Measured, kernel us, k_solve_quad / k_solve_once / k_solve_ws, 24 states per point on a 64x64x16 grid: 12 k pairs
+// 43 / 52 / 69; 48 k 47 / 49 / 74; 98 k 77 / 57 / 81; 192 k 111 / 78 / 93; 288 k 148 / 124 / 115.  The lines are where
+// the chip is full: three quad waves per SIMD; all pairs of k_solve_once resident at once (3 waves per SIMD of 64).
+// With voxel-based candidates the share of pairs that have one is not known here (rays 1/7, scans 6/10), k_solve_ws needs
+// its list of them first (five launches) and most quads of a sparse batch end at once: rays, 74 k pairs 26 / 33 / 64,
+// 180 k 33 / 35 / 64; scans, 74 k 43 / 33 / 38, 180 k 65 / 44 / 47, 270 k 85 / 63 / 53.
+enum { SOLVE_QUAD, SOLVE_ONCE, SOLVE_LARGE };
+int solve_kind(const fs_ctx *c, long long pairs, bool candidates)
+{
+    const long long quad = (candidates ? 320 : 192) * (long long)c->n_cus, once = (candidates ? 1152 : 768) * (long long)c->n_cus;
+    return pairs <= quad ? SOLVE_QUAD : (pairs <= once ? SOLVE_ONCE : SOLVE_LARGE);
+}
+
 int lanes_K(const fs_ctx *c) { return c->prm.init_mode == FS_INIT_BONE ? c->desc.n_bones : c->prm.corr_k; }
 
 }  // namespace
@@ -323,7 +349,9 @@ fs_status fs_create(const fs_grid_desc *desc, const fs_params *params, void *hip
             (void)hipGetLastError();
             if (c->lds_big) {       // more dynamic LDS than the default limit of a block: say so for every variant
                 const void *fns[] = {(const void *)k_solve<true, true, FS_LDS_BIG_WAVES>, (const void *)k_solve<true, false, FS_LDS_BIG_WAVES>,
-                                     (const void *)k_solve<false, true, FS_LDS_BIG_WAVES>, (const void *)k_solve<false, false, FS_LDS_BIG_WAVES>};
+                                     (const void *)k_solve<false, true, FS_LDS_BIG_WAVES>, (const void *)k_solve<false, false, FS_LDS_BIG_WAVES>,
+                                     (const void *)k_solve_quad<0, true>, (const void *)k_solve_quad<1, true>, (const void *)k_solve_quad<2, true>,
+                                     (const void *)k_solve_once<0, true>, (const void *)k_solve_once<1, true>, (const void *)k_solve_once<2, true>};
                 for (const void *f : fns)
                     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gb) != hipSuccess) {
                         (void)hipGetLastError();
@@ -564,7 +592,9 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     I.ccnt = ctx->ccnt;
     I.cinit = ctx->cinit;
     const bool with_J = d_Jinv != nullptr || d_slot != nullptr;     // with d_slot alone J~ stays in the result records
-    const size_t need = (size_t)S.total * (with_J ? 4 : 1);
+    const int kind = solve_kind(ctx, S.total, voxel_list);
+    const bool quad = kind == SOLVE_QUAD;
+    const size_t need = kind != SOLVE_LARGE ? (d_slot ? (size_t)S.total * 4 : 0) : (size_t)S.total * (with_J ? 4 : 1);
     if (need > ctx->srec_cap) {
         (void)hipStreamSynchronize(ctx->stream);
         if (ctx->srec) (void)hipFree(ctx->srec);
@@ -574,6 +604,59 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         ctx->srec_cap = need;
     }
     hipStream_t st = ctx->stream;
+    const int ncell = (ctx->G.nx - 1) * (ctx->G.ny - 1) * (ctx->G.nz - 1);
+    if (kind != SOLVE_LARGE) {
+        ctx->slots_N = 0;
+        int *counts = nullptr;
+        if (d_slot) {
+            fs_status cs = clear_solve_counts(ctx, ncell, 0u, 0u);
+            if (cs != FS_OK) return cs;
+            counts = ctx->gcount_solve;
+        }
+        hipEvent_t ev0 = nullptr, ev1 = nullptr;
+        if (ctx->timing && hipEventCreate(&ev0) == hipSuccess && hipEventCreate(&ev1) == hipSuccess) (void)hipEventRecord(ev0, st);
+        // grid in LDS: about one block per CU, as many waves in it as the batch gives it; else blocks of four waves
+        S.ki = d_slot && K >= 8 ? 8 : 1;
+        const int pts = (quad ? QUADS : WAVE) / S.ki;          // points per wave
+        const long long waves = ((N + pts - 1) / pts) * ((K + S.ki - 1) / S.ki);
+        const int most = quad ? 16 : FS_LDS_BIG_WAVES;
+        const int threads = lds ? WAVE * (int)std::min<long long>(most, std::max<long long>(1, (waves + ctx->n_cus - 1) / ctx->n_cus)) : 256;
+        const dim3 qg(grid1d(waves * 64, threads));
+        const int *nonfinite = reinterpret_cast<const int *>(ctx->cursor + CUR_NONFINITE);
+#define FS_LAUNCH_QUAD(IM, L)                                                                                          \
+    do {                                                                                                               \
+        if (quad)                                                                                                      \
+            k_solve_quad<IM, L><<<qg, threads, (L) ? grid_bytes : 0, st>>>(                                            \
+                ctx->G, S, I, ctx->T, d_xq, d_pose, d_x0, d_Jinv0, d_valid0, d_xc, d_conv, d_Jinv, d_iters, d_slot,    \
+                d_slot ? ctx->srec : nullptr, counts, ncell);                                                          \
+        else                                                                                                           \
+            k_solve_once<IM, L><<<qg, threads, (L) ? grid_bytes : 0, st>>>(                                            \
+                ctx->G, S, I, ctx->T, d_xq, d_pose, d_x0, d_Jinv0, d_valid0, d_xc, d_conv, d_Jinv, d_iters, d_slot,    \
+                d_slot ? ctx->srec : nullptr, counts, ncell, nonfinite, ctx->pre_serial);                              \
+    } while (0)
+        const int im = !fused ? 2 : (voxel_list ? 1 : 0);
+        if (lds) {
+            if (im == 0) FS_LAUNCH_QUAD(0, true);
+            else if (im == 1) FS_LAUNCH_QUAD(1, true);
+            else FS_LAUNCH_QUAD(2, true);
+        } else {
+            if (im == 0) FS_LAUNCH_QUAD(0, false);
+            else if (im == 1) FS_LAUNCH_QUAD(1, false);
+            else FS_LAUNCH_QUAD(2, false);
+        }
+#undef FS_LAUNCH_QUAD
+        if (ev0 && ev1) {
+            (void)hipEventRecord(ev1, st);
+            ctx->timed->emplace_back(ev0, ev1);
+        }
+        fs_status qs = launch_status(ctx, "fs_solve");
+        if (qs == FS_OK && d_slot) {
+            ctx->slots_N = N;
+            ctx->slots_K = K;
+            ctx->slots_list = false;
+        }
+        return qs;
+    }
     const int2 *list = nullptr;
     const int *list_len = nullptr;
     S.xcd_ranges = 0;
@@ -620,17 +703,14 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         }
         list = ctx->vlist;
     }
-    const int ncell = (ctx->G.nx - 1) * (ctx->G.ny - 1) * (ctx->G.nz - 1);
     int *cell_count = nullptr;
     ctx->slots_N = 0;
     // every wave that draws chunks (all four of a k_solve block, the producer of a k_solve_ws block) owns the
     // chunk of its own number to begin with; the shared cursor starts behind those
     const unsigned drawers = (unsigned)(blocks * wpb);
     if (d_slot) {
-        const long long ncp = (long long)ctx->G.P * ncell;
-        if (ncp + 1 >= (1ll << 31)) return fail(ctx, FS_E_SHAPE, "fs_solve: too many grid cells for d_slot");
-        if (!ctx->gcount_solve && !dev_alloc(&ctx->gcount_solve, (size_t)ncp + 1)) return fail(ctx, FS_E_ALLOC, "fs_solve: out of device memory");
-        k_fill_zero_i32<<<(int)std::min<long long>(grid1d(ncp + 1, 256), 4096), 256, 0, st>>>(ncp + 1, ctx->gcount_solve, ctx->cursor, drawers, (unsigned)S.chunk);
+        fs_status cs = clear_solve_counts(ctx, ncell, drawers, (unsigned)S.chunk);
+        if (cs != FS_OK) return cs;
         cell_count = ctx->gcount_solve;
     } else {
         k_reset_cursor<<<1, 64, 0, st>>>(ctx->cursor, drawers, (unsigned)S.chunk);

@@ -597,6 +597,7 @@ struct SolveP {
     float tol2, div2;
     int K;
     int point_major;     // order in which pairs are handed out
+    int ki;              // kernels of small batches: initial states per wave (pair_of)
     int spin_limit;      // producer / consumer kernel: polls of a work queue before a wave gives up
     int xcd_ranges;      // producer / consumer kernel: the list is cut into 8 ranges, one per XCD, each with its own cursor
     int prefetch;        // producer / consumer kernel: consumers ask for the next cell's records at the end of a pass
@@ -786,6 +787,36 @@ __global__ void k_reset_cursor(unsigned *__restrict__ cursor, unsigned nblocks, 
     if (blockIdx.x == 0) reset_cursors(cursor, (int)threadIdx.x, nblocks, chunk);
 }
 
+// One position in its cell's list for every lane with `want` (wave-wide call; cell: pose * ncell + grid cell): the lanes of
+// the wave that name the same cell are counted together and one of them adds the group to the cell's counter.  The
+// answer is used by group_position(), so that several requests can be on their way before the first wait.
+struct CellGroup {
+    int leader, rank, base;
+};
+__device__ __forceinline__ CellGroup group_request(bool want, int cell, int lane, int *__restrict__ cell_count)
+{
+    CellGroup g;
+    g.leader = lane;
+    g.rank = 0;
+    int members = 1;
+    unsigned long long todo = __ballot(want);
+    while (todo) {
+        const int first = __ffsll((long long)todo) - 1;
+        const int key = __builtin_amdgcn_readlane(cell, first);
+        const unsigned long long same = __ballot(want && cell == key);
+        if (want && cell == key) {
+            g.leader = first;
+            g.rank = __popcll(same & ((1ull << lane) - 1ull));
+            members = __popcll(same);
+        }
+        todo &= ~same;
+    }
+    g.base = 0;
+    if (want && g.leader == lane) g.base = atomicAdd(cell_count + cell, members);
+    return g;
+}
+__device__ __forceinline__ int group_position(const CellGroup &g) { return __shfl(g.base, g.leader) + g.rank; }
+
 // The parked requests of one wave: entry i = {cell, pair}, one per SIMD lane.  Lanes of one point that reach
 // the same root are neighbours in the wave and finish within a few passes of each other, so many entries name
 // the same cell: those are counted together and one lane adds the group to the cell's counter.
@@ -799,38 +830,227 @@ __device__ __forceinline__ void flush_slots(int (&pend)[2][PEND], int npend, int
     __builtin_amdgcn_wave_barrier();
     // two rounds of 64 entries; the atomics of both are on their way before either answer is used
     bool valid[2];
-    int pq[2], leader[2], rank[2], base[2];
+    int pq[2];
+    CellGroup g[2];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         valid[b] = 64 * b + lane < npend;
         const int c = valid[b] ? pend[0][64 * b + lane] : -1;
         pq[b] = valid[b] ? pend[1][64 * b + lane] : 0;
-        int members = 1;
-        leader[b] = lane;
-        rank[b] = 0;
-        unsigned long long todo = __ballot(valid[b]);
-        while (todo) {
-            const int first = __ffsll((long long)todo) - 1;
-            const int key = __builtin_amdgcn_readlane(c, first);
-            const unsigned long long same = __ballot(valid[b] && c == key);
-            if (valid[b] && c == key) {
-                leader[b] = first;
-                rank[b] = __popcll(same & ((1ull << lane) - 1ull));
-                members = __popcll(same);
-            }
-            todo &= ~same;
-        }
-        base[b] = 0;
-        if (valid[b] && leader[b] == lane) base[b] = atomicAdd(cell_count + c, members);
+        g[b] = group_request(valid[b], c, lane, cell_count);
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-        const int bs = __shfl(base[b], leader[b]);
+        const int at = group_position(g[b]);
         // into the pair's own result record (written a few passes ago, still in the L2), not into an array of its own
-        if (valid[b]) reinterpret_cast<int *>(rec)[(long long)pq[b] * 16 + REC_POS] = bs + rank[b];
+        if (valid[b]) reinterpret_cast<int *>(rec)[(long long)pq[b] * 16 + REC_POS] = at;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // before the entries are overwritten
     __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ void park_slots(bool want_slot, int slot_cell, int pair, int (&pend)[2][PEND], int &npend, int lane,
+                                           int *__restrict__ cell_count, float4 *__restrict__ rec)
+{
+    const unsigned long long m = __ballot(want_slot);
+    if (m) {
+        if (npend + __popcll(m) > PEND) {
+            flush_slots(pend, npend, lane, cell_count, rec);
+            npend = 0;
+        }
+        if (want_slot) {
+            const int at = npend + __popcll(m & ((1ull << lane) - 1ull));
+            pend[0][at] = slot_cell;
+            pend[1][at] = pair;
+        }
+        npend += __popcll(m);
+    }
+    if (npend >= PEND_SEND) {
+        flush_slots(pend, npend, lane, cell_count, rec);
+        npend = 0;
+    }
+}
+
+// ---- four SIMD lanes per pair ---------------------------------------------------------------------------------------
+// A pair whose trajectory is long is bound by the latency of a step: a chain of cell lookup, 8 corner records, blend,
+// rank-one update.  With one lane per pair a step costs the wave some 320 vector instructions and 24 gathered loads
+// whoever else is active.  Here the four lanes of a quad work on one pair: lane r = 0, 1, 2 looks up axis r, fetches row r
+// of every corner record (8 loads of 16 bytes; the three lanes read 48 contiguous bytes) and blends that row; the rest of
+// the state is kept by all four lanes alike and costs what it costs one lane.  Lane 3 repeats lane 2.  The operations
+// on every number, and their order, are those of one lane per pair, so the results are the same bits.
+template <int R>
+__device__ __forceinline__ float quad_get(float v)      // the value of lane R of the quad
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), R * 0x55, 0xf, 0xf, true));
+}
+template <int R>
+__device__ __forceinline__ int quad_get(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, R * 0x55, 0xf, 0xf, true);
+}
+__device__ __forceinline__ float pick3(int row, float a, float b, float c) { return row == 0 ? a : (row == 1 ? b : c); }
+
+// what a lane needs to look its axis up
+struct QuadAxis {
+    float lo, inv_h, m;
+    int n, stride, row;
+};
+__device__ __forceinline__ QuadAxis quad_axis(const GridP &G)
+{
+    QuadAxis A;
+    A.row = min((int)(threadIdx.x & 3), 2);
+    A.lo = pick3(A.row, G.lo[0], G.lo[1], G.lo[2]);
+    A.inv_h = pick3(A.row, G.inv_h[0], G.inv_h[1], G.inv_h[2]);
+    A.m = pick3(A.row, G.m[0], G.m[1], G.m[2]);
+    A.n = A.row == 0 ? G.nx : (A.row == 1 ? G.ny : G.nz);
+    A.stride = A.row == 0 ? G.sx : (A.row == 1 ? G.sy : 12);
+    return A;
+}
+
+// the cell of x, every lane of the quad holding the whole x: base and fractions (ci and cl are not set)
+__device__ __forceinline__ Cell quad_locate(const QuadAxis &A, const float x[3])
+{
+    Cell c;
+    int i0;
+    float f;
+    bool cl;
+    locate_axis(pick3(A.row, x[0], x[1], x[2]), A.lo, A.inv_h, A.m, A.n, i0, f, cl);
+    const int b = i0 * A.stride;
+    c.base = quad_get<0>(b) + quad_get<1>(b) + quad_get<2>(b);
+    c.f[0] = quad_get<0>(f);
+    c.f[1] = quad_get<1>(f);
+    c.f[2] = quad_get<2>(f);
+    return c;
+}
+
+// the lane's row of the 8 corner records
+__device__ __forceinline__ void quad_load(const float *__restrict__ Tcell, const GridP &G, int row, float (&q)[8][4])
+{
+    const float *t = Tcell + row * 4;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int c = (i >> 1) + 4 * (i & 1);        // the two z-neighbours of an (x, y) corner one after the other
+        const float4 v = *reinterpret_cast<const float4 *>(t + corner_off(G, c));
+        q[c][0] = v.x; q[c][1] = v.y; q[c][2] = v.z; q[c][3] = v.w;
+    }
+}
+
+// row r of the blended transform applied to x (blend_apply, one row)
+__device__ __forceinline__ float quad_apply(const float (&T)[4], const float x[3])
+{
+    return FS_FMA(T[0], x[0], FS_FMA(T[1], x[1], FS_FMA(T[2], x[2], T[3])));
+}
+__device__ __forceinline__ void quad_blend(const float (&om)[8], const float (&q)[8][4], float (&T)[4])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) T[e] = om[0] * q[0][e];
+#pragma unroll
+    for (int k = 1; k < 8; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) T[e] = FS_FMA(om[k], q[k][e], T[e]);
+}
+
+// One Broyden step of the pair of every active quad.  x, g, J: its state, xpr: x' along the lane's axis, it: steps taken;
+// q, held: the lane's row of the corner records and the base of the cell they belong to (-1: none).  Returns bit 0: the
+// pair has ended, bit 1: it has converged.
+__device__ __forceinline__ int quad_step(const GridP &G, const QuadAxis &A, float tol2, float div2, int max_iters,
+                                         const float *__restrict__ Tp, float xpr, float (&x)[3], float (&g)[3], float (&J)[9],
+                                         int &it, float (&q)[8][4], int &held)
+{
+    float dx[3], gn[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
+        x[r] = x[r] + dx[r];
+    }
+    const Cell cell = quad_locate(A, x);
+    if (cell.base != held) {
+        quad_load(Tp + cell.base, G, A.row, q);
+        held = cell.base;
+    }
+    float om[8], T[4];
+    corner_weights(cell, om);
+    quad_blend(om, q, T);
+    const float gr = quad_apply(T, x) - xpr;
+    gn[0] = quad_get<0>(gr);
+    gn[1] = quad_get<1>(gr);
+    gn[2] = quad_get<2>(gr);
+    float dg[3], v[3], u[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) dg[r] = gn[r] - g[r];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[c] = FS_FMA(dx[2], J[6 + c], FS_FMA(dx[1], J[3 + c], dx[0] * J[c]));
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        u[r] = dx[r] - FS_FMA(J[r * 3 + 2], dg[2], FS_FMA(J[r * 3 + 1], dg[1], J[r * 3] * dg[0]));
+    const float den = FS_FMA(v[2], dg[2], FS_FMA(v[1], dg[1], v[0] * dg[0]));
+    if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
+        const float rinv = 1.0f / den;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const float sc = u[r] * rinv;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) J[r * 3 + c] = FS_FMA(sc, v[c], J[r * 3 + c]);
+        }
+    }
+    ++it;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) g[r] = gn[r];
+    const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
+    const bool conv = r2 < tol2;
+    return ((conv || !(r2 < div2) || it >= max_iters) ? 1 : 0) | (conv ? 2 : 0);
+}
+
+// A wave whose last QUAD_LANES pairs (or fewer) are all that is left for it hands them from single lanes to quads: quad j
+// takes the pair of the j-th active lane.  Returns the lane to take from, and whether the quad gets a pair.
+constexpr int QUADS = 16;
+__device__ __forceinline__ int quad_source(unsigned long long active, int lane, bool &gets)
+{
+    int src = 0;
+    gets = false;
+    for (int j = 0; active; ++j, active &= active - 1ull) {      // wave-uniform
+        const int b = __ffsll((long long)active) - 1;
+        if ((lane >> 2) == j) {
+            src = b;
+            gets = true;
+        }
+    }
+    return src;
+}
+
+// Steps of the wave's last pairs (at most QUADS active lanes, none of them fresh) in quads until all have ended; then
+// emit(ends, conv, x, J, it, n, k, p), one wave-wide call with `ends` in one lane of every quad that had a pair.
+template <class Emit>
+__device__ __forceinline__ void quad_tail(const GridP &G, const SolveP &S, const float *__restrict__ T, bool active, int lane,
+                                          const float (&xp)[3], float (&x)[3], float (&g)[3], float (&J)[9], int it, int n, int k,
+                                          int pz, Emit emit)
+{
+    const unsigned long long m = __ballot(active);
+    if (m == 0) return;
+    bool on;
+    const int src = quad_source(m, lane, on);
+    const QuadAxis A = quad_axis(G);
+    const float xpr = pick3(A.row, __shfl(xp[0], src), __shfl(xp[1], src), __shfl(xp[2], src));
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        x[r] = __shfl(x[r], src);
+        g[r] = __shfl(g[r], src);
+    }
+#pragma unroll
+    for (int e = 0; e < 9; ++e) J[e] = __shfl(J[e], src);
+    it = __shfl(it, src);
+    n = __shfl(n, src);
+    k = __shfl(k, src);
+    pz = __shfl(pz, src);
+    const float *Tp = T + (long long)pz * G.V * 12;
+    int end = 0;
+    if (on) {
+        float q[8][4];
+        int held = -1;
+        do end = quad_step(G, A, S.tol2, S.div2, S.max_iters, Tp, xpr, x, g, J, it, q, held);
+        while (!(end & 1));
+    }
+    emit(on && (lane & 3) == 0, (end & 2) != 0, x, J, it, n, k, pz);
 }
 
 // Broyden solve for a transform grid (all poses) small enough to be held in LDS: every block copies it there
@@ -981,10 +1201,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
             idle = __ballot(!active);
             nidle = __popcll(idle);
         }
-        if (!__any(active)) {
-            if (exhausted) break;
-            continue;
-        }
+        if (exhausted && 64 - nidle <= QUADS && !__any(active && fresh)) break;
+        if (nidle == 64) continue;
         bool want_slot = false;
         int slot_cell = 0;
         if (active) {
@@ -1046,26 +1264,19 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
         // For the backward every converged lane needs its arrival position in the list of its grid cell: one
         // returning atomic on the cell's counter.  A wave would wait for that answer in every pass (a few of
         // its lanes finish in each), so the requests are parked in LDS and sent 112 or more at a time, one per cell and round of 64.
-        if (WITH_J && cell_count) {
-            const unsigned long long m = __ballot(want_slot);
-            if (m) {
-                if (npend + __popcll(m) > PEND) {
-                    flush_slots(s_pend[wib], npend, lane, cell_count, rec);
-                    npend = 0;
-                }
-                if (want_slot) {
-                    const int at = npend + __popcll(m & ((1ull << lane) - 1ull));
-                    s_pend[wib][0][at] = slot_cell;
-                    s_pend[wib][1][at] = (int)((long long)k * N + n);
-                }
-                npend += __popcll(m);
-            }
-            if (npend >= PEND_SEND) {
-                flush_slots(s_pend[wib], npend, lane, cell_count, rec);
-                npend = 0;
-            }
-        }
+        if (WITH_J && cell_count) park_slots(want_slot, slot_cell, (int)((long long)k * N + n), s_pend[wib], npend, lane, cell_count, rec);
     }
+    // the wave's last pairs, four lanes each
+    quad_tail(G, S, T, active, lane, xp, x, g, J, it, (int)n, k, pz,
+              [&](bool ends, bool conv, const float (&xe)[3], const float (&Je)[9], int ite, int ne, int ke, int pe) {
+                  int cell = 0;
+                  if (ends) {
+                      write_record<WITH_J>(rec, (long long)ke * N + ne, xe, Je, (conv ? 1 : 0) | (ite << 8));
+                      if (WITH_J && cell_count && conv) cell = pe * ncell + cell_linear(G, locate(G, xe));
+                  }
+                  if (WITH_J && cell_count)
+                      park_slots(ends && conv, cell, (int)((long long)ke * N + ne), s_pend[wib], npend, lane, cell_count, rec);
+              });
     if (WITH_J && cell_count && npend > 0) flush_slots(s_pend[wib], npend, lane, cell_count, rec);
 }
 
@@ -1088,7 +1299,7 @@ constexpr int FS_WS_CONSUMERS = 3;           // measured: a producer that comput
 // only compete for the vector cache: measured on the multi-pose / training / ray batches, kernel ms with 2 blocks per
 // CU: 3 consumers 1.73 / 0.175 / 0.120, 4 consumers 1.87 / 0.196 / 0.124, 5 consumers 1.92 / 0.213 / 0.138.
 constexpr int FS_VX_CONSUMERS = 3;
-constexpr int ST_XP = 0, ST_X = 3, ST_G = 6, ST_DX = 9, ST_J = 12, ST_N = 21, ST_K = 22, ST_P = 23, ST_FIELDS = 24;
+constexpr int ST_XP = 0, ST_X = 3, ST_G = 6, ST_J = 9, ST_N = 18, ST_K = 19, ST_P = 20, ST_FIELDS = 21;
 
 __device__ __forceinline__ int lds_load_acquire(const int *p)
 {
@@ -1097,28 +1308,6 @@ __device__ __forceinline__ int lds_load_acquire(const int *p)
 __device__ __forceinline__ void lds_store_release(int *p, int v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-__device__ __forceinline__ void park_slots(bool want_slot, int slot_cell, int pair, int (&pend)[2][PEND], int &npend, int lane,
-                                           int *__restrict__ cell_count, float4 *__restrict__ rec)
-{
-    const unsigned long long m = __ballot(want_slot);
-    if (m) {
-        if (npend + __popcll(m) > PEND) {
-            flush_slots(pend, npend, lane, cell_count, rec);
-            npend = 0;
-        }
-        if (want_slot) {
-            const int at = npend + __popcll(m & ((1ull << lane) - 1ull));
-            pend[0][at] = slot_cell;
-            pend[1][at] = pair;
-        }
-        npend += __popcll(m);
-    }
-    if (npend >= PEND_SEND) {
-        flush_slots(pend, npend, lane, cell_count, rec);
-        npend = 0;
-    }
 }
 
 // ---- result records of k_solve_ws leave through LDS ---------------------------------------------------------------
@@ -1131,7 +1320,7 @@ __device__ __forceinline__ void park_slots(bool want_slot, int slot_cell, int pa
 constexpr int OUT_PEND = 128, OUT_SEND = 112;
 struct OutQ {
     float4 rec[OUT_PEND][4];
-    int cell[OUT_PEND];      // grid cell (pose * ncell + cell) of a converged lane that wants a position, else -1
+    int cell[OUT_PEND];       // grid cell (pose * ncell + cell) of a converged lane that wants a position, else -1
     int pair[OUT_PEND];
 };
 
@@ -1142,33 +1331,17 @@ __device__ __forceinline__ void out_flush(OutQ &q, int npend, int lane, int *__r
     if (cell_count) {
         // two rounds of 64 entries; the atomics of both are on their way before either answer is used
         bool valid[2];
-        int leader[2], rank[2], base[2];
+        CellGroup g[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             const int c = 64 * b + lane < npend ? q.cell[64 * b + lane] : -1;
             valid[b] = c >= 0;
-            int members = 1;
-            leader[b] = lane;
-            rank[b] = 0;
-            unsigned long long todo = __ballot(valid[b]);
-            while (todo) {
-                const int first = __ffsll((long long)todo) - 1;
-                const int key = __builtin_amdgcn_readlane(c, first);
-                const unsigned long long same = __ballot(valid[b] && c == key);
-                if (valid[b] && c == key) {
-                    leader[b] = first;
-                    rank[b] = __popcll(same & ((1ull << lane) - 1ull));
-                    members = __popcll(same);
-                }
-                todo &= ~same;
-            }
-            base[b] = 0;
-            if (valid[b] && leader[b] == lane) base[b] = atomicAdd(cell_count + c, members);
+            g[b] = group_request(valid[b], c, lane, cell_count);
         }
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const int bs = __shfl(base[b], leader[b]);
-            if (valid[b]) reinterpret_cast<int *>(&q.rec[64 * b + lane][1])[0] = bs + rank[b];
+            const int at = group_position(g[b]);
+            if (valid[b]) reinterpret_cast<int *>(&q.rec[64 * b + lane][1])[0] = at;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1276,6 +1449,74 @@ __device__ __forceinline__ bool blend_apply_z(const Cell &c, const float (&q)[8]
     return m == 0.0f;
 }
 
+// One Broyden step of one pair per lane: the field at xt, the update of J~, the test, and if the pair goes on, the next
+// step.  q, held, held_mask: the corner records the lane holds, their cell's base inside the pose's grid (-1: none) and
+// with SKIP which of them.  cell: of the new x.  Returns bit 0: the pair has ended, bit 1: it has converged.
+template <bool SKIP>
+__device__ __forceinline__ int lane_step(const GridP &G, const SolveP &S, const float *__restrict__ Tp, bool may_skip,
+                                         const float (&xp)[3], float (&x)[3], float (&xt)[3], float (&dx)[3], float (&g)[3],
+                                         float (&J)[9], int &it, float (&q)[8][12], int &held, int &held_mask, Cell &cell)
+{
+    float d[3], gn[3];
+    // steps shrink as a lane converges, so it often stays in the cell it was in: the records are fetched again only when
+    // the cell changed
+    cell = locate(G, xt);
+    if (SKIP) {
+        const int need = may_skip ? corners_needed(cell) : 0xFF;
+        if (cell.base != held) {
+            held = cell.base;
+            held_mask = 0;
+        }
+        if (need & ~held_mask) {
+            load_corners(Tp + cell.base, G, need & ~held_mask, q);
+            held_mask |= need;
+        }
+        if (blend_apply_z(cell, q, xt, d) && held_mask != 0xFF) {
+            load_corners(Tp + cell.base, G, 0xFF & ~held_mask, q);
+            held_mask = 0xFF;
+            blend_apply(cell, q, xt, d);
+        }
+    } else {
+        if (cell.base != held) {
+            load_cell(Tp + cell.base, G, q);
+            held = cell.base;
+        }
+        blend_apply(cell, q, xt, d);
+    }
+#pragma unroll
+    for (int r = 0; r < 3; ++r) gn[r] = d[r] - xp[r];
+    float dg[3], v[3], u[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) dg[r] = gn[r] - g[r];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[c] = FS_FMA(dx[2], J[6 + c], FS_FMA(dx[1], J[3 + c], dx[0] * J[c]));
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        u[r] = dx[r] - FS_FMA(J[r * 3 + 2], dg[2], FS_FMA(J[r * 3 + 1], dg[1], J[r * 3] * dg[0]));
+    const float den = FS_FMA(v[2], dg[2], FS_FMA(v[1], dg[1], v[0] * dg[0]));
+    if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
+        const float rinv = 1.0f / den;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const float sc = u[r] * rinv;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) J[r * 3 + c] = FS_FMA(sc, v[c], J[r * 3 + c]);
+        }
+    }
+    ++it;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) { x[r] = xt[r]; g[r] = gn[r]; }
+    const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
+    const bool conv = r2 < S.tol2;
+    if (conv || !(r2 < S.div2) || it >= S.max_iters) return conv ? 3 : 1;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
+        xt[r] = x[r] + dx[r];
+    }
+    return 0;
+}
+
 template <bool FUSED, bool WITH_J, int NCONS, bool SKIP>
 __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, SolveP S, InitP I, const float *__restrict__ T,
                                                const float *__restrict__ xq, const int32_t *__restrict__ pose,
@@ -1366,7 +1607,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
             bool keep = false, want_out = false;
             int out_cell = -1, out_flags = 0, pair = 0;
             int nn = 0, nk = 0, np = 0;
-            float nxp[3] = {0, 0, 0}, nx[3] = {0, 0, 0}, ng[3] = {0, 0, 0}, ndx[3] = {0, 0, 0};
+            float nxp[3] = {0, 0, 0}, nx[3] = {0, 0, 0}, ng[3] = {0, 0, 0};
             float nJ[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
             if (pq < c1) {
                 const unsigned upq = (unsigned)pq;        // K * N < 2^31
@@ -1478,9 +1719,6 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                         }
                     } else {
                         keep = true;
-#pragma unroll
-                        for (int r = 0; r < 3; ++r)
-                            ndx[r] = -FS_FMA(nJ[r * 3 + 2], ng[2], FS_FMA(nJ[r * 3 + 1], ng[1], nJ[r * 3] * ng[0]));
                     }
                 }
                 if (!ok && !norec) {
@@ -1516,7 +1754,6 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                         ring[ST_XP + r][at] = nxp[r];
                         ring[ST_X + r][at] = nx[r];
                         ring[ST_G + r][at] = ng[r];
-                        ring[ST_DX + r][at] = ndx[r];
                     }
 #pragma unroll
                     for (int e = 0; e < 9; ++e) ring[ST_J + e][at] = nJ[e];
@@ -1542,13 +1779,24 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
 
     // ---------------------------------------------------- consumer ----------------------------------------------------
     float (&ring)[ST_FIELDS][WS_RING] = s_ring[wib];
+    // what becomes of a pair that has ended in a quad (wave-wide call; `ends` in one lane of the quad)
+    auto emit = [&](bool ends, bool conv, const float (&xe)[3], const float (&Je)[9], int ite, int ne, int ke, int pe) {
+        const int flags = (conv ? 1 : 0) | (ite << 8), pair = (int)((long long)ke * N + ne);
+        if (WITH_J) {
+            int cell = -1;
+            if (ends && cell_count && conv) cell = pe * ncell + cell_linear(G, locate(G, xe));
+            out_park(ends, xe, Je, flags, cell, pair, outq, npend, lane, cell_count, rec);
+        } else if (ends) {
+            write_record<false>(rec, pair, xe, Je, flags);
+        }
+    };
     bool active = false;
     int n = 0, k = 0, it = 0, pz = 0, head = 0;
     const float *Tp = T;
     float xp[3] = {0, 0, 0}, x[3] = {0, 0, 0}, xt[3] = {0, 0, 0}, g[3] = {0, 0, 0}, dx[3] = {0, 0, 0};
     float J[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     float q[8][12];                  // corner records of the lane's current cell, kept across iterations
-    long long held = -1;             // grid offset of the cell whose corners q holds (-1: none)
+    int held = -1;                   // base of the cell whose corners q holds (-1: none)
     int held_mask = 0;               // SKIP: which of them
     // SKIP needs a grid of finite entries (k_precompute says if this one is not)
     const bool may_skip = SKIP && __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
@@ -1558,13 +1806,17 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
 #pragma unroll
             for (int e = 0; e < 12; ++e) q[c][e] = 0.0f;
     }
-    bool run = true;                 // wave-uniform
-    while (run) {
+    bool fin = false;                // wave-uniform: the producer has left and the queue is empty
+    while (true) {
         const unsigned long long idle = __ballot(!active);
         const int nidle = __popcll(idle);
-        if (nidle >= S.refill_min) {
+        if (fin && 64 - nidle <= QUADS) break;
+        if (nidle >= S.refill_min && !fin) {
+            // s_done is read before the tail: the producer raises it last
+            const int d = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_done));
             const int tail = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_tail[wib]));
             const int avail = tail - head;
+            fin = d && avail <= nidle;
             if (avail > 0) {
                 const int rank = __popcll(idle & ((1ull << lane) - 1ull));
                 if (!active && rank < avail) {
@@ -1574,7 +1826,6 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                         xp[r] = ring[ST_XP + r][e];
                         x[r] = ring[ST_X + r][e];
                         g[r] = ring[ST_G + r][e];
-                        dx[r] = ring[ST_DX + r][e];
                     }
 #pragma unroll
                     for (int c = 0; c < 9; ++c) J[c] = ring[ST_J + c][e];
@@ -1582,7 +1833,10 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                     k = __float_as_int(ring[ST_K][e]);
                     pz = __float_as_int(ring[ST_P][e]);
 #pragma unroll
-                    for (int r = 0; r < 3; ++r) xt[r] = x[r] + dx[r];
+                    for (int r = 0; r < 3; ++r) {
+                        dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
+                        xt[r] = x[r] + dx[r];
+                    }
                     Tp = T + (long long)pz * G.V * 12;
                     it = 0;
                     held = -1;
@@ -1594,103 +1848,359 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                 if (lane == 0) lds_store_release(&s_head[wib], head);
             }
         }
-        if (!__any(active)) {
-            // nothing in flight: more to come?  (s_done is read before the tail: the producer raises it last)
-            const int d = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_done));
-            const int tail = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_tail[wib]));
-            // a consumer waits for nothing but its own block's producer, whose waits are all bounded and which
-            // raises s_done on every way out: this loop ends when the producer has
-            if (tail == head) {
-                if (d) run = false;
-                else __builtin_amdgcn_s_sleep(8);
-            }
-        }
+        // a consumer waits for nothing but its own block's producer, whose waits are all bounded and which raises
+        // s_done on every way out: this loop ends when the producer has
+        if (!__any(active) && !fin) __builtin_amdgcn_s_sleep(8);
         bool want_out = false;
         int out_cell = -1, out_flags = 0;
         if (active) {
-            float d[3], gn[3];
-            const Cell cell = locate(G, xt);
-            const long long want = (long long)(Tp - T) + cell.base;
-            if (SKIP) {
-                const int need = may_skip ? corners_needed(cell) : 0xFF;
-                if (want != held) {
-                    held = want;
-                    held_mask = 0;
-                }
-                if (need & ~held_mask) {
-                    load_corners(Tp + cell.base, G, need & ~held_mask, q);
-                    held_mask |= need;
-                }
-                if (blend_apply_z(cell, q, xt, d) && held_mask != 0xFF) {
-                    load_corners(Tp + cell.base, G, 0xFF & ~held_mask, q);
-                    held_mask = 0xFF;
-                    blend_apply(cell, q, xt, d);
-                }
-            } else {
-                if (want != held) {
-                    load_cell(Tp + cell.base, G, q);
-                    held = want;
-                }
-                blend_apply(cell, q, xt, d);
-            }
-#pragma unroll
-            for (int r = 0; r < 3; ++r) gn[r] = d[r] - xp[r];
-            float dg[3], v[3], u[3];
-#pragma unroll
-            for (int r = 0; r < 3; ++r) dg[r] = gn[r] - g[r];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) v[c] = FS_FMA(dx[2], J[6 + c], FS_FMA(dx[1], J[3 + c], dx[0] * J[c]));
-#pragma unroll
-            for (int r = 0; r < 3; ++r)
-                u[r] = dx[r] - FS_FMA(J[r * 3 + 2], dg[2], FS_FMA(J[r * 3 + 1], dg[1], J[r * 3] * dg[0]));
-            const float den = FS_FMA(v[2], dg[2], FS_FMA(v[1], dg[1], v[0] * dg[0]));
-            if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
-                const float rinv = 1.0f / den;
-#pragma unroll
-                for (int r = 0; r < 3; ++r) {
-                    const float sc = u[r] * rinv;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) J[r * 3 + c] = FS_FMA(sc, v[c], J[r * 3 + c]);
-                }
-            }
-            ++it;
-#pragma unroll
-            for (int r = 0; r < 3; ++r) { x[r] = xt[r]; g[r] = gn[r]; }
-            const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
-            const bool conv = r2 < S.tol2;
-            const bool done = conv || !(r2 < S.div2) || it >= S.max_iters;
-            if (done) {
+            Cell cell;
+            const int end = lane_step<SKIP>(G, S, Tp, may_skip, xp, x, xt, dx, g, J, it, q, held, held_mask, cell);
+            if (end & 1) {
                 if (WITH_J) {
                     want_out = true;
-                    out_flags = (conv ? 1 : 0) | (it << 8);
-                    if (cell_count && conv) out_cell = pz * ncell + cell_linear(G, cell);
+                    out_flags = (end >> 1) | (it << 8);
+                    if (cell_count && (end & 2)) out_cell = pz * ncell + cell_linear(G, cell);
                 } else {
-                    write_record<false>(rec, (long long)k * N + n, x, J, (conv ? 1 : 0) | (it << 8));
+                    write_record<false>(rec, (long long)k * N + n, x, J, (end >> 1) | (it << 8));
                 }
                 active = false;
-            } else {
-#pragma unroll
-                for (int r = 0; r < 3; ++r) {
-                    dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
-                    xt[r] = x[r] + dx[r];
-                }
-                if (!SKIP && S.prefetch) {
-                    // the corner records the next pass will need are asked for now: they travel while this pass parks
-                    // its results and the next one looks for work (q is free: its records went into d above).  On the
-                    // 8-pose grid, whose records come from beyond the L2: 1.34 -> 1.32 ms; on a grid the L2 holds the
-                    // second cell lookup costs more than the head start gains (0.172 -> 0.186 ms), hence the switch
-                    const Cell cn = locate(G, xt);
-                    const long long wn = (long long)(Tp - T) + cn.base;
-                    if (wn != held) {
-                        load_cell(Tp + cn.base, G, q);
-                        held = wn;
-                    }
+            } else if (!SKIP && S.prefetch) {
+                // the corner records the next pass will need are asked for now: they travel while this pass parks
+                // its results and the next one looks for work (q is free: its records went into d above).  On the
+                // 8-pose grid, whose records come from beyond the L2: 1.34 -> 1.32 ms; on a grid the L2 holds the
+                // second cell lookup costs more than the head start gains (0.172 -> 0.186 ms), hence the switch
+                const Cell cn = locate(G, xt);
+                if (cn.base != held) {
+                    load_cell(Tp + cn.base, G, q);
+                    held = cn.base;
                 }
             }
         }
         if (WITH_J) out_park(want_out, x, J, out_flags, out_cell, (int)((long long)k * N + n), outq, npend, lane, cell_count, rec);
     }
+    // the wave's last pairs, four lanes each
+    quad_tail(G, S, T, active, lane, xp, x, g, J, it, n, k, pz, emit);
     if (WITH_J && npend > 0) out_flush(outq, npend, lane, cell_count, rec);
+}
+
+// Which pairs a wave of the kernels for small batches takes: `per` pairs (64, or 16 quads), as a tile of ki initial states
+// times per / ki consecutive points.  Consecutive points share cache lines in the caller's arrays.  Initial states of one
+// point often reach the same root and then share one atomic when positions are handed out (d_slot), but a point
+// without a root keeps all its lanes busy to the last step, and a wave that holds 24 of those cannot go on in quads.
+// ki = 1 without positions, 8 with them (16x16x4 grid, 98 k pairs with positions: ki 1 71, 4 50, 8 45, 24 52 us; 64x64x16:
+// 72, 66, 66, 79 us).
+__device__ __forceinline__ bool pair_of(unsigned index, unsigned per, const SolveP &S, int &n, int &k)
+{
+    const unsigned pts = per / (unsigned)S.ki, tiles = ((unsigned)S.N + pts - 1u) / pts, w = index / per, i = index - w * per;
+    const unsigned kb = w / tiles;
+    k = (int)(kb * (unsigned)S.ki + i / pts);
+    n = (int)((w - kb * tiles) * pts + i % pts);
+    const bool live = k < S.K && n < (int)S.N;
+    if (!live) n = k = 0;
+    return live;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Broyden solve of a small batch: one quad of SIMD lanes per pair (see quad_iterate), no queue, no list, no records to
+// unpack.  Pairs q = k*N + n in order, so that the 16 pairs of a wave are consecutive points and the outputs, which go
+// straight to the caller's arrays, share cache lines.  A batch this small is bound by its longest trajectories, i.e. by
+// max_iters times the latency of a step.
+// INIT: 0 one state per bone (Eq. (8)), 1 candidates of the correspondence grid, 2 the caller's initial states.
+// LDS: the transform grids of all poses are copied into LDS first.
+// rec (may be null): result records for the backward, with the positions in the cells' lists (cell_count not null).
+// ------------------------------------------------------------------------------------------------
+template <int INIT, bool LDS>
+__global__ __launch_bounds__(LDS ? 1024 : 256) void k_solve_quad(GridP G, SolveP S, InitP I, const float *__restrict__ Tglobal,
+                                               const float *__restrict__ xq, const int32_t *__restrict__ pose,
+                                               const float *__restrict__ x0, const float *__restrict__ J0,
+                                               const uint8_t *__restrict__ valid0, float *__restrict__ o_x,
+                                               uint8_t *__restrict__ o_conv, float *__restrict__ o_J,
+                                               uint8_t *__restrict__ o_it, int32_t *__restrict__ o_slot,
+                                               float4 *__restrict__ rec, int *__restrict__ cell_count, int ncell)
+{
+    extern __shared__ float4 s_grid[];
+    if (LDS) {
+        const int n4 = (int)((long long)G.P * G.V * 3);      // float4 per record: 3
+        const float4 *src = reinterpret_cast<const float4 *>(Tglobal);
+        for (int i = threadIdx.x; i < n4; i += blockDim.x) s_grid[i] = src[i];
+        __syncthreads();
+    }
+    const float *T = LDS ? reinterpret_cast<const float *>(s_grid) : Tglobal;
+    const QuadAxis A = quad_axis(G);
+    const int row = A.row, lane3 = (int)(threadIdx.x & 3);
+    const long long N = S.N;
+    int n, k;
+    const bool live = pair_of((blockIdx.x * blockDim.x + threadIdx.x) >> 2, QUADS, S, n, k);
+    const unsigned pair = (unsigned)k * (unsigned)N + (unsigned)n;
+    const int p = pose_of(pose, n, G.P);
+    const float *Tp = T + (long long)p * G.V * 12;
+    float xp[3], x[3] = {0, 0, 0}, g[3] = {0, 0, 0}, J[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < 3; ++r) xp[r] = xq[r * N + n];
+    const float xpr = pick3(row, xp[0], xp[1], xp[2]);
+    bool ok;
+    float dr = 0.0f;                 // d(x0) along the lane's axis
+    if (INIT == 0) {
+        const float *bi = I.Binv + ((long long)p * G.nb + k) * 12;
+        ok = live && I.Bok[p * G.nb + k] != 0;
+        if (ok) {
+            const float y[3] = {xp[0] - bi[9], xp[1] - bi[10], xp[2] - bi[11]};
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+                x[r] = FS_FMA(bi[r * 3 + 0], y[0], FS_FMA(bi[r * 3 + 1], y[1], bi[r * 3 + 2] * y[2]));
+            const Cell c = locate(G, x);
+            float q[8][4], om[8], Tr[4];
+            quad_load(Tp + c.base, G, row, q);
+            corner_weights(c, om);
+            quad_blend(om, q, Tr);
+            dr = quad_apply(Tr, x);
+            // row r of jacobian_from_corners
+            const float wx[2] = {1.0f - c.f[0], c.f[0]};
+            const float wy[2] = {1.0f - c.f[1], c.f[1]};
+            const float wz[2] = {1.0f - c.f[2], c.f[2]};
+            float Jr[3] = {Tr[0], Tr[1], Tr[2]}, Jac[9];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int a = e & 1, b = (e >> 1) & 1, cz = (e >> 2) & 1;
+                const float dc = quad_apply(q[e], x);
+                float dw[3];
+                dw[0] = c.cl[0] ? 0.0f : (a ? G.inv_h[0] : -G.inv_h[0]) * (wy[b] * wz[cz]);
+                dw[1] = c.cl[1] ? 0.0f : (b ? G.inv_h[1] : -G.inv_h[1]) * (wx[a] * wz[cz]);
+                dw[2] = c.cl[2] ? 0.0f : (cz ? G.inv_h[2] : -G.inv_h[2]) * (wx[a] * wy[b]);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) Jr[j] = FS_FMA(dw[j], dc, Jr[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                Jac[j] = quad_get<0>(Jr[j]);
+                Jac[3 + j] = quad_get<1>(Jr[j]);
+                Jac[6 + j] = quad_get<2>(Jr[j]);
+            }
+            ok = inv3(Jac, J);
+            if (!ok) {
+#pragma unroll
+                for (int e = 0; e < 9; ++e) J[e] = 0.0f;
+            }
+        }
+    } else if (INIT == 1) {
+        const int gcell = p * I.C.ncell + cell_index(I.C, I.bbox + p * 6, xp);
+        const float4 *ci = I.cinit + ((long long)gcell * I.C.ck + k) * 4;
+        const float4 a = ci[0], b = ci[1], c = ci[2], e = ci[3];
+        ok = live && (__float_as_int(a.w) & 1) != 0;
+        x[0] = a.x; x[1] = a.y; x[2] = a.z;
+        dr = pick3(row, b.x, b.y, b.z);
+        J[0] = b.w; J[1] = c.x; J[2] = c.y; J[3] = c.z; J[4] = c.w;
+        J[5] = e.x; J[6] = e.y; J[7] = e.z; J[8] = e.w;
+    } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) x[r] = x0[((long long)k * 3 + r) * N + n];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) J[e] = J0[((long long)k * 9 + e) * N + n];
+        ok = live && valid0[pair] != 0;
+        if (ok) {
+            const Cell c = quad_locate(A, x);
+            float q[8][4], om[8], Tr[4];
+            quad_load(Tp + c.base, G, row, q);
+            corner_weights(c, om);
+            quad_blend(om, q, Tr);
+            dr = quad_apply(Tr, x);
+        }
+    }
+    bool conv = false;
+    int it = 0;
+    if (ok) {
+        const float gr = dr - xpr;
+        g[0] = quad_get<0>(gr);
+        g[1] = quad_get<1>(gr);
+        g[2] = quad_get<2>(gr);
+        const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
+        conv = r2 < S.tol2;
+        if (!(conv || !(r2 < S.div2) || 0 >= S.max_iters)) {
+            float q[8][4];
+            int held = -1, end;
+            do end = quad_step(G, A, S.tol2, S.div2, S.max_iters, Tp, xpr, x, g, J, it, q, held);
+            while (!(end & 1));
+            conv = (end & 2) != 0;
+        }
+    }
+    int pos = -1;
+    if (cell_count) {
+        const bool want = conv && lane3 == 0;
+        const int cell = want ? p * ncell + cell_linear(G, locate(G, x)) : -1;
+        const CellGroup cg = group_request(want, cell, threadIdx.x & 63, cell_count);
+        const int at = group_position(cg);
+        if (want) pos = at;
+    }
+    if (!live) return;
+    if (lane3 < 3) {
+        o_x[((long long)k * 3 + row) * N + n] = pick3(row, x[0], x[1], x[2]);
+        if (o_J) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) o_J[((long long)k * 9 + row * 3 + j) * N + n] = pick3(row, J[j], J[3 + j], J[6 + j]);
+        }
+    } else {
+        o_conv[pair] = conv ? 1 : 0;
+        if (o_it) o_it[pair] = (uint8_t)it;
+    }
+    if (lane3 == 0 && o_slot) o_slot[pair] = pos;
+    if (rec) {
+        // lane i of the quad writes the i-th quarter of the record
+        pos = quad_get<0>(pos);
+        float4 v;
+        if (lane3 == 0) v = make_float4(x[0], x[1], x[2], __int_as_float((conv ? 1 : 0) | (it << 8)));
+        else if (lane3 == 1) v = make_float4(__int_as_float(pos), J[0], J[1], J[2]);
+        else if (lane3 == 2) v = make_float4(J[3], J[4], J[5], J[6]);
+        else v = make_float4(J[7], J[8], 0.0f, 0.0f);
+        rec[(long long)pair * 4 + lane3] = v;
+    }
+}
+
+// Broyden solve of a batch of medium size: one pair per SIMD lane for the steps that most pairs need, four lanes per pair
+// for the rest (quad_tail).  Every wave owns 64 pairs and is done when they are: no queue, no cursor, no list, no
+// records to unpack.  Pairs and outputs as in k_solve_quad.
+template <int INIT, bool LDS>
+__global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(GridP G, SolveP S, InitP I, const float *__restrict__ Tglobal,
+                                               const float *__restrict__ xq, const int32_t *__restrict__ pose,
+                                               const float *__restrict__ x0, const float *__restrict__ J0,
+                                               const uint8_t *__restrict__ valid0, float *__restrict__ o_x,
+                                               uint8_t *__restrict__ o_conv, float *__restrict__ o_J,
+                                               uint8_t *__restrict__ o_it, int32_t *__restrict__ o_slot,
+                                               float4 *__restrict__ rec, int *__restrict__ cell_count, int ncell,
+                                               const int *__restrict__ nonfinite, int serial)
+{
+    extern __shared__ float4 s_grid[];
+    if (LDS) {
+        const int n4 = (int)((long long)G.P * G.V * 3);      // float4 per record: 3
+        const float4 *src = reinterpret_cast<const float4 *>(Tglobal);
+        for (int i = threadIdx.x; i < n4; i += blockDim.x) s_grid[i] = src[i];
+        __syncthreads();
+    }
+    constexpr bool SKIP = INIT != 1 && !LDS;      // as in k_solve_ws
+    const float *T = LDS ? reinterpret_cast<const float *>(s_grid) : Tglobal;
+    const int lane = threadIdx.x & 63;
+    const long long N = S.N;
+    int n, k;
+    const bool live = pair_of(blockIdx.x * blockDim.x + threadIdx.x, WAVE, S, n, k);
+    const unsigned pair = (unsigned)k * (unsigned)N + (unsigned)n;
+    const int p = pose_of(pose, n, G.P);
+    const float *Tp = T + (long long)p * G.V * 12;
+    float xp[3], x[3] = {0, 0, 0}, xt[3], dx[3], g[3] = {0, 0, 0}, d[3] = {0, 0, 0}, J[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    float q[8][12];
+    int held = -1, held_mask = 0, it = 0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int e = 0; e < 12; ++e) q[c][e] = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) xp[r] = xq[r * N + n];
+    bool ok = false;
+    if (live) {
+        if (INIT == 0) {
+            const float *bi = I.Binv + ((long long)p * G.nb + k) * 12;
+            ok = I.Bok[p * G.nb + k] != 0;
+            if (ok) {
+                const float y[3] = {xp[0] - bi[9], xp[1] - bi[10], xp[2] - bi[11]};
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+                    x[r] = FS_FMA(bi[r * 3 + 0], y[0], FS_FMA(bi[r * 3 + 1], y[1], bi[r * 3 + 2] * y[2]));
+                const Cell c = locate(G, x);
+                load_cell(Tp + c.base, G, q);
+                held = c.base;
+                held_mask = 0xFF;
+                float Jac[9];
+                jacobian_from_corners(G, c, q, x, d, Jac);
+                ok = inv3(Jac, J);
+                if (!ok) {
+#pragma unroll
+                    for (int e = 0; e < 9; ++e) J[e] = 0.0f;
+                }
+            }
+        } else if (INIT == 1) {
+            const int gcell = p * I.C.ncell + cell_index(I.C, I.bbox + p * 6, xp);
+            const float4 *ci = I.cinit + ((long long)gcell * I.C.ck + k) * 4;
+            const float4 a = ci[0], b = ci[1], c = ci[2], e = ci[3];
+            ok = (__float_as_int(a.w) & 1) != 0;
+            x[0] = a.x; x[1] = a.y; x[2] = a.z;
+            d[0] = b.x; d[1] = b.y; d[2] = b.z;
+            J[0] = b.w; J[1] = c.x; J[2] = c.y; J[3] = c.z; J[4] = c.w;
+            J[5] = e.x; J[6] = e.y; J[7] = e.z; J[8] = e.w;
+        } else {
+#pragma unroll
+            for (int r = 0; r < 3; ++r) x[r] = x0[((long long)k * 3 + r) * N + n];
+#pragma unroll
+            for (int e = 0; e < 9; ++e) J[e] = J0[((long long)k * 9 + e) * N + n];
+            ok = valid0[pair] != 0;
+            if (ok) {
+                const Cell c = locate(G, x);
+                load_cell(Tp + c.base, G, q);
+                held = c.base;
+                held_mask = 0xFF;
+                blend_apply(c, q, x, d);
+            }
+        }
+    }
+    bool active = false;
+    int flags = 0;                   // conv
+    if (ok) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) g[r] = d[r] - xp[r];
+        const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
+        const bool conv = r2 < S.tol2;
+        flags = conv ? 1 : 0;
+        active = !(conv || !(r2 < S.div2) || 0 >= S.max_iters);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
+            xt[r] = x[r] + dx[r];
+        }
+    }
+    const bool may_skip = SKIP && __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
+    while (__popcll(__ballot(active)) > QUADS) {
+        if (active) {
+            Cell cell;
+            const int end = lane_step<SKIP>(G, S, Tp, may_skip, xp, x, xt, dx, g, J, it, q, held, held_mask, cell);
+            if (end & 1) {
+                active = false;
+                flags = end >> 1;
+            }
+        }
+    }
+    auto output = [&](bool ends, unsigned pr, bool conv, const float (&xe)[3], const float (&Je)[9], int ite, int ne, int ke, int pe) {
+        int pos = -1;
+        if (cell_count) {
+            const bool want = ends && conv;
+            if (__any(want)) {
+                const int cell = want ? pe * ncell + cell_linear(G, locate(G, xe)) : -1;
+                const CellGroup cg = group_request(want, cell, lane, cell_count);
+                const int at = group_position(cg);
+                if (want) pos = at;
+            }
+        }
+        if (!ends) return;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) o_x[((long long)ke * 3 + r) * N + ne] = xe[r];
+        o_conv[pr] = conv ? 1 : 0;
+        if (o_it) o_it[pr] = (uint8_t)ite;
+        if (o_J) {
+#pragma unroll
+            for (int e = 0; e < 9; ++e) o_J[((long long)ke * 9 + e) * N + ne] = Je[e];
+        }
+        if (o_slot) o_slot[pr] = pos;
+        if (rec) {
+            float4 *o = rec + (long long)pr * 4;
+            o[0] = make_float4(xe[0], xe[1], xe[2], __int_as_float((conv ? 1 : 0) | (ite << 8)));
+            o[1] = make_float4(__int_as_float(pos), Je[0], Je[1], Je[2]);
+            o[2] = make_float4(Je[3], Je[4], Je[5], Je[6]);
+            o[3] = make_float4(Je[7], Je[8], 0.0f, 0.0f);
+        }
+    };
+    // what has ended so far leaves together: consecutive lanes, consecutive points
+    output(live && !active, pair, flags != 0, x, J, it, n, k, p);
+    quad_tail(G, S, T, active, lane, xp, x, g, J, it, n, k, p,
+              [&](bool ends, bool conv, const float (&xe)[3], const float (&Je)[9], int ite, int ne, int ke, int pe) {
+                  output(ends, (unsigned)ke * (unsigned)N + (unsigned)ne, conv, xe, Je, ite, ne, ke, pe);
+              });
 }
 
 // ------------------------------------------------------------------------------------------------

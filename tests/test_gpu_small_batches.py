@@ -1,0 +1,49 @@
+"""The solve kernels of small and medium batches (four lanes per pair; one pass of one lane per pair and a tail of four)
+and the hand-over of a wave's last pairs to quads in the others: all give the bits of the strict-fp32 oracle."""
+import numpy as np
+import pytest
+
+import gpu_util as gu
+import oracle
+from paper_2211_15601_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CUS = 256
+BONE_QUAD, BONE_ONCE = 192 * CUS, 768 * CUS          # largest batches (pairs) of the two kernels, one state per bone
+VOXEL_QUAD, VOXEL_ONCE = 320 * CUS, 1152 * CUS       # ... and with voxel-based candidates
+
+
+@pytest.mark.parametrize("case", [
+    # (dims, bones, poses, points, voxel): a wave takes 16 or 64 pairs, as 8 states times 2 or 8 points with positions
+    ((9, 8, 7), 1, 1, 1, False), ((9, 8, 7), 7, 1, 17, False), ((9, 8, 7), 8, 2, 63, False), ((9, 8, 7), 9, 3, 65, False),
+    ((20, 18, 9), 24, 1, BONE_QUAD // 24, False), ((20, 18, 9), 24, 2, BONE_QUAD // 24 + 1, False),
+    ((12, 10, 6), 24, 1, BONE_QUAD // 24, False), ((12, 10, 6), 24, 1, BONE_QUAD // 24 + 1, False),
+    ((20, 18, 9), 24, 1, BONE_ONCE // 24, False), ((20, 18, 9), 24, 1, BONE_ONCE // 24 + 1, False),
+    ((12, 10, 6), 24, 2, BONE_ONCE // 24, False), ((12, 10, 6), 24, 1, BONE_ONCE // 24 + 1, False),
+    ((20, 18, 9), 6, 1, 5, True), ((20, 18, 9), 6, 2, VOXEL_QUAD // 3, True), ((20, 18, 9), 6, 1, VOXEL_QUAD // 3 + 1, True),
+    ((12, 10, 6), 6, 1, VOXEL_QUAD // 3 + 1, True), ((20, 18, 9), 6, 2, VOXEL_ONCE // 3, True),
+    ((20, 18, 9), 6, 1, VOXEL_ONCE // 3 + 1, True), ((12, 10, 6), 6, 1, VOXEL_ONCE // 3 + 1, True)],
+    ids=lambda c: f"g{c[0][0]}-b{c[1]}-p{c[2]}-n{c[3]}-{'voxel' if c[4] else 'bone'}")
+def test_batch_sizes_around_the_kernels_limits(gpu_lib, case):
+    dims, nb, P, n, voxel = case
+    s = wl.random_affine_scene(300 + nb, dims=dims, n_bones=nb, n_poses=P, n_points=n)
+    w = wl.Workload("small", s["dims"], nb, P, s["lo"], s["hi"], s["W"], s["B"], s["x"], s["pose"], s["x"], 1e-5, 10.0, 50,
+                    wl.INIT_VOXEL if voxel else wl.INIT_BONE, 3 if voxel else nb, (6, 5, 4, 3))
+    run = gu.GpuRun(w)
+    T = run.precompute()
+    x0, J0, v0 = gu.oracle_inits(w, T)
+    ref = gu.oracle_solve(w, T, x0, J0, v0)
+    for kw in (dict(fused=True), dict(fused=True, slots=True), dict(x0=x0, J0=J0, v0=v0, slots=True)):
+        out = run.solve(**kw)
+        for name, a, b in zip(("roots", "masks", "J", "iterations"), out, ref):
+            np.testing.assert_array_equal(a.view(np.uint8), b.view(np.uint8), err_msg=f"{name} {sorted(kw)}")
+        if kw.get("slots"):
+            slot = run.slot.cpu().numpy()
+            assert ((slot >= 0) == (ref[1] == 1)).all()
+    # the positions and the records of the last solve carry the backward
+    gxc = np.random.default_rng(3).standard_normal(out[0].shape).astype(np.float32)
+    want = oracle.grad(w.dims, w.lo, w.hi, T, w.W, w.B, ref[0], ref[2], ref[1], gxc, pose=w.pose if P > 1 else None, mode=0, prec="f64")
+    got = run.grad(out[0], None, out[1], gxc, slot=run.slot)
+    for name, a, b in zip(("gW", "gB", "gxq"), got, want):
+        gu.assert_grad_close(name, a, b, f"small batch {case}")
