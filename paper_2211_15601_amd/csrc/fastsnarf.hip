@@ -56,6 +56,7 @@ struct fs_ctx {
     float4 *srec;      // per-pair result records of the solve kernel (grows on demand)
     size_t srec_cap;   // float4 entries srec can hold
     int *scan_sums;    // tile sums of the prefix scans
+    int *dd_sums;      // [DD_TILES] tile sums of fs_dedupe (behind the cursor's words)
     int *voffs;        // [N + 1] candidates per point, then offsets (fused voxel solve; grows on demand)
     uint8_t *vcnt;     // [N] candidates per point
     int *vgcell;       // [N] pose * ncell + correspondence cell of every point
@@ -80,8 +81,7 @@ struct fs_ctx {
     char err[256];
 };
 
-constexpr int FS_NOALLOC_TILES = 4096;
-static __device__ __align__(256) int scratch[FS_NOALLOC_TILES + 64];     // see scratch_on_device()
+static __device__ __align__(256) int scratch[DD_TILES];     // see scratch_on_device()
 
 namespace {
 
@@ -208,11 +208,10 @@ fs_status scan_exclusive(fs_ctx *c, int n, int *a, const int *src = nullptr, int
 }
 
 // ---- scratch memory of fs_dedupe_noalloc: a file-scope device array instead of a context-owned allocation ----
-// The prefix scan over the per-point counts of kept roots needs one partial sum per tile of SCAN_TILE points.
-// FS_NOALLOC_MAX_N points = FS_NOALLOC_TILES tiles; every GPU the library runs on holds its own 16 KiB copy of the
-// array until the process ends.  In host code the array's name is only a handle for hipGetSymbolAddress: the
-// device address is looked up once per device (with that device current) and kept in g_scratch_ptr.
-constexpr long long FS_NOALLOC_MAX_N = (long long)FS_NOALLOC_TILES * SCAN_TILE;     // 2^24 points
+// The sums of the at most DD_TILES tiles of points; every GPU the library runs on holds its own 8 KiB copy of the array
+// until the process ends.  In host code the array's name is only a handle for hipGetSymbolAddress: the device address is
+// looked up once per device (with that device current) and kept in g_scratch_ptr.
+constexpr long long FS_NOALLOC_MAX_N = 1ll << 24;
 constexpr int FS_MAX_DEVICES = 64;
 int *g_scratch_ptr[FS_MAX_DEVICES];       // device address of `scratch` on device i, nullptr until looked up
 std::mutex g_scratch_mutex;
@@ -335,7 +334,8 @@ fs_status fs_create(const fs_grid_desc *desc, const fs_params *params, void *hip
     }
     const size_t P = desc->n_poses, nb = desc->n_bones;
     bool ok = dev_alloc(&c->T, P * V * 12) && dev_alloc(&c->Bdev, P * nb * 12) && dev_alloc(&c->Binv, P * nb * 12) &&
-              dev_alloc(&c->Bok, P * nb) && dev_alloc(&c->cursor, CUR_WORDS);
+              dev_alloc(&c->Bok, P * nb) && dev_alloc(&c->cursor, CUR_WORDS + DD_TILES);
+    if (ok) c->dd_sums = reinterpret_cast<int *>(c->cursor + CUR_WORDS);
     if (ok) ok = hipMemset(c->cursor, 0, CUR_WORDS * sizeof(unsigned)) == hipSuccess;
     {
         int per_cu = 0, cus = 0;
@@ -879,15 +879,14 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
     return launch_status(ctx, "fs_grad");
 }
 
-// shared body of fs_dedupe and fs_dedupe_noalloc: `sums` = nullptr: the tile sums of the scan live in the context's
-// buffer, which grows on demand; otherwise they live in `sums` (room for FS_NOALLOC_TILES) and nothing is allocated
+// shared body of fs_dedupe and fs_dedupe_noalloc, which differ in where the tile sums live
 static fs_status dedupe_impl(fs_ctx *ctx, const char *who, int *sums, const float *d_xc, const uint8_t *d_conv, int64_t N,
                              int32_t K, float min_dist, uint8_t *d_keep, int32_t *d_offsets, float *d_roots, int32_t *d_lane,
                              int64_t cap)
 {
     if (K < 1 || K > FS_MAX_BONES) return fail(ctx, FS_E_SHAPE, "%s: K must be in 1..%d", who, (int)FS_MAX_BONES);
     if (N < 0 || (long long)N * K >= (1ll << 31)) return fail(ctx, FS_E_SHAPE, "%s: need 0 <= N and K*N < 2^31", who);
-    if (sums && N > FS_NOALLOC_MAX_N)
+    if (sums != ctx->dd_sums && N > FS_NOALLOC_MAX_N)
         return fail(ctx, FS_E_SHAPE, "%s: N = %lld exceeds the %lld points its fixed scratch memory is sized for; use fs_dedupe",
                     who, (long long)N, FS_NOALLOC_MAX_N);
     if (!(min_dist >= 0.0f) || !std::isfinite(min_dist)) return fail(ctx, FS_E_ARG, "%s: min_dist must be finite and >= 0", who);
@@ -900,24 +899,21 @@ static fs_status dedupe_impl(fs_ctx *ctx, const char *who, int *sums, const floa
         FS_CHECK_PTR(ctx, d_xc, false);
         FS_CHECK_PTR(ctx, d_conv, false);
         FS_CHECK_PTR(ctx, d_keep, false);
-        k_dedupe<<<grid1d(N, 256), 256, 0, st>>>(N, K, min_dist * min_dist, d_xc, d_conv, d_keep, d_offsets);
-    }
-    if (sums) {
-        // at most FS_NOALLOC_TILES tiles: every block of the second pass adds up the tile sums before its own, all
-        // of which the first pass has just written (nothing of an earlier call is read)
-        if (N > 0) {
-            const int m = (int)((N + SCAN_TILE - 1) / SCAN_TILE);
-            k_scan_tile_sums<<<m, 1024, 0, st>>>((int)N, d_offsets, sums);
-            k_scan_tiles<false><<<m, 1024, 0, st>>>((int)N, d_offsets, d_offsets, sums, m, nullptr);
-        } else {
-            k_fill_zero_i32<<<1, 64, 0, st>>>(1, d_offsets, nullptr);
-        }
+        int tile = K <= DD_FEW ? 256 : 32;          // what a block takes in one pass
+        while ((N + tile - 1) / tile > DD_TILES) tile *= 2;
+        const int tiles = grid1d(N, tile);
+#define FS_LAUNCH_DEDUPE(KERNEL) KERNEL<<<tiles, 256, 0, st>>>(N, K, min_dist * min_dist, d_xc, d_conv, d_keep, d_offsets, tile, sums)
+        if (K <= DD_FEW) FS_LAUNCH_DEDUPE(k_dedupe_few);
+        else if (K <= 8) FS_LAUNCH_DEDUPE(k_dedupe<1>);
+        else if (K <= 16) FS_LAUNCH_DEDUPE(k_dedupe<2>);
+        else if (K <= 24) FS_LAUNCH_DEDUPE(k_dedupe<3>);
+        else if (K <= 32) FS_LAUNCH_DEDUPE(k_dedupe<4>);
+        else FS_LAUNCH_DEDUPE(k_dedupe<8>);
+#undef FS_LAUNCH_DEDUPE
+        k_dedupe_pack<<<tiles, 256, 0, st>>>(N, K, cap, d_xc, d_keep, d_offsets, tile, sums, d_roots, d_lane);
     } else {
-        fs_status ss = scan_exclusive(ctx, (int)N, d_offsets);
-        if (ss != FS_OK) return ss;
+        k_fill_zero_i32<<<1, 64, 0, st>>>(1, d_offsets, nullptr);
     }
-    if (N > 0 && (d_roots || d_lane))
-        k_pack_roots<<<grid1d(N, 256), 256, 0, st>>>(N, K, cap, d_xc, d_keep, d_offsets, d_roots, d_lane);
     return launch_status(ctx, who);
 }
 
@@ -926,7 +922,7 @@ fs_status fs_dedupe(fs_ctx *ctx, const float *d_xc, const uint8_t *d_conv, int64
 {
     if (!ctx) return FS_E_ARG;
     { fs_status gs = check_gave_up(ctx, "fs_dedupe"); if (gs != FS_OK) return gs; }
-    return dedupe_impl(ctx, "fs_dedupe", nullptr, d_xc, d_conv, N, K, min_dist, d_keep, d_offsets, d_roots, d_lane, cap);
+    return dedupe_impl(ctx, "fs_dedupe", ctx->dd_sums, d_xc, d_conv, N, K, min_dist, d_keep, d_offsets, d_roots, d_lane, cap);
 }
 
 fs_status fs_dedupe_noalloc(fs_ctx *ctx, const float *d_xc, const uint8_t *d_conv, int64_t N, int32_t K, float min_dist,

@@ -2955,48 +2955,190 @@ __global__ __launch_bounds__(64) void k_grad_bones_final(int P, int nblk, int no
 
 // ------------------------------------------------------------------------------------------------
 // Duplicate removal (Sec. 3.1 "Remove Duplicate Correspondences") and packing of the surviving roots.
-// One thread per point; lanes in increasing k; a converged lane is kept iff no lane kept before it is
-// closer than min_dist.  The kept set lives in a 64-bit mask; kept roots are re-read when needed.
+// Lanes in increasing k; a converged lane is kept iff no lane kept before it is closer than min_dist.  In other words: the
+// first lane not yet settled is kept and settles every later one that is closer than min_dist to it, and again, as many
+// rounds as the point has distinct roots (1 to 4) instead of one per lane.
+// Two launches.  The points are cut into at most DD_TILES tiles.  k_dedupe leaves what it kept of a point in offsets[n]
+// (the mask itself for K <= 32, else the number) and the sum of every tile; k_dedupe_pack adds up the sums before its
+// tile, scans its points and packs.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_dedupe(long long N, int K, float md2, const float *__restrict__ xc,
-                                                const uint8_t *__restrict__ conv, uint8_t *__restrict__ keep,
-                                                int *__restrict__ count)
+constexpr int DD_TILES = 2048;
+
+__device__ __forceinline__ bool closer(const float (&a)[3], const float (&b)[3], float md2)
 {
-    const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    unsigned long long kept = 0ull;
-    for (int k = 0; k < K; ++k) {
-        bool kp = conv[(long long)k * N + n] != 0;
-        if (kp) {
-            const float x0 = xc[((long long)k * 3 + 0) * N + n], x1 = xc[((long long)k * 3 + 1) * N + n],
-                        x2 = xc[((long long)k * 3 + 2) * N + n];
-            unsigned long long m = kept;
-            while (m && kp) {
-                const int j = __builtin_ctzll(m);
-                m &= m - 1ull;
-                const float e0 = x0 - xc[((long long)j * 3 + 0) * N + n], e1 = x1 - xc[((long long)j * 3 + 1) * N + n],
-                            e2 = x2 - xc[((long long)j * 3 + 2) * N + n];
-                const float d2 = FS_FMA(e2, e2, FS_FMA(e1, e1, e0 * e0));
-                if (d2 < md2) kp = false;
-            }
-        }
-        if (kp) kept |= 1ull << k;
-        keep[(long long)k * N + n] = kp ? 1 : 0;
-    }
-    count[n] = __popcll(kept);
+    const float e0 = a[0] - b[0], e1 = a[1] - b[1], e2 = a[2] - b[2];
+    return FS_FMA(e2, e2, FS_FMA(e1, e1, e0 * e0)) < md2;
 }
 
-// packed list: roots [total][3] and lane index k, point n owns entries offsets[n] .. offsets[n+1]
-__global__ __launch_bounds__(256) void k_pack_roots(long long N, int K, long long cap, const float *__restrict__ xc,
-                                                    const uint8_t *__restrict__ keep, const int *__restrict__ offsets,
-                                                    float *__restrict__ roots, int32_t *__restrict__ lane)
+// a block's sum of `mine` into sums[block]
+__device__ __forceinline__ void tile_sum(int mine, int *__restrict__ sums)
 {
-    const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    long long o = offsets[n];
-    for (int k = 0; k < K; ++k) {
-        if (!keep[(long long)k * N + n]) continue;
-        if (o < cap) {
+    __shared__ int s_sum[4];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) sums[blockIdx.x] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+}
+
+// K <= DD_FEW: one thread per point, everything in registers
+constexpr int DD_FEW = 4;
+__global__ __launch_bounds__(256) void k_dedupe_few(long long N, int K, float md2, const float *__restrict__ xc,
+                                                    const uint8_t *__restrict__ conv, uint8_t *__restrict__ keep,
+                                                    int *__restrict__ offsets, int tile, int *__restrict__ sums)
+{
+    const long long n0 = (long long)blockIdx.x * tile, n1 = min(N, n0 + tile);
+    int mine = 0;
+    for (long long n = n0 + threadIdx.x; n < n1; n += 256) {
+        bool on[DD_FEW];
+        float x[DD_FEW][3];
+#pragma unroll
+        for (int k = 0; k < DD_FEW; ++k) on[k] = k < K && conv[(long long)min(k, K - 1) * N + n] != 0;
+#pragma unroll
+        for (int k = 0; k < DD_FEW; ++k)
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                x[k][r] = 0.0f;
+                if (on[k]) x[k][r] = xc[((long long)k * 3 + r) * N + n];
+            }
+        unsigned kept = 0u;
+#pragma unroll
+        for (int k = 0; k < DD_FEW; ++k) {
+#pragma unroll
+            for (int j = 0; j < k; ++j)
+                if (((kept >> j) & 1u) && closer(x[k], x[j], md2)) on[k] = false;
+            kept |= (on[k] ? 1u : 0u) << k;
+        }
+        offsets[n] = (int)kept;
+        mine += __popc(kept);
+#pragma unroll
+        for (int k = 0; k < DD_FEW; ++k)
+            if (k < K) keep[(long long)k * N + n] = (uint8_t)((kept >> k) & 1u);
+    }
+    tile_sum(mine, sums);
+}
+
+// Eight threads per point: SIMD lane 8 g + i holds lanes k = g, 8 + g, ... (at most 8 T) of the i-th of the wave's 8 points,
+// so that all loads of a point travel together.
+// Bound: memory (13 bytes per lane) on large batches, two round trips and the launch on small ones.  (One thread per point
+// and lane after lane, kept roots read again for every comparison: 48 us on 200,000 points x 24 lanes, 19 us on 37; now
+// 21 and 4.5.)
+template <int T>
+__global__ __launch_bounds__(256) void k_dedupe(long long N, int K, float md2, const float *__restrict__ xc,
+                                                const uint8_t *__restrict__ conv, uint8_t *__restrict__ keep,
+                                                int *__restrict__ offsets, int tile, int *__restrict__ sums)
+{
+    const int lane = threadIdx.x & 63, i = lane & 7, g = lane >> 3;
+    const unsigned long long point = 0x0101010101010101ull << i;        // the SIMD lanes of this lane's point
+    const long long n0 = (long long)blockIdx.x * tile, n1 = min(N, n0 + tile);
+    int mine = 0;
+    for (long long b = n0 + (threadIdx.x >> 6) * 8; b < n1; b += 32) {  // wave-uniform
+        const bool live = b + i < n1;
+        const long long n = live ? b + i : n1 - 1;
+        unsigned open = 0u, kept = 0u;          // bit t: lane 8 t + g of the point
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+            if (8 * t + g < K && live) open |= (conv[(long long)(8 * t + g) * N + n] != 0 ? 1u : 0u) << t;
+        float x[T][3];
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                x[t][r] = 0.0f;
+                if ((open >> t) & 1u) x[t][r] = xc[((long long)(8 * t + g) * 3 + r) * N + n];
+            }
+        while (__any(open != 0u)) {
+            // the point's first open lane: slot ft of SIMD lane src
+            int ft = 0, src = lane;
+            bool found = false;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const unsigned long long m = __ballot((open >> t) & 1u) & point;
+                if (!found && m) {
+                    found = true;
+                    ft = t;
+                    src = __ffsll((long long)m) - 1;
+                }
+            }
+            float y[3] = {x[0][0], x[0][1], x[0][2]}, c[3];
+#pragma unroll
+            for (int t = 1; t < T; ++t)
+#pragma unroll
+                for (int r = 0; r < 3; ++r) y[r] = ft == t ? x[t][r] : y[r];      // ft is the same in all lanes of the point
+#pragma unroll
+            for (int r = 0; r < 3; ++r) c[r] = __shfl(y[r], src);
+            if (found) {
+                if (lane == src) {
+                    kept |= 1u << ft;
+                    open &= ~(1u << ft);
+                }
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    if (closer(x[t], c, md2)) open &= ~(1u << t);
+            }
+        }
+        int count = 0;
+        unsigned mask = 0u;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const unsigned long long m = __ballot((kept >> t) & 1u) & point;
+            count += __popcll(m);
+            // the bits of the point's 8 lanes, 8 places apart, side by side
+            if (t < 4) mask |= (unsigned)(((m >> i) * 0x0102040810204080ull) >> 56) << (8 * t);
+            if (8 * t + g < K && live) keep[(long long)(8 * t + g) * N + n] = (uint8_t)((kept >> t) & 1u);
+        }
+        if (g == 0 && live) {
+            offsets[n] = K <= 32 ? (int)mask : count;
+            mine += count;
+        }
+    }
+    tile_sum(mine, sums);
+}
+
+// offsets and the packed list: roots [total][3] and lane index k, point n owns entries offsets[n] .. offsets[n+1]
+__global__ __launch_bounds__(256) void k_dedupe_pack(long long N, int K, long long cap, const float *__restrict__ xc,
+                                                     const uint8_t *__restrict__ keep, int *__restrict__ offsets, int tile,
+                                                     const int *__restrict__ sums, float *__restrict__ roots,
+                                                     int32_t *__restrict__ lane)
+{
+    __shared__ int s_sum[4];
+    const int wid = threadIdx.x >> 6, l = threadIdx.x & 63;
+    int before = 0;
+    for (int j = threadIdx.x; j < (int)blockIdx.x; j += 256) before += sums[j];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) before += __shfl_xor(before, d);
+    if (l == 0) s_sum[wid] = before;
+    __syncthreads();
+    int run = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+    const long long n0 = (long long)blockIdx.x * tile, n1 = min(N, n0 + tile);
+    for (long long b = n0; b < n1; b += 256) {
+        const long long n = b + threadIdx.x;
+        const int info = n < n1 ? offsets[n] : 0;
+        const int c = K <= 32 ? __popc((unsigned)info) : info;
+        int inc = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(inc, d);
+            if (l >= d) inc += o;
+        }
+        __syncthreads();                     // s_sum is still read for the step before
+        if (l == 63) s_sum[wid] = inc;
+        __syncthreads();
+        const int t0 = s_sum[0], t1 = s_sum[1], t2 = s_sum[2], t3 = s_sum[3];
+        const int at = run + inc - c + (wid > 0 ? t0 : 0) + (wid > 1 ? t1 : 0) + (wid > 2 ? t2 : 0);
+        run += t0 + t1 + t2 + t3;
+        if (n >= n1) continue;
+        offsets[n] = at;
+        if (!roots && !lane) continue;
+        long long o = at;
+        unsigned long long m = (unsigned)info;
+        if (K > 32) {
+            m = 0ull;
+            if (c > 0)
+                for (int k = 0; k < K; ++k) m |= (unsigned long long)(keep[(long long)k * N + n] != 0) << k;
+        }
+        for (; m && o < cap; m &= m - 1ull, ++o) {
+            const int k = __builtin_ctzll(m);
             if (roots) {
                 roots[o * 3 + 0] = xc[((long long)k * 3 + 0) * N + n];
                 roots[o * 3 + 1] = xc[((long long)k * 3 + 1) * N + n];
@@ -3004,8 +3146,8 @@ __global__ __launch_bounds__(256) void k_pack_roots(long long N, int K, long lon
             }
             if (lane) lane[o] = k;
         }
-        ++o;
     }
+    if (threadIdx.x == 0 && n1 == N) offsets[N] = run;
 }
 
 }  // namespace fs
