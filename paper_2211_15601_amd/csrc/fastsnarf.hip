@@ -55,16 +55,15 @@ struct fs_ctx {
     int gb_blocks;
     float4 *srec;      // per-pair result records of the solve kernel (grows on demand)
     size_t srec_cap;   // float4 entries srec can hold
-    int *scan_sums;    // tile sums of the prefix scans
+    u64 *look;         // look-back words of the kernels that scan in one pass, zero between kernels (grows on demand)
     int *dd_sums;      // [DD_TILES] tile sums of fs_dedupe (behind the cursor's words)
-    int *voffs;        // [N + 1] candidates per point, then offsets (fused voxel solve; grows on demand)
     uint8_t *vcnt;     // [N] candidates per point
     int *vgcell;       // [N] pose * ncell + correspondence cell of every point
     int2 *vlist;       // [K*N] pairs that have a candidate: {point, cell << 3 | k}
-    size_t vcap;       // points voffs / vcnt / vgcell / vlist can hold
+    size_t vcap, vgcell_cap;       // points vcnt / vlist, vgcell can hold
     int *vhist;        // [buckets][blocks] + 1: counts, then places, of the counting sort that orders the list by place
     size_t vhist_cap;
-    int scan_cap;      // tiles scan_sums can hold
+    int look_cap;      // words look holds
     int n_cus, occ_blocks_per_cu, occ_ws_blocks_per_cu, occ_vx_blocks_per_cu, chunk, refill_min, blocks_per_cu, point_major, lds_grid;
     bool lds_big;      // the grid is larger than 60 KiB and fits the LDS of a CU as one block of 12 waves
     int sort_list;     // order the list of (point, candidate) pairs by place (large voxel-mode batches)
@@ -175,35 +174,39 @@ int grid1d(long long n, int block) { return (int)((n + block - 1) / block); }
 void free_all(fs_ctx *c)
 {
     void *ptrs[] = {c->T, c->Bdev, c->Binv, c->Bok, c->GT, c->Y, c->bb_ord, c->bbox,
-                    c->cell_of, c->count, c->fill, c->order, c->cand, c->cursor, c->gcount, c->gcount_solve, c->gpos, c->grec, c->scan_sums, c->srec, c->gpart, c->voffs, c->vlist, c->cinit, c->vcnt, c->vgcell, c->vhist, c->ccnt};
+                    c->cell_of, c->count, c->fill, c->order, c->cand, c->cursor, c->gcount, c->gcount_solve, c->gpos, c->grec, c->look, c->srec, c->gpart, c->vlist, c->cinit, c->vcnt, c->vgcell, c->vhist, c->ccnt};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
 
-// exclusive scan of src[0..n) into a[0..n) (src == nullptr: in place) on the context's stream,
-// a[n] = total; *also_zero (may be null) is cleared on the way
-fs_status scan_exclusive(fs_ctx *c, int n, int *a, const int *src = nullptr, int *also_zero = nullptr)
+// look-back words for a kernel of `blocks` blocks (zero between kernels); grows on demand
+fs_status need_look(fs_ctx *c, int blocks)
 {
+    if (blocks <= c->look_cap) return FS_OK;
+    (void)hipStreamSynchronize(c->stream);
+    if (c->look) (void)hipFree(c->look);
+    c->look_cap = 0;
+    if (!dev_alloc(&c->look, (size_t)blocks + LOOK_HEAD)) return fail(c, FS_E_ALLOC, "out of device memory (scan)");
+    k_fill_zero_i32<<<grid1d(2ll * (blocks + LOOK_HEAD), 256), 256, 0, c->stream>>>(2ll * (blocks + LOOK_HEAD), reinterpret_cast<int *>(c->look));
+    c->look_cap = blocks;
+    return FS_OK;
+}
+
+// exclusive scan of src[0..n) into a[0..n) (src == nullptr: in place) on the context's stream, a[n] = total; *blocks: what
+// the kernel after it has to clear of the look-back words
+fs_status scan_exclusive(fs_ctx *c, int n, int *a, const int *src, int *blocks)
+{
+    *blocks = 0;
     if (n <= 0) {
         k_fill_zero_i32<<<1, 64, 0, c->stream>>>(1, a);
-        if (also_zero) k_fill_zero_i32<<<1, 64, 0, c->stream>>>(1, also_zero);
         return FS_OK;
     }
-    const int m = (n + SCAN_TILE - 1) / SCAN_TILE;
-    if (m + 1 > c->scan_cap) {
-        (void)hipStreamSynchronize(c->stream);
-        if (c->scan_sums) (void)hipFree(c->scan_sums);
-        c->scan_cap = 0;
-        if (!dev_alloc(&c->scan_sums, (size_t)m + 1)) return fail(c, FS_E_ALLOC, "out of device memory (scan)");
-        c->scan_cap = m + 1;
-    }
-    k_scan_tile_sums<<<m, 1024, 0, c->stream>>>(n, src ? src : a, c->scan_sums);
-    if (m <= 4096) {
-        k_scan_tiles<false><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->scan_sums, m, also_zero);
-    } else {
-        k_scan_sums<<<1, 1024, 0, c->stream>>>(m, c->scan_sums, also_zero);
-        k_scan_tiles<true><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->scan_sums, m, nullptr);
-    }
+    const int per = n <= (1 << 19) ? 4 : 16, m = grid1d(n, 1024 * per);
+    fs_status ls = need_look(c, m);
+    if (ls != FS_OK) return ls;
+    if (per == 4) k_scan<4><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->look);
+    else k_scan<16><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->look);
+    *blocks = m;
     return FS_OK;
 }
 
@@ -247,13 +250,12 @@ constexpr size_t FS_LDS_GRID_MAX = 60 * 1024;
 constexpr int FS_LDS_BIG_WAVES = 12;
 constexpr size_t FS_LDS_GRID_MAX_BIG = 148 * 1024;
 
-// the counts of converged lanes per grid cell that a solve with slots keeps, cleared; the work cursor is reset on the way
-fs_status clear_solve_counts(fs_ctx *c, int ncell, unsigned drawers, unsigned chunk)
+// the counts of converged lanes per grid cell that a solve with slots keeps
+fs_status need_solve_counts(fs_ctx *c, int ncell)
 {
     const long long ncp = (long long)c->G.P * ncell;
     if (ncp + 1 >= (1ll << 31)) return fail(c, FS_E_SHAPE, "fs_solve: too many grid cells for d_slot");
     if (!c->gcount_solve && !dev_alloc(&c->gcount_solve, (size_t)ncp + 1)) return fail(c, FS_E_ALLOC, "fs_solve: out of device memory");
-    k_fill_zero_i32<<<(int)std::min<long long>(grid1d(ncp + 1, 256), 4096), 256, 0, c->stream>>>(ncp + 1, c->gcount_solve, c->cursor, drawers, chunk);
     return FS_OK;
 }
 
@@ -491,8 +493,9 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
         k_corr_extent<<<dim3(eblk, G.P), 256, 0, st>>>(G, ctx->Y, ctx->bb_ord);
         k_corr_bbox<<<G.P, 384, 0, st>>>(eblk, ctx->bb_ord, ctx->bbox);
         k_corr_count<<<gv, 256, 0, st>>>(G, C, ctx->Y, ctx->bbox, ctx->cell_of, ctx->count, ctx->fill);
-        { fs_status ss = scan_exclusive(ctx, ncp, ctx->count); if (ss != FS_OK) return ss; }
-        k_corr_scatter<<<gv, 256, 0, st>>>(G, C, ctx->Y, ctx->cell_of, ctx->count, ctx->fill, ctx->order);
+        int look_blocks;
+        { fs_status ss = scan_exclusive(ctx, ncp, ctx->count, nullptr, &look_blocks); if (ss != FS_OK) return ss; }
+        k_corr_scatter<<<gv, 256, 0, st>>>(G, C, ctx->Y, ctx->cell_of, ctx->count, ctx->fill, ctx->order, ctx->look, look_blocks);
         k_corr_select<<<grid1d((long long)ncp * WAVE, 256), 256, 0, st>>>(G, C, ctx->Y, ctx->bbox, ctx->count, ctx->order, ctx->cand, ctx->ccnt);
         k_corr_init<<<grid1d((long long)ncp * C.ck, 256), 256, 0, st>>>(G, C, ctx->T, ctx->cand, ctx->cinit);
     }
@@ -609,9 +612,11 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         ctx->slots_N = 0;
         int *counts = nullptr;
         if (d_slot) {
-            fs_status cs = clear_solve_counts(ctx, ncell, 0u, 0u);
+            fs_status cs = need_solve_counts(ctx, ncell);
             if (cs != FS_OK) return cs;
             counts = ctx->gcount_solve;
+            const long long nc = (long long)ctx->G.P * ncell + 1;
+            k_fill_zero_i32<<<(int)std::min<long long>(grid1d(nc, 256), 4096), 256, 0, st>>>(nc, counts);
         }
         hipEvent_t ev0 = nullptr, ev1 = nullptr;
         if (ctx->timing && hipEventCreate(&ev0) == hipSuccess && hipEventCreate(&ev1) == hipSuccess) (void)hipEventRecord(ev0, st);
@@ -660,61 +665,76 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const int2 *list = nullptr;
     const int *list_len = nullptr;
     S.xcd_ranges = 0;
+    int *cell_count = nullptr;
+    ctx->slots_N = 0;
+    // every wave that draws chunks (all four of a k_solve block, the producer of a k_solve_ws block) owns the
+    // chunk of its own number to begin with; the shared cursor starts behind those
+    const unsigned drawers = (unsigned)(blocks * wpb);
+    int look_blocks = 0;         // look-back words that the last kernel of this call has to clear
+    bool cleared = false;        // the counts and the cursor are cleared by the kernel that makes the list
+    if (d_slot) {
+        fs_status cs = need_solve_counts(ctx, ncell);
+        if (cs != FS_OK) return cs;
+        cell_count = ctx->gcount_solve;
+    }
+    const long long ncounts = cell_count ? (long long)ctx->G.P * ncell + 1 : 0;
     if (voxel_list) {
-        if ((size_t)N > ctx->vcap) {
-            (void)hipStreamSynchronize(st);
-            for (void *q : {(void *)ctx->voffs, (void *)ctx->vlist, (void *)ctx->vcnt, (void *)ctx->vgcell})
-                if (q) (void)hipFree(q);
-            ctx->voffs = ctx->vgcell = nullptr;
-            ctx->vlist = nullptr;
-            ctx->vcnt = nullptr;
-            ctx->vcap = 0;
-            if (!dev_alloc(&ctx->voffs, (size_t)N + 1) || !dev_alloc(&ctx->vlist, (size_t)N * K) ||
-                !dev_alloc(&ctx->vcnt, (size_t)N) || !dev_alloc(&ctx->vgcell, (size_t)N))
-                return fail(ctx, FS_E_ALLOC, "fs_solve: out of device memory for the pair list");
-            ctx->vcap = (size_t)N;
-        }
-        k_voxel_count<<<grid1d(N, 256), 256, sizeof(float) * 6 * ctx->G.P, st>>>(ctx->G, I, N, d_xq, d_pose, ctx->voffs, ctx->vcnt, ctx->vgcell);
         // On request (fs_set_list_order) large batches are ordered by place (pose, then column of correspondence cells)
         // with a counting sort; small ones, or correspondence grids with more columns than the sort's LDS counters hold,
         // keep the order of the points.
         const int nb = ctx->G.P * ctx->C.cx * ctx->C.cy;
         const long long sblk = (N + SORT_TILE - 1) / SORT_TILE;
         const bool sorted = ctx->sort_list && N >= 4 * SORT_TILE && nb <= SORT_MAX_BUCKETS && (long long)nb * sblk < (1ll << 24);
+        const size_t need_h = (size_t)nb * sblk + 1;
+        if ((size_t)N > ctx->vcap) {
+            (void)hipStreamSynchronize(st);
+            for (void *q : {(void *)ctx->vlist, (void *)ctx->vcnt})
+                if (q) (void)hipFree(q);
+            ctx->vlist = nullptr;
+            ctx->vcnt = nullptr;
+            ctx->vcap = 0;
+            if (!dev_alloc(&ctx->vlist, (size_t)N * K) || !dev_alloc(&ctx->vcnt, (size_t)N))
+                return fail(ctx, FS_E_ALLOC, "fs_solve: out of device memory for the pair list");
+            ctx->vcap = (size_t)N;
+        }
+        if (sorted && ((size_t)N > ctx->vgcell_cap || need_h > ctx->vhist_cap)) {
+            (void)hipStreamSynchronize(st);
+            for (void *q : {(void *)ctx->vgcell, (void *)ctx->vhist})
+                if (q) (void)hipFree(q);
+            ctx->vgcell = ctx->vhist = nullptr;
+            ctx->vgcell_cap = ctx->vhist_cap = 0;
+            if (!dev_alloc(&ctx->vgcell, (size_t)N) || !dev_alloc(&ctx->vhist, need_h))
+                return fail(ctx, FS_E_ALLOC, "fs_solve: out of device memory for the pair list");
+            ctx->vgcell_cap = (size_t)N;
+            ctx->vhist_cap = need_h;
+        }
+        const size_t boxes = sizeof(float) * 6 * ctx->G.P;
         if (sorted) {
-            const size_t need_h = (size_t)nb * sblk + 1;
-            if (need_h > ctx->vhist_cap) {
-                (void)hipStreamSynchronize(st);
-                if (ctx->vhist) (void)hipFree(ctx->vhist);
-                ctx->vhist = nullptr;
-                ctx->vhist_cap = 0;
-                if (!dev_alloc(&ctx->vhist, need_h)) return fail(ctx, FS_E_ALLOC, "fs_solve: out of device memory for the pair list");
-                ctx->vhist_cap = need_h;
-            }
+            k_voxel_count<<<grid1d(N, 256), 256, boxes, st>>>(ctx->G, I, N, d_xq, d_pose, ctx->vcnt, ctx->vgcell);
             k_sort_hist<<<(unsigned)sblk, 1024, nb * sizeof(int), st>>>(N, ctx->C.cz, nb, ctx->vgcell, ctx->vcnt, ctx->vhist);
-            { fs_status ss = scan_exclusive(ctx, (int)((long long)nb * sblk), ctx->vhist); if (ss != FS_OK) return ss; }
-            k_sort_scatter<<<(unsigned)sblk, 1024, nb * sizeof(int), st>>>(N, ctx->C.cz, nb, ctx->vgcell, ctx->vcnt, ctx->vhist, ctx->vlist);
+            { fs_status ss = scan_exclusive(ctx, (int)((long long)nb * sblk), ctx->vhist, nullptr, &look_blocks); if (ss != FS_OK) return ss; }
+            k_sort_scatter<<<(unsigned)sblk, 1024, nb * sizeof(int), st>>>(N, ctx->C.cz, nb, ctx->vgcell, ctx->vcnt, ctx->vhist, ctx->vlist, ctx->look, look_blocks);
+            look_blocks = 0;
             list_len = ctx->vhist + (long long)nb * sblk;
             S.xcd_ranges = (!lds && ctx->xcd_ranges) ? 1 : 0;
         } else {
-            { fs_status ss = scan_exclusive(ctx, (int)N, ctx->voffs); if (ss != FS_OK) return ss; }
-            k_voxel_expand<<<grid1d(N, 256), 256, 0, st>>>(N, ctx->voffs, ctx->vgcell, ctx->vlist);
-            list_len = ctx->voffs + N;
+#define FS_LAUNCH_LIST(U)                                                                                              \
+    k_voxel_list<U><<<grid1d(N, 1024 * (U)), 1024, boxes, st>>>(ctx->G, I, N, K, d_xq, d_pose, ctx->vcnt, ctx->vlist,  \
+                                                                ctx->cursor, drawers, (unsigned)S.chunk, cell_count, ncounts, ctx->look)
+            // kernel us for 2 / 4 / 8 thousand points per block: 0.3 M points 9 / 10 / 16, 1 M 17 / 13 / 16, 2 M 30 / 24 / 22, 4.2 M 76 / 65 / 62
+            const int U = N <= (1 << 19) ? 2 : (N <= (1 << 21) ? 4 : 8);
+            look_blocks = grid1d(N, 1024 * U);
+            { fs_status ss = need_look(ctx, look_blocks); if (ss != FS_OK) return ss; }
+            if (U == 2) FS_LAUNCH_LIST(2);
+            else if (U == 4) FS_LAUNCH_LIST(4);
+            else FS_LAUNCH_LIST(8);
+#undef FS_LAUNCH_LIST
+            list_len = reinterpret_cast<const int *>(ctx->cursor + CUR_LIST);
+            cleared = true;
         }
         list = ctx->vlist;
     }
-    int *cell_count = nullptr;
-    ctx->slots_N = 0;
-    // every wave that draws chunks (all four of a k_solve block, the producer of a k_solve_ws block) owns the
-    // chunk of its own number to begin with; the shared cursor starts behind those
-    const unsigned drawers = (unsigned)(blocks * wpb);
-    if (d_slot) {
-        fs_status cs = clear_solve_counts(ctx, ncell, drawers, (unsigned)S.chunk);
-        if (cs != FS_OK) return cs;
-        cell_count = ctx->gcount_solve;
-    } else {
-        k_reset_cursor<<<1, 64, 0, st>>>(ctx->cursor, drawers, (unsigned)S.chunk);
-    }
+    if (!cleared) k_fill_zero_i32<<<cell_count ? (int)std::min<long long>(grid1d(ncounts, 256), 4096) : 1, 256, 0, st>>>(ncounts, cell_count, ctx->cursor, drawers, (unsigned)S.chunk);
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (ctx->timing && hipEventCreate(&ev0) == hipSuccess && hipEventCreate(&ev1) == hipSuccess) (void)hipEventRecord(ev0, st);
     if (lds) {
@@ -763,13 +783,13 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     }
     const dim3 ub(grid1d(N, 256), K);       // one thread per pair: x = point, y = initial state
     if (with_J && voxel_list)
-        k_solve_unpack<true, true><<<ub, 256, 0, st>>>(N, S.total, ctx->vcnt, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot);
+        k_solve_unpack<true, true><<<ub, 256, 0, st>>>(N, S.total, ctx->vcnt, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot, ctx->look, look_blocks);
     else if (with_J)
-        k_solve_unpack<true, false><<<ub, 256, 0, st>>>(N, S.total, nullptr, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot);
+        k_solve_unpack<true, false><<<ub, 256, 0, st>>>(N, S.total, nullptr, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot, ctx->look, look_blocks);
     else if (voxel_list)
-        k_solve_unpack<false, true><<<ub, 256, 0, st>>>(N, S.total, ctx->vcnt, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot);
+        k_solve_unpack<false, true><<<ub, 256, 0, st>>>(N, S.total, ctx->vcnt, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot, ctx->look, look_blocks);
     else
-        k_solve_unpack<false, false><<<ub, 256, 0, st>>>(N, S.total, nullptr, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot);
+        k_solve_unpack<false, false><<<ub, 256, 0, st>>>(N, S.total, nullptr, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot, ctx->look, look_blocks);
     fs_status lst = launch_status(ctx, "fs_solve");
     if (lst == FS_OK && d_slot) {
         ctx->slots_N = N;
@@ -836,7 +856,8 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
         k_fill_zero_i32<<<(int)std::min<long long>(grid1d(ncp + 1, 256), 4096), 256, 0, st>>>(ncp + 1, ctx->gcount);
         if (N > 0) k_grad_count<<<grid1d((long long)N * K, 256), 256, 0, st>>>(G, d_xc, d_conv, d_pose, N, K, ncell, ctx->gcount, ctx->gpos);
     }
-    { fs_status ss = scan_exclusive(ctx, (int)ncp, ctx->gcount, counts); if (ss != FS_OK) return ss; }
+    int look_blocks;
+    { fs_status ss = scan_exclusive(ctx, (int)ncp, ctx->gcount, counts, &look_blocks); if (ss != FS_OK) return ss; }
     if (N > 0) {
         // small batches: several threads share a point's lanes so that the chip has enough threads in flight
         const int groups = N >= (1 << 19) ? 1 : (K >= 8 ? 8 : (K >= 4 ? 4 : (K >= 2 ? 2 : 1)));
@@ -866,7 +887,7 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
         k_grad_nodes_z<<<grid1d(nodes, 256), 256, 0, st>>>(G, ncell, ctx->gcount, ctx->grec, ctx->GT);
     // (dL/dW on a second stream beside dL/dB, joined before the call returns: both kernels then take twice as long,
     // 156 + 132 us instead of 77 + 79 on the 8-pose grid, and the step gains nothing.)
-    k_grad_weights_node<<<grid1d(G.V * ((G.nb + 7) / 8), 256), 256, sizeof(float) * G.P * G.nb * 12, st>>>(G, ctx->GT, ctx->Bdev, d_gW);
+    k_grad_weights_node<<<grid1d(G.V * ((G.nb + 7) / 8), 256), 256, sizeof(float) * G.P * G.nb * 12, st>>>(G, ctx->GT, ctx->Bdev, d_gW, ctx->look, look_blocks);
     const int nout = G.nb * 12, nparts = ctx->gb_blocks * 4;
     const dim3 gbg(ctx->gb_blocks, (G.P + GB_POSES - 1) / GB_POSES);
     switch ((G.nb + 15) / 16) {

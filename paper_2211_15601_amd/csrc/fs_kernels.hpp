@@ -360,103 +360,141 @@ __global__ __launch_bounds__(256) void k_corr_count(GridP G, CorrP C, const floa
     if (valid) slot[(long long)p * G.V + v] = base + rank;      // a position inside the cell's list
 }
 
-// Exclusive prefix sum of a[0..n) in place, a[n] = total.  Three launches: per-tile sums (tile = 4096
-// entries), a single-block scan of the tile sums, then every tile scans itself from its carry-in.
-constexpr int SCAN_TILE = 4096;   // 1024 threads x 4 entries
+// ---- prefix sums over blocks in one pass (decoupled look-back) ------------------------------------------------------
+// Every block takes a ticket (its place in the order), publishes the sum of its part, and adds up what the blocks before
+// it have published until it meets one that knows the sum of everything up to itself.  A block waits only for blocks with
+// lower tickets, which are running already and publish their own sums before they wait for anything: every wait ends.
+// look[0]: tickets given out; look[LOOK_HEAD + t]: {state, value} of ticket t.  All words are zero when the kernel starts: the
+// kernel that follows it in the same call clears what it used (look_clear), so that nothing about a call is kept on the
+// host and a captured graph replays.  (A count of finished blocks, whose last one clears, is a second atomic per block.)
+// Tickets are atomics on one address, served one after the other, hence a few hundred blocks at most for all but the
+// largest inputs.
+typedef unsigned long long u64;
+constexpr u64 LOOK_SUM = 1ull << 32, LOOK_PREFIX = 2ull << 32;
+constexpr int LOOK_HEAD = 16;        // the ticket counter has a cache line of its own
 
-__device__ __forceinline__ int block_exclusive_scan_1024(int v, int *total)
+__device__ __forceinline__ u64 look_load(u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void look_store(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// the block's ticket (all threads; one barrier)
+__device__ __forceinline__ int look_ticket(u64 *__restrict__ look)
 {
-    __shared__ int wsum[16];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    int inc = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(inc, d);
-        if (lane >= d) inc += o;
-    }
-    __syncthreads();                       // wsum may still be read by a previous call
-    if (lane == 63) wsum[wid] = inc;
+    __shared__ int s_ticket;
+    if (threadIdx.x == 0) s_ticket = (int)atomicAdd(reinterpret_cast<unsigned *>(look), 1u);
     __syncthreads();
-    int carry = 0, tot = 0;
+    return s_ticket;
+}
+// sum of the blocks before ticket t, whose own sum is `mine`; by one whole wave
+__device__ __forceinline__ int look_back(u64 *__restrict__ look, int t, int mine, int lane)
+{
+    u64 *st = look + LOOK_HEAD;
+    if (lane == 0) look_store(st + t, (t == 0 ? LOOK_PREFIX : LOOK_SUM) | (unsigned)mine);
+    int before = 0;
+    for (int at = t; at > 0; at -= 64) {          // lane l looks at ticket at - 1 - l
+        const int i = at - 1 - lane;
+        u64 w;
+        unsigned long long prefix, unknown;
+        int first;
+        do {
+            w = i >= 0 ? look_load(st + i) : LOOK_PREFIX;
+            prefix = __ballot((w >> 32) == 2ull);
+            unknown = __ballot((w >> 32) == 0ull);
+            first = prefix ? __ffsll((long long)prefix) - 1 : 63;       // nearest block that knows everything up to itself
+            if (unknown & ((2ull << first) - 1ull)) __builtin_amdgcn_s_sleep(1);
+        } while (unknown & ((2ull << first) - 1ull));
+        int v = lane <= first ? (int)(unsigned)w : 0;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) {
-        const int x = wsum[w];
-        if (w < wid) carry += x;
-        tot += x;
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+        before += v;
+        if (prefix) break;
     }
-    *total = tot;
-    return carry + inc - v;
+    if (lane == 0 && t > 0) look_store(st + t, LOOK_PREFIX | (unsigned)(before + mine));
+    return before;
+}
+// by a kernel that runs after: the words that one of `blocks` blocks used (0: none)
+__device__ __forceinline__ void look_clear(u64 *__restrict__ look, int blocks)
+{
+    if (blocks == 0) return;
+    const long long stride = (long long)gridDim.x * gridDim.y * blockDim.x;
+    for (long long i = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < LOOK_HEAD + blocks; i += stride) look[i] = 0ull;
 }
 
-__global__ __launch_bounds__(1024) void k_scan_tile_sums(int n, const int *__restrict__ a, int *__restrict__ sums)
+// sums of the block's waves (up to 16 U of them per thread group) -> exclusive prefix within the block in s_tot[0 .. n),
+// return value (first wave only): the block's sum
+__device__ __forceinline__ int scan_totals(int *s_tot, int n, int lane)
 {
-    const long long base = (long long)blockIdx.x * SCAN_TILE + threadIdx.x * 4;
-    int v = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (base + e < n) v += a[base + e];
-    int tot;
-    block_exclusive_scan_1024(v, &tot);
-    if (threadIdx.x == 0) sums[blockIdx.x] = tot;
-}
-
-// sums[0..m) -> exclusive scan in place, sums[m] = total (one block, loops over m in steps of 1024);
-// also clears *also_zero when given (saves the caller a launch)
-__global__ __launch_bounds__(1024) void k_scan_sums(int m, int *__restrict__ sums, int *__restrict__ also_zero)
-{
-    if (also_zero && threadIdx.x == 0) *also_zero = 0;
     int run = 0;
-    for (int s0 = 0; s0 < m; s0 += 1024) {
-        const int i = s0 + threadIdx.x;
-        const int v = i < m ? sums[i] : 0;
-        int tot;
-        const int ex = block_exclusive_scan_1024(v, &tot);
-        if (i < m) sums[i] = run + ex;
-        run += tot;
+    for (int b = 0; b < n; b += 64) {
+        const int t = b + lane < n ? s_tot[b + lane] : 0;
+        int inc = t;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(inc, d);
+            if (lane >= d) inc += o;
+        }
+        if (b + lane < n) s_tot[b + lane] = run + inc - t;
+        run += __shfl(inc, 63);
     }
-    if (threadIdx.x == 0) sums[m] = run;
+    return run;
 }
 
-// out[i] = exclusive prefix of a (out may be a itself), out[n] = total.  SCANNED: sums holds the exclusive scan
-// of the tile sums (k_scan_sums ran); otherwise it holds the raw tile sums and every block adds up the ones
-// before its own tile itself (worth it while there are few tiles: one launch less).
-template <bool SCANNED>
-__global__ __launch_bounds__(1024) void k_scan_tiles(int n, const int *a, int *out, const int *__restrict__ sums, int m,
-                                                     int *__restrict__ also_zero)
+// Exclusive prefix sum of src[0..n) into out (may be src), out[n] = total; src and out 16-byte aligned.  PER (a multiple of 4) entries per
+// thread, 1024 threads.  Bound: memory, and the launch.  (Tile sums and a second pass over the tiles, two launches: 21 us
+// on 4.2 M entries, 9 us on 65 k; now 13 and 5.)
+template <int PER>
+__global__ __launch_bounds__(1024) void k_scan(int n, const int *src, int *out, u64 *__restrict__ look)
 {
-    const long long base = (long long)blockIdx.x * SCAN_TILE + threadIdx.x * 4;
-    int e4[4], v = 0;
+    __shared__ int s_tot[16 * (PER / 4)], s_before;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int t = look_ticket(look);
+    const long long base = (long long)t * (1024 * PER) + threadIdx.x * 4;
+    int4 e[PER / 4];
+    int sum[PER / 4], at[PER / 4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        e4[e] = base + e < n ? a[base + e] : 0;
-        v += e4[e];
-    }
-    int carry_in, grand = 0;
-    if (SCANNED) {
-        carry_in = sums[blockIdx.x];
-        if (blockIdx.x == 0 && threadIdx.x == 0) grand = sums[m];
-    } else {
-        int before = 0, all = 0;
-        for (int j = threadIdx.x; j < m; j += 1024) {
-            const int x = sums[j];
-            all += x;
-            if (j < (int)blockIdx.x) before += x;
+    for (int b = 0; b < PER / 4; ++b) {
+        const long long i = base + b * 4096;
+        e[b] = make_int4(0, 0, 0, 0);
+        if (i + 3 < n) e[b] = *reinterpret_cast<const int4 *>(src + i);
+        else if (i < n) {
+            e[b].x = src[i];
+            if (i + 1 < n) e[b].y = src[i + 1];
+            if (i + 2 < n) e[b].z = src[i + 2];
         }
-        int t0, t1;
-        (void)block_exclusive_scan_1024(before, &t0);
-        (void)block_exclusive_scan_1024(all, &t1);
-        carry_in = t0;
-        grand = t1;
-        if (also_zero && blockIdx.x == 0 && threadIdx.x == 0) *also_zero = 0;
-    }
-    int tot;
-    int run = carry_in + block_exclusive_scan_1024(v, &tot);
+        sum[b] = e[b].x + e[b].y + e[b].z + e[b].w;
+        int inc = sum[b];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if (base + e < n) out[base + e] = run;
-        run += e4[e];
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(inc, d);
+            if (lane >= d) inc += o;
+        }
+        at[b] = inc - sum[b];
+        if (lane == 63) s_tot[b * 16 + wid] = inc;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = grand;
+    __syncthreads();
+    if (wid == 0) {
+        const int mine = scan_totals(s_tot, 16 * (PER / 4), lane);
+        const int before = look_back(look, t, mine, lane);
+        if (lane == 0) {
+            s_before = before;
+            if (t == (int)gridDim.x - 1) out[n] = before + mine;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < PER / 4; ++b) {
+        const long long i = base + b * 4096;
+        int4 o;
+        o.x = s_before + s_tot[b * 16 + wid] + at[b];
+        o.y = o.x + e[b].x;
+        o.z = o.y + e[b].y;
+        o.w = o.z + e[b].z;
+        if (i + 3 < n) *reinterpret_cast<int4 *>(out + i) = o;
+        else if (i < n) {
+            out[i] = o.x;
+            if (i + 1 < n) out[i + 1] = o.y;
+            if (i + 2 < n) out[i + 2] = o.z;
+        }
+    }
 }
 
 // Every node goes to its place in its cell's list as {image[3], node index}: the selection below then reads its
@@ -464,8 +502,10 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(int n, const int *a, int *o
 // loads of its image in each of the three passes: k_corr_select 127 us on the 8-pose grid.)
 __global__ __launch_bounds__(256) void k_corr_scatter(GridP G, CorrP C, const float *__restrict__ Y,
                                                       const int *__restrict__ cell_of, const int *__restrict__ offset,
-                                                      const int *__restrict__ slot, float4 *__restrict__ sample)
+                                                      const int *__restrict__ slot, float4 *__restrict__ sample, u64 *__restrict__ look,
+                                                      int look_blocks)
 {
+    look_clear(look, look_blocks);
     const long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const int p = blockIdx.y;
     if (v >= G.V) return;
@@ -644,18 +684,26 @@ __device__ __forceinline__ void read_record_J(const float4 *__restrict__ r, floa
     J[0] = b.y; J[1] = b.z; J[2] = b.w; J[3] = c.x; J[4] = c.y; J[5] = c.z; J[6] = c.w; J[7] = d.x; J[8] = d.y;
 }
 
-// Voxel-based initial states leave most lanes without a candidate (a ray sample in empty space has
-// none).  Pre-pass for the fused solve: candidates per point, prefix sum, then the list of pairs
-// that do have one, so that the solve kernel draws only those.
-// Per pose the lower corner of the box of node images and the size of a correspondence cell are put into LDS once per
-// block (the arithmetic of cell_index), and the number of candidates of a cell is one byte written by k_corr_select:
-// with the six box entries and the three candidate slots read per point through the vector cache -- nine gathered
-// loads of four bytes -- this kernel took 77 us on the 8-pose batch.
-__global__ __launch_bounds__(256) void k_voxel_count(GridP G, InitP I, long long N, const float *__restrict__ xq,
-                                                     const int32_t *__restrict__ pose, int *__restrict__ cnt,
-                                                     uint8_t *__restrict__ cnt8, int *__restrict__ gcell)
+// Words of the context's cursor array: CUR_ALL is the work cursor of the solve kernels; CUR_NONFINITE holds the serial
+// number of the last fs_precompute whose grid had an entry that is not finite.
+// CUR_XCD + j (j = 0 .. 7): the cursor of the j-th eighth of an ordered pair list, relative to the start of that eighth.
+// CUR_LIST: length of the list of pairs that have a candidate (k_voxel_list).
+constexpr int CUR_ALL = 0, CUR_LIST = 1, CUR_NONFINITE = 2, CUR_XCD = 4, CUR_WORDS = 12, N_XCD = 8;
+
+// The blocks of the solve kernel own their first chunk without asking: the shared cursor starts behind `nblocks`
+// chunks, the cursor of range j behind one chunk for every block b with b mod 8 = j.
+__device__ __forceinline__ void reset_cursors(unsigned *__restrict__ cursor, int i, unsigned nblocks, unsigned chunk)
 {
-    extern __shared__ float s_pose[];            // [P][6]: lower corner, cell size
+    if (i == 0) cursor[CUR_ALL] = nblocks * chunk;
+    if (i < N_XCD) cursor[CUR_XCD + i] = ((nblocks + (N_XCD - 1) - (unsigned)i) / N_XCD) * chunk;
+}
+
+// Per pose the lower corner of the box of node images and the size of a correspondence cell (the arithmetic of cell_index)
+// into LDS, by all threads of the block; corr_cell: pose * ncell + correspondence cell of a point.
+// (With the six box entries and the three candidate slots read per point through the vector cache -- nine gathered loads
+// of four bytes instead of one byte -- counting the candidates of the 8-pose batch took 77 instead of 43 us.)
+__device__ __forceinline__ void corr_boxes(const GridP &G, const InitP &I, float *s_pose)
+{
     for (int i = threadIdx.x; i < G.P * 3; i += blockDim.x) {
         const int p = i / 3, a = i - 3 * p;
         const float *bb = I.bbox + p * 6;
@@ -664,27 +712,102 @@ __global__ __launch_bounds__(256) void k_voxel_count(GridP G, InitP I, long long
         s_pose[p * 6 + 3 + a] = (bb[3 + a] - bb[a]) / (float)na;
     }
     __syncthreads();
-    const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    const int p = pose_of(pose, n, G.P);
+}
+__device__ __forceinline__ int corr_cell(const InitP &I, const float *s_pose, int p, const float y[3])
+{
     const float *sp = s_pose + p * 6;
-    const int ci = (cell_coord(xq[n], sp[0], sp[3], I.C.cx) * I.C.cy + cell_coord(xq[N + n], sp[1], sp[4], I.C.cy)) * I.C.cz +
-                   cell_coord(xq[2 * N + n], sp[2], sp[5], I.C.cz);
-    const int gc = p * I.C.ncell + ci;
-    const int m = I.ccnt[gc];
-    cnt[n] = m;
-    cnt8[n] = (uint8_t)m;
-    gcell[n] = gc;
+    return p * I.C.ncell + (cell_coord(y[0], sp[0], sp[3], I.C.cx) * I.C.cy + cell_coord(y[1], sp[1], sp[4], I.C.cy)) * I.C.cz +
+           cell_coord(y[2], sp[2], sp[5], I.C.cz);
 }
 
-// list entry of a pair: {point n, (pose * ncell + correspondence cell) << 3 | k}
-__global__ __launch_bounds__(256) void k_voxel_expand(long long N, const int *__restrict__ offs, const int *__restrict__ gcell,
-                                                      int2 *__restrict__ list)
+// Voxel-based initial states leave most lanes without a candidate (a ray sample in empty space has none): the list of the
+// pairs that have one, {point n, (pose * ncell + correspondence cell) << 3 | k}, from which the solve draws.  The
+// list is in the order of the points: parts of it in the order in which blocks arrive would mix up to two million
+// points, i.e. several poses' grids (Broyden kernel on the 8-pose batch 1447 instead of 1330 us).  A block takes 1024 U
+// consecutive points.  The counts of the solve's converged lanes (may be null) and its cursor are cleared on the way.
+// Bound: the chain of tickets and memory (17 bytes read or written per point, 8 per pair).  (A counting pass, a scan of two launches,
+// an expanding pass and a clearing pass: 28 us on 1 M ray samples, 42 us on 2 M, 85 us on the 8-pose batch; now 13, 24 and 62.)
+template <int U>
+__global__ __launch_bounds__(1024) void k_voxel_list(GridP G, InitP I, long long N, int K, const float *__restrict__ xq,
+                                                     const int32_t *__restrict__ pose, uint8_t *__restrict__ cnt8,
+                                                     int2 *__restrict__ list, unsigned *__restrict__ cursor,
+                                                     unsigned nblocks, unsigned chunk, int *__restrict__ counts, long long ncounts,
+                                                     u64 *__restrict__ look)
 {
+    extern __shared__ float s_pose[];            // [P][6]
+    __shared__ int s_tot[16 * U], s_base;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, ticket = look_ticket(look);
+    if (blockIdx.x == 0 && threadIdx.x < N_XCD) reset_cursors(cursor, (int)threadIdx.x, nblocks, chunk);
+    if (counts)
+        for (long long i = (long long)blockIdx.x * 1024 + threadIdx.x; i < ncounts; i += (long long)gridDim.x * 1024) counts[i] = 0;
+    const long long n0 = (long long)ticket * (1024 * U);
+    float y[U][3];
+    int p[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const long long n = n0 + u * 1024 + threadIdx.x;
+        p[u] = -1;
+        y[u][0] = y[u][1] = y[u][2] = 0.0f;
+        if (n < N) {
+            p[u] = pose_of(pose, n, G.P);
+#pragma unroll
+            for (int r = 0; r < 3; ++r) y[u][r] = xq[r * N + n];
+        }
+    }
+    corr_boxes(G, I, s_pose);
+    int gc[U], m[U], at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        gc[u] = m[u] = 0;
+        if (p[u] >= 0) {
+            gc[u] = corr_cell(I, s_pose, p[u], y[u]);
+            m[u] = I.ccnt[gc[u]];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (p[u] >= 0) cnt8[n0 + u * 1024 + threadIdx.x] = (uint8_t)m[u];
+        int all = 0;
+        at[u] = 0;
+        for (int k = 0; k < K; ++k) {
+            const unsigned long long b = __ballot(k < m[u]);
+            at[u] += __popcll(b & ((1ull << lane) - 1ull));
+            all += __popcll(b);
+        }
+        if (lane == 0) s_tot[u * 16 + wid] = all;
+    }
+    __syncthreads();
+    if (wid == 0) {
+        const int mine = scan_totals(s_tot, 16 * U, lane);
+        const int before = look_back(look, ticket, mine, lane);
+        if (lane == 0) {
+            s_base = before;
+            if (ticket == (int)gridDim.x - 1) cursor[CUR_LIST] = (unsigned)(before + mine);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int n = (int)(n0 + u * 1024 + threadIdx.x);
+        const long long o = (long long)s_base + s_tot[u * 16 + wid] + at[u];
+        for (int k = 0; k < m[u]; ++k)
+            list[o + k] = make_int2(n, (gc[u] << 3) | k);
+    }
+}
+
+// Candidates and cells of the points for a list that is to be ordered by place.
+__global__ __launch_bounds__(256) void k_voxel_count(GridP G, InitP I, long long N, const float *__restrict__ xq,
+                                                     const int32_t *__restrict__ pose, uint8_t *__restrict__ cnt8,
+                                                     int *__restrict__ gcell)
+{
+    extern __shared__ float s_pose[];            // [P][6]
+    corr_boxes(G, I, s_pose);
     const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= N) return;
-    const int b = offs[n], e = offs[n + 1], gc = gcell[n];
-    for (int j = b; j < e; ++j) list[j] = make_int2((int)n, (gc << 3) | (j - b));
+    const float y[3] = {xq[n], xq[N + n], xq[2 * N + n]};
+    const int gc = corr_cell(I, s_pose, pose_of(pose, n, G.P), y);
+    cnt8[n] = I.ccnt[gc];
+    gcell[n] = gc;
 }
 
 // The list of pairs, ordered by place: all pairs whose query point falls into the same column of correspondence cells
@@ -716,8 +839,9 @@ __global__ __launch_bounds__(1024) void k_sort_hist(long long N, int cz, int nb,
 // list entry of a pair: {point n, (pose * ncell + correspondence cell) << 3 | k}
 __global__ __launch_bounds__(1024) void k_sort_scatter(long long N, int cz, int nb, const int *__restrict__ gcell,
                                                        const uint8_t *__restrict__ cnt8, const int *__restrict__ start,
-                                                       int2 *__restrict__ list)
+                                                       int2 *__restrict__ list, u64 *__restrict__ look, int look_blocks)
 {
+    look_clear(look, look_blocks);
     extern __shared__ int s_cnt[];
     for (int i = threadIdx.x; i < nb; i += blockDim.x) s_cnt[i] = start[(long long)i * gridDim.x + blockIdx.x];
     __syncthreads();
@@ -741,8 +865,10 @@ template <bool WITH_J, bool NOCAND>
 __global__ __launch_bounds__(256) void k_solve_unpack(long long N, long long total, const uint8_t *__restrict__ cand_cnt,
                                                       const float4 *__restrict__ rec, float *__restrict__ o_x,
                                                       uint8_t *__restrict__ o_conv, float *__restrict__ o_J,
-                                                      uint8_t *__restrict__ o_it, int32_t *__restrict__ o_slot)
+                                                      uint8_t *__restrict__ o_it, int32_t *__restrict__ o_slot,
+                                                      u64 *__restrict__ look, int look_blocks)
 {
+    look_clear(look, look_blocks);
     const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;      // grid: points x initial states
     if (n >= N) return;
     const long long pq = k * N + n;
@@ -767,24 +893,6 @@ __global__ __launch_bounds__(256) void k_solve_unpack(long long N, long long tot
 #pragma unroll
         for (int e = 0; e < 9; ++e) o_J[(k * 9 + e) * N + n] = J[e];
     }
-}
-
-// Words of the context's cursor array: CUR_ALL is the work cursor of the solve kernels; CUR_NONFINITE holds the serial
-// number of the last fs_precompute whose grid had an entry that is not finite.
-// CUR_XCD + j (j = 0 .. 7): the cursor of the j-th eighth of an ordered pair list, relative to the start of that eighth.
-constexpr int CUR_ALL = 0, CUR_NONFINITE = 2, CUR_XCD = 4, CUR_WORDS = 12, N_XCD = 8;
-
-// The blocks of the solve kernel own their first chunk without asking: the shared cursor starts behind `nblocks`
-// chunks, the cursor of range j behind one chunk for every block b with b mod 8 = j.
-__device__ __forceinline__ void reset_cursors(unsigned *__restrict__ cursor, int i, unsigned nblocks, unsigned chunk)
-{
-    if (i == 0) cursor[CUR_ALL] = nblocks * chunk;
-    if (i < N_XCD) cursor[CUR_XCD + i] = ((nblocks + (N_XCD - 1) - (unsigned)i) / N_XCD) * chunk;
-}
-
-__global__ void k_reset_cursor(unsigned *__restrict__ cursor, unsigned nblocks, unsigned chunk)
-{
-    if (blockIdx.x == 0) reset_cursors(cursor, (int)threadIdx.x, nblocks, chunk);
 }
 
 // One position in its cell's list for every lane with `want` (wave-wide call; cell: pose * ncell + grid cell): the lanes of
@@ -2212,7 +2320,7 @@ __global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(Gri
 // cell of x* (pass 1 below, or the positions k_solve hands out), crowded cells are summed once per
 // corner (k_grad_pieces), and every grid node then adds what its 8 adjacent cells hold (k_grad_nodes_p).
 
-// a[0..n) = 0; `cursors` (may be null): the solve kernels' work cursor is reset on the way (as k_reset_cursor does)
+// a[0..n) = 0; `cursors` (may be null): the solve kernels' work cursor is reset on the way
 __global__ void k_fill_zero_i32(long long n, int *__restrict__ a, unsigned *__restrict__ cursors = nullptr,
                                 unsigned nblocks = 0u, unsigned chunk = 0u)
 {
@@ -2822,8 +2930,10 @@ __global__ __launch_bounds__(256) void k_grad_nodes_z(GridP G, int ncell, const 
 // in neighbouring threads, so the node's G_T records come from the same cache lines and the stores are
 // contiguous); the bone transforms are staged in LDS.
 __global__ __launch_bounds__(256) void k_grad_weights_node(GridP G, const float *__restrict__ GT,
-                                                           const float *__restrict__ B, float *__restrict__ gW)
+                                                           const float *__restrict__ B, float *__restrict__ gW, u64 *__restrict__ look,
+                                                           int look_blocks)
 {
+    look_clear(look, look_blocks);
     extern __shared__ float sB[];
     const int nB = G.P * G.nb * 12;
     for (int i = threadIdx.x; i < nB; i += blockDim.x) sB[i] = B[i];
