@@ -33,10 +33,10 @@ struct fs_ctx {
     float *GT;         // [P][V][12] gradient w.r.t. the transform grid (allocated on first fs_grad)
     // correspondence grid (voxel init)
     float *Y;          // [P][V][3]
-    unsigned *bb_ord;  // [P][EXTENT_BLOCKS][6]: per-block extents of the node images (k_corr_extent)
+    unsigned *bb_ord;  // [P][6][blocks of k_precompute]: per-block extents of the node images
     float *bbox;       // [P][6]
     int *cell_of;      // [P][V]
-    int *count;        // [P*ncell + 1] counts, then offsets
+    int *count, *offset;   // [P*ncell] nodes per correspondence cell; [P*ncell + 1] where its list starts
     int *fill;         // [P][V] arrival slot of a node inside its cell
     float4 *order;     // [P][V] the nodes sorted by correspondence cell: {image[3], node index}
     int32_t *cand;     // [P][ncell][ck]
@@ -174,7 +174,7 @@ int grid1d(long long n, int block) { return (int)((n + block - 1) / block); }
 void free_all(fs_ctx *c)
 {
     void *ptrs[] = {c->T, c->Bdev, c->Binv, c->Bok, c->GT, c->Y, c->bb_ord, c->bbox,
-                    c->cell_of, c->count, c->fill, c->order, c->cand, c->cursor, c->gcount, c->gcount_solve, c->gpos, c->grec, c->look, c->srec, c->gpart, c->vlist, c->cinit, c->vcnt, c->vgcell, c->vhist, c->ccnt};
+                    c->cell_of, c->count, c->offset, c->fill, c->order, c->cand, c->cursor, c->gcount, c->gcount_solve, c->gpos, c->grec, c->look, c->srec, c->gpart, c->vlist, c->cinit, c->vcnt, c->vgcell, c->vhist, c->ccnt};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -384,8 +384,8 @@ fs_status fs_create(const fs_grid_desc *desc, const fs_params *params, void *hip
         CorrP &C = c->C;
         C.cx = params->corr_nx; C.cy = params->corr_ny; C.cz = params->corr_nz; C.ck = params->corr_k;
         C.ncell = C.cx * C.cy * C.cz;
-        ok = dev_alloc(&c->Y, P * V * 3) && dev_alloc(&c->bb_ord, P * EXTENT_BLOCKS * 6) && dev_alloc(&c->bbox, P * 6) &&
-             dev_alloc(&c->cell_of, P * V) && dev_alloc(&c->count, P * C.ncell + 1) && dev_alloc(&c->fill, P * V) &&
+        ok = dev_alloc(&c->Y, P * V * 3) && dev_alloc(&c->bb_ord, P * 6 * (size_t)grid1d(V, 256)) && dev_alloc(&c->bbox, P * 6) &&
+             dev_alloc(&c->cell_of, P * V) && dev_alloc(&c->count, P * C.ncell) && dev_alloc(&c->offset, P * C.ncell + 1) && dev_alloc(&c->fill, P * V) &&
              dev_alloc(&c->order, P * V) && dev_alloc(&c->cand, P * (size_t)C.ncell * C.ck) && dev_alloc(&c->ccnt, P * (size_t)C.ncell) &&
              dev_alloc(&c->cinit, P * (size_t)C.ncell * C.ck * 4);
     }
@@ -478,25 +478,27 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
     hipStream_t st = ctx->stream;
     ++ctx->pre_serial;
     const bool voxel = ctx->prm.init_mode == FS_INIT_VOXEL;
-    if (voxel) {
-        const int ncp0 = G.P * ctx->C.ncell;
-        k_corr_reset<<<grid1d(ncp0, 256), 256, 0, st>>>(G.P, ctx->C.ncell, ctx->count);
-    }
-    k_precompute<<<dim3(grid1d(G.V, 256), (G.P + PRE_POSES - 1) / PRE_POSES), 256, 0, st>>>(G, d_W, d_B, ctx->T, ctx->Bdev, ctx->Binv, ctx->Bok,
-                                                   reinterpret_cast<int *>(ctx->cursor + CUR_NONFINITE), ctx->pre_serial,
-                                                   voxel ? ctx->Y : nullptr);
+    const int ncp = voxel ? G.P * ctx->C.ncell : 0, vblocks = grid1d(G.V, 256);
+    // poses per pass over the weights: see k_precompute
+    const bool wide = (long long)vblocks * ((G.P + 3) / 4) >= 4ll * ctx->n_cus;
+#define FS_LAUNCH_PRE(NP)                                                                                              \
+    k_precompute<NP><<<(vblocks + N_XCD - 1) / N_XCD * N_XCD * ((G.P + (NP) - 1) / (NP)), 256, 0, st>>>(               \
+        G, d_W, d_B, ctx->T, ctx->Bdev, ctx->Binv, ctx->Bok, reinterpret_cast<int *>(ctx->cursor + CUR_NONFINITE),     \
+        ctx->pre_serial, voxel ? ctx->Y : nullptr, ctx->bb_ord, ctx->count, ncp, vblocks, (G.P + (NP) - 1) / (NP))
+    if (wide) FS_LAUNCH_PRE(4);
+    else FS_LAUNCH_PRE(1);
+#undef FS_LAUNCH_PRE
     if (voxel) {
         const CorrP &C = ctx->C;
-        const int ncp = G.P * C.ncell;
-        const dim3 gv(grid1d(G.V, 256), G.P);
-        const int eblk = std::min(grid1d(G.V, 256), EXTENT_BLOCKS);
-        k_corr_extent<<<dim3(eblk, G.P), 256, 0, st>>>(G, ctx->Y, ctx->bb_ord);
-        k_corr_bbox<<<G.P, 384, 0, st>>>(eblk, ctx->bb_ord, ctx->bbox);
-        k_corr_count<<<gv, 256, 0, st>>>(G, C, ctx->Y, ctx->bbox, ctx->cell_of, ctx->count, ctx->fill);
+        const bool own_box = vblocks <= EXTENT_OWN;
+        if (!own_box) k_corr_bbox<<<G.P * 6, 1024, 0, st>>>(vblocks, ctx->bb_ord, ctx->bbox);
+        const int lz = G.nz > 8 ? 4 : (G.nz > 4 ? 3 : 2), nbx = grid1d(G.nx, BRICK >> (lz + 3)), nby = grid1d(G.ny, 8), nbz = grid1d(G.nz, 1 << lz);
+        k_corr_count<<<dim3(nbx * nby * nbz, G.P), BRICK, 0, st>>>(G, C, ctx->Y, ctx->bb_ord, vblocks, own_box, ctx->bbox, lz, nby, nbz,
+                                                                   ctx->cell_of, ctx->count, ctx->fill);
         int look_blocks;
-        { fs_status ss = scan_exclusive(ctx, ncp, ctx->count, nullptr, &look_blocks); if (ss != FS_OK) return ss; }
-        k_corr_scatter<<<gv, 256, 0, st>>>(G, C, ctx->Y, ctx->cell_of, ctx->count, ctx->fill, ctx->order, ctx->look, look_blocks);
-        k_corr_select<<<grid1d((long long)ncp * WAVE, 256), 256, 0, st>>>(G, C, ctx->Y, ctx->bbox, ctx->count, ctx->order, ctx->cand, ctx->ccnt);
+        { fs_status ss = scan_exclusive(ctx, ncp, ctx->offset, ctx->count, &look_blocks); if (ss != FS_OK) return ss; }
+        k_corr_scatter<<<dim3(vblocks, G.P), 256, 0, st>>>(G, C, ctx->Y, ctx->cell_of, ctx->offset, ctx->fill, ctx->order, ctx->look, look_blocks);
+        k_corr_select<<<dim3(grid1d(C.ncell, 4), G.P), 256, 0, st>>>(G, C, ctx->bbox, ctx->offset, ctx->order, ctx->cand, ctx->ccnt);
         k_corr_init<<<grid1d((long long)ncp * C.ck, 256), 256, 0, st>>>(G, C, ctx->T, ctx->cand, ctx->cinit);
     }
     fs_status s = launch_status(ctx, "fs_precompute");

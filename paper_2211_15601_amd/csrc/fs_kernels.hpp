@@ -4,7 +4,7 @@
 
 namespace fs {
 
-constexpr int WAVE = 64;
+constexpr int WAVE = 64, N_XCD = 8;
 
 // pose index of point n, forced into [0, P) so that a bad index in the caller's array cannot send
 // a kernel outside the transform grids
@@ -62,94 +62,131 @@ __device__ __forceinline__ float ord2f(unsigned o)
     return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
 }
 
+// smallest v of the 64 lanes in lane 31, complement of the largest in lane 63; all lanes must call.  Lanes without a value: lo = hi = ~0.
+// (lo = v, hi = ~v: one exchange of the wave's halves leaves 32 lanes to each of the two.)
+__device__ __forceinline__ unsigned wave_extent(unsigned lo, unsigned hi)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+    unsigned v = min((unsigned)s[0], (unsigned)s[1]);
+#define FS_EXTENT_STEP(ctrl, rows) v = min(v, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)v, (ctrl), (rows), 0xf, false))
+    FS_EXTENT_STEP(0x111, 0xf);         // row_shr 1, 2, 4, 8: within rows of 16 lanes
+    FS_EXTENT_STEP(0x112, 0xf);
+    FS_EXTENT_STEP(0x114, 0xf);
+    FS_EXTENT_STEP(0x118, 0xf);
+    FS_EXTENT_STEP(0x142, 0xa);         // row_bcast 15 into rows 1 and 3
+#undef FS_EXTENT_STEP
+    return v;
+}
+
 // The first n_poses*n_bones threads also invert their bone's linear part for Eq. (8) and keep a copy
 // of the bone transforms for the backward.
 // Y (may be null; voxel-based initial states): the image y_v = T_v x_v of every node is written as well -- the
 // correspondence grid is built on those, and the transforms are in registers here anyway (a pass of its own would
-// read all of T again).
-#ifndef FS_PRE_POSES
-#define FS_PRE_POSES 4
-#endif
-constexpr int PRE_POSES = FS_PRE_POSES;     // poses that share one pass over a node's weights (8-pose grid: 2 -> 144 us, 4 -> 105, 8 -> 138)
+// read all of T again).  So are the extents of a block's images (bb_part[p][entry][block], ordered-integer images of the
+// floats: min x, y, z, max x, y, z), and the counters of the correspondence cells are cleared on the way.  (A kernel
+// each for the extents and the counters: two launches, 16 us together on the 8-pose grid.)
+// NP: poses that share one pass over a node's weights.  Large grids, bound by memory: four (8-pose 128x128x32 grid: 1 -> 109 us,
+// 2 -> 86, 4 -> 87; all groups of a node on one XCD: 110 -> 87).  Grids of fewer than four blocks of 256 nodes per CU: one,
+// so that there are waves to hide the latency of weights and transforms (4 poses of 61x47x13 nodes: 4 -> 27 us, 2 -> 16, 1 -> 10).
+template <int NP>
 __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__restrict__ W,
                                                     const float *__restrict__ B, float *__restrict__ T,
                                                     float *__restrict__ Bcopy, float *__restrict__ Binv,
                                                     uint8_t *__restrict__ Bok, int *__restrict__ nonfinite,
-                                                    int serial, float *__restrict__ Y)
+                                                    int serial, float *__restrict__ Y, unsigned *__restrict__ bb_part,
+                                                    int *__restrict__ ccount, int ncount, int vblocks, int groups)
 {
+    // block -> (nodes, group of poses): blocks go to the 8 XCDs in turn, the groups of the same nodes to the same XCD one
+    // after the other, so that its L2 has the weights
+    const int t = (int)blockIdx.x / N_XCD, bt = t / groups, group = t - bt * groups, blk = bt * N_XCD + (int)blockIdx.x % N_XCD;
+    if (blk >= vblocks) return;
     // *nonfinite = serial (the number of this call) tells the solve that this grid holds an entry that is not
     // finite: a record with weight zero may then not be skipped (0 * inf is not 0)
     __shared__ __attribute__((aligned(16))) float s_tiles[4][64 * 12];
-    float *s_tile = s_tiles[threadIdx.x >> 6];
-    const long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x, v0 = v - (threadIdx.x & 63);   // v0: the wave's first node
-    if (blockIdx.y == 0)
-        for (long long i = v; i < (long long)G.P * G.nb; i += (long long)gridDim.x * blockDim.x)
+    __shared__ unsigned s_ext[NP][4][6];
+    const int wib = threadIdx.x >> 6;
+    float *s_tile = s_tiles[wib];
+    const long long v = (long long)blk * blockDim.x + threadIdx.x, v0 = v - (threadIdx.x & 63);   // v0: the wave's first node
+    if (group == 0) {
+        for (long long i = v; i < (long long)G.P * G.nb; i += (long long)vblocks * blockDim.x)
             bone_inverse((int)i, B, Bcopy, Binv, Bok);
+        if (Y)
+            for (long long i = v; i < ncount; i += (long long)vblocks * blockDim.x) ccount[i] = 0;
+    }
     const bool live = v < G.V;                   // the last wave: its other lanes stay for the wave-wide stores
     const int nrows = (int)min(64ll, G.V - v0);
     const float *w = W + (live ? v : 0) * G.nb;
     const bool vec = (G.nb & 3) == 0;        // weight rows are 16-byte aligned: read them four at a time
     float xv[3] = {0.0f, 0.0f, 0.0f};
     if (Y && live) node_pos(G, v, xv);
-    // four poses share one pass over the node's weights; per pose the sum runs over the bones in order,
-    // first term a product, the rest fused multiply-adds
-    // blockIdx.y = group of PRE_POSES poses: twice the waves of one block per node tile, in different phases of
-    // load, arithmetic and store at any one time
-    for (int p0 = blockIdx.y * PRE_POSES; p0 < G.P; p0 += gridDim.y * PRE_POSES) {
-        const int np = min(PRE_POSES, G.P - p0);
-        float acc[PRE_POSES][12];
+    // per pose the sum runs over the bones in order, first term a product, the rest fused multiply-adds
+    const int p0 = group * NP, np = min(NP, G.P - p0);
+    float acc[NP][12];
 #pragma unroll
-        for (int q = 0; q < PRE_POSES; ++q)
+    for (int q = 0; q < NP; ++q)
 #pragma unroll
-            for (int e = 0; e < 12; ++e) acc[q][e] = 0.0f;
-        if (live) {
-            for (int b0 = 0; b0 < G.nb; b0 += 4) {
-                float wv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (vec) {
-                    const float4 w4 = *reinterpret_cast<const float4 *>(w + b0);
-                    wv[0] = w4.x; wv[1] = w4.y; wv[2] = w4.z; wv[3] = w4.w;
-                } else {
+        for (int e = 0; e < 12; ++e) acc[q][e] = 0.0f;
+    if (live) {
+        for (int b0 = 0; b0 < G.nb; b0 += 4) {
+            float wv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (vec) {
+                const float4 w4 = *reinterpret_cast<const float4 *>(w + b0);
+                wv[0] = w4.x; wv[1] = w4.y; wv[2] = w4.z; wv[3] = w4.w;
+            } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (b0 + j < G.nb) wv[j] = w[b0 + j];
-                }
+                for (int j = 0; j < 4; ++j)
+                    if (b0 + j < G.nb) wv[j] = w[b0 + j];
+            }
 #pragma unroll
-                for (int q = 0; q < PRE_POSES; ++q) {
-                    if (q < np) {
-                        const float *Bp = B + (long long)(p0 + q) * G.nb * 12;
+            for (int q = 0; q < NP; ++q) {
+                if (q < np) {
+                    const float *Bp = B + (long long)(p0 + q) * G.nb * 12;
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            if (b0 + j < G.nb) {
-                                if (b0 == 0 && j == 0) {
+                    for (int j = 0; j < 4; ++j) {
+                        if (b0 + j < G.nb) {
+                            if (b0 == 0 && j == 0) {
 #pragma unroll
-                                    for (int e = 0; e < 12; ++e) acc[q][e] = wv[0] * Bp[e];
-                                } else {
+                                for (int e = 0; e < 12; ++e) acc[q][e] = wv[0] * Bp[e];
+                            } else {
 #pragma unroll
-                                    for (int e = 0; e < 12; ++e) acc[q][e] = FS_FMA(wv[j], Bp[(b0 + j) * 12 + e], acc[q][e]);
-                                }
+                                for (int e = 0; e < 12; ++e) acc[q][e] = FS_FMA(wv[j], Bp[(b0 + j) * 12 + e], acc[q][e]);
                             }
                         }
                     }
                 }
             }
         }
+    }
 #pragma unroll
-        for (int q = 0; q < PRE_POSES; ++q) {
-            if (q < np) {                        // wave-uniform
-                if (live) {
-                    float big = 0.0f;
+    for (int q = 0; q < NP; ++q) {
+        if (q < np) {                        // wave-uniform
+            if (live) {
+                float big = 0.0f;
 #pragma unroll
-                    for (int e = 0; e < 12; ++e) big = __builtin_fmaxf(big, __builtin_fabsf(acc[q][e]) < __builtin_inff() ? 0.0f : 1.0f);
-                    if (big != 0.0f) *nonfinite = serial;
-                }
-                wave_store_rows<12>(T + ((long long)(p0 + q) * G.V + v0) * 12, acc[q], nrows, s_tile);
-                if (Y) {
-                    float y[3] = {0.0f, 0.0f, 0.0f};
-                    if (live) apply12(acc[q], xv, y);
-                    wave_store_rows<3>(Y + ((long long)(p0 + q) * G.V + v0) * 3, y, nrows, s_tile);
+                for (int e = 0; e < 12; ++e) big = __builtin_fmaxf(big, __builtin_fabsf(acc[q][e]) < __builtin_inff() ? 0.0f : 1.0f);
+                if (big != 0.0f) *nonfinite = serial;
+            }
+            wave_store_rows<12>(T + ((long long)(p0 + q) * G.V + v0) * 12, acc[q], nrows, s_tile);
+            if (Y) {
+                float y[3] = {0.0f, 0.0f, 0.0f};
+                if (live) apply12(acc[q], xv, y);
+                wave_store_rows<3>(Y + ((long long)(p0 + q) * G.V + v0) * 3, y, nrows, s_tile);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const unsigned o = f2ord(y[a]);
+                    const unsigned r = wave_extent(live ? o : ~0u, live ? ~o : ~0u);
+                    if ((threadIdx.x & 63) == 31) s_ext[q][wib][a] = r;
+                    if ((threadIdx.x & 63) == 63) s_ext[q][wib][3 + a] = ~r;
                 }
             }
         }
+    }
+    if (!Y) return;
+    __syncthreads();
+    if (threadIdx.x < 6 * np) {
+        const int q = threadIdx.x / 6, e = threadIdx.x - 6 * q;
+        const unsigned a = s_ext[q][0][e], b = s_ext[q][1][e], c = s_ext[q][2][e], d = s_ext[q][3][e];
+        bb_part[((long long)(p0 + q) * 6 + e) * vblocks + blk] = e < 3 ? min(min(a, b), min(c, d)) : max(max(a, b), max(c, d));
     }
 }
 
@@ -238,7 +275,7 @@ __global__ __launch_bounds__(256) void k_init_voxel(GridP G, CorrP C, const floa
                                                     float *__restrict__ o_x0, float *__restrict__ o_J,
                                                     uint8_t *__restrict__ o_v)
 {
-    // the candidate's initial state was computed once per pose by k_corr_init
+    // the candidate's initial state was computed once per pose (k_corr_init)
     const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= N * C.ck) return;
     const int k = (int)(q / N);
@@ -256,108 +293,98 @@ __global__ __launch_bounds__(256) void k_init_voxel(GridP G, CorrP C, const floa
 // ------------------------------------------------------------------------------------------------
 // Correspondence grid build (voxel-based initialisation).
 // ------------------------------------------------------------------------------------------------
-__global__ void k_corr_reset(int P, int ncell, int *__restrict__ count)
+// Bounding box of the images of all nodes of a pose, without atomics: k_precompute leaves the extent of every block's
+// share, one wave per entry reduces the blocks' values (all lanes of the wave; the answer in every lane).  (With atomicMin / atomicMax on the 6
+// words of a pose -- all in one cache line -- the atomics were the cost: about 3 ns each, 37 of 40 us on the 8-pose grid
+// with 256 blocks per pose, 145 us with 1024.)
+__device__ __forceinline__ unsigned reduce_extent(const unsigned *__restrict__ bb_part, int nblk, int p, int e, int first, int step)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < P * ncell) count[i] = 0;
-    if (i == 0) count[P * ncell] = 0;
-}
-
-// Bounding box per pose of the images of all nodes, in two steps without atomics: every block leaves the extent of its
-// share of the nodes in bb_part[p][block][6] (ordered-integer images of the floats: min x, y, z, max x, y, z), then one
-// wave per pose and entry reduces the blocks' values.  (With atomicMin / atomicMax on the 6 words of a pose -- all in
-// one cache line -- the atomics were the cost of the kernel: about 3 ns each, 37 of its 40 us on the 8-pose grid with
-// 256 blocks per pose, 145 us with 1024.)
-constexpr int EXTENT_BLOCKS = 512;      // blocks per pose at most
-__global__ __launch_bounds__(256) void k_corr_extent(GridP G, const float *__restrict__ Y, unsigned *__restrict__ bb_part)
-{
-    __shared__ unsigned smn[4][3], smx[4][3];
-    const int p = blockIdx.y;
-    unsigned mn[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, mx[3] = {0u, 0u, 0u};
-    for (long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x; v < G.V; v += (long long)gridDim.x * blockDim.x) {
-        const float *y = Y + ((long long)p * G.V + v) * 3;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const unsigned ov = f2ord(y[a]);
-            mn[a] = min(mn[a], ov);
-            mx[a] = max(mx[a], ov);
-        }
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-#pragma unroll
-        for (int sft = 32; sft >= 1; sft >>= 1) {
-            mn[a] = min(mn[a], (unsigned)__shfl_xor((int)mn[a], sft));
-            mx[a] = max(mx[a], (unsigned)__shfl_xor((int)mx[a], sft));
-        }
-    }
-    const int wid = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) { smn[wid][a] = mn[a]; smx[wid][a] = mx[a]; }
-    }
-    __syncthreads();
-    if (threadIdx.x < 3) {
-        const int a = threadIdx.x;
-        unsigned *o = bb_part + ((long long)p * gridDim.x + blockIdx.x) * 6;
-        o[a] = min(min(smn[0][a], smn[1][a]), min(smn[2][a], smn[3][a]));
-        o[3 + a] = max(max(smx[0][a], smx[1][a]), max(smx[2][a], smx[3][a]));
-    }
-}
-
-// one block of 6 waves per pose: wave e reduces entry e over the nblk blocks of k_corr_extent
-__global__ __launch_bounds__(384) void k_corr_bbox(int nblk, const unsigned *__restrict__ bb_part, float *__restrict__ bbox)
-{
-    const int p = blockIdx.x, e = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const unsigned *q = bb_part + ((long long)p * 6 + e) * nblk;
     const bool is_min = e < 3;
     unsigned r = is_min ? 0xffffffffu : 0u;
-    for (int b = lane; b < nblk; b += 64) {
-        const unsigned t = bb_part[((long long)p * nblk + b) * 6 + e];
-        r = is_min ? min(r, t) : max(r, t);
-    }
+    for (int b = first; b < nblk; b += step) r = is_min ? min(r, q[b]) : max(r, q[b]);
 #pragma unroll
     for (int sft = 32; sft >= 1; sft >>= 1) {
         const unsigned o = (unsigned)__shfl_xor((int)r, sft);
         r = is_min ? min(r, o) : max(r, o);
     }
-    if (lane == 0) bbox[p * 6 + e] = ord2f(r);
+    return r;
 }
 
-// Neighbouring nodes have neighbouring images, so the 64 nodes of a wave fall into a handful of cells: the
-// lanes of a wave that share a cell are counted together and one of them adds the group to the cell's
-// counter (device-scope atomics are executed outside the L2 and are the cost of this kernel).
-__global__ __launch_bounds__(256) void k_corr_count(GridP G, CorrP C, const float *__restrict__ Y,
-                                                    const float *__restrict__ bbox, int *__restrict__ cell_of,
-                                                    int *__restrict__ count, int *__restrict__ slot)
+// one block per pose and entry; only for grids of more than EXTENT_OWN blocks
+__global__ __launch_bounds__(1024) void k_corr_bbox(int nblk, const unsigned *__restrict__ bb_part, float *__restrict__ bbox)
 {
-    const long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int p = blockIdx.y;
-    const int lane = threadIdx.x & 63;
-    const bool valid = v < G.V;
-    int c = -1;
-    if (valid) {
-        const float *yp = Y + ((long long)p * G.V + v) * 3;
-        const float y[3] = {yp[0], yp[1], yp[2]};
-        c = cell_index(C, bbox + p * 6, y);
-        cell_of[(long long)p * G.V + v] = c;
+    __shared__ unsigned s_part[16];
+    const int p = blockIdx.x / 6, e = blockIdx.x - 6 * p;
+    const unsigned r = reduce_extent(bb_part, nblk, p, e, threadIdx.x, 1024);
+    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = r;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned t = s_part[0];
+        for (int i = 1; i < 16; ++i) t = e < 3 ? min(t, s_part[i]) : max(t, s_part[i]);
+        bbox[blockIdx.x] = ord2f(t);
     }
-    int leader = lane, rank = 0, members = 1;
-    unsigned long long todo = __ballot(valid);
-    while (todo) {
-        const int first = __ffsll((long long)todo) - 1;
-        const int key = __shfl(c, first);
-        const unsigned long long same = __ballot(valid && c == key);
-        if (valid && c == key) {
-            leader = first;
-            rank = __popcll(same & ((1ull << lane) - 1ull));
-            members = __popcll(same);
+}
+
+// The cell of every node's image, and the node's place in its cell's list.  Device-scope atomics are executed outside the
+// L2 and were the cost of this kernel, so a block of 1024 threads takes a brick of nodes (8 x 8 x 16; images of neighbours are
+// neighbours, a brick falls into a few dozen cells), counts per cell in an LDS hash table, and adds each cell once to its
+// counter.  (Lanes of a wave grouped by cell instead, 64 nodes along z: some 14 atomics per 64 nodes: 67 us on the
+// 8-pose grid, now 36.)
+// own_box: the block reduces the extents itself (up to EXTENT_OWN blocks of k_precompute; block 0 of a pose keeps the box).
+constexpr int EXTENT_OWN = 512;
+constexpr int BRICK = 1024, HASH = 2 * BRICK;
+__global__ __launch_bounds__(BRICK) void k_corr_count(GridP G, CorrP C, const float *__restrict__ Y, const unsigned *__restrict__ bb_part,
+                                                      int nblk, bool own_box, float *__restrict__ bbox, int lz, int nby, int nbz,
+                                                      int *__restrict__ cell_of, int *__restrict__ count, int *__restrict__ slot)
+{
+    __shared__ int s_key[HASH], s_cnt[HASH];
+    __shared__ float s_box[6];
+    const int p = blockIdx.y, wib = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int i = threadIdx.x; i < HASH; i += BRICK) {
+        s_key[i] = -1;
+        s_cnt[i] = 0;
+    }
+    if (wib < 6) {
+        const float r = own_box ? ord2f(reduce_extent(bb_part, nblk, p, wib, lane, 64)) : bbox[p * 6 + wib];
+        if (lane == 0) {
+            s_box[wib] = r;
+            if (own_box && blockIdx.x == 0) bbox[p * 6 + wib] = r;
         }
-        todo &= ~same;
     }
-    int base = 0;
-    if (valid && leader == lane) base = atomicAdd(count + p * C.ncell + c, members);
-    base = __shfl(base, leader);
-    if (valid) slot[(long long)p * G.V + v] = base + rank;      // a position inside the cell's list
+    __syncthreads();
+    // brick of 2^lz nodes along z, 8 along y, the rest along x
+    const int bz = (int)blockIdx.x % nbz, bt = (int)blockIdx.x / nbz, by = bt % nby, bx = bt / nby;
+    const int iz = (bz << lz) + (int)(threadIdx.x & ((1u << lz) - 1u)), iy = by * 8 + (int)((threadIdx.x >> lz) & 7u);
+    const int ix = bx * (BRICK >> (lz + 3)) + (int)(threadIdx.x >> (lz + 3));
+    const bool valid = ix < G.nx && iy < G.ny && iz < G.nz;
+    const long long i = (long long)p * G.V + ((long long)ix * G.ny + iy) * G.nz + iz;
+    int c = -1, h = 0, rank = 0;
+    if (valid) {
+        const float y[3] = {Y[i * 3], Y[i * 3 + 1], Y[i * 3 + 2]};
+        c = cell_index(C, s_box, y);
+        // at most BRICK keys in a table of twice the size: the search ends
+        h = (int)(((unsigned)c * 2654435761u) >> 21);
+        static_assert(HASH == 1 << 11, "hash bits");
+        while (true) {
+            int k = __hip_atomic_load(&s_key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (k == -1) {
+                k = atomicCAS(&s_key[h], -1, c);
+                if (k == -1) k = c;
+            }
+            if (k == c) break;
+            h = (h + 1) & (HASH - 1);
+        }
+        rank = atomicAdd(&s_cnt[h], 1);
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < HASH; t += BRICK)
+        if (s_cnt[t] > 0) s_cnt[t] = atomicAdd(count + p * C.ncell + s_key[t], s_cnt[t]);
+    __syncthreads();
+    if (valid) {
+        cell_of[i] = c;
+        slot[i] = s_cnt[h] + rank;      // a position inside the cell's list
+    }
 }
 
 // ---- prefix sums over blocks in one pass (decoupled look-back) ------------------------------------------------------
@@ -500,6 +527,7 @@ __global__ __launch_bounds__(1024) void k_scan(int n, const int *src, int *out, 
 // Every node goes to its place in its cell's list as {image[3], node index}: the selection below then reads its
 // samples as consecutive 16-byte entries.  (With a list of node indices alone every sample cost three gathered 4-byte
 // loads of its image in each of the three passes: k_corr_select 127 us on the 8-pose grid.)
+// (Up to 8192 cells scanned by every block in LDS instead of by a launch of its own: 9.6 instead of 4.8 + 4.6 us.)
 __global__ __launch_bounds__(256) void k_corr_scatter(GridP G, CorrP C, const float *__restrict__ Y,
                                                       const int *__restrict__ cell_of, const int *__restrict__ offset,
                                                       const int *__restrict__ slot, float4 *__restrict__ sample, u64 *__restrict__ look,
@@ -515,24 +543,45 @@ __global__ __launch_bounds__(256) void k_corr_scatter(GridP G, CorrP C, const fl
     sample[offset[c] + slot[i]] = make_float4(y[0], y[1], y[2], __int_as_float((int)v));
 }
 
+// smallest value of the 64 lanes; all lanes must call
+__device__ __forceinline__ u64 wave_min(u64 v)
+{
+#define FS_MIN_STEP(ctrl, rows)                                                                                        \
+    do {                                                                                                               \
+        const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(-1, (int)(unsigned)v, (ctrl), (rows), 0xf, false);   \
+        const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(-1, (int)(unsigned)(v >> 32), (ctrl), (rows), 0xf, false); \
+        const u64 o = (u64)hi << 32 | lo;                                                                              \
+        v = o < v ? o : v;                                                                                             \
+    } while (0)
+    FS_MIN_STEP(0x111, 0xf);            // row_shr 1, 2, 4, 8: within rows of 16 lanes
+    FS_MIN_STEP(0x112, 0xf);
+    FS_MIN_STEP(0x114, 0xf);
+    FS_MIN_STEP(0x118, 0xf);
+    FS_MIN_STEP(0x142, 0xa);            // row_bcast 15 into rows 1 and 3, row_bcast 31 into rows 2 and 3
+    FS_MIN_STEP(0x143, 0xc);
+#undef FS_MIN_STEP
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63), hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
+    return (u64)hi << 32 | lo;
+}
+
 // One wave per cell.  Candidate j is the sample with the smallest (distance^2 of its image to the
 // cell centre, node index) among those farther than r_sep (canonical distance) from candidates
 // 0..j-1: the same set, in the same order, as visiting the samples by increasing key and accepting
-// greedily.
-__global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const float *__restrict__ Y,
-                                                     const float *__restrict__ bbox, const int *__restrict__ offset,
+// greedily.  Bound: instruction issue, so the wave's minimum runs on DPP moves (the two halves of the key with lane
+// shuffles through the LDS, canonical positions also before any candidate: 84 us for 65,536 cells, 8.6 for 8192; now 72 and 6.6.)
+__global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const float *__restrict__ bbox, const int *__restrict__ offset,
                                                      const float4 *__restrict__ sample, int32_t *__restrict__ cand,
                                                      uint8_t *__restrict__ ccnt)
 {
     // accepted candidates' positions, per wave: the same for all lanes and indexed by a loop counter -- in registers
     // that indexing turns into chains of selects, from LDS it is one broadcast read per candidate
     __shared__ float4 s_acc[4][FS_MAX_CORR_K_DEV];
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    if (wave >= G.P * C.ncell) return;
-    const int p = wave / C.ncell, c = wave - p * C.ncell;
+    const int lane = threadIdx.x & 63, wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int p = blockIdx.y, c = blockIdx.x * 4 + wib;
+    if (c >= C.ncell) return;
+    const long long gc = (long long)p * C.ncell + c;
     const float *bb = bbox + p * 6;
-    const int beg = offset[wave], end = offset[wave + 1];
+    const int beg = offset[gc], end = offset[gc + 1];
     const int ciz = c % C.cz, ciy = (c / C.cz) % C.cy, cix = c / (C.cz * C.cy);
     const float cs0 = (bb[3] - bb[0]) / (float)C.cx;
     const float cs1 = (bb[4] - bb[1]) / (float)C.cy;
@@ -541,34 +590,33 @@ __global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const flo
                           FS_FMA((float)ciz + 0.5f, cs2, bb[2])};
     const float rs2 = 6.25f * FS_FMA(G.h[2], G.h[2], FS_FMA(G.h[1], G.h[1], G.h[0] * G.h[0]));
     int na = 0;
-    int32_t *out = cand + (long long)wave * C.ck;
+    int32_t *out = cand + gc * C.ck;
     for (int j = 0; j < C.ck; ++j) {
-        float bkey = __builtin_inff();
-        int bv = 0x7fffffff;
+        // {distance^2 (its bits order like the number, which is not negative), node}; a distance that is no number never wins
+        u64 best = ~0ull;
         for (int s = beg + lane; s < end; s += WAVE) {
             const float4 sm = sample[s];
             const int v = __float_as_int(sm.w);
-            float x[3];
-            node_pos(G, v, x);
-            bool far = true;
-            for (int a = 0; a < na; ++a) {
-                const float4 ac = s_acc[wib][a];
-                const float ex = x[0] - ac.x, ey = x[1] - ac.y, ez = x[2] - ac.z;
-                const float d2 = FS_FMA(ez, ez, FS_FMA(ey, ey, ex * ex));
-                if (!(d2 > rs2)) far = false;
+            if (na > 0) {
+                float x[3];
+                node_pos(G, v, x);
+                bool far = true;
+                for (int a = 0; a < na; ++a) {
+                    const float4 ac = s_acc[wib][a];
+                    const float ex = x[0] - ac.x, ey = x[1] - ac.y, ez = x[2] - ac.z;
+                    const float d2 = FS_FMA(ez, ez, FS_FMA(ey, ey, ex * ex));
+                    if (!(d2 > rs2)) far = false;
+                }
+                if (!far) continue;
             }
-            if (!far) continue;
             const float dx = sm.x - ctr[0], dy = sm.y - ctr[1], dz = sm.z - ctr[2];
             const float key = FS_FMA(dz, dz, FS_FMA(dy, dy, dx * dx));
-            if (key < bkey || (key == bkey && v < bv)) { bkey = key; bv = v; }
+            const u64 k = (u64)__float_as_uint(key) << 32 | (unsigned)v;
+            if (key == key && k < best) best = k;
         }
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) {
-            const float ok = __shfl_xor(bkey, s);
-            const int ov = __shfl_xor(bv, s);
-            if (ok < bkey || (ok == bkey && ov < bv)) { bkey = ok; bv = ov; }
-        }
-        if (bv == 0x7fffffff) break;     // wave-uniform
+        best = wave_min(best);
+        if (best == ~0ull) break;     // wave-uniform
+        const int bv = (int)(unsigned)best;
         float xa[3];
         node_pos(G, bv, xa);
         if (lane == 0) s_acc[wib][na] = make_float4(xa[0], xa[1], xa[2], 0.0f);
@@ -579,7 +627,7 @@ __global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const flo
     }
     if (lane == 0) {
         for (int j = na; j < C.ck; ++j) out[j] = -1;
-        ccnt[wave] = (uint8_t)na;            // candidates of this cell (they are packed at the front)
+        ccnt[gc] = (uint8_t)na;              // candidates of this cell (they are packed at the front)
     }
 }
 
@@ -589,7 +637,8 @@ __global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const flo
 // {x0[3], flags | d(x0)[3], J~0[0] | J~0[1..4] | J~0[5..8]}, flags (integer bits) = 0: no such candidate,
 // 1: usable, 2: Jacobian singular (J~0 = 0), plus the linear index of x0's grid cell << 2.
 // Same arithmetic as a lane computing it for itself (node_pos, the 8 corner records of x0's cell,
-// jacobian_from_corners, inv3).
+// jacobian_from_corners, inv3).  (By the selecting wave's first lanes, which know the candidate: 136 instead of 30 registers
+// there, 15.7 instead of 8.6 + 4.8 us for 8192 cells, 180 instead of 84 + 24 for 65,536.)
 __global__ __launch_bounds__(256) void k_corr_init(GridP G, CorrP C, const float *__restrict__ T,
                                                    const int32_t *__restrict__ cand, float4 *__restrict__ cinit)
 {
@@ -688,7 +737,7 @@ __device__ __forceinline__ void read_record_J(const float4 *__restrict__ r, floa
 // number of the last fs_precompute whose grid had an entry that is not finite.
 // CUR_XCD + j (j = 0 .. 7): the cursor of the j-th eighth of an ordered pair list, relative to the start of that eighth.
 // CUR_LIST: length of the list of pairs that have a candidate (k_voxel_list).
-constexpr int CUR_ALL = 0, CUR_LIST = 1, CUR_NONFINITE = 2, CUR_XCD = 4, CUR_WORDS = 12, N_XCD = 8;
+constexpr int CUR_ALL = 0, CUR_LIST = 1, CUR_NONFINITE = 2, CUR_XCD = 4, CUR_WORDS = 12;
 
 // The blocks of the solve kernel own their first chunk without asking: the shared cursor starts behind `nblocks`
 // chunks, the cursor of range j behind one chunk for every block b with b mod 8 = j.
