@@ -51,7 +51,7 @@ struct fs_ctx {
     int *gpos;         // [K*N] position of a lane inside its cell's list (grows on demand)
     float *grec;       // [K*N][8] cell-sorted {x*, lambda, cell} records (grows on demand)
     size_t gcap;       // lanes gpos / grec can hold
-    float *gpart;      // [P][gb_blocks][nb*12] partial sums of dL/dB, one per block of k_grad_bones_mfma
+    float *gpart;      // [P][gb_blocks][nb*12] partial sums of dL/dB, one per block of k_grad_outputs
     int gb_blocks;
     float4 *srec;      // per-pair result records of the solve kernel (grows on demand)
     size_t srec_cap;   // float4 entries srec can hold
@@ -834,7 +834,9 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
     if (!ctx->GT && !dev_alloc(&ctx->GT, (size_t)G.P * G.V * 12)) return fail(ctx, FS_E_ALLOC, "fs_grad: out of device memory");
     if (!ctx->gcount && !dev_alloc(&ctx->gcount, (size_t)ncp + 1)) return fail(ctx, FS_E_ALLOC, "fs_grad: out of device memory");
     if (!ctx->gpart) {
-        ctx->gb_blocks = (int)std::min<long long>(grid1d(G.V, 256), 1024);      // 4 waves each, >= 16 node quads per wave
+        // 16 nodes per wave and pass, so 128 nodes are two passes of a block; no more blocks than are resident with six slots
+        // (8 poses of 128x128x32 nodes, us: 512 blocks 82, 768 103, 1024 89; one pose of 65 k nodes: 256 blocks 8.6, 512 6.6)
+        ctx->gb_blocks = (int)std::min<long long>(grid1d(G.V, 128), 2ll * ctx->n_cus);
         if (!dev_alloc(&ctx->gpart, (size_t)G.P * ctx->gb_blocks * G.nb * 12)) return fail(ctx, FS_E_ALLOC, "fs_grad: out of device memory");
     }
     const size_t lanes = (size_t)N * K;
@@ -887,18 +889,28 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
         k_grad_nodes_p<8><<<grid1d(nodes * 8, 256), 256, 0, st>>>(G, ncell, ctx->gcount, ctx->grec, ctx->GT);
     else
         k_grad_nodes_z<<<grid1d(nodes, 256), 256, 0, st>>>(G, ncell, ctx->gcount, ctx->grec, ctx->GT);
-    // (dL/dW on a second stream beside dL/dB, joined before the call returns: both kernels then take twice as long,
-    // 156 + 132 us instead of 77 + 79 on the 8-pose grid, and the step gains nothing.)
-    k_grad_weights_node<<<grid1d(G.V * ((G.nb + 7) / 8), 256), 256, sizeof(float) * G.P * G.nb * 12, st>>>(G, ctx->GT, ctx->Bdev, d_gW, ctx->look, look_blocks);
-    const int nout = G.nb * 12, nparts = ctx->gb_blocks * 4;
-    const dim3 gbg(ctx->gb_blocks, (G.P + GB_POSES - 1) / GB_POSES);
+    const int nout = G.nb * 12;
+#define FS_LAUNCH_OUT_S(MT, S) k_grad_outputs<MT, S><<<ctx->gb_blocks, 256, 0, st>>>(G, d_W, ctx->GT, ctx->Bdev, d_gW, ctx->gpart, ctx->look, look_blocks)
+#define FS_LAUNCH_OUT(MT)                                                                                              \
+    do {                                                                                                               \
+        if (G.P == 1) FS_LAUNCH_OUT_S(MT, 1);                                                                          \
+        else FS_LAUNCH_OUT_S(MT, 3);                                                                                   \
+    } while (0)
     switch ((G.nb + 15) / 16) {
-    case 1: k_grad_bones_mfma<1><<<gbg, 256, 0, st>>>(G, d_W, ctx->GT, ctx->gpart, nparts); break;
-    case 2: k_grad_bones_mfma<2><<<gbg, 256, 0, st>>>(G, d_W, ctx->GT, ctx->gpart, nparts); break;
-    case 3: k_grad_bones_mfma<3><<<gbg, 256, 0, st>>>(G, d_W, ctx->GT, ctx->gpart, nparts); break;
-    default: k_grad_bones_mfma<4><<<gbg, 256, 0, st>>>(G, d_W, ctx->GT, ctx->gpart, nparts); break;
+    case 1:
+        if (G.P > 4) FS_LAUNCH_OUT_S(1, 6);
+        else FS_LAUNCH_OUT(1);
+        break;
+    case 2:
+        if (G.P > 4) FS_LAUNCH_OUT_S(2, 6);
+        else FS_LAUNCH_OUT(2);
+        break;
+    case 3: FS_LAUNCH_OUT(3); break;
+    default: FS_LAUNCH_OUT(4); break;
     }
-    k_grad_bones_final<<<G.P * nout, 64, 0, st>>>(G.P, ctx->gb_blocks, nout, ctx->gpart, d_gB);
+#undef FS_LAUNCH_OUT
+#undef FS_LAUNCH_OUT_S
+    k_grad_bones_final<<<dim3(grid1d(nout, 16), G.P), 1024, 0, st>>>(ctx->gb_blocks, nout, ctx->gpart, d_gB);
     return launch_status(ctx, "fs_grad");
 }
 

@@ -2975,141 +2975,204 @@ __global__ __launch_bounds__(256) void k_grad_nodes_z(GridP G, int ncell, const 
     wave_store_rows<12>(GT + i0 * 12, acc, (int)min(64ll, (long long)G.P * G.V - i0), s_tiles[threadIdx.x >> 6]);
 }
 
-// gW[v][b] = sum_p sum_e G_T[p][v][e] B[p][b][e]: one thread per node and group of 8 bones (groups of a node
-// in neighbouring threads, so the node's G_T records come from the same cache lines and the stores are
-// contiguous); the bone transforms are staged in LDS.
-__global__ __launch_bounds__(256) void k_grad_weights_node(GridP G, const float *__restrict__ GT,
-                                                           const float *__restrict__ B, float *__restrict__ gW, u64 *__restrict__ look,
-                                                           int look_blocks)
+// The two gradients that are read off G_T, in one pass over it:
+//   gW[v][b]    = sum_p sum_e G_T[p][v][e] B[p][b][e]     per node a 12 P x n_b product
+//   gB[p][b][e] = sum_v W[v][b] G_T[p][v][e]              n_b x V by V x 12 P, a long inner dimension
+// Bound: memory, 48 P + 8 n_b bytes per node, with many poses the matrix cores beside it.  A wave takes 16 nodes at a time;
+// the 12 entries of up to eight poses are one row of 12 P, of which a lane holds 16-byte quarters: quarter 4s + k of
+// node i in slot s of lane 16k + i.  Both products run on the 16x16x4 fp32 MFMA with no padding between poses.  The quarters
+// are the A operand of gW as they lie, entry u of each in step u (the order in the inner sum is free).  gB contracts over
+// the nodes and reads the same tile back from LDS the other way round, 16 columns per slot.  gB stays in registers over all
+// tiles of a wave; a block leaves one partial result [n_b][12] per pose, which k_grad_bones_final adds.  Weights come
+// and gW goes through LDS as whole lines.  The next tile's loads are under way while one is multiplied.
+// MT = number of 16-bone tiles, S = slots: 1 for one pose, 3 for four, 6 for eight (with up to 32 bones: beyond, the
+// registers of two waves per SIMD are used up); more poses take further passes, which add to gW.
+// Two kernels, gW with vector FMAs on bones in LDS and gB on the MFMA, both over all of G_T: 85 + 82 us on 8 poses of 128x128x32
+// nodes, 5.5 + 8.8 on one of 64x64x16; this one 82 (3.7 TB/s) and 6.6.  With 16 padded columns per pose it took 128, without
+// the way through LDS for weights and gW 146.
+template <int MT, int S>
+__global__ __launch_bounds__(256, 2) void k_grad_outputs(GridP G, const float *__restrict__ W, const float *__restrict__ GT,
+                                                         const float *__restrict__ B, float *gW, float *__restrict__ part,
+                                                         u64 *__restrict__ look, int look_blocks)
 {
     look_clear(look, look_blocks);
-    extern __shared__ float sB[];
-    const int nB = G.P * G.nb * 12;
-    for (int i = threadIdx.x; i < nB; i += blockDim.x) sB[i] = B[i];
-    __syncthreads();
-    const int nch = (G.nb + 7) / 8;
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long v = t / nch;
-    const int b0 = (int)(t - v * nch) * 8;
-    if (v >= G.V) return;
-    float acc[8];
-#pragma unroll
-    for (int bb = 0; bb < 8; ++bb) acc[bb] = 0.0f;
-    for (int p = 0; p < G.P; ++p) {
-        float gt[12];
-        load12(GT + ((long long)p * G.V + v) * 12, gt);
-#pragma unroll
-        for (int bb = 0; bb < 8; ++bb) {
-            if (b0 + bb < G.nb) {
-                const float4 *Bp = reinterpret_cast<const float4 *>(sB + ((long long)p * G.nb + b0 + bb) * 12);
-                const float4 u0 = Bp[0], u1 = Bp[1], u2 = Bp[2];
-                const float bq[12] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w, u2.x, u2.y, u2.z, u2.w};
-#pragma unroll
-                for (int e = 0; e < 12; ++e) acc[bb] = FS_FMA(gt[e], bq[e], acc[bb]);
-            }
-        }
-    }
-    float *o = gW + v * G.nb + b0;
-    if ((G.nb & 3) == 0 && b0 + 8 <= G.nb) {
-        reinterpret_cast<float4 *>(o)[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-        reinterpret_cast<float4 *>(o)[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
-    } else {
-#pragma unroll
-        for (int bb = 0; bb < 8; ++bb)
-            if (b0 + bb < G.nb) o[bb] = acc[bb];
-    }
-}
-
-// gB[p][b][e] = sum_v W[v][b] G_T[p][v][e]: per pose an n_b x V by V x 12 product with a long inner dimension.
-// Each wave walks its share of the nodes four at a time with the 16x16x4 fp32 MFMA (A = 16 bones x 4 nodes of
-// W^T, B = 4 nodes x 12 entries of G_T), up to 8 poses against the same weights; a block of 4 waves writes one
-// partial result [n_b][12] per pose (part[p][block]) and k_grad_bones_final adds the partials.  MT = number of 16-bone tiles.
-constexpr int GB_POSES = 8;
-#ifndef FS_GB_QUADS
-#define FS_GB_QUADS 4
-#endif
-constexpr int GB_QUADS = FS_GB_QUADS;
-template <int MT>
-__global__ __launch_bounds__(256) void k_grad_bones_mfma(GridP G, const float *__restrict__ W,
-                                                         const float *__restrict__ GT, float *__restrict__ part,
-                                                         int nparts)
-{
-    const int lane = threadIdx.x & 63;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;      // < nparts
-    const int p0 = blockIdx.y * GB_POSES;
-    const int np = min(GB_POSES, G.P - p0);
-    const int col = lane & 15, kq = lane >> 4;
-    const long long quads = (G.V + 3) / 4;
-    v4f acc[GB_POSES][MT];
-#pragma unroll
-    for (int pc = 0; pc < GB_POSES; ++pc)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[pc][mt] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-    // GB_QUADS node quads per pass: their loads are in flight together
-    for (long long q = wave; q < quads; q += (long long)GB_QUADS * nparts) {
-        float a[GB_QUADS][MT], bv[GB_QUADS][GB_POSES];
-#pragma unroll
-        for (int u = 0; u < GB_QUADS; ++u) {
-            const long long v = (q + (long long)u * nparts) * 4 + kq;
-            const bool inv = v < G.V;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                a[u][mt] = (inv && mt * 16 + col < G.nb) ? W[v * G.nb + mt * 16 + col] : 0.0f;
-#pragma unroll
-            for (int pc = 0; pc < GB_POSES; ++pc)
-                bv[u][pc] = (pc < np && inv && col < 12) ? GT[((long long)(p0 + pc) * G.V + v) * 12 + col] : 0.0f;
-        }
-#pragma unroll
-        for (int pc = 0; pc < GB_POSES; ++pc) {
-            if (pc < np) {
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int u = 0; u < GB_QUADS; ++u)
-                        acc[pc][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][mt], bv[u][pc], acc[pc][mt], 0, 0, 0);
-            }
-        }
-    }
-    // the block's 4 waves add their results in LDS, pose by pose; wave 0 writes the block's partial
+    constexpr int PC = S * 4 / 3, ROW = S * 16 + 8;          // poses per pass; floats per row of the tile in LDS (padded: no bank twice)
+    __shared__ float4 s_bone[S * 4][MT * 16];    // quarter x bone, zero where there is no such pose or bone
+    __shared__ float4 s_tile[4][16 * ROW / 4];
+    __shared__ float4 s_w[4][MT * 64];          // the weights of a wave's tile, then its part of gW
     __shared__ v4f s_acc[3][MT][64];
-    const int nout = G.nb * 12, wib = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6, col = lane & 15, kq = lane >> 4;
+    const int wave = blockIdx.x * 4 + wib, nwaves = gridDim.x * 4;
+    const int tiles = (int)((G.V + 15) / 16), nout = G.nb * 12, V = (int)G.V;      // 12 P V < 2^31
+    float *const tw = reinterpret_cast<float *>(s_w[wib]);
+    const float *const tile = reinterpret_cast<const float *>(s_tile[wib]);
+    for (int p0 = 0; p0 < G.P; p0 += PC) {
+        const int np = min(PC, G.P - p0);
+        for (int i = threadIdx.x; i < S * 4 * MT * 16; i += 256) {
+            const int q = i / (MT * 16), b = i - q * (MT * 16), pose = q / 3;
+            float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (pose < np && b < G.nb) o = *reinterpret_cast<const float4 *>(B + ((p0 + pose) * G.nb + b) * 12 + (q - 3 * pose) * 4);
+            s_bone[q][b] = o;
+        }
+        v4f acc[S][MT];
+        int src[S];                             // this lane's quarter of node 0 (12 P V < 2^31)
+        bool have[S];
 #pragma unroll
-    for (int pc = 0; pc < GB_POSES; ++pc) {
-        if (pc < np) {                                  // np is the same for the whole block
-            if (wib > 0) {
+        for (int s = 0; s < S; ++s) {
+            const int q = 4 * s + kq, pose = q / 3, part4 = q - 3 * pose;
+            have[s] = pose < np;
+            src[s] = (p0 + (have[s] ? pose : 0)) * V * 12 + 4 * part4;
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) s_acc[wib - 1][mt][lane] = acc[pc][mt];
+            for (int mt = 0; mt < MT; ++mt) acc[s][mt] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        float4 g[S], w[MT];
+        auto fetch = [&](int t) {
+            const int v0 = t * 16;
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                g[s] = *reinterpret_cast<const float4 *>(GT + src[s] + min(v0 + col, V - 1) * 12);
+                if (!(have[s] && v0 + col < V)) g[s] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
-            __syncthreads();
-            if (wib == 0) {
-                float *o = part + ((long long)(p0 + pc) * gridDim.x + blockIdx.x) * nout;
+            // the rows of a tile are contiguous and start at a multiple of 64 bytes
+            const float *wsrc = W + (long long)v0 * G.nb;
+            if (v0 + 16 <= V) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m) w[m] = *reinterpret_cast<const float4 *>(wsrc + min((m * 64 + lane) * 4, 16 * G.nb - 4));
+            } else {
+                const int n = (V - v0) * G.nb;
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    const int i = (m * 64 + lane) * 4;
+                    w[m].x = i < n ? wsrc[i] : 0.0f;
+                    w[m].y = i + 1 < n ? wsrc[i + 1] : 0.0f;
+                    w[m].z = i + 2 < n ? wsrc[i + 2] : 0.0f;
+                    w[m].w = i + 3 < n ? wsrc[i + 3] : 0.0f;
+                }
+            }
+        };
+        if (wave < tiles) fetch(wave);
+        __syncthreads();                       // s_bone
+        for (int t = wave; t < tiles; t += nwaves) {
+            float wc[4][MT];
+            // the wave's own part of LDS: its accesses stay in order, the fences only keep the compiler from moving them
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int s = 0; s < S; ++s) s_tile[wib][col * (ROW / 4) + 4 * s + kq] = g[s];
+#pragma unroll
+            for (int m = 0; m < MT; ++m) s_w[wib][m * 64 + lane] = w[m];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (t + nwaves < tiles) fetch(t + nwaves);
+            const int v0 = t * 16;
+            v4f gw[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                gw[mt] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int u = 0; u < 4; ++u) wc[u][mt] = tw[(4 * u + kq) * G.nb + mt * 16 + col];      // beyond n_b: sums that nobody stores
+            }
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                // one slot's reads of LDS at a time: all of them at once need more registers than there are
+                if (S > 1) __builtin_amdgcn_sched_barrier(0);
+                int at = 0;
+                if (S > 1) asm volatile("" : "+v"(at));            // ... and the bones are read again for every tile
+                const float4 g4 = s_tile[wib][col * (ROW / 4) + 4 * s + kq];
+                const float gs[4] = {g4.x, g4.y, g4.z, g4.w};
+                float e[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) e[u] = tile[(4 * u + kq) * ROW + 16 * s + col];
+                float bs[MT][4];
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
-                    const v4f t = acc[pc][mt] + s_acc[0][mt][lane] + s_acc[1][mt][lane] + s_acc[2][mt][lane];
+                    const float4 b4 = s_bone[4 * s + kq + at][mt * 16 + col];
+                    bs[mt][0] = b4.x; bs[mt][1] = b4.y; bs[mt][2] = b4.z; bs[mt][3] = b4.w;
+                }
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int b = mt * 16 + 4 * kq + r;
-                        if (b < G.nb && col < 12) o[b * 12 + col] = t[r];
+                for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        gw[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(gs[u], bs[mt][u], gw[mt], 0, 0, 0);
+                        acc[s][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[u][mt], e[u], acc[s][mt], 0, 0, 0);
                     }
                 }
             }
-            __syncthreads();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                if (mt * 16 + col < G.nb) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) tw[(4 * kq + r) * G.nb + mt * 16 + col] = gw[mt][r];
+                }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            float *dst = gW + (long long)v0 * G.nb;
+            const int n = min(16, V - v0) * G.nb;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const int i = (m * 64 + lane) * 4;
+                if (i + 4 <= n) {
+                    float4 o = s_w[wib][m * 64 + lane];
+                    if (p0 > 0) {                           // on top of what this lane stored in the pass before
+                        const float4 before = *reinterpret_cast<const float4 *>(dst + i);
+                        o.x += before.x; o.y += before.y; o.z += before.z; o.w += before.w;
+                    }
+                    *reinterpret_cast<float4 *>(dst + i) = o;
+                } else
+                    for (int j = i; j < n; ++j) dst[j] = p0 > 0 ? dst[j] + tw[j] : tw[j];
+            }
+        }
+        // the block's 4 waves add their results in LDS, 16 columns at a time; wave 0 writes the block's partial
+        int first = 4 * kq;
+        asm volatile("" : "+v"(first));            // addresses are made here, not before the loop, where they would fill the registers
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            if (4 * s < 3 * np) {                           // the same for the whole block
+                if (wib > 0) {
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) s_acc[wib - 1][mt][lane] = acc[s][mt];
+                }
+                __syncthreads();
+                const int c = 16 * s + col, pose = c / 12, e = c - 12 * pose;
+                if (wib == 0 && pose < np) {
+                    float *o = part + ((long long)(p0 + pose) * gridDim.x + blockIdx.x) * nout;
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const v4f t = acc[s][mt] + s_acc[0][mt][lane] + s_acc[1][mt][lane] + s_acc[2][mt][lane];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int b = mt * 16 + first + r;
+                            if (b < G.nb) o[b * 12 + e] = t[r];
+                        }
+                    }
+                }
+                __syncthreads();
+            }
         }
     }
 }
 
-// sum of the per-block partial results of k_grad_bones_mfma: one wave per output
-__global__ __launch_bounds__(64) void k_grad_bones_final(int P, int nblk, int nout, const float *__restrict__ part,
-                                                         float *__restrict__ gB)
+// sum of the per-block partial results of k_grad_outputs: a block takes 16 outputs (64 contiguous bytes of every partial;
+// a wave reads four of them), 64 threads share the partials of one (one wave per output, 4 bytes of a line per
+// load: 14.7 us on 8 poses, now 4.7).
+__global__ __launch_bounds__(1024) void k_grad_bones_final(int nblk, int nout, const float *__restrict__ part, float *__restrict__ gB)
 {
-    const int i = blockIdx.x;
-    if (i >= P * nout) return;
-    const int p = i / nout, o = i - p * nout;
+    __shared__ float s_sum[16][16];
+    const int j = threadIdx.x & 15, h = threadIdx.x >> 4, p = blockIdx.y, o = blockIdx.x * 16 + j;
     float a = 0.0f;
-    for (int b = threadIdx.x; b < nblk; b += WAVE) a += part[((long long)p * nblk + b) * nout + o];
+    if (o < nout)
+        for (int b = h; b < nblk; b += 64) a += part[((long long)p * nblk + b) * nout + o];
+    a += __shfl_xor(a, 16);
+    a += __shfl_xor(a, 32);
+    if ((threadIdx.x & 63) < 16) s_sum[threadIdx.x >> 6][j] = a;
+    __syncthreads();
+    if (threadIdx.x < 16 && o < nout) {
+        a = 0.0f;
 #pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) a += __shfl_xor(a, s);
-    if (threadIdx.x == 0) gB[i] = a;
+        for (int i = 0; i < 16; ++i) a += s_sum[i][j];
+        gB[p * nout + o] = a;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
