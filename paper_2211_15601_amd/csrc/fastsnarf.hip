@@ -858,7 +858,11 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
         counts = ctx->gcount_solve;
     } else {
         k_fill_zero_i32<<<(int)std::min<long long>(grid1d(ncp + 1, 256), 4096), 256, 0, st>>>(ncp + 1, ctx->gcount);
-        if (N > 0) k_grad_count<<<grid1d((long long)N * K, 256), 256, 0, st>>>(G, d_xc, d_conv, d_pose, N, K, ncell, ctx->gcount, ctx->gpos);
+        if (N > 0) {
+            const int ki = K >= 8 ? 8 : 1;
+            const long long waves = ((N + WAVE / ki - 1) / (WAVE / ki)) * ((K + ki - 1) / ki);
+            k_grad_count<<<grid1d(waves * WAVE, 256), 256, 0, st>>>(G, d_xc, d_conv, d_pose, N, K, ki, ncell, ctx->gcount, ctx->gpos);
+        }
     }
     int look_blocks;
     { fs_status ss = scan_exclusive(ctx, (int)ncp, ctx->gcount, counts, &look_blocks); if (ss != FS_OK) return ss; }

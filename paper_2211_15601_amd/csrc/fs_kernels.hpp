@@ -2047,13 +2047,13 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
 // without a root keeps all its lanes busy to the last step, and a wave that holds 24 of those cannot go on in quads.
 // ki = 1 without positions, 8 with them (16x16x4 grid, 98 k pairs with positions: ki 1 71, 4 50, 8 45, 24 52 us; 64x64x16:
 // 72, 66, 66, 79 us).
-__device__ __forceinline__ bool pair_of(unsigned index, unsigned per, const SolveP &S, int &n, int &k)
+__device__ __forceinline__ bool pair_of(unsigned index, unsigned per, unsigned N, int K, int ki, int &n, int &k)
 {
-    const unsigned pts = per / (unsigned)S.ki, tiles = ((unsigned)S.N + pts - 1u) / pts, w = index / per, i = index - w * per;
+    const unsigned pts = per / (unsigned)ki, tiles = (N + pts - 1u) / pts, w = index / per, i = index - w * per;
     const unsigned kb = w / tiles;
-    k = (int)(kb * (unsigned)S.ki + i / pts);
+    k = (int)(kb * (unsigned)ki + i / pts);
     n = (int)((w - kb * tiles) * pts + i % pts);
-    const bool live = k < S.K && n < (int)S.N;
+    const bool live = k < K && n < (int)N;
     if (!live) n = k = 0;
     return live;
 }
@@ -2088,7 +2088,7 @@ __global__ __launch_bounds__(LDS ? 1024 : 256) void k_solve_quad(GridP G, SolveP
     const int row = A.row, lane3 = (int)(threadIdx.x & 3);
     const long long N = S.N;
     int n, k;
-    const bool live = pair_of((blockIdx.x * blockDim.x + threadIdx.x) >> 2, QUADS, S, n, k);
+    const bool live = pair_of((blockIdx.x * blockDim.x + threadIdx.x) >> 2, QUADS, (unsigned)S.N, S.K, S.ki, n, k);
     const unsigned pair = (unsigned)k * (unsigned)N + (unsigned)n;
     const int p = pose_of(pose, n, G.P);
     const float *Tp = T + (long long)p * G.V * 12;
@@ -2238,7 +2238,7 @@ __global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(Gri
     const int lane = threadIdx.x & 63;
     const long long N = S.N;
     int n, k;
-    const bool live = pair_of(blockIdx.x * blockDim.x + threadIdx.x, WAVE, S, n, k);
+    const bool live = pair_of(blockIdx.x * blockDim.x + threadIdx.x, WAVE, (unsigned)S.N, S.K, S.ki, n, k);
     const unsigned pair = (unsigned)k * (unsigned)N + (unsigned)n;
     const int p = pose_of(pose, n, G.P);
     const float *Tp = T + (long long)p * G.V * 12;
@@ -2380,22 +2380,28 @@ __global__ void k_fill_zero_i32(long long n, int *__restrict__ a, unsigned *__re
 }
 
 // pass 1 (only when the solve did not hand out positions): one thread per lane; position of the lane
-// inside its cell's list (arrival order)
+// inside its cell's list.  Bound: atomics on the cells' counters, which serialise on crowded cells; lanes of a wave in one
+// cell share one.  A wave takes ki initial states of 64 / ki consecutive points (pair_of): states of one point often
+// reach the same root.  (720 k lanes of 17 bones on 32x32x8 nodes: one atomic per lane 32 us, now 14.)
 __global__ __launch_bounds__(256) void k_grad_count(GridP G, const float *__restrict__ xc,
                                                     const uint8_t *__restrict__ conv, const int32_t *__restrict__ pose,
-                                                    long long N, int K, int ncell, int *__restrict__ count,
+                                                    long long N, int K, int ki, int ncell, int *__restrict__ count,
                                                     int *__restrict__ pos)
 {
-    const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N * K) return;
-    if (!conv[q]) return;
-    const int k = (int)(q / N);
-    const long long n = q - (long long)k * N;
-    const float x[3] = {xc[((long long)k * 3 + 0) * N + n], xc[((long long)k * 3 + 1) * N + n],
-                        xc[((long long)k * 3 + 2) * N + n]};
-    const Cell c = locate(G, x);
-    const int p = pose_of(pose, n, G.P);
-    pos[q] = atomicAdd(count + p * ncell + cell_linear(G, c), 1);
+    int n, k;
+    const bool live = pair_of(blockIdx.x * 256u + threadIdx.x, WAVE, (unsigned)N, K, ki, n, k);
+    const long long q = (long long)k * N + n;
+    const bool want = live && conv[q];
+    int cell = 0;
+    if (want) {
+        const float x[3] = {xc[((long long)k * 3 + 0) * N + n], xc[((long long)k * 3 + 1) * N + n],
+                            xc[((long long)k * 3 + 2) * N + n]};
+        const Cell c = locate(G, x);
+        cell = pose_of(pose, n, G.P) * ncell + cell_linear(G, c);
+    }
+    const CellGroup g = group_request(want, cell, threadIdx.x & 63, count);
+    const int at = group_position(g);
+    if (want) pos[q] = at;
 }
 
 // pass 2: a few threads per point share its lanes: lambda = -M^T g_x; the 32-byte record {x*[3], lambda[3],
