@@ -266,8 +266,10 @@ fs_status need_solve_counts(fs_ctx *c, int ncell)
 // 43 / 52 / 69; 48 k 47 / 49 / 74; 98 k 77 / 57 / 81; 192 k 111 / 78 / 93; 288 k 148 / 124 / 115.  The lines are where
 // the chip is full: three quad waves per SIMD; all pairs of k_solve_once resident at once (3 waves per SIMD of 64).
 // With voxel-based candidates the share of pairs that have one is not known here (rays 1/7, scans 6/10), k_solve_ws needs
-// its list of them first (five launches) and most quads of a sparse batch end at once: rays, 74 k pairs 26 / 33 / 64,
-// 180 k 33 / 35 / 64; scans, 74 k 43 / 33 / 38, 180 k 65 / 44 / 47, 270 k 85 / 63 / 53.
+// its list of them first and most quads of a sparse batch end at once: rays, 74 k pairs 26 (quad) / 33 (once), 180 k 33 / 35;
+// scans, 74 k 43 / 33, 180 k 65 / 44.  Whole calls, solve and dedupe, k_solve_once / k_solve_ws: rays, 90 k pairs 38 / 59,
+// 285 k 47 / 74; scans, 90 k 39 / 52, 210 k 54 / 56, 285 k 61 / 59 (with the backward 141 / 143): the line is where scans gain
+// no more.
 enum { SOLVE_QUAD, SOLVE_ONCE, SOLVE_LARGE };
 int solve_kind(const fs_ctx *c, long long pairs, bool candidates)
 {
