@@ -602,6 +602,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const int kind = solve_kind(ctx, S.total, voxel_list);
     const bool quad = kind == SOLVE_QUAD;
     const size_t need = kind != SOLVE_LARGE ? (d_slot ? (size_t)S.total * 4 : 0) : (size_t)S.total * (with_J ? 4 : 1);
+    ctx->slots_N = 0;            // from here on the records of the solve before are lost, also when this call fails
     if (need > ctx->srec_cap) {
         (void)hipStreamSynchronize(ctx->stream);
         if (ctx->srec) (void)hipFree(ctx->srec);
@@ -613,7 +614,6 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     hipStream_t st = ctx->stream;
     const int ncell = (ctx->G.nx - 1) * (ctx->G.ny - 1) * (ctx->G.nz - 1);
     if (kind != SOLVE_LARGE) {
-        ctx->slots_N = 0;
         int *counts = nullptr;
         if (d_slot) {
             fs_status cs = need_solve_counts(ctx, ncell);
@@ -670,7 +670,6 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const int *list_len = nullptr;
     S.xcd_ranges = 0;
     int *cell_count = nullptr;
-    ctx->slots_N = 0;
     // every wave that draws chunks (all four of a k_solve block, the producer of a k_solve_ws block) owns the
     // chunk of its own number to begin with; the shared cursor starts behind those
     const unsigned drawers = (unsigned)(blocks * wpb);
