@@ -192,6 +192,9 @@ fs_status need_look(fs_ctx *c, int blocks)
     return FS_OK;
 }
 
+int scan_per_thread(int n) { return n <= (1 << 19) ? 4 : 16; }
+int scan_blocks(int n) { return grid1d(n, 1024 * scan_per_thread(n)); }
+
 // exclusive scan of src[0..n) into a[0..n) (src == nullptr: in place) on the context's stream, a[n] = total; *blocks: what
 // the kernel after it has to clear of the look-back words
 fs_status scan_exclusive(fs_ctx *c, int n, int *a, const int *src, int *blocks)
@@ -201,10 +204,10 @@ fs_status scan_exclusive(fs_ctx *c, int n, int *a, const int *src, int *blocks)
         k_fill_zero_i32<<<1, 64, 0, c->stream>>>(1, a);
         return FS_OK;
     }
-    const int per = n <= (1 << 19) ? 4 : 16, m = grid1d(n, 1024 * per);
+    const int m = scan_blocks(n);
     fs_status ls = need_look(c, m);
     if (ls != FS_OK) return ls;
-    if (per == 4) k_scan<4><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->look);
+    if (scan_per_thread(n) == 4) k_scan<4><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->look);
     else k_scan<16><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->look);
     *blocks = m;
     return FS_OK;
@@ -478,9 +481,13 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
     FS_CHECK_PTR(ctx, d_B, false);
     const GridP &G = ctx->G;
     hipStream_t st = ctx->stream;
-    ++ctx->pre_serial;
     const bool voxel = ctx->prm.init_mode == FS_INIT_VOXEL;
     const int ncp = voxel ? G.P * ctx->C.ncell : 0, vblocks = grid1d(G.V, 256);
+    if (voxel) {        // what can fail comes before the first launch: the grid and the candidates of the call before stay a pair
+        fs_status ls = need_look(ctx, scan_blocks(ncp));
+        if (ls != FS_OK) return ls;
+    }
+    ++ctx->pre_serial;
     // poses per pass over the weights: see k_precompute
     const bool wide = (long long)vblocks * ((G.P + 3) / 4) >= 4ll * ctx->n_cus;
 #define FS_LAUNCH_PRE(NP)                                                                                              \
@@ -504,7 +511,7 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
         k_corr_init<<<grid1d((long long)ncp * C.ck, 256), 256, 0, st>>>(G, C, ctx->T, ctx->cand, ctx->cinit);
     }
     fs_status s = launch_status(ctx, "fs_precompute");
-    if (s == FS_OK) ctx->have_T = true;
+    ctx->have_T = s == FS_OK;
     return s;
 }
 
