@@ -55,7 +55,9 @@ struct fs_ctx {
     int gb_blocks;
     float4 *srec;      // per-pair result records of the solve kernel (grows on demand)
     size_t srec_cap;   // float4 entries srec can hold
-    u64 *look;         // look-back words of the kernels that scan in one pass, zero between kernels (grows on demand)
+    u64 *look;         // look-back words of the kernels that scan in one pass, zero between kernels
+    size_t look_words; // words look holds: enough for every call the context accepts
+    bool look_dirty;   // a launch has failed: the words may have been used and not cleared
     int *dd_sums;      // [DD_TILES] tile sums of fs_dedupe (behind the cursor's words)
     uint8_t *vcnt;     // [N] candidates per point
     int *vgcell;       // [N] pose * ncell + correspondence cell of every point
@@ -63,7 +65,6 @@ struct fs_ctx {
     size_t vcap, vgcell_cap;       // points vcnt / vlist, vgcell can hold
     int *vhist;        // [buckets][blocks] + 1: counts, then places, of the counting sort that orders the list by place
     size_t vhist_cap;
-    int look_cap;      // words look holds
     int n_cus, occ_blocks_per_cu, occ_ws_blocks_per_cu, occ_vx_blocks_per_cu, chunk, refill_min, blocks_per_cu, point_major, lds_grid;
     bool lds_big;      // the grid is larger than 60 KiB and fits the LDS of a CU as one block of 12 waves
     int sort_list;     // order the list of (point, candidate) pairs by place (large voxel-mode batches)
@@ -128,8 +129,9 @@ bool device_ptr_ok(fs_ctx *c, const void *p, bool nullable)
 fs_status launch_status(fs_ctx *c, const char *what)
 {
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(c, FS_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
-    return FS_OK;
+    if (e == hipSuccess) return FS_OK;
+    c->look_dirty = true;        // the kernel that clears the look-back words may be the one that did not run
+    return fail(c, FS_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
 // A wave of the solve kernel that waited too long for its block's work queue has left early: the results
@@ -179,38 +181,53 @@ void free_all(fs_ctx *c)
         if (p) (void)hipFree(p);
 }
 
-// look-back words for a kernel of `blocks` blocks (zero between kernels); grows on demand
-fs_status need_look(fs_ctx *c, int blocks)
+int scan_per_thread(int n) { return n <= (1 << 19) ? 4 : 16; }
+int scan_blocks(int n) { return grid1d(n, 1024 * scan_per_thread(n)); }
+// thousand points that a block of k_voxel_list takes
+// (kernel us for 2 / 4 / 8 thousand: 0.3 M points 9 / 10 / 16, 1 M 17 / 13 / 16, 2 M 30 / 24 / 22, 4.2 M 76 / 65 / 62)
+int list_per_thread(long long N) { return N <= (1 << 19) ? 2 : (N <= (1 << 21) ? 4 : 8); }
+constexpr long long SORT_MAX_COUNTS = 1ll << 24;          // (buckets x blocks) of the sort that orders the list by place
+
+// The look-back words are made and cleared with the context, for the largest call it accepts: 8 bytes per 8192 points of
+// K * N < 2^31, 2 MiB at most.  Growing them on demand, with a launch that clears them, breaks where the stream records a graph:
+// the launch does not run, and calls before the graph's first replay find words of any value.
+bool look_create(fs_ctx *c)
 {
-    if (blocks <= c->look_cap) return FS_OK;
-    (void)hipStreamSynchronize(c->stream);
-    if (c->look) (void)hipFree(c->look);
-    c->look_cap = 0;
-    if (!dev_alloc(&c->look, (size_t)blocks + LOOK_HEAD)) return fail(c, FS_E_ALLOC, "out of device memory (scan)");
-    k_fill_zero_i32<<<grid1d(2ll * (blocks + LOOK_HEAD), 256), 256, 0, c->stream>>>(2ll * (blocks + LOOK_HEAD), reinterpret_cast<int *>(c->look));
-    c->look_cap = blocks;
+    const GridP &G = c->G;
+    long long blocks = scan_blocks(G.P * (G.nx - 1) * (G.ny - 1) * (G.nz - 1));
+    if (c->prm.init_mode == FS_INIT_VOXEL) {
+        const long long N = ((1ll << 31) - 1) / c->C.ck;
+        blocks = std::max({blocks, (long long)scan_blocks(G.P * c->C.ncell), (long long)scan_blocks((int)SORT_MAX_COUNTS),
+                           (long long)grid1d(N, 1024 * list_per_thread(N)), 1ll << 9});
+    }
+    c->look_words = (size_t)blocks + LOOK_HEAD;
+    c->look_dirty = false;
+    return dev_alloc(&c->look, c->look_words) && hipMemset(c->look, 0, c->look_words * sizeof(u64)) == hipSuccess;
+}
+
+// Before the first launch of a call that scans: clears the words if a launch has failed since they were used.
+fs_status look_ready(fs_ctx *c, const char *what)
+{
+    if (!c->look_dirty) return FS_OK;
+    if (hipStreamSynchronize(c->stream) != hipSuccess || hipMemset(c->look, 0, c->look_words * sizeof(u64)) != hipSuccess ||
+        hipStreamSynchronize(nullptr) != hipSuccess)
+        return launch_status(c, what);
+    c->look_dirty = false;
     return FS_OK;
 }
 
-int scan_per_thread(int n) { return n <= (1 << 19) ? 4 : 16; }
-int scan_blocks(int n) { return grid1d(n, 1024 * scan_per_thread(n)); }
-
-// exclusive scan of src[0..n) into a[0..n) (src == nullptr: in place) on the context's stream, a[n] = total; *blocks: what
+// exclusive scan of src[0..n) into a[0..n) (src == nullptr: in place) on the context's stream, a[n] = total; returns what
 // the kernel after it has to clear of the look-back words
-fs_status scan_exclusive(fs_ctx *c, int n, int *a, const int *src, int *blocks)
+int scan_exclusive(fs_ctx *c, int n, int *a, const int *src)
 {
-    *blocks = 0;
     if (n <= 0) {
         k_fill_zero_i32<<<1, 64, 0, c->stream>>>(1, a);
-        return FS_OK;
+        return 0;
     }
     const int m = scan_blocks(n);
-    fs_status ls = need_look(c, m);
-    if (ls != FS_OK) return ls;
     if (scan_per_thread(n) == 4) k_scan<4><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->look);
     else k_scan<16><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->look);
-    *blocks = m;
-    return FS_OK;
+    return m;
 }
 
 // ---- scratch memory of fs_dedupe_noalloc: a file-scope device array instead of a context-owned allocation ----
@@ -394,6 +411,7 @@ fs_status fs_create(const fs_grid_desc *desc, const fs_params *params, void *hip
              dev_alloc(&c->order, P * V) && dev_alloc(&c->cand, P * (size_t)C.ncell * C.ck) && dev_alloc(&c->ccnt, P * (size_t)C.ncell) &&
              dev_alloc(&c->cinit, P * (size_t)C.ncell * C.ck * 4);
     }
+    if (ok) ok = look_create(c) && hipStreamSynchronize(nullptr) == hipSuccess;      // cleared before the first call, whichever stream that is on
     if (ok) {
         ok = hipHostMalloc(reinterpret_cast<void **>(&c->gave_up), sizeof(int), hipHostMallocMapped) == hipSuccess;
         if (ok) {
@@ -483,10 +501,7 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
     hipStream_t st = ctx->stream;
     const bool voxel = ctx->prm.init_mode == FS_INIT_VOXEL;
     const int ncp = voxel ? G.P * ctx->C.ncell : 0, vblocks = grid1d(G.V, 256);
-    if (voxel) {        // what can fail comes before the first launch: the grid and the candidates of the call before stay a pair
-        fs_status ls = need_look(ctx, scan_blocks(ncp));
-        if (ls != FS_OK) return ls;
-    }
+    { fs_status ls = look_ready(ctx, "fs_precompute"); if (ls != FS_OK) return ls; }
     ++ctx->pre_serial;
     // poses per pass over the weights: see k_precompute
     const bool wide = (long long)vblocks * ((G.P + 3) / 4) >= 4ll * ctx->n_cus;
@@ -504,8 +519,7 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
         const int lz = G.nz > 8 ? 4 : (G.nz > 4 ? 3 : 2), nbx = grid1d(G.nx, BRICK >> (lz + 3)), nby = grid1d(G.ny, 8), nbz = grid1d(G.nz, 1 << lz);
         k_corr_count<<<dim3(nbx * nby * nbz, G.P), BRICK, 0, st>>>(G, C, ctx->Y, ctx->bb_ord, vblocks, own_box, ctx->bbox, lz, nby, nbz,
                                                                    ctx->cell_of, ctx->count, ctx->fill);
-        int look_blocks;
-        { fs_status ss = scan_exclusive(ctx, ncp, ctx->offset, ctx->count, &look_blocks); if (ss != FS_OK) return ss; }
+        const int look_blocks = scan_exclusive(ctx, ncp, ctx->offset, ctx->count);
         k_corr_scatter<<<dim3(vblocks, G.P), 256, 0, st>>>(G, C, ctx->Y, ctx->cell_of, ctx->offset, ctx->fill, ctx->order, ctx->look, look_blocks);
         k_corr_select<<<dim3(grid1d(C.ncell, 4), G.P), 256, 0, st>>>(G, C, ctx->bbox, ctx->offset, ctx->order, ctx->cand, ctx->ccnt);
         k_corr_init<<<grid1d((long long)ncp * C.ck, 256), 256, 0, st>>>(G, C, ctx->T, ctx->cand, ctx->cinit);
@@ -689,12 +703,13 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     }
     const long long ncounts = cell_count ? (long long)ctx->G.P * ncell + 1 : 0;
     if (voxel_list) {
+        { fs_status ls = look_ready(ctx, "fs_solve"); if (ls != FS_OK) return ls; }
         // On request (fs_set_list_order) large batches are ordered by place (pose, then column of correspondence cells)
         // with a counting sort; small ones, or correspondence grids with more columns than the sort's LDS counters hold,
         // keep the order of the points.
         const int nb = ctx->G.P * ctx->C.cx * ctx->C.cy;
         const long long sblk = (N + SORT_TILE - 1) / SORT_TILE;
-        const bool sorted = ctx->sort_list && N >= 4 * SORT_TILE && nb <= SORT_MAX_BUCKETS && (long long)nb * sblk < (1ll << 24);
+        const bool sorted = ctx->sort_list && N >= 4 * SORT_TILE && nb <= SORT_MAX_BUCKETS && (long long)nb * sblk < SORT_MAX_COUNTS;
         const size_t need_h = (size_t)nb * sblk + 1;
         if ((size_t)N > ctx->vcap) {
             (void)hipStreamSynchronize(st);
@@ -722,19 +737,16 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         if (sorted) {
             k_voxel_count<<<grid1d(N, 256), 256, boxes, st>>>(ctx->G, I, N, d_xq, d_pose, ctx->vcnt, ctx->vgcell);
             k_sort_hist<<<(unsigned)sblk, 1024, nb * sizeof(int), st>>>(N, ctx->C.cz, nb, ctx->vgcell, ctx->vcnt, ctx->vhist);
-            { fs_status ss = scan_exclusive(ctx, (int)((long long)nb * sblk), ctx->vhist, nullptr, &look_blocks); if (ss != FS_OK) return ss; }
-            k_sort_scatter<<<(unsigned)sblk, 1024, nb * sizeof(int), st>>>(N, ctx->C.cz, nb, ctx->vgcell, ctx->vcnt, ctx->vhist, ctx->vlist, ctx->look, look_blocks);
-            look_blocks = 0;
+            const int scanned = scan_exclusive(ctx, (int)((long long)nb * sblk), ctx->vhist, nullptr);
+            k_sort_scatter<<<(unsigned)sblk, 1024, nb * sizeof(int), st>>>(N, ctx->C.cz, nb, ctx->vgcell, ctx->vcnt, ctx->vhist, ctx->vlist, ctx->look, scanned);
             list_len = ctx->vhist + (long long)nb * sblk;
             S.xcd_ranges = (!lds && ctx->xcd_ranges) ? 1 : 0;
         } else {
 #define FS_LAUNCH_LIST(U)                                                                                              \
     k_voxel_list<U><<<grid1d(N, 1024 * (U)), 1024, boxes, st>>>(ctx->G, I, N, K, d_xq, d_pose, ctx->vcnt, ctx->vlist,  \
                                                                 ctx->cursor, drawers, (unsigned)S.chunk, cell_count, ncounts, ctx->look)
-            // kernel us for 2 / 4 / 8 thousand points per block: 0.3 M points 9 / 10 / 16, 1 M 17 / 13 / 16, 2 M 30 / 24 / 22, 4.2 M 76 / 65 / 62
-            const int U = N <= (1 << 19) ? 2 : (N <= (1 << 21) ? 4 : 8);
+            const int U = list_per_thread(N);
             look_blocks = grid1d(N, 1024 * U);
-            { fs_status ss = need_look(ctx, look_blocks); if (ss != FS_OK) return ss; }
             if (U == 2) FS_LAUNCH_LIST(2);
             else if (U == 4) FS_LAUNCH_LIST(4);
             else FS_LAUNCH_LIST(8);
@@ -857,6 +869,7 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
             return fail(ctx, FS_E_ALLOC, "fs_grad: out of device memory for %zu lanes", lanes);
         ctx->gcap = lanes;
     }
+    { fs_status ls = look_ready(ctx, "fs_grad"); if (ls != FS_OK) return ls; }
     hipStream_t st = ctx->stream;
     const int *pos = ctx->gpos, *counts = nullptr;
     if (d_slot) {
@@ -872,8 +885,7 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
             k_grad_count<<<grid1d(waves * WAVE, 256), 256, 0, st>>>(G, d_xc, d_conv, d_pose, N, K, ki, ncell, ctx->gcount, ctx->gpos);
         }
     }
-    int look_blocks;
-    { fs_status ss = scan_exclusive(ctx, (int)ncp, ctx->gcount, counts, &look_blocks); if (ss != FS_OK) return ss; }
+    const int look_blocks = scan_exclusive(ctx, (int)ncp, ctx->gcount, counts);
     if (N > 0) {
         // small batches: several threads share a point's lanes so that the chip has enough threads in flight
         const int groups = N >= (1 << 19) ? 1 : (K >= 8 ? 8 : (K >= 4 ? 4 : (K >= 2 ? 2 : 1)));

@@ -15,12 +15,15 @@ static int n_names;
 static struct { const char *name; unsigned grid[3], block[3]; size_t shared; } launches[MAX_LAUNCHES];
 static int n_launches;
 static struct { char *at; size_t bytes; } blocks[MAX_BLOCKS];
-static int n_blocks, bad_frees, fail_in = -1, n_cus = 256, occupancy = 3;
+static int n_blocks, bad_frees, fail_in = -1, fail_launch_in = -1, memsets, n_cus = 256, occupancy = 3;
+static hipError_t last_error = hipSuccess;
 static char *next_address = (char *)0x100000000000ull;
 static struct { dim3 grid, block; size_t shared; hipStream_t stream; } config;
 
 /* ---- what the tests call ---- */
 void stub_fail_allocation(int n) { fail_in = n; }      /* the n-th allocation from now fails (0: the next one; < 0: none) */
+void stub_fail_launch(int n) { fail_launch_in = n; }   /* the n-th launch from now fails */
+int stub_memsets(void) { return memsets; }             /* calls of hipMemset so far */
 int stub_live_blocks(void) { return n_blocks; }
 int stub_bad_frees(void) { return bad_frees; }
 void stub_clear_launches(void) { n_launches = 0; }
@@ -60,10 +63,10 @@ hipError_t hipFree(void *p)
 hipError_t hipHostMalloc(void **p, size_t n, unsigned flags) { (void)flags; return (*p = calloc(1, n)) ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipHostGetDevicePointer(void **d, void *p, unsigned flags) { (void)flags; *d = p; return hipSuccess; }
-hipError_t hipMemset(void *p, int v, size_t n) { (void)p; (void)v; (void)n; return hipSuccess; }
+hipError_t hipMemset(void *p, int v, size_t n) { (void)p; (void)v; (void)n; ++memsets; return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t st) { (void)d; (void)s; (void)n; (void)k; (void)st; return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetLastError(void) { hipError_t e = last_error; last_error = hipSuccess; return e; }
 const char *hipGetErrorString(hipError_t e) { (void)e; return "stub"; }
 hipError_t hipStreamSynchronize(hipStream_t s) { (void)s; return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
@@ -117,6 +120,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
 {
     int i;
     (void)args; (void)stream;
+    if (fail_launch_in >= 0 && fail_launch_in-- == 0) return last_error = hipErrorLaunchFailure;
     if (n_launches == MAX_LAUNCHES) abort();
     launches[n_launches].name = "?";
     for (i = 0; i < n_names; ++i)

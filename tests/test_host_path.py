@@ -20,30 +20,45 @@ assert S.stub_bad_frees() == 0 and S.stub_live_blocks() == 0
 """, tmp_path)
 
 
-def test_precompute_that_runs_out_of_memory_leaves_the_old_grid_whole(tmp_path):
-    # The words that the scan of the correspondence build needs grow on demand, and are gone when growing them failed
-    # in another call.  fs_precompute has to ask for them before it launches anything: with a new transform grid beside
-    # the candidates of the old one the context would answer fs_solve with a mixture of both.
+def test_words_of_the_scans_are_cleared_where_no_graph_can_record_it(tmp_path):
+    # The scans in one pass need words that are zero when they start; a block waits for what it reads there.  They are
+    # made and cleared with the context.  Made on demand, and cleared by a launch on the stream of the call that
+    # needed more of them, they stayed uncleared when that stream was recording a graph instead of running it.
     host_path.run("""
 h, n, K = ctx((64, 64, 16), init=VOXEL), 1 << 23, 3
-assert precompute(h) == OK and solve(h, n, K) == OK
-launched()
-look = 0
-for i in range(8):                          # a larger solve, its i-th allocation fails; one of them is the scan's
-    S.stub_fail_allocation(i)
-    st = solve(h, n * (i + 2), K)
-    S.stub_fail_allocation(-1)
-    assert st in (OK, E_ALLOC)
-    if b"(scan)" in L.fs_last_error(h):
-        look = 1
-        break
-assert look
-launched()
 S.stub_fail_allocation(0)
-assert precompute(h) == E_ALLOC
-assert launched() == [], "half a pose"
+assert precompute(h) == OK                  # asks for nothing: the grid and its candidates stay a pair
 S.stub_fail_allocation(-1)
-assert precompute(h) == OK and solve(h, n, K) == OK
+launched()
+for k in range(1, 4):                       # every solve longer than any before
+    assert solve(h, k * n, K) == OK
+    assert [x.split("<")[0] for x in names()] == ["k_voxel_list", "k_solve_ws", "k_solve_unpack"]
 L.fs_destroy(h)
 assert S.stub_bad_frees() == 0 and S.stub_live_blocks() == 0
+""", tmp_path)
+
+
+def test_scans_after_a_failed_launch_find_their_words_cleared(tmp_path):
+    # The kernel that clears the words is not the one that uses them: when a launch of a call has failed, nobody knows
+    # what they hold, and the next scan would add it up or wait for it for ever.
+    host_path.run("""
+def failing(h, call, kernels):
+    for i in range(kernels):
+        S.stub_fail_launch(i)
+        assert call() == E_DEVICE, i
+        S.stub_fail_launch(-1)
+        before = S.stub_memsets()
+        launched()
+        assert precompute(h) == OK and call() == OK
+        assert S.stub_memsets() == before + 1, (i, names())
+        before = S.stub_memsets()
+        assert precompute(h) == OK and call() == OK and S.stub_memsets() == before
+
+h, n, K = ctx((64, 64, 16), init=VOXEL), 1 << 20, 3
+assert precompute(h) == OK and solve(h, n, K, slot=True) == OK and grad(h, n, K, slot=True) == OK
+for call in (lambda: precompute(h), lambda: solve(h, n, K, slot=True), lambda: grad(h, n, K)):
+    launched()
+    assert call() == OK
+    failing(h, call, len(launched()))
+L.fs_destroy(h)
 """, tmp_path)
