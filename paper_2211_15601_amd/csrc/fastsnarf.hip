@@ -620,7 +620,14 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     I.ccnt = ctx->ccnt;
     I.cinit = ctx->cinit;
     const bool with_J = d_Jinv != nullptr || d_slot != nullptr;     // with d_slot alone J~ stays in the result records
-    const int kind = solve_kind(ctx, S.total, voxel_list);
+    // On request (fs_set_list_order) batches of at least four tiles of the counting sort are ordered by place (pose, then
+    // column of correspondence cells), whatever kernel their size would take otherwise: only k_solve and k_solve_ws draw
+    // from a list.  Smaller ones, or correspondence grids with more columns than the sort's LDS counters hold, keep the order
+    // of the points.
+    const int nb = ctx->G.P * ctx->C.cx * ctx->C.cy;
+    const long long sblk = (N + SORT_TILE - 1) / SORT_TILE;
+    const bool sorted = voxel_list && ctx->sort_list && N >= 4 * SORT_TILE && nb <= SORT_MAX_BUCKETS && (long long)nb * sblk < SORT_MAX_COUNTS;
+    const int kind = sorted ? SOLVE_LARGE : solve_kind(ctx, S.total, voxel_list);
     const bool quad = kind == SOLVE_QUAD;
     const size_t need = kind != SOLVE_LARGE ? (d_slot ? (size_t)S.total * 4 : 0) : (size_t)S.total * (with_J ? 4 : 1);
     ctx->slots_N = 0;            // from here on the records of the solve before are lost, also when this call fails
@@ -704,12 +711,6 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const long long ncounts = cell_count ? (long long)ctx->G.P * ncell + 1 : 0;
     if (voxel_list) {
         { fs_status ls = look_ready(ctx, "fs_solve"); if (ls != FS_OK) return ls; }
-        // On request (fs_set_list_order) large batches are ordered by place (pose, then column of correspondence cells)
-        // with a counting sort; small ones, or correspondence grids with more columns than the sort's LDS counters hold,
-        // keep the order of the points.
-        const int nb = ctx->G.P * ctx->C.cx * ctx->C.cy;
-        const long long sblk = (N + SORT_TILE - 1) / SORT_TILE;
-        const bool sorted = ctx->sort_list && N >= 4 * SORT_TILE && nb <= SORT_MAX_BUCKETS && (long long)nb * sblk < SORT_MAX_COUNTS;
         const size_t need_h = (size_t)nb * sblk + 1;
         if ((size_t)N > ctx->vcap) {
             (void)hipStreamSynchronize(st);

@@ -62,3 +62,21 @@ for call in (lambda: precompute(h), lambda: solve(h, n, K, slot=True), lambda: g
     failing(h, call, len(launched()))
 L.fs_destroy(h)
 """, tmp_path)
+
+
+def test_lists_are_ordered_on_request_from_the_size_the_header_states(tmp_path):
+    # whatever number of candidates makes the batch small enough for a kernel without a list
+    host_path.run("""
+for ck in (1, 3, 8):
+    h = ctx((64, 64, 16), init=VOXEL, ck=ck)
+    assert precompute(h) == OK
+    for order in (1, 2):
+        assert L.fs_set_list_order(h, order) == OK
+        for n, ordered in ((65535, False), (65536, True), (70001, True), (400000, True)):
+            launched()
+            for slot in (False, True):
+                assert solve(h, n, ck, slot=slot) == OK
+                assert ("k_sort_hist" in names()) == ordered, (ck, order, n, slot)
+    assert L.fs_set_list_order(h, 0) == OK and solve(h, 65536, ck) == OK and "k_sort_hist" not in names()
+    L.fs_destroy(h)
+""", tmp_path)
