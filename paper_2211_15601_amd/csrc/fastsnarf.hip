@@ -297,6 +297,20 @@ int solve_kind(const fs_ctx *c, long long pairs, bool candidates)
     return pairs <= quad ? SOLVE_QUAD : (pairs <= once ? SOLVE_ONCE : SOLVE_LARGE);
 }
 
+// Should the kernels of small batches copy the grid (it fits the LDS) into every block's LDS?  A block of one wave moves
+// 0.09 us per KiB before its first step, and a step from LDS is 0.1 to 0.2 us shorter than one through the caches, so a wave
+// can afford to move some 60 KiB where most trajectories are long (one state per bone), 24 with candidates, which
+// need few steps.  Measured, whole fs_solve in us, LDS / caches (50 steps, 24 states or 3 candidates per point):
+//   states per bone:  48 KiB, 100 points 32 / 38, 500 36 / 38;  96 KiB, 37 points (a wave per block) 37 / 32, 800 (5) 40 / 42;
+//                     146 KiB, 1 point 25 / 13, 100 (1) 44 / 35, 300 (2) 42 / 36, 800 (5) 39 / 39, 4096 (6) 46 / 52
+//   candidates:       48 KiB, 37 points (1) 29 / 24, 4096 (3) 31 / 29;  96 KiB, 500 (1) 36 / 27, 8000 (6) 40 / 37;
+//                     146 KiB, 1 point 21 / 6, 500 (1) 42 / 29, 4096 (3) 36 / 31, 28000 (6) 48 / 46
+bool small_in_lds(const fs_ctx *c, size_t grid_bytes, int waves_per_block)
+{
+    const size_t per_wave = c->prm.init_mode == FS_INIT_VOXEL ? 24 * 1024 : 60 * 1024;
+    return grid_bytes <= per_wave * waves_per_block;
+}
+
 int lanes_K(const fs_ctx *c) { return c->prm.init_mode == FS_INIT_BONE ? c->desc.n_bones : c->prm.corr_k; }
 
 }  // namespace
@@ -657,7 +671,9 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         const int pts = (quad ? QUADS : WAVE) / S.ki;          // points per wave
         const long long waves = ((N + pts - 1) / pts) * ((K + S.ki - 1) / S.ki);
         const int most = quad ? 16 : FS_LDS_BIG_WAVES;
-        const int threads = lds ? WAVE * (int)std::min<long long>(most, std::max<long long>(1, (waves + ctx->n_cus - 1) / ctx->n_cus)) : 256;
+        const int per_block = (int)std::min<long long>(most, std::max<long long>(1, (waves + ctx->n_cus - 1) / ctx->n_cus));
+        const bool staged = lds && small_in_lds(ctx, grid_bytes, per_block);
+        const int threads = staged ? WAVE * per_block : 256;
         const dim3 qg(grid1d(waves * 64, threads));
         const int *nonfinite = reinterpret_cast<const int *>(ctx->cursor + CUR_NONFINITE);
 #define FS_LAUNCH_QUAD(IM, L)                                                                                          \
@@ -672,7 +688,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
                 d_slot ? ctx->srec : nullptr, counts, ncell, nonfinite, ctx->pre_serial);                              \
     } while (0)
         const int im = !fused ? 2 : (voxel_list ? 1 : 0);
-        if (lds) {
+        if (staged) {
             if (im == 0) FS_LAUNCH_QUAD(0, true);
             else if (im == 1) FS_LAUNCH_QUAD(1, true);
             else FS_LAUNCH_QUAD(2, true);

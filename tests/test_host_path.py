@@ -80,3 +80,37 @@ for ck in (1, 3, 8):
     assert L.fs_set_list_order(h, 0) == OK and solve(h, 65536, ck) == OK and "k_sort_hist" not in names()
     L.fs_destroy(h)
 """, tmp_path)
+
+
+def test_small_batches_copy_the_grid_into_lds_only_where_a_block_has_the_waves_for_it(tmp_path):
+    # A batch of no more waves than the GPU has compute units runs in blocks of one wave: one that first copies a grid
+    # of 146 KiB takes longer than the whole call does through the caches.
+    host_path.run("""
+def kernel(h, n, K, **kw):
+    launched()
+    assert solve(h, n, K, **kw) == OK
+    (k,) = [x for x in launched() if x[0].startswith("k_solve_")]
+    return k[0].replace(" ", ""), k[2][0] // 64, k[3]
+
+h = ctx((13, 15, 16))
+big = 13 * 15 * 16 * 48
+assert precompute(h) == OK
+for kw, im in ((dict(), 0), (dict(slot=True), 0), (dict(fused=False, J=True), 2)):
+    for n in (1, 37, 160, 300):                      # one or two waves per block
+        assert kernel(h, n, 24, **kw) == (f"k_solve_quad<{im},false>", 4, 0), n
+    for n, waves in ((400, 3), (1000, 6), (2048, 12)):
+        assert kernel(h, n, 24, **kw) == (f"k_solve_quad<{im},true>", waves, big), n
+    assert kernel(h, 8192, 24, **kw) == (f"k_solve_once<{im},true>", 12, big)
+L.fs_destroy(h)
+h = ctx((16, 16, 4))                                 # 48 KiB
+assert precompute(h) == OK and kernel(h, 1, 24) == ("k_solve_quad<0,true>", 1, 48 << 10)
+L.fs_destroy(h)
+h = ctx((16, 16, 4), init=VOXEL)
+assert precompute(h) == OK
+assert kernel(h, 500, 3) == ("k_solve_quad<1,false>", 4, 0) and kernel(h, 2000, 3) == ("k_solve_quad<1,true>", 2, 48 << 10)
+assert L.fs_set_tuning(h, 0, 0, 0, -1, 0) == OK and kernel(h, 2000, 3) == ("k_solve_quad<1,false>", 4, 0)
+L.fs_destroy(h)
+h = ctx((13, 15, 17))                                # larger than what is kept in LDS
+assert precompute(h) == OK and kernel(h, 8192, 24) == ("k_solve_once<0,false>", 4, 0)
+L.fs_destroy(h)
+""", tmp_path)
