@@ -282,8 +282,8 @@ def test_step_replays_from_a_hip_graph(lib):
 
 
 def test_dedupe_offsets_over_a_very_long_list(lib):
-    # one lane per point: the keep mask is the convergence mask and the offsets are its prefix sums.  2^24 + 5 points
-    # need more than 4096 scan tiles, the case in which the tile sums are scanned by a pass of their own.
+    # one lane per point: the keep mask is the convergence mask and the offsets are its prefix sums.  2^24 + 5 points in
+    # at most 2048 tiles: a tile is 2^14 points, 64 passes of a block, and the last one is nearly empty.
     N = (1 << 24) + 5
     w = wl.make_config(1, n_points=64, dims=(8, 8, 4))
     run = gu.GpuRun(w)
@@ -326,14 +326,16 @@ def test_autograd_hook_matches_oracle_gradient(lib):
 @pytest.mark.parametrize("shape", [((2, 2, 2), 1, 1, 40), ((5, 4, 3), 5, 3, 1000), ((7, 3, 9), 17, 2, 777),
                                    ((4, 6, 5), 33, 1, 513), ((3, 3, 3), 64, 2, 300), ((9, 8, 7), 3, 4, 20011),
                                    ((8, 10, 16), 6, 1, 4099), ((8, 10, 16), 5, 2, 1500), ((16, 16, 8), 24, 1, 5000),
-                                   ((13, 15, 16), 4, 1, 3001), ((13, 15, 17), 4, 1, 1200)],
+                                   ((13, 15, 16), 4, 1, 3001), ((13, 15, 17), 4, 1, 1200),
+                                   ((9, 8, 7), 3, 4, 66001), ((4, 6, 5), 33, 1, 5981), ((8, 10, 16), 5, 2, 39401),
+                                   ((13, 15, 16), 24, 1, 8209)],
                          ids=lambda t: f"g{t[0]}-b{t[1]}-p{t[2]}-n{t[3]}")
 @pytest.mark.parametrize("lds_grid", [1, 0], ids=["grid_in_lds", "grid_cached"])
 def test_odd_shapes_full_path(lib, shape, lds_grid):
     # bone counts on both sides of the 16-bone MFMA tiles and of the 4-wide weight reads, grids down to one cell,
-    # several poses, ragged N: transform grid, solve (both solve kernels: the one that holds these small grids
-    # in LDS, and the producer / consumer one that reads them through the caches) and both gradient paths
-    # against the oracle.  8 x 10 x 16 nodes x 1 pose = 60 KiB is the largest grid that blocks of 4 waves hold in LDS;
+    # several poses, ragged N: transform grid, solve (batches of up to 196,608 pairs: the kernels without queues, with the
+    # grid in LDS and through the caches; the last four shapes lie above: the kernel that holds these small grids in LDS, and
+    # the producer / consumer one that reads them through the caches) and both gradient paths against the oracle.  8 x 10 x 16 nodes x 1 pose = 60 KiB is the largest grid that blocks of 4 waves hold in LDS;
     # with 2 poses (120 KiB), as 16 x 16 x 8 (96 KiB) and 13 x 15 x 16 (146.25 KiB, just under the limit of 148) one
     # block of 12 waves per CU holds it; 13 x 15 x 17 is too large and goes through the caches whatever lds_grid says
     dims, nb, P, n = shape
@@ -380,9 +382,10 @@ def test_one_hot_weights_closed_form_on_gpu(lib):
         np.testing.assert_allclose(xc[kk], ref, atol=2e-6)
 
 
+@pytest.mark.parametrize("n_points", [77, 8209], ids=["small_batch", "kernels_with_queues"])
 @pytest.mark.parametrize("lds_grid", [1, 0], ids=["grid_in_lds", "grid_cached"])
-def test_edge_cases(lib, lds_grid):
-    w = wl.make_config(1, n_points=77, dims=(8, 8, 4))
+def test_edge_cases(lib, lds_grid, n_points):
+    w = wl.make_config(1, n_points=n_points, dims=(8, 8, 4))
     run = gu.GpuRun(w)
     ctx = run.ctx
     ctx.set_tuning(lds_grid=lds_grid)
@@ -485,11 +488,13 @@ def test_wave_that_gives_up_is_reported(lib):
     np.testing.assert_array_equal(out[3], ref[3])
 
 
-def test_grid_entries_that_are_not_finite(lib):
-    # the consumers of the producer / consumer kernel skip corner records of weight zero (one state per bone);
+@pytest.mark.parametrize("n_points", [3001, 8209], ids=["k_solve_once", "k_solve_ws"])
+def test_grid_entries_that_are_not_finite(lib, n_points):
+    # the kernels that read the grid through the caches skip corner records of weight zero (one state per bone; both waves of
+    # the producer / consumer kernel, and the one-pass kernel of smaller batches);
     # 0 * inf is not 0, so a grid with an entry that is not finite must turn that off: weights of +inf in the
     # layer of nodes next to the x-high face, which has weight zero for every lane clamped to that face
-    w = wl.make_config(2, n_points=3001, dims=(32, 32, 8))
+    w = wl.make_config(2, n_points=n_points, dims=(32, 32, 8))
     W = w.W.copy()
     W[-2, :, :, 0] = np.inf
     w2 = wl.Workload(**{**w.__dict__, "W": W})
@@ -605,12 +610,14 @@ def test_list_order_does_not_change_results(lib, n_points):
     # voxel-based candidates, fused: on request batches of 65,536 points and more are ordered by place with a counting
     # sort before the solve; every pair's result must be the same bits as with the list in point order, every lane must be written,
     # and the backward (cell positions from the solve) must agree with the oracle in both orders
-    # 160,000 points: ten sort tiles, ragged; 70,001 points: fewer chunks of pairs than the GPU takes blocks, so the
-    # number of blocks is not a multiple of the 8 ranges of order 2; 3,001 points: below the size from which the list is
-    # ordered at all (the setting is then ignored)
+    # 160,000 points: ten sort tiles, ragged; 70,001 points in chunks of 4096 pairs: fewer chunks (52) than the GPU takes
+    # blocks, so the number of blocks is not a multiple of the 8 ranges of order 2 (without an order this batch runs in a
+    # kernel that has no list); 3,001 points: below the size from which the list is ordered at all (the setting is then ignored)
     w = wl.make_config(5, n_points=n_points, dims=(32, 32, 16), n_poses=4)
     pose = w.pose
     run = gu.GpuRun(w)
+    if n_points == 70001:
+        run.ctx.set_tuning(chunk=4096)
     assert run.ctx.set_list_order(3, check=False) != 0 and run.ctx.set_list_order(-1, check=False) != 0      # 0, 1, 2 only
     T = run.precompute()
     outs = []

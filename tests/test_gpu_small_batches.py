@@ -21,8 +21,9 @@ VOXEL_QUAD, VOXEL_ONCE = 320 * CUS, 1152 * CUS       # ... and with voxel-based 
     ((12, 10, 6), 24, 1, BONE_QUAD // 24, False), ((12, 10, 6), 24, 1, BONE_QUAD // 24 + 1, False),
     ((20, 18, 9), 24, 1, BONE_ONCE // 24, False), ((20, 18, 9), 24, 1, BONE_ONCE // 24 + 1, False),
     ((12, 10, 6), 24, 2, BONE_ONCE // 24, False), ((12, 10, 6), 24, 1, BONE_ONCE // 24 + 1, False),
+    ((13, 15, 16), 24, 1, 37, False), ((13, 15, 16), 24, 1, 1001, False), ((13, 15, 16), 24, 1, BONE_QUAD // 24 + 1, False),
     ((20, 18, 9), 6, 1, 5, True), ((20, 18, 9), 6, 2, VOXEL_QUAD // 3, True), ((20, 18, 9), 6, 1, VOXEL_QUAD // 3 + 1, True),
-    ((12, 10, 6), 6, 1, VOXEL_QUAD // 3 + 1, True), ((20, 18, 9), 6, 2, VOXEL_ONCE // 3, True),
+    ((12, 10, 6), 6, 1, 4099, True), ((12, 10, 6), 6, 1, VOXEL_QUAD // 3 + 1, True), ((20, 18, 9), 6, 2, VOXEL_ONCE // 3, True),
     ((20, 18, 9), 6, 1, VOXEL_ONCE // 3 + 1, True), ((12, 10, 6), 6, 1, VOXEL_ONCE // 3 + 1, True)],
     ids=lambda c: f"g{c[0][0]}-b{c[1]}-p{c[2]}-n{c[3]}-{'voxel' if c[4] else 'bone'}")
 def test_batch_sizes_around_the_kernels_limits(gpu_lib, case):

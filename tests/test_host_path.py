@@ -1,5 +1,6 @@
 """Host code of the library on a stub runtime (host_path.py): what it launches and what it answers when memory runs out."""
 import host_path
+import test_gpu_large_kernels as large
 
 
 def test_positions_of_a_solve_whose_records_are_gone_are_refused(tmp_path):
@@ -113,4 +114,22 @@ L.fs_destroy(h)
 h = ctx((13, 15, 17))                                # larger than what is kept in LDS
 assert precompute(h) == OK and kernel(h, 8192, 24) == ("k_solve_once<0,false>", 4, 0)
 L.fs_destroy(h)
+""", tmp_path)
+
+
+def test_batches_of_the_gpu_tests_run_the_kernels_they_are_meant_for(tmp_path):
+    host_path.run(f"""
+for dims, nb, voxel, fused, n, with_J, without in {large.CASES!r}:
+    h, K = ctx(dims, nb=nb, init=VOXEL if voxel else BONE), 3 if voxel else nb
+    assert precompute(h) == OK
+    for kernel, kw in ((with_J, dict(slot=True)), (without, dict())):
+        launched()
+        assert solve(h, n, K, fused=fused, **kw) == OK
+        assert kernel in [x.replace(" ", "") for x in names()], (kernel, n)
+    # the largest batch of the kernels without queues is just below
+    per, last = (294912, n - 1) if voxel and fused else (196608, None)
+    if last is None:
+        last = per // K
+    assert solve(h, last, K, fused=fused) == OK and not [x for x in names() if x.startswith(("k_solve<", "k_solve_ws"))]
+    L.fs_destroy(h)
 """, tmp_path)
