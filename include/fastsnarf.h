@@ -151,6 +151,7 @@ fs_status fs_init(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_t
  *   init_mode itself (same arithmetic as fs_init, bit-identical results) and fs_init is not needed.
  *   out: d_xc [K][3][N] last iterate; d_conv [K][N] 1 = converged; d_Jinv [K][9][N] last J~ (may be
  *   NULL); d_iters [K][N] steps taken (may be NULL).  Lanes with valid0 == 0 return x0, conv 0.
+ *   Outputs may lie over inputs (a solve in place).
  *   d_slot [K][N] (may be NULL): bookkeeping for fs_grad.  The kernel counts its converged lanes per
  *   grid cell of x* as they finish and writes each lane's arrival position in its cell (-1 where
  *   conv == 0); the counts, and the solve's result records (roots, masks, J~), stay in the context

@@ -297,6 +297,13 @@ int solve_kind(const fs_ctx *c, long long pairs, bool candidates)
     return pairs <= quad ? SOLVE_QUAD : (pairs <= once ? SOLVE_ONCE : SOLVE_LARGE);
 }
 
+// Do [a, a + na) and [b, b + nb) share a byte?  (nullptr: an array that is not there)
+bool overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + nb && y < x + na;
+}
+
 // Should the kernels of small batches copy the grid (it fits the LDS) into every block's LDS?  A block of one wave moves
 // 0.09 us per KiB before its first step, and a step from LDS is 0.1 to 0.2 us shorter than one through the caches, so a wave
 // can afford to move some 60 KiB where most trajectories are long (one state per bone), 24 with candidates, which
@@ -641,7 +648,17 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const int nb = ctx->G.P * ctx->C.cx * ctx->C.cy;
     const long long sblk = (N + SORT_TILE - 1) / SORT_TILE;
     const bool sorted = voxel_list && ctx->sort_list && N >= 4 * SORT_TILE && nb <= SORT_MAX_BUCKETS && (long long)nb * sblk < SORT_MAX_COUNTS;
-    const int kind = sorted ? SOLVE_LARGE : solve_kind(ctx, S.total, voxel_list);
+    // The kernels of small batches write the caller's outputs while other waves still read the inputs; the others leave
+    // records, which are unpacked when the solve has ended: a solve in place (roots over the query points) takes those.
+    bool in_place = false;
+    {
+        const size_t n = (size_t)N, kn = (size_t)S.total;
+        const std::pair<const void *, size_t> in[] = {{d_xq, 12 * n}, {d_pose, 4 * n}, {d_x0, 12 * kn}, {d_Jinv0, 36 * kn}, {d_valid0, kn}};
+        const std::pair<const void *, size_t> out[] = {{d_xc, 12 * kn}, {d_conv, kn}, {d_Jinv, 36 * kn}, {d_iters, kn}, {d_slot, 4 * kn}};
+        for (const auto &i : in)
+            for (const auto &o : out) in_place = in_place || overlap(i.first, i.second, o.first, o.second);
+    }
+    const int kind = sorted || in_place ? SOLVE_LARGE : solve_kind(ctx, S.total, voxel_list);
     const bool quad = kind == SOLVE_QUAD;
     const size_t need = kind != SOLVE_LARGE ? (d_slot ? (size_t)S.total * 4 : 0) : (size_t)S.total * (with_J ? 4 : 1);
     ctx->slots_N = 0;            // from here on the records of the solve before are lost, also when this call fails

@@ -52,9 +52,9 @@ def ctx(dims, nb=24, P=1, init=BONE, ck=3, corr=(6, 5, 4)):
     return h
 
 
-def buf():
-    """an address that is accepted as device memory (nothing reads or writes it)"""
-    return ctypes.c_void_p(0x300000000000)
+def buf(i=0):
+    """an address that is accepted as device memory (nothing reads or writes it), 64 GiB of it for every i"""
+    return ctypes.c_void_p(0x300000000000 + (i << 36))
 
 
 def precompute(h):
@@ -62,9 +62,8 @@ def precompute(h):
 
 
 def solve(h, N, K, fused=True, J=False, slot=False):
-    b, i64 = buf(), ctypes.c_int64
-    init = (None, None, None) if fused else (b, b, b)
-    return L.fs_solve(h, b, b, i64(N), K, *init, b, b, b if J else None, b, b if slot else None)
+    init = (None, None, None) if fused else (buf(2), buf(3), buf(4))
+    return L.fs_solve(h, buf(0), buf(1), ctypes.c_int64(N), K, *init, buf(5), buf(6), buf(7) if J else None, buf(8), buf(9) if slot else None)
 
 
 def grad(h, N, K, slot=False):

@@ -2,6 +2,7 @@
 and the hand-over of a wave's last pairs to quads in the others: all give the bits of the strict-fp32 oracle."""
 import numpy as np
 import pytest
+import torch
 
 import gpu_util as gu
 import oracle
@@ -48,3 +49,30 @@ def test_batch_sizes_around_the_kernels_limits(gpu_lib, case):
     got = run.grad(out[0], None, out[1], gxc, slot=run.slot)
     for name, a, b in zip(("gW", "gB", "gxq"), got, want):
         gu.assert_grad_close(name, a, b, f"small batch {case}")
+
+
+@pytest.mark.parametrize("n,voxel", [(40, False), (6004, False), (5000, True), (40000, True)])
+def test_a_solve_in_place_gives_the_same_bits(gpu_lib, n, voxel):
+    # the query points lie in the first lanes' roots, the pose numbers in the last lanes' positions
+    s = wl.random_affine_scene(307, dims=(20, 18, 9), n_bones=8, n_poses=2, n_points=n)
+    w = wl.Workload("place", s["dims"], 8, 2, s["lo"], s["hi"], s["W"], s["B"], s["x"], s["pose"], s["x"], 1e-5, 10.0, 50,
+                    wl.INIT_VOXEL if voxel else wl.INIT_BONE, 3 if voxel else 8, (6, 5, 4, 3))
+    run = gu.GpuRun(w)
+    run.precompute()
+    N, K = w.N, w.K
+    ref = run.solve(fused=True)
+    run.init()
+    new = lambda *shape, dtype=torch.float32: torch.empty(shape, dtype=dtype, device=gu.DEV)
+    for given in (False, True):
+        xc, J, cv, it, slot = new(K, 3, N), new(K, 9, N), new(K, N, dtype=torch.uint8), new(K, N, dtype=torch.uint8), new(K, N, dtype=torch.int32)
+        init = (None, None, None)
+        if given:
+            xc.copy_(run.x0), J.copy_(run.J0), cv.copy_(run.v0)
+            xq, pose, init = run.xq, run.pose, (xc, J, cv)
+        else:
+            xq, pose = xc[0], slot[K - 1]
+            xq.copy_(run.xq), pose.copy_(run.pose)
+        run.ctx.solve(xq, pose, N, K, *init, xc, cv, J, it, slot)
+        torch.cuda.synchronize()
+        for name, a, b in zip(("roots", "masks", "J", "iterations"), (xc, cv, J, it), ref):
+            np.testing.assert_array_equal(a.cpu().numpy().view(np.uint8), b.view(np.uint8), err_msg=f"{name} {given}")

@@ -133,3 +133,35 @@ for dims, nb, voxel, fused, n, with_J, without in {large.CASES!r}:
     assert solve(h, last, K, fused=fused) == OK and not [x for x in names() if x.startswith(("k_solve<", "k_solve_ws"))]
     L.fs_destroy(h)
 """, tmp_path)
+
+
+def test_arrays_that_overlap_go_to_the_kernels_that_write_last(tmp_path):
+    # The kernels for small batches write the caller's arrays while other waves still read theirs; the others write
+    # records, which a kernel of its own unpacks when the solve has ended.  A solve in place needs the latter.
+    host_path.run("""
+A, G = 0x300000000000, 1 << 30
+p = ctypes.c_void_p
+def kernels(h, N, K, xq=0, pose=1, x0=None, J0=None, v0=None, xc=5, conv=6, J=7, it=8, slot=9):
+    launched()
+    at = [None if a is None else p(A + int(a * G)) for a in (xq, pose, x0, J0, v0, xc, conv, J, it, slot)]
+    assert L.fs_solve(h, *at[:2], ctypes.c_int64(N), K, *at[2:]) == OK
+    return [x.split("<")[0] for x in names() if x.startswith("k_solve")]
+
+small, large = (["k_solve_quad"], ["k_solve_once"]), ["k_solve_ws", "k_solve_unpack"]
+h, K = ctx((64, 64, 16), P=2), 24
+assert precompute(h) == OK
+for N in (40, 5000):
+    given = dict(x0=2, J0=3, v0=4)
+    assert kernels(h, N, K) in small and kernels(h, N, K, **given) in small
+    end = 12 * N * K / G                                     # of d_xc
+    assert kernels(h, N, K, xq=5 + end) in small and kernels(h, N, K, xq=5 - 12 * N / G) in small       # side by side
+    for kw in (dict(xq=5), dict(xq=5 + end - 16 / G), dict(xq=5 - 12 * N / G + 16 / G), dict(pose=5), dict(pose=6), dict(pose=7), dict(xq=8),
+               dict(pose=9), dict(given, x0=5), dict(given, J0=7), dict(given, v0=6), dict(given, v0=8), dict(given, x0=7)):
+        assert kernels(h, N, K, **kw) == large, (N, kw)
+    assert kernels(h, N, K, pose=7, J=None) in small and kernels(h, N, K, **dict(given, v0=8, it=None)) in small
+L.fs_destroy(h)
+h = ctx((16, 16, 4), init=VOXEL)
+assert precompute(h) == OK
+assert kernels(h, 100, 3, pose=None) in small and kernels(h, 100, 3, pose=None, xq=5) == ["k_solve", "k_solve_unpack"]
+L.fs_destroy(h)
+""", tmp_path)
