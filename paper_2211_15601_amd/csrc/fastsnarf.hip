@@ -70,7 +70,7 @@ struct fs_ctx {
     int sort_list;     // order the list of (point, candidate) pairs by place (large voxel-mode batches)
     int xcd_ranges;    // with an ordered list: one range of it, and one cursor, per XCD
     int spin_limit;    // polls for room in its consumers' queues before the producer wave of a solve block gives up
-    int pre_serial;    // number of the last fs_precompute; cursor[CUR_NONFINITE] == pre_serial: that grid has an entry that is not finite
+    int pre_serial;    // number of the last fs_precompute; cursor[CUR_NONFINITE] == pre_serial: that grid has an entry that is not finite or not below SKIP_MAX
     int *gave_up;      // pinned host word, mapped into the device: a wave that gave up sets it
     int *gave_up_dev;  // the device's address of it
     // optional timing of the Broyden kernel alone (events on the context's stream)

@@ -6,6 +6,10 @@ namespace fs {
 
 constexpr int WAVE = 64, N_XCD = 8;
 
+// Corner records of weight zero may be left out while no product of an entry with a position is infinite (0 * inf is not 0):
+// entries and positions below this number, whose products add up to less than 2^123.
+constexpr float SKIP_MAX = 0x1p60f;
+
 // pose index of point n, forced into [0, P) so that a bad index in the caller's array cannot send
 // a kernel outside the transform grids
 __device__ __forceinline__ int pose_of(const int32_t *__restrict__ pose, long long n, int P)
@@ -101,7 +105,7 @@ __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__rest
     const int t = (int)blockIdx.x / N_XCD, bt = t / groups, group = t - bt * groups, blk = bt * N_XCD + (int)blockIdx.x % N_XCD;
     if (blk >= vblocks) return;
     // *nonfinite = serial (the number of this call) tells the solve that this grid holds an entry that is not
-    // finite: a record with weight zero may then not be skipped (0 * inf is not 0)
+    // finite, or too large: a record with weight zero may then not be skipped (SKIP_MAX)
     __shared__ __attribute__((aligned(16))) float s_tiles[4][64 * 12];
     __shared__ unsigned s_ext[NP][4][6];
     const int wib = threadIdx.x >> 6;
@@ -163,7 +167,7 @@ __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__rest
             if (live) {
                 float big = 0.0f;
 #pragma unroll
-                for (int e = 0; e < 12; ++e) big = __builtin_fmaxf(big, __builtin_fabsf(acc[q][e]) < __builtin_inff() ? 0.0f : 1.0f);
+                for (int e = 0; e < 12; ++e) big = __builtin_fmaxf(big, __builtin_fabsf(acc[q][e]) < SKIP_MAX ? 0.0f : 1.0f);
                 if (big != 0.0f) *nonfinite = serial;
             }
             wave_store_rows<12>(T + ((long long)(p0 + q) * G.V + v0) * 12, acc[q], nrows, s_tile);
@@ -734,7 +738,7 @@ __device__ __forceinline__ void read_record_J(const float4 *__restrict__ r, floa
 }
 
 // Words of the context's cursor array: CUR_ALL is the work cursor of the solve kernels; CUR_NONFINITE holds the serial
-// number of the last fs_precompute whose grid had an entry that is not finite.
+// number of the last fs_precompute whose grid had an entry that is not finite or not below SKIP_MAX.
 // CUR_XCD + j (j = 0 .. 7): the cursor of the j-th eighth of an ordered pair list, relative to the start of that eighth.
 // CUR_LIST: length of the list of pairs that have a candidate (k_voxel_list).
 constexpr int CUR_ALL = 0, CUR_LIST = 1, CUR_NONFINITE = 2, CUR_XCD = 4, CUR_WORDS = 12;
@@ -1805,7 +1809,8 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                         // their weight vanishes along the clamped axis by definition and carries the zero factor
                         // along the others): fetch the rest, zeros in their place, and if an entry of the blend
                         // or of the Jacobian comes out as an exact zero, do it again with all eight
-                        const int need = prod_skip ? corners_needed(c0) : 0xFF;
+                        const bool near = __builtin_fabsf(nx[0]) < SKIP_MAX && __builtin_fabsf(nx[1]) < SKIP_MAX && __builtin_fabsf(nx[2]) < SKIP_MAX;
+                        const int need = prod_skip && near ? corners_needed(c0) : 0xFF;
 #pragma unroll
                         for (int c = 0; c < 8; ++c) {
 #pragma unroll
@@ -1955,7 +1960,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
     float q[8][12];                  // corner records of the lane's current cell, kept across iterations
     int held = -1;                   // base of the cell whose corners q holds (-1: none)
     int held_mask = 0;               // SKIP: which of them
-    // SKIP needs a grid of finite entries (k_precompute says if this one is not)
+    // SKIP needs a grid of entries below SKIP_MAX (k_precompute says if this one is not)
     const bool may_skip = SKIP && __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
     if (SKIP) {
 #pragma unroll

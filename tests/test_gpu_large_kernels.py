@@ -71,6 +71,36 @@ def test_edge_inputs_above_the_small_batch_limits(gpu_lib, case):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n", [BONE // 24 + 1, 4001])
+@pytest.mark.parametrize("weight, far", [(1.5e38, 1.0), (1e15, 1e25)])
+def test_products_beyond_the_largest_number(gpu_lib, n, weight, far):
+    # Nodes next to two faces of the box blend to numbers whose product with a position is infinite, though the entries
+    # are finite.  For a state clamped to such a face they are corners of weight zero, and 0 * inf is no number: the
+    # kernels that do not fetch corners of weight zero must give what fs_init gives.
+    s = wl.random_affine_scene(517, dims=CACHED, n_bones=24, n_poses=1, n_points=n)
+    W = s["W"].copy()
+    W[1, :, :, 3] = weight
+    W[2:, -2, :, 5] = weight
+    xq = (s["x"] * np.where(np.arange(n) % 3 == 0, far, 1.0)).astype(np.float32)
+    w = wl.Workload("beyond", s["dims"], 24, 1, s["lo"], s["hi"], W, s["B"], xq, s["pose"], xq, 1e-5, 10.0, 50, wl.INIT_BONE, 24, (6, 5, 4, 3))
+    run = gu.GpuRun(w)
+    T = run.precompute()
+    assert np.isfinite(T).all()
+    with np.errstate(all="ignore"):
+        x0, J0, v0 = gu.oracle_inits(w, T)
+        ref = gu.oracle_solve(w, T, x0, J0, v0)
+    assert np.isnan(J0).any() or (v0 == 0).any()
+    for out in (run.solve(fused=True), run.solve(x0, J0, v0)):
+        np.testing.assert_array_equal(out[1], ref[1])
+        np.testing.assert_array_equal(out[3], ref[3])
+        for a, b in ((out[0], ref[0]), (out[2], ref[2])):
+            num = ~np.isnan(b)
+            np.testing.assert_array_equal(np.isnan(a), ~num)
+            np.testing.assert_array_equal(a.view(np.uint32)[num], b.view(np.uint32)[num])
+    run.ctx.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("by_place", [0, 1, 2])
 def test_a_step_with_candidates_replays_from_a_hip_graph(gpu_lib, by_place):
     # k_voxel_list, or the sort, then k_solve_ws, and the scans of the grid build and of the backward: kernels that use words
