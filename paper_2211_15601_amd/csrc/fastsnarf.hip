@@ -231,7 +231,8 @@ int scan_exclusive(fs_ctx *c, int n, int *a, const int *src)
 }
 
 // ---- scratch memory of fs_dedupe_noalloc: a file-scope device array instead of a context-owned allocation ----
-// The sums of the at most DD_TILES tiles of points; every GPU the library runs on holds its own 8 KiB copy of the array
+// The sums of the at most DD_TILES tiles of points (whatever their number; the limit of points is the entry point's own, kept
+// from when the array held a sum per fixed number of points); every GPU the library runs on holds its own 8 KiB copy of the array
 // until the process ends.  In host code the array's name is only a handle for hipGetSymbolAddress: the device address is
 // looked up once per device (with that device current) and kept in g_scratch_ptr.
 constexpr long long FS_NOALLOC_MAX_N = 1ll << 24;
@@ -260,9 +261,6 @@ int *scratch_on_device(fs_ctx *c)
     return g_scratch_ptr[c->device];
 }
 
-#ifndef FS_TPN8_AT
-#define FS_TPN8_AT 8
-#endif
 // largest transform grid (all poses) kept in LDS by the solve: a block may ask for 64 KiB in all, and k_solve has 4 KiB of
 // its own (the parked cell-position requests of its four waves)
 constexpr size_t FS_LDS_GRID_MAX = 60 * 1024;
@@ -287,9 +285,10 @@ fs_status need_solve_counts(fs_ctx *c, int ncell)
 // the chip is full: three quad waves per SIMD; all pairs of k_solve_once resident at once (3 waves per SIMD of 64).
 // With voxel-based candidates the share of pairs that have one is not known here (rays 1/7, scans 6/10), k_solve_ws needs
 // its list of them first and most quads of a sparse batch end at once: rays, 74 k pairs 26 (quad) / 33 (once), 180 k 33 / 35;
-// scans, 74 k 43 / 33, 180 k 65 / 44.  Whole calls, solve and dedupe, k_solve_once / k_solve_ws: rays, 90 k pairs 38 / 59,
-// 285 k 47 / 74; scans, 90 k 39 / 52, 210 k 54 / 56, 285 k 61 / 59 (with the backward 141 / 143): the line is where scans gain
-// no more.
+// scans, 74 k 43 / 33, 180 k 65 / 44.  The upper line there, 4.5 waves per SIMD of which 3 are resident, is a compromise: whole calls,
+// solve and dedupe, k_solve_once / k_solve_ws, on 32x32x8, 64x64x16 and 128x128x32 nodes: rays, 198 k pairs 33 / 50, 34 / 56, 43 / 67,
+// 295 k 33 / 50, 37 / 57, 45 / 71; scans, 198 k 57 / 64, 58 / 68, 75 / 80, 246 k 59 / 65, 69 / 71, 85 / 84, 295 k 58 / 67, 77 / 72, 93 / 87.
+// Scans on large grids would gain 7 % from a line at 210 k to 270 k pairs, rays would lose 35 %.
 enum { SOLVE_QUAD, SOLVE_ONCE, SOLVE_LARGE };
 int solve_kind(const fs_ctx *c, long long pairs, bool candidates)
 {
@@ -943,8 +942,8 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
     // crowded grids: one thread per (node, adjacent cell); sparse ones: one thread per node, which walks the 4 cells at
     // its height and hands their share for the node above to the next SIMD lane
     const long long nodes = (long long)G.P * G.V;
-    if ((long long)lanes >= FS_TPN8_AT * nodes)
-        k_grad_nodes_p<8><<<grid1d(nodes * 8, 256), 256, 0, st>>>(G, ncell, ctx->gcount, ctx->grec, ctx->GT);
+    if ((long long)lanes >= 8 * nodes)
+        k_grad_nodes_p<<<grid1d(nodes * 8, 256), 256, 0, st>>>(G, ncell, ctx->gcount, ctx->grec, ctx->GT);
     else
         k_grad_nodes_z<<<grid1d(nodes, 256), 256, 0, st>>>(G, ncell, ctx->gcount, ctx->grec, ctx->GT);
     const int nout = G.nb * 12;
@@ -980,7 +979,7 @@ static fs_status dedupe_impl(fs_ctx *ctx, const char *who, int *sums, const floa
     if (K < 1 || K > FS_MAX_BONES) return fail(ctx, FS_E_SHAPE, "%s: K must be in 1..%d", who, (int)FS_MAX_BONES);
     if (N < 0 || (long long)N * K >= (1ll << 31)) return fail(ctx, FS_E_SHAPE, "%s: need 0 <= N and K*N < 2^31", who);
     if (sums != ctx->dd_sums && N > FS_NOALLOC_MAX_N)
-        return fail(ctx, FS_E_SHAPE, "%s: N = %lld exceeds the %lld points its fixed scratch memory is sized for; use fs_dedupe",
+        return fail(ctx, FS_E_SHAPE, "%s: N = %lld exceeds the %lld points this call takes; use fs_dedupe",
                     who, (long long)N, FS_NOALLOC_MAX_N);
     if (!(min_dist >= 0.0f) || !std::isfinite(min_dist)) return fail(ctx, FS_E_ARG, "%s: min_dist must be finite and >= 0", who);
     if (cap < 0) return fail(ctx, FS_E_SHAPE, "%s: cap must be >= 0", who);

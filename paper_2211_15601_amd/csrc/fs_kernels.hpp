@@ -1162,7 +1162,7 @@ __device__ __forceinline__ int quad_step(const GridP &G, const QuadAxis &A, floa
     return ((conv || !(r2 < div2) || it >= max_iters) ? 1 : 0) | (conv ? 2 : 0);
 }
 
-// A wave whose last QUAD_LANES pairs (or fewer) are all that is left for it hands them from single lanes to quads: quad j
+// A wave whose last QUADS pairs (or fewer) are all that is left for it hands them from single lanes to quads: quad j
 // takes the pair of the j-th active lane.  Returns the lane to take from, and whether the quad gets a pair.
 constexpr int QUADS = 16;
 __device__ __forceinline__ int quad_source(unsigned long long active, int lane, bool &gets)
@@ -2064,9 +2064,9 @@ __device__ __forceinline__ bool pair_of(unsigned index, unsigned per, unsigned N
 }
 
 // ------------------------------------------------------------------------------------------------
-// Broyden solve of a small batch: one quad of SIMD lanes per pair (see quad_iterate), no queue, no list, no records to
-// unpack.  Pairs q = k*N + n in order, so that the 16 pairs of a wave are consecutive points and the outputs, which go
-// straight to the caller's arrays, share cache lines.  A batch this small is bound by its longest trajectories, i.e. by
+// Broyden solve of a small batch: one quad of SIMD lanes per pair (see quad_step), no queue, no list, no records to
+// unpack.  A wave takes 16 pairs of consecutive points (with positions and at least 8 states two points times eight states,
+// see pair_of); the outputs go straight to the caller's arrays.  A batch this small is bound by its longest trajectories, i.e. by
 // max_iters times the latency of a step.
 // INIT: 0 one state per bone (Eq. (8)), 1 candidates of the correspondence grid, 2 the caller's initial states.
 // LDS: the transform grids of all poses are copied into LDS first.
@@ -2764,21 +2764,20 @@ __global__ __launch_bounds__(64 * PIECE_WAVES) void k_grad_pieces(GridP G, long 
     }
 }
 
-// G_T of every node from the pieces of its 8 adjacent cells; TPN threads share a node (1, or 8 = one
-// per adjacent cell followed by a butterfly sum).
-// Measured on the multi-pose batch (7.7 M records over 4.2 M nodes, TPN = 1: 450 us) and not adopted: a block per brick
+// G_T of every node from the pieces of its 8 adjacent cells, for crowded cells (k_grad_nodes_z takes the sparse ones): 8 threads
+// share a node, one per adjacent cell, and add what they have in a butterfly.
+// Measured on the multi-pose batch (7.7 M records over 4.2 M nodes, one thread per node: 450 us) and not adopted: a block per brick
 // of 4 x 4 x 16 nodes that first copies the records of the cells around it into LDS and gathers from there, same loops:
 // 450 .. 518 us (fewer resident threads, three barriers per block); the same with one loop over all records of a node's
 // 8 cells instead of a loop per cell: 751 us (the bookkeeping costs more than the shorter loop saves); a block per brick
 // that adds every record's 8 x 12 contributions into LDS sums with LDS float atomics: 4.5 ms (about 0.5 SIMD lanes per
 // clock and CU).
-template <int TPN>
 __global__ __launch_bounds__(256) void k_grad_nodes_p(GridP G, int ncell, const int *__restrict__ offset,
                                                       const float *__restrict__ rec, float *__restrict__ GT)
 {
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long i = t / TPN;
-    const int sub = (int)(t - i * TPN);
+    const long long i = t >> 3;
+    const int cn = (int)(t & 7);
     if (i >= (long long)G.P * G.V) return;
     const int p = (int)div_by((unsigned)i, (unsigned)G.V, G.mag_V);          // P * V < 2^31
     const unsigned v = (unsigned)(i - (long long)p * G.V), tz = div_by(v, (unsigned)G.nz, G.mag_nz);
@@ -2787,11 +2786,9 @@ __global__ __launch_bounds__(256) void k_grad_nodes_p(GridP G, int ncell, const 
     float acc[12];
 #pragma unroll
     for (int e = 0; e < 12; ++e) acc[e] = 0.0f;
-    for (int cn = sub; cn < 8; cn += TPN) {
-        const int c = adjacent_cell(G, ncell, p, ix, iy, iz, cn);
-        if (c < 0) continue;
-        const int a = offset[c], b = offset[c + 1];
-        if (a == b) continue;
+    const int c = adjacent_cell(G, ncell, p, ix, iy, iz, cn);
+    const int a = c < 0 ? 0 : offset[c], b = c < 0 ? 0 : offset[c + 1];
+    if (a < b) {
         for (int j = a / PIECE_R; j <= (b - 1) / PIECE_R; ++j) {
             const int ps = max(a, j * PIECE_R), pe = min(b, (j + 1) * PIECE_R);
             if (pe - ps >= PIECE_MIN) {
@@ -2811,14 +2808,12 @@ __global__ __launch_bounds__(256) void k_grad_nodes_p(GridP G, int ncell, const 
             }
         }
     }
-    if (TPN > 1) {
 #pragma unroll
-        for (int e = 0; e < 12; ++e) {
+    for (int e = 0; e < 12; ++e) {
 #pragma unroll
-            for (int d = TPN >> 1; d >= 1; d >>= 1) acc[e] += __shfl_xor(acc[e], d);
-        }
+        for (int d = 4; d >= 1; d >>= 1) acc[e] += __shfl_xor(acc[e], d);
     }
-    if (sub == 0) {
+    if (cn == 0) {
         float4 *o = reinterpret_cast<float4 *>(GT + i * 12);
         o[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         o[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
@@ -2826,10 +2821,7 @@ __global__ __launch_bounds__(256) void k_grad_nodes_p(GridP G, int ncell, const 
     }
 }
 
-// What the records of cell (cx, cy, cz), list entries [a, b), add to the two nodes at its (x, y) corner `ab`
-// (= a + 2b): `lo` is the node at cz, `hi` the one at cz + 1.  Pieces that k_grad_pieces replaced by their corner
-// sums enter as those sums.  Either output may be switched off.
-// one record {x*, lambda} of the cell with origin (cx, cy, cz): its share for the cell's (x, y) corner (bx, by) at the lower
+// One record {x*, lambda} of the cell with origin (cx, cy, cz): its share for the cell's (x, y) corner (bx, by) at the lower
 // z (into lo) and at the upper z (into hi)
 template <bool LO, bool HI>
 __device__ __forceinline__ void grad_record_pair(const GridP &G, const float4 r0, const float4 r1, bool bx, bool by, int cx, int cy,
@@ -2861,6 +2853,9 @@ __device__ __forceinline__ void grad_record_pair(const GridP &G, const float4 r0
     }
 }
 
+// What the records of cell (cx, cy, cz), list entries [a, b), add to the two nodes at its (x, y) corner `ab`
+// (= a + 2b): `lo` is the node at cz, `hi` the one at cz + 1.  Pieces that k_grad_pieces replaced by their corner
+// sums enter as those sums.  Either output may be switched off.
 template <bool LO, bool HI>
 __device__ __forceinline__ void grad_cell_pair(const GridP &G, const float *__restrict__ rec, int a, int b, int ab, int cx,
                                                int cy, int cz, float (&lo)[12], float (&hi)[12])
