@@ -12,7 +12,7 @@ voxel-based initial states with up to 3 candidates, max 50 iterations, tol 1e-5)
 configurations are timed too and reported, shorter, under `per_config`.
 
 Prints ONE JSON line.  `value` = converged (point, init) root solves per second over the whole
-step.  `roofline` describes the Broyden kernel (k_solve_ws, k_solve when the grid fits in LDS, k_solve_once for small batches: the
+step.  `roofline` describes the Broyden kernel (k_solve_ws, k_solve when the grid fits in LDS, k_solve_once or k_solve_quad for small batches: the
 dominant one), timed by the library with HIP events around that kernel on the stream it runs on.
 `cpu_baseline` is the CPU oracle timed on this machine's host cores.
 """
@@ -39,7 +39,8 @@ BYTES_EVAL = 384     # ... = 8 x 48 bytes gathered per field evaluation
 PEAK_FP32_TFLOPS = 157.3            # published fp32 vector peak (needs packed fp32 instructions)
 PEAK_FP32_UNPACKED_TFLOPS = 78.6    # 256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2.4 GHz: one FMA per lane per clock
 PEAK_HBM_BPS = 8.0e12
-ONCE_MAX_PAIRS = (196608, 294912)   # pairs up to which k_solve_once runs (one state per bone, voxel-based candidates)
+# pairs per CU up to which the kernels without queues run: (states per bone or given, voxel-based candidates looked up inside)
+QUAD_MAX, ONCE_MAX = (192, 320), (768, 1152)
 LDS_GRID_MAX = 148 * 1024           # transform grids (all poses) up to this size are held in LDS by k_solve
 
 
@@ -84,9 +85,10 @@ class Case:
         # with the cell positions handed on, J~ can stay in the library's result records
         self.Jarg = None if self.slot is not None else e((K, 9, N), f32)
         self.grid_bytes = int(w.n_poses * w.dims[0] * w.dims[1] * w.dims[2] * 48)
-        # batches whose pairs are all resident at once run in a kernel without queues
-        small = N * K <= ONCE_MAX_PAIRS[w.init_mode]
-        self.kernel = "k_solve_once" if small else ("k_solve" if self.grid_bytes <= LDS_GRID_MAX else "k_solve_ws")
+        per_cu = N * K / torch.cuda.get_device_properties(dev).multi_processor_count
+        kind = 1 if w.init_mode == 1 and not args.unfused else 0
+        self.kernel = ("k_solve_quad" if per_cu <= QUAD_MAX[kind] else "k_solve_once" if per_cu <= ONCE_MAX[kind]
+                       else "k_solve" if self.grid_bytes <= LDS_GRID_MAX else "k_solve_ws")
 
     def step(self, marks=None):
         a, c, t = self.args, self.ctx, self.torch
