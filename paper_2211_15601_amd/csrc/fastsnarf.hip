@@ -278,7 +278,7 @@ fs_status need_solve_counts(fs_ctx *c, int ncell)
 }
 
 // Kernels of the solve by the size of a batch (pairs = K * N; all three give the same bits).  What bounds a small batch is
-// max_iters times the latency of a step, and a step is half as long with four lanes per pair (0.45 instead of 1.0 us);
+// max_iters times the latency of a step, and a step is half as long with four lanes per pair (0.5 to 0.6 instead of 1.0 to 1.2 us);
 // what bounds a large one is instruction issue and the vector cache, where one lane per pair and refilled waves win.
 // Measured, kernel us, k_solve_quad / k_solve_once / k_solve_ws, 24 states per point on a 64x64x16 grid: 12 k pairs
 // 43 / 52 / 69; 48 k 47 / 49 / 74; 98 k 77 / 57 / 81; 192 k 111 / 78 / 93; 288 k 148 / 124 / 115.  The lines are where
@@ -979,7 +979,7 @@ static fs_status dedupe_impl(fs_ctx *ctx, const char *who, int *sums, const floa
     if (K < 1 || K > FS_MAX_BONES) return fail(ctx, FS_E_SHAPE, "%s: K must be in 1..%d", who, (int)FS_MAX_BONES);
     if (N < 0 || (long long)N * K >= (1ll << 31)) return fail(ctx, FS_E_SHAPE, "%s: need 0 <= N and K*N < 2^31", who);
     if (sums != ctx->dd_sums && N > FS_NOALLOC_MAX_N)
-        return fail(ctx, FS_E_SHAPE, "%s: N = %lld exceeds the %lld points this call takes; use fs_dedupe",
+        return fail(ctx, FS_E_SHAPE, "%s: N = %lld exceeds the %lld points that the call with fixed scratch memory takes; use fs_dedupe",
                     who, (long long)N, FS_NOALLOC_MAX_N);
     if (!(min_dist >= 0.0f) || !std::isfinite(min_dist)) return fail(ctx, FS_E_ARG, "%s: min_dist must be finite and >= 0", who);
     if (cap < 0) return fail(ctx, FS_E_SHAPE, "%s: cap must be >= 0", who);
