@@ -31,8 +31,10 @@ fs_status fs_get_timing(fs_ctx *ctx, double *solve_kernel_ms, int32_t *launches)
  *   FS_MB_GATHER_SEGMENT  16-byte loads per second when every lane reads the six pieces of a random pair of adjacent
  *                      48-byte records with six consecutive instructions: the solve kernel's own pattern (two
  *                      z-neighbours of the transform grid), so that this is its ceiling for a grid of array_bytes
+ *   FS_MB_RECIP        *result = how many of the 2^32 floats a have a reciprocal, as the solve computes it (reciprocal
+ *                      instruction and one Newton step), that is a normal number and not the bits of 1 / a: 0
  * array_bytes is used by the three global gathers only (4 KiB .. 4 GiB). */
-enum { FS_MB_FMA = 0, FS_MB_GATHER_LANE = 1, FS_MB_GATHER_LINE = 2, FS_MB_LDS_GATHER = 3, FS_MB_GATHER_SEGMENT = 4 };
+enum { FS_MB_FMA = 0, FS_MB_GATHER_LANE = 1, FS_MB_GATHER_LINE = 2, FS_MB_LDS_GATHER = 3, FS_MB_GATHER_SEGMENT = 4, FS_MB_RECIP = 5 };
 fs_status fs_microbench(int32_t which, int64_t array_bytes, double *result);
 
 #ifdef __cplusplus

@@ -195,11 +195,11 @@ class Context:
         return self._ret(self._L.fs_get_corr(self._h, _ptr(bbox), _ptr(cand)), check)
 
 
-MB_FMA, MB_GATHER_LANE, MB_GATHER_LINE, MB_LDS_GATHER, MB_GATHER_SEGMENT = range(5)
+MB_FMA, MB_GATHER_LANE, MB_GATHER_LINE, MB_LDS_GATHER, MB_GATHER_SEGMENT, MB_RECIP = range(6)
 
 
 def microbench(which: int, array_bytes: int = 3 << 20) -> float:
-    """Run one of the library's micro-benchmarks; returns flop/s (MB_FMA) or 16-byte loads/s."""
+    """Run one of the library's micro-benchmarks; returns flop/s (MB_FMA), a count (MB_RECIP) or 16-byte loads/s."""
     L = load()
     r = ctypes.c_double()
     st = L.fs_microbench(int(which), int(array_bytes), ctypes.byref(r))

@@ -43,15 +43,12 @@ struct Cell {
 
 __device__ __forceinline__ void locate_axis(float x, float lo, float inv_h, float m, int n, int &i0, float &f, bool &cl)
 {
-    float u = (x - lo) * inv_h;
-    bool below = !(u >= 0.0f);          // also true for NaN
-    bool above = u > m;
-    cl = below || above;
-    u = below ? 0.0f : (above ? m : u);
-    int i = (int)__builtin_floorf(u);
-    i = i > n - 2 ? n - 2 : i;
-    i0 = i;
-    f = u - (float)i;
+    // the median of (u, 0, m) is both clamps in one instruction, NaN to 0 included
+    const float u = (x - lo) * inv_h, in = __builtin_amdgcn_fmed3f(u, 0.0f, m);
+    cl = !(u == in);                    // also true for NaN
+    const int i = (int)__builtin_floorf(in);
+    i0 = i > n - 2 ? n - 2 : i;
+    f = in - (float)i0;
 }
 
 __device__ __forceinline__ Cell locate(const GridP &G, const float x[3])
@@ -132,9 +129,26 @@ __device__ __forceinline__ void field_d(const float *__restrict__ Tp, const Grid
     blend_apply(c, q, x, d);
 }
 
-// Forward map plus spatial Jacobian dd/dx (row-major 3x3) from the 8 corner records q of cell c:
-// interpolated rotation part plus the derivative of the interpolation weights applied to every
-// corner's image of x; no weight derivative along an axis on which the lookup was clamped.
+// what corner k with image dc of x adds to the Jacobian: the derivative of its interpolation weight times dc; none along an axis on
+// which the lookup was clamped
+__device__ __forceinline__ void add_weight_derivative(const GridP &G, const Cell &c, int k, const float dc[3], float J[9])
+{
+    const float wx[2] = {1.0f - c.f[0], c.f[0]};
+    const float wy[2] = {1.0f - c.f[1], c.f[1]};
+    const float wz[2] = {1.0f - c.f[2], c.f[2]};
+    const int a = k & 1, b = (k >> 1) & 1, cz = (k >> 2) & 1;
+    float dw[3];
+    dw[0] = c.cl[0] ? 0.0f : (a ? G.inv_h[0] : -G.inv_h[0]) * (wy[b] * wz[cz]);
+    dw[1] = c.cl[1] ? 0.0f : (b ? G.inv_h[1] : -G.inv_h[1]) * (wx[a] * wz[cz]);
+    dw[2] = c.cl[2] ? 0.0f : (cz ? G.inv_h[2] : -G.inv_h[2]) * (wx[a] * wy[b]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) J[r * 3 + j] = FS_FMA(dw[j], dc[r], J[r * 3 + j]);
+}
+
+// Forward map plus spatial Jacobian dd/dx (row-major 3x3) from the 8 corner records q of cell c: interpolated rotation part plus
+// the derivative of the interpolation weights applied to every corner's image of x.
 __device__ __forceinline__ void jacobian_from_corners(const GridP &G, const Cell &c, const float (&q)[8][12],
                                                       const float x[3], float d[3], float J[9])
 {
@@ -148,26 +162,15 @@ __device__ __forceinline__ void jacobian_from_corners(const GridP &G, const Cell
 #pragma unroll
         for (int e = 0; e < 12; ++e) T[e] = FS_FMA(om[k], q[k][e], T[e]);
     apply12(T, x, d);
-    const float wx[2] = {1.0f - c.f[0], c.f[0]};
-    const float wy[2] = {1.0f - c.f[1], c.f[1]};
-    const float wz[2] = {1.0f - c.f[2], c.f[2]};
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
         for (int j = 0; j < 3; ++j) J[r * 3 + j] = T[r * 4 + j];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const int a = k & 1, b = (k >> 1) & 1, cz = (k >> 2) & 1;
         float dc[3];
         apply12(q[k], x, dc);
-        float dw[3];
-        dw[0] = c.cl[0] ? 0.0f : (a ? G.inv_h[0] : -G.inv_h[0]) * (wy[b] * wz[cz]);
-        dw[1] = c.cl[1] ? 0.0f : (b ? G.inv_h[1] : -G.inv_h[1]) * (wx[a] * wz[cz]);
-        dw[2] = c.cl[2] ? 0.0f : (cz ? G.inv_h[2] : -G.inv_h[2]) * (wx[a] * wy[b]);
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) J[r * 3 + j] = FS_FMA(dw[j], dc[r], J[r * 3 + j]);
+        add_weight_derivative(G, c, k, dc, J);
     }
 }
 
@@ -180,6 +183,15 @@ __device__ __forceinline__ void field_dJ(const float *__restrict__ Tp, const Gri
     for (int k = 0; k < 8; ++k) load12(Tp + c.base + corner_off(G, k), q[k]);
     jacobian_from_corners(G, c, q, x, d, J);
 }
+
+// 1 / a from the reciprocal instruction and one Newton step: the bits of the division wherever the result is a normal
+// number, which is for the caller to test (every float compared: fs_microbench kind FS_MB_RECIP).
+__device__ __forceinline__ float recip(float a)
+{
+    const float r = __builtin_amdgcn_rcpf(a);
+    return FS_FMA(FS_FMA(-a, r, 1.0f), r, r);
+}
+__device__ __forceinline__ bool is_normal(float a) { return __builtin_amdgcn_classf(a, 0x108); }
 
 // Adjugate / determinant inverse of a row-major 3x3; false if |det| < 1e-12 or NaN.
 __device__ __forceinline__ bool inv3(const float m[9], float o[9])

@@ -20,6 +20,9 @@ __device__ __forceinline__ int pose_of(const int32_t *__restrict__ pose, long lo
 }
 constexpr int FS_MAX_CORR_K_DEV = 8;
 
+// number of lanes of the wave with `on`, as a scalar (the compiler compares a 64-bit population count on the vector unit)
+__device__ __forceinline__ int lanes_on(bool on) { return __builtin_amdgcn_readfirstlane(__popcll(__ballot(on))); }
+
 // ------------------------------------------------------------------------------------------------
 // Pre-computed LBS (Eq. (13)): one thread per node, all poses.  The bone transforms are read with
 // wave-uniform addresses, i.e. through the scalar cache into SGPR operands of the multiply-adds.
@@ -639,7 +642,7 @@ __global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const flo
 // candidate is a grid node, so its x0, its image d(x0) and J~0 = (dd/dx at x0)^-1 depend on the pose alone, not on
 // the query point.  Entry (4 float4) of candidate k of cell gc, at [(gc * ck + k) * 4]:
 // {x0[3], flags | d(x0)[3], J~0[0] | J~0[1..4] | J~0[5..8]}, flags (integer bits) = 0: no such candidate,
-// 1: usable, 2: Jacobian singular (J~0 = 0), plus the linear index of x0's grid cell << 2.
+// 1: usable, 2: Jacobian singular (J~0 = 0), plus the lower corner node of x0's grid cell << 2.
 // Same arithmetic as a lane computing it for itself (node_pos, the 8 corner records of x0's cell,
 // jacobian_from_corners, inv3).  (By the selecting wave's first lanes, which know the candidate: 136 instead of 30 registers
 // there, 15.7 instead of 8.6 + 4.8 us for 8192 cells, 180 instead of 84 + 24 for 65,536.)
@@ -665,7 +668,7 @@ __global__ __launch_bounds__(256) void k_corr_init(GridP G, CorrP C, const float
 #pragma unroll
             for (int e = 0; e < 9; ++e) Ji[e] = 0.0f;
         }
-        flags = (ok ? 1 : 2) | (cell_linear(G, c0) << 2);
+        flags = (ok ? 1 : 2) | (c0.base / 12 << 2);
     }
     float4 *o = cinit + i * 4;
     o[0] = make_float4(x0[0], x0[1], x0[2], __int_as_float(flags));
@@ -1032,6 +1035,58 @@ __device__ __forceinline__ void park_slots(bool want_slot, int slot_cell, int pa
     }
 }
 
+// Rank-one update of J~ (good Broyden, inverse form) with u = dx - J~ dg, v = dx^T J~, den = v dg; none where den is 0 or not finite.
+__device__ __forceinline__ void rank_one(float (&J)[9], const float (&u)[3], const float (&v)[3], float den)
+{
+    if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
+        float rinv = recip(den);
+        if (__builtin_expect(__any(!is_normal(rinv)), 0)) {
+            asm volatile("");                // a branch: the division is not to be computed in every step
+            rinv = 1.0f / den;
+        }
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const float sc = u[r] * rinv;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) J[r * 3 + c] = FS_FMA(sc, v[c], J[r * 3 + c]);
+        }
+    }
+}
+
+// the next step dx = -J~ g, and x moved by it
+__device__ __forceinline__ void advance(const float (&J)[9], const float (&g)[3], float (&x)[3], float (&dx)[3])
+{
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
+        x[r] = x[r] + dx[r];
+    }
+}
+
+// What follows once the field's residual gn at the new x is known: the update of J~ and the test.  True: the pair has ended.
+// A step begins with advance() rather than ending with it, so that x and J~ have one place each and the test has no branch: with the next
+// step computed in a branch after the test, and loops that end at their head, the compiler copied the state to other registers and back
+// in every pass (a pass of k_solve_once 311 vector instructions, now 233; of a quad 155, now 145).
+__device__ __forceinline__ bool finish_step(const SolveP &S, const float (&dx)[3], const float (&gn)[3], float (&g)[3], float (&J)[9],
+                                            int &it, bool &conv)
+{
+    float dg[3], v[3], u[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) dg[r] = gn[r] - g[r];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[c] = FS_FMA(dx[2], J[6 + c], FS_FMA(dx[1], J[3 + c], dx[0] * J[c]));
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        u[r] = dx[r] - FS_FMA(J[r * 3 + 2], dg[2], FS_FMA(J[r * 3 + 1], dg[1], J[r * 3] * dg[0]));
+    rank_one(J, u, v, FS_FMA(v[2], dg[2], FS_FMA(v[1], dg[1], v[0] * dg[0])));
+    ++it;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) g[r] = gn[r];
+    const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
+    conv = r2 < S.tol2;
+    return conv || !(r2 < S.div2) || it >= S.max_iters;
+}
+
 // ---- four SIMD lanes per pair ---------------------------------------------------------------------------------------
 // A pair whose trajectory is long is bound by the latency of a step: a chain of cell lookup, 8 corner records, blend,
 // rank-one update.  With one lane per pair a step costs the wave some 320 vector instructions and 24 gathered loads
@@ -1112,18 +1167,12 @@ __device__ __forceinline__ void quad_blend(const float (&om)[8], const float (&q
 }
 
 // One Broyden step of the pair of every active quad.  x, g, J: its state, xpr: x' along the lane's axis, it: steps taken;
-// q, held: the lane's row of the corner records and the base of the cell they belong to (-1: none).  Returns bit 0: the
-// pair has ended, bit 1: it has converged.
-__device__ __forceinline__ int quad_step(const GridP &G, const QuadAxis &A, float tol2, float div2, int max_iters,
-                                         const float *__restrict__ Tp, float xpr, float (&x)[3], float (&g)[3], float (&J)[9],
-                                         int &it, float (&q)[8][4], int &held)
+// q, held: the lane's row of the corner records and the base of the cell they belong to (-1: none).  True: the pair has ended.
+__device__ __forceinline__ bool quad_step(const GridP &G, const SolveP &S, const QuadAxis &A, const float *__restrict__ Tp, float xpr,
+                                          float (&x)[3], float (&g)[3], float (&J)[9], int &it, float (&q)[8][4], int &held, bool &conv)
 {
-    float dx[3], gn[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
-        x[r] = x[r] + dx[r];
-    }
+    float dx[3];
+    advance(J, g, x, dx);
     const Cell cell = quad_locate(A, x);
     if (cell.base != held) {
         quad_load(Tp + cell.base, G, A.row, q);
@@ -1133,33 +1182,8 @@ __device__ __forceinline__ int quad_step(const GridP &G, const QuadAxis &A, floa
     corner_weights(cell, om);
     quad_blend(om, q, T);
     const float gr = quad_apply(T, x) - xpr;
-    gn[0] = quad_get<0>(gr);
-    gn[1] = quad_get<1>(gr);
-    gn[2] = quad_get<2>(gr);
-    float dg[3], v[3], u[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) dg[r] = gn[r] - g[r];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) v[c] = FS_FMA(dx[2], J[6 + c], FS_FMA(dx[1], J[3 + c], dx[0] * J[c]));
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-        u[r] = dx[r] - FS_FMA(J[r * 3 + 2], dg[2], FS_FMA(J[r * 3 + 1], dg[1], J[r * 3] * dg[0]));
-    const float den = FS_FMA(v[2], dg[2], FS_FMA(v[1], dg[1], v[0] * dg[0]));
-    if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
-        const float rinv = 1.0f / den;
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const float sc = u[r] * rinv;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) J[r * 3 + c] = FS_FMA(sc, v[c], J[r * 3 + c]);
-        }
-    }
-    ++it;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) g[r] = gn[r];
-    const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
-    const bool conv = r2 < tol2;
-    return ((conv || !(r2 < div2) || it >= max_iters) ? 1 : 0) | (conv ? 2 : 0);
+    const float gn[3] = {quad_get<0>(gr), quad_get<1>(gr), quad_get<2>(gr)};
+    return finish_step(S, dx, gn, g, J, it, conv);
 }
 
 // A wave whose last QUADS pairs (or fewer) are all that is left for it hands them from single lanes to quads: quad j
@@ -1204,14 +1228,13 @@ __device__ __forceinline__ void quad_tail(const GridP &G, const SolveP &S, const
     k = __shfl(k, src);
     pz = __shfl(pz, src);
     const float *Tp = T + (long long)pz * G.V * 12;
-    int end = 0;
+    bool conv = false;
     if (on) {
         float q[8][4];
         int held = -1;
-        do end = quad_step(G, A, S.tol2, S.div2, S.max_iters, Tp, xpr, x, g, J, it, q, held);
-        while (!(end & 1));
+        while (!quad_step(G, S, A, Tp, xpr, x, g, J, it, q, held, conv)) {}
     }
-    emit(on && (lane & 3) == 0, (end & 2) != 0, x, J, it, n, k, pz);
+    emit(on && (lane & 3) == 0, conv, x, J, it, n, k, pz);
 }
 
 // Broyden solve for a transform grid (all poses) small enough to be held in LDS: every block copies it there
@@ -1261,7 +1284,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
     long long n = 0;
     int k = 0, it = 0, pz = 0;
     const float *Tp = T;
-    float xp[3] = {0, 0, 0}, x[3] = {0, 0, 0}, xt[3] = {0, 0, 0}, g[3] = {0, 0, 0}, dx[3] = {0, 0, 0};
+    float xp[3] = {0, 0, 0}, x[3] = {0, 0, 0}, g[3] = {0, 0, 0};
     float J[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     float q[8][12];                  // corner records of the lane's current cell, kept across iterations
     long long held = -1;             // grid offset of the cell whose corners q holds (-1: none)
@@ -1311,7 +1334,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
                     for (int r = 0; r < 3; ++r) xp[r] = xq[r * N + n];
                     if (FUSED) {
 #pragma unroll
-                        for (int r = 0; r < 3; ++r) xt[r] = 0.0f;
+                        for (int r = 0; r < 3; ++r) x[r] = 0.0f;
 #pragma unroll
                         for (int e = 0; e < 9; ++e) J[e] = 0.0f;
                         if (I.mode == 0) {
@@ -1321,22 +1344,22 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
                                 const float y[3] = {xp[0] - bi[9], xp[1] - bi[10], xp[2] - bi[11]};
 #pragma unroll
                                 for (int r = 0; r < 3; ++r)
-                                    xt[r] = FS_FMA(bi[r * 3 + 0], y[0], FS_FMA(bi[r * 3 + 1], y[1], bi[r * 3 + 2] * y[2]));
+                                    x[r] = FS_FMA(bi[r * 3 + 0], y[0], FS_FMA(bi[r * 3 + 1], y[1], bi[r * 3 + 2] * y[2]));
                             }
                         } else {
                             const int cidx = cell_index(I.C, I.bbox + p * 6, xp);
                             const int v = I.cand[((long long)p * I.C.ncell + cidx) * I.C.ck + k];
                             ok = v >= 0;
                             norec = !ok;
-                            if (ok) node_pos(G, v, xt);
+                            if (ok) node_pos(G, v, x);
                         }
                         if (ok) {
-                            const Cell c0 = locate(G, xt);
+                            const Cell c0 = locate(G, x);
 #pragma unroll
                             for (int c = 0; c < 8; ++c) load12(Tp + c0.base + corner_off(G, c), q[c]);
                             held = (long long)(Tp - T) + c0.base;
                             float d0[3], Jac[9];
-                            jacobian_from_corners(G, c0, q, xt, d0, Jac);
+                            jacobian_from_corners(G, c0, q, x, d0, Jac);
                             ok = inv3(Jac, J);
                             if (!ok) {
 #pragma unroll
@@ -1345,7 +1368,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
                         }
                     } else {
 #pragma unroll
-                        for (int r = 0; r < 3; ++r) xt[r] = x0[((long long)k * 3 + r) * N + n];
+                        for (int r = 0; r < 3; ++r) x[r] = x0[((long long)k * 3 + r) * N + n];
 #pragma unroll
                         for (int e = 0; e < 9; ++e) J[e] = J0[((long long)k * 9 + e) * N + n];
                         ok = valid0[(long long)k * N + n] != 0;
@@ -1354,7 +1377,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
                         active = true;
                         fresh = true;
                     } else if (!norec) {
-                        write_record<WITH_J>(rec, (long long)k * N + n, xt, J, 0);
+                        write_record<WITH_J>(rec, (long long)k * N + n, x, J, 0);
                     }
                 }
                 next += min((long long)nidle, c1 - next);
@@ -1367,59 +1390,37 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
         bool want_slot = false;
         int slot_cell = 0;
         if (active) {
-            float d[3], gn[3];
+            float dx[3], d[3], gn[3];
+            if (!fresh) advance(J, g, x, dx);
             // steps shrink as a lane converges, so it often stays in the cell it was in: reload the
             // 8 corner records only when the cell changed
-            const Cell cell = locate(G, xt);
+            const Cell cell = locate(G, x);
             const long long want = (long long)(Tp - T) + cell.base;
             if (want != held) {
 #pragma unroll
                 for (int c = 0; c < 8; ++c) load12(Tp + cell.base + corner_off(G, c), q[c]);
                 held = want;
             }
-            blend_apply(cell, q, xt, d);
+            blend_apply(cell, q, x, d);
 #pragma unroll
             for (int r = 0; r < 3; ++r) gn[r] = d[r] - xp[r];
-            if (!fresh) {
-                float dg[3], v[3], u[3];
+            bool conv, ends;
+            if (!fresh) ends = finish_step(S, dx, gn, g, J, it, conv);
+            else {
+                fresh = false;
 #pragma unroll
-                for (int r = 0; r < 3; ++r) dg[r] = gn[r] - g[r];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) v[c] = FS_FMA(dx[2], J[6 + c], FS_FMA(dx[1], J[3 + c], dx[0] * J[c]));
-#pragma unroll
-                for (int r = 0; r < 3; ++r)
-                    u[r] = dx[r] - FS_FMA(J[r * 3 + 2], dg[2], FS_FMA(J[r * 3 + 1], dg[1], J[r * 3] * dg[0]));
-                const float den = FS_FMA(v[2], dg[2], FS_FMA(v[1], dg[1], v[0] * dg[0]));
-                if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
-                    const float rinv = 1.0f / den;
-#pragma unroll
-                    for (int r = 0; r < 3; ++r) {
-                        const float s = u[r] * rinv;
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) J[r * 3 + c] = FS_FMA(s, v[c], J[r * 3 + c]);
-                    }
-                }
-                ++it;
+                for (int r = 0; r < 3; ++r) g[r] = gn[r];
+                const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
+                conv = r2 < S.tol2;
+                ends = conv || !(r2 < S.div2) || 0 >= S.max_iters;
             }
-            fresh = false;
-#pragma unroll
-            for (int r = 0; r < 3; ++r) { x[r] = xt[r]; g[r] = gn[r]; }
-            const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
-            const bool conv = r2 < S.tol2;
-            const bool done = conv || !(r2 < S.div2) || it >= S.max_iters;
-            if (done) {
+            if (ends) {
                 write_record<WITH_J>(rec, (long long)k * N + n, x, J, (conv ? 1 : 0) | (it << 8));
                 if (WITH_J && cell_count && conv) {
                     want_slot = true;
                     slot_cell = pz * ncell + cell_linear(G, cell);
                 }
                 active = false;
-            } else {
-#pragma unroll
-                for (int r = 0; r < 3; ++r) {
-                    dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
-                    xt[r] = x[r] + dx[r];
-                }
             }
         }
         // For the backward every converged lane needs its arrival position in the list of its grid cell: one
@@ -1481,11 +1482,20 @@ __device__ __forceinline__ void lds_store_release(int *p, int v)
 constexpr int OUT_PEND = 128, OUT_SEND = 112;
 struct OutQ {
     float4 rec[OUT_PEND][4];
-    int cell[OUT_PEND];       // grid cell (pose * ncell + cell) of a converged lane that wants a position, else -1
+    int place[OUT_PEND];      // where in the transform grids the cell of a converged lane that wants a position begins, else -1
     int pair[OUT_PEND];
 };
 
-__device__ __forceinline__ void out_flush(OutQ &q, int npend, int lane, int *__restrict__ cell_count, float4 *__restrict__ rec)
+// pose * ncell + grid cell, from where the cell's lower corner record lies in the grids of all poses (in floats)
+__device__ __forceinline__ int cell_at(const GridP &G, int ncell, int place)
+{
+    const unsigned t = (unsigned)place / 12u, p = div_by(t, (unsigned)G.V, G.mag_V), v = t - p * (unsigned)G.V;
+    const unsigned c = div_by(v, (unsigned)G.nz, G.mag_nz), ix = div_by(c, (unsigned)G.ny, G.mag_ny);       // c = ix * ny + iy
+    return (int)(p * (unsigned)ncell + (c - ix) * (unsigned)(G.nz - 1) + v - c * (unsigned)G.nz);
+}
+
+__device__ __forceinline__ void out_flush(const GridP &G, OutQ &q, int npend, int lane, int *__restrict__ cell_count, int ncell,
+                                          float4 *__restrict__ rec)
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the LDS writes of the wave's other lanes
     __builtin_amdgcn_wave_barrier();
@@ -1495,8 +1505,9 @@ __device__ __forceinline__ void out_flush(OutQ &q, int npend, int lane, int *__r
         CellGroup g[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const int c = 64 * b + lane < npend ? q.cell[64 * b + lane] : -1;
-            valid[b] = c >= 0;
+            const int at = 64 * b + lane < npend ? q.place[64 * b + lane] : -1;
+            valid[b] = at >= 0;
+            const int c = valid[b] ? cell_at(G, ncell, at) : -1;
             g[b] = group_request(valid[b], c, lane, cell_count);
         }
 #pragma unroll
@@ -1512,14 +1523,14 @@ __device__ __forceinline__ void out_flush(OutQ &q, int npend, int lane, int *__r
     __builtin_amdgcn_wave_barrier();
 }
 
-// park the record of every lane with `want` (wave-wide call); cell < 0: no position wanted
-__device__ __forceinline__ void out_park(bool want, const float x[3], const float J[9], int flags, int cell, int pair, OutQ &q,
-                                         int &npend, int lane, int *__restrict__ cell_count, float4 *__restrict__ rec)
+// park the record of every lane with `want` (wave-wide call); place < 0: no position wanted
+__device__ __forceinline__ void out_park(const GridP &G, bool want, const float x[3], const float J[9], int flags, int place, int pair,
+                                         OutQ &q, int &npend, int lane, int *__restrict__ cell_count, int ncell, float4 *__restrict__ rec)
 {
     const unsigned long long m = __ballot(want);
     if (m) {
         if (npend + __popcll(m) > OUT_PEND) {
-            out_flush(q, npend, lane, cell_count, rec);
+            out_flush(G, q, npend, lane, cell_count, ncell, rec);
             npend = 0;
         }
         if (want) {
@@ -1528,13 +1539,13 @@ __device__ __forceinline__ void out_park(bool want, const float x[3], const floa
             q.rec[at][1] = make_float4(__int_as_float(-1), J[0], J[1], J[2]);
             q.rec[at][2] = make_float4(J[3], J[4], J[5], J[6]);
             q.rec[at][3] = make_float4(J[7], J[8], 0.0f, 0.0f);
-            q.cell[at] = cell;
+            q.place[at] = place;
             q.pair[at] = pair;
         }
         npend += __popcll(m);
     }
     if (npend >= OUT_SEND) {
-        out_flush(q, npend, lane, cell_count, rec);
+        out_flush(G, q, npend, lane, cell_count, ncell, rec);
         npend = 0;
     }
 }
@@ -1610,18 +1621,18 @@ __device__ __forceinline__ bool blend_apply_z(const Cell &c, const float (&q)[8]
     return m == 0.0f;
 }
 
-// One Broyden step of one pair per lane: the field at xt, the update of J~, the test, and if the pair goes on, the next
-// step.  q, held, held_mask: the corner records the lane holds, their cell's base inside the pose's grid (-1: none) and
-// with SKIP which of them.  cell: of the new x.  Returns bit 0: the pair has ended, bit 1: it has converged.
+// One Broyden step of one pair per lane: the step, the field at the new x, the update of J~, the test.  q, held, held_mask: the corner records the lane holds, their cell's base inside the pose's grid (-1: none) and
+// with SKIP which of them.  True: the pair has ended.
 template <bool SKIP>
-__device__ __forceinline__ int lane_step(const GridP &G, const SolveP &S, const float *__restrict__ Tp, bool may_skip,
-                                         const float (&xp)[3], float (&x)[3], float (&xt)[3], float (&dx)[3], float (&g)[3],
-                                         float (&J)[9], int &it, float (&q)[8][12], int &held, int &held_mask, Cell &cell)
+__device__ __forceinline__ bool lane_step(const GridP &G, const SolveP &S, const float *__restrict__ Tp, bool may_skip,
+                                          const float (&xp)[3], float (&x)[3], float (&g)[3], float (&J)[9], int &it,
+                                          float (&q)[8][12], int &held, int &held_mask, bool &conv)
 {
-    float d[3], gn[3];
+    float dx[3], d[3], gn[3];
+    advance(J, g, x, dx);
     // steps shrink as a lane converges, so it often stays in the cell it was in: the records are fetched again only when
     // the cell changed
-    cell = locate(G, xt);
+    const Cell cell = locate(G, x);
     if (SKIP) {
         const int need = may_skip ? corners_needed(cell) : 0xFF;
         if (cell.base != held) {
@@ -1632,50 +1643,21 @@ __device__ __forceinline__ int lane_step(const GridP &G, const SolveP &S, const 
             load_corners(Tp + cell.base, G, need & ~held_mask, q);
             held_mask |= need;
         }
-        if (blend_apply_z(cell, q, xt, d) && held_mask != 0xFF) {
+        if (blend_apply_z(cell, q, x, d) && held_mask != 0xFF) {
             load_corners(Tp + cell.base, G, 0xFF & ~held_mask, q);
             held_mask = 0xFF;
-            blend_apply(cell, q, xt, d);
+            blend_apply(cell, q, x, d);
         }
     } else {
         if (cell.base != held) {
             load_cell(Tp + cell.base, G, q);
             held = cell.base;
         }
-        blend_apply(cell, q, xt, d);
+        blend_apply(cell, q, x, d);
     }
 #pragma unroll
     for (int r = 0; r < 3; ++r) gn[r] = d[r] - xp[r];
-    float dg[3], v[3], u[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) dg[r] = gn[r] - g[r];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) v[c] = FS_FMA(dx[2], J[6 + c], FS_FMA(dx[1], J[3 + c], dx[0] * J[c]));
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-        u[r] = dx[r] - FS_FMA(J[r * 3 + 2], dg[2], FS_FMA(J[r * 3 + 1], dg[1], J[r * 3] * dg[0]));
-    const float den = FS_FMA(v[2], dg[2], FS_FMA(v[1], dg[1], v[0] * dg[0]));
-    if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
-        const float rinv = 1.0f / den;
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const float sc = u[r] * rinv;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) J[r * 3 + c] = FS_FMA(sc, v[c], J[r * 3 + c]);
-        }
-    }
-    ++it;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) { x[r] = xt[r]; g[r] = gn[r]; }
-    const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
-    const bool conv = r2 < S.tol2;
-    if (conv || !(r2 < S.div2) || it >= S.max_iters) return conv ? 3 : 1;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
-        xt[r] = x[r] + dx[r];
-    }
-    return 0;
+    return finish_step(S, dx, gn, g, J, it, conv);
 }
 
 template <bool FUSED, bool WITH_J, int NCONS, bool SKIP>
@@ -1703,6 +1685,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
     const long long N = S.N;
     int npend = 0;                   // wave-uniform: entries of the wave's s_out in use
     OutQ &outq = s_out[WITH_J ? wib : 0];
+    const int stride = (int)G.V * 12;          // of the poses' grids; P of them are below 2^31
 
     if (wib == NCONS) {
         // ------------------------------------------------ producer ------------------------------------------------
@@ -1766,7 +1749,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
             const long long pq = next + lane;
             next += min(64ll, c1 - next);
             bool keep = false, want_out = false;
-            int out_cell = -1, out_flags = 0, pair = 0;
+            int out_place = -1, out_flags = 0, pair = 0;
             int nn = 0, nk = 0, np = 0;
             float nxp[3] = {0, 0, 0}, nx[3] = {0, 0, 0}, ng[3] = {0, 0, 0};
             float nJ[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -1790,7 +1773,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                 const float *Tn = T + (long long)np * G.V * 12;
                 bool ok, norec = false;     // norec: no record needed, k_solve_unpack knows the answer
                 float d[3] = {0, 0, 0};
-                int c0lin = 0;              // grid cell of the initial state
+                int base0 = 0;              // of the initial state's cell
 #pragma unroll
                 for (int r = 0; r < 3; ++r) nxp[r] = xq[r * N + nn];
                 if (FUSED && SKIP) {
@@ -1803,7 +1786,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                         for (int r = 0; r < 3; ++r)
                             nx[r] = FS_FMA(bi[r * 3 + 0], y[0], FS_FMA(bi[r * 3 + 1], y[1], bi[r * 3 + 2] * y[2]));
                         const Cell c0 = locate(G, nx);
-                        c0lin = cell_linear(G, c0);
+                        base0 = c0.base;
                         float qn[8][12];
                         // corner records of weight zero contribute nothing to the Jacobian either (the derivative of
                         // their weight vanishes along the clamped axis by definition and carries the zero factor
@@ -1846,7 +1829,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                     const int fl = __float_as_int(a.w);
                     ok = (fl & 1) != 0;
                     norec = (fl & 3) == 0;
-                    c0lin = fl >> 2;
+                    base0 = (fl >> 2) * 12;
                     nx[0] = a.x; nx[1] = a.y; nx[2] = a.z;
                     d[0] = b.x; d[1] = b.y; d[2] = b.z;
                     nJ[0] = b.w; nJ[1] = c.x; nJ[2] = c.y; nJ[3] = c.z; nJ[4] = c.w;
@@ -1859,7 +1842,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                     ok = valid0[(long long)nk * N + nn] != 0;
                     if (ok) {
                         const Cell c0 = locate(G, nx);
-                        c0lin = cell_linear(G, c0);
+                        base0 = c0.base;
                         float qn[8][12];
 #pragma unroll
                         for (int c = 0; c < 8; ++c) load12(Tn + c0.base + corner_off(G, c), qn[c]);
@@ -1875,7 +1858,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                         if (WITH_J) {
                             want_out = true;
                             out_flags = conv ? 1 : 0;
-                            if (cell_count && conv) out_cell = np * ncell + c0lin;
+                            if (cell_count && conv) out_place = np * stride + base0;
                         } else {
                             write_record<false>(rec, pair, nx, nJ, conv ? 1 : 0);
                         }
@@ -1930,10 +1913,10 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                 for (int c = 0; c < NCONS; ++c) if (c == best) tails[c] = tl;
                 if (lane == 0) lds_store_release(&s_tail[best], tl);
             }
-            if (WITH_J) out_park(want_out, nx, nJ, out_flags, out_cell, pair, outq, npend, lane, cell_count, rec);
+            if (WITH_J) out_park(G, want_out, nx, nJ, out_flags, out_place, pair, outq, npend, lane, cell_count, ncell, rec);
         }
         if (lost && lane == 0) *give_up = 1;
-        if (WITH_J && npend > 0) out_flush(outq, npend, lane, cell_count, rec);
+        if (WITH_J && npend > 0) out_flush(G, outq, npend, lane, cell_count, ncell, rec);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         if (lane == 0) lds_store_release(&s_done, 1);
         return;
@@ -1945,9 +1928,9 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
     auto emit = [&](bool ends, bool conv, const float (&xe)[3], const float (&Je)[9], int ite, int ne, int ke, int pe) {
         const int flags = (conv ? 1 : 0) | (ite << 8), pair = (int)((long long)ke * N + ne);
         if (WITH_J) {
-            int cell = -1;
-            if (ends && cell_count && conv) cell = pe * ncell + cell_linear(G, locate(G, xe));
-            out_park(ends, xe, Je, flags, cell, pair, outq, npend, lane, cell_count, rec);
+            int place = -1;
+            if (ends && cell_count && conv) place = pe * stride + locate(G, xe).base;
+            out_park(G, ends, xe, Je, flags, place, pair, outq, npend, lane, cell_count, ncell, rec);
         } else if (ends) {
             write_record<false>(rec, pair, xe, Je, flags);
         }
@@ -1955,7 +1938,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
     bool active = false;
     int n = 0, k = 0, it = 0, pz = 0, head = 0;
     const float *Tp = T;
-    float xp[3] = {0, 0, 0}, x[3] = {0, 0, 0}, xt[3] = {0, 0, 0}, g[3] = {0, 0, 0}, dx[3] = {0, 0, 0};
+    float xp[3] = {0, 0, 0}, x[3] = {0, 0, 0}, g[3] = {0, 0, 0};
     float J[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     float q[8][12];                  // corner records of the lane's current cell, kept across iterations
     int held = -1;                   // base of the cell whose corners q holds (-1: none)
@@ -1969,10 +1952,8 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
             for (int e = 0; e < 12; ++e) q[c][e] = 0.0f;
     }
     bool fin = false;                // wave-uniform: the producer has left and the queue is empty
-    while (true) {
-        const unsigned long long idle = __ballot(!active);
-        const int nidle = __popcll(idle);
-        if (fin && 64 - nidle <= QUADS) break;
+    int nidle = 64;
+    do {                             // (test at the end: see k_solve_once)
         if (nidle >= S.refill_min && !fin) {
             // s_done is read before the tail: the producer raises it last
             const int d = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_done));
@@ -1980,6 +1961,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
             const int avail = tail - head;
             fin = d && avail <= nidle;
             if (avail > 0) {
+                const unsigned long long idle = __ballot(!active);
                 const int rank = __popcll(idle & ((1ull << lane) - 1ull));
                 if (!active && rank < avail) {
                     const int e = (head + rank) & (WS_RING - 1);
@@ -1994,11 +1976,6 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                     n = __float_as_int(ring[ST_N][e]);
                     k = __float_as_int(ring[ST_K][e]);
                     pz = __float_as_int(ring[ST_P][e]);
-#pragma unroll
-                    for (int r = 0; r < 3; ++r) {
-                        dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
-                        xt[r] = x[r] + dx[r];
-                    }
                     Tp = T + (long long)pz * G.V * 12;
                     it = 0;
                     held = -1;
@@ -2014,17 +1991,16 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
         // s_done on every way out: this loop ends when the producer has
         if (!__any(active) && !fin) __builtin_amdgcn_s_sleep(8);
         bool want_out = false;
-        int out_cell = -1, out_flags = 0;
+        int out_place = -1, out_flags = 0;
         if (active) {
-            Cell cell;
-            const int end = lane_step<SKIP>(G, S, Tp, may_skip, xp, x, xt, dx, g, J, it, q, held, held_mask, cell);
-            if (end & 1) {
+            bool conv;
+            if (lane_step<SKIP>(G, S, Tp, may_skip, xp, x, g, J, it, q, held, held_mask, conv)) {
                 if (WITH_J) {
                     want_out = true;
-                    out_flags = (end >> 1) | (it << 8);
-                    if (cell_count && (end & 2)) out_cell = pz * ncell + cell_linear(G, cell);
+                    out_flags = (conv ? 1 : 0) | (it << 8);
+                    if (cell_count && conv) out_place = pz * stride + held;
                 } else {
-                    write_record<false>(rec, (long long)k * N + n, x, J, (end >> 1) | (it << 8));
+                    write_record<false>(rec, (long long)k * N + n, x, J, (conv ? 1 : 0) | (it << 8));
                 }
                 active = false;
             } else if (!SKIP && S.prefetch) {
@@ -2032,18 +2008,21 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                 // its results and the next one looks for work (q is free: its records went into d above).  On the
                 // 8-pose grid, whose records come from beyond the L2: 1.34 -> 1.32 ms; on a grid the L2 holds the
                 // second cell lookup costs more than the head start gains (0.172 -> 0.186 ms), hence the switch
-                const Cell cn = locate(G, xt);
+                float xn[3] = {x[0], x[1], x[2]}, dn[3];
+                advance(J, g, xn, dn);
+                const Cell cn = locate(G, xn);
                 if (cn.base != held) {
                     load_cell(Tp + cn.base, G, q);
                     held = cn.base;
                 }
             }
         }
-        if (WITH_J) out_park(want_out, x, J, out_flags, out_cell, (int)((long long)k * N + n), outq, npend, lane, cell_count, rec);
-    }
+        if (WITH_J) out_park(G, want_out, x, J, out_flags, out_place, (int)((long long)k * N + n), outq, npend, lane, cell_count, ncell, rec);
+        nidle = 64 - lanes_on(active);
+    } while (!(fin && 64 - nidle <= QUADS));
     // the wave's last pairs, four lanes each
     quad_tail(G, S, T, active, lane, xp, x, g, J, it, n, k, pz, emit);
-    if (WITH_J && npend > 0) out_flush(outq, npend, lane, cell_count, rec);
+    if (WITH_J && npend > 0) out_flush(G, outq, npend, lane, cell_count, ncell, rec);
 }
 
 // Which pairs a wave of the kernels for small batches takes: `per` pairs (64, or 16 quads), as a tile of ki initial states
@@ -2180,10 +2159,8 @@ __global__ __launch_bounds__(LDS ? 1024 : 256) void k_solve_quad(GridP G, SolveP
         conv = r2 < S.tol2;
         if (!(conv || !(r2 < S.div2) || 0 >= S.max_iters)) {
             float q[8][4];
-            int held = -1, end;
-            do end = quad_step(G, A, S.tol2, S.div2, S.max_iters, Tp, xpr, x, g, J, it, q, held);
-            while (!(end & 1));
-            conv = (end & 2) != 0;
+            int held = -1;
+            while (!quad_step(G, S, A, Tp, xpr, x, g, J, it, q, held, conv)) {}
         }
     }
     int pos = -1;
@@ -2247,7 +2224,7 @@ __global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(Gri
     const unsigned pair = (unsigned)k * (unsigned)N + (unsigned)n;
     const int p = pose_of(pose, n, G.P);
     const float *Tp = T + (long long)p * G.V * 12;
-    float xp[3], x[3] = {0, 0, 0}, xt[3], dx[3], g[3] = {0, 0, 0}, d[3] = {0, 0, 0}, J[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    float xp[3], x[3] = {0, 0, 0}, g[3] = {0, 0, 0}, d[3] = {0, 0, 0}, J[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     float q[8][12];
     int held = -1, held_mask = 0, it = 0;
 #pragma unroll
@@ -2311,22 +2288,19 @@ __global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(Gri
         const bool conv = r2 < S.tol2;
         flags = conv ? 1 : 0;
         active = !(conv || !(r2 < S.div2) || 0 >= S.max_iters);
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            dx[r] = -FS_FMA(J[r * 3 + 2], g[2], FS_FMA(J[r * 3 + 1], g[1], J[r * 3] * g[0]));
-            xt[r] = x[r] + dx[r];
-        }
     }
     const bool may_skip = SKIP && __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
-    while (__popcll(__ballot(active)) > QUADS) {
-        if (active) {
-            Cell cell;
-            const int end = lane_step<SKIP>(G, S, Tp, may_skip, xp, x, xt, dx, g, J, it, q, held, held_mask, cell);
-            if (end & 1) {
-                active = false;
-                flags = end >> 1;
+    // the test stands at the loop's end: at its head the compiler moves the whole state to other registers and back in every pass
+    if (lanes_on(active) > QUADS) {
+        do {
+            if (active) {
+                bool conv;
+                if (lane_step<SKIP>(G, S, Tp, may_skip, xp, x, g, J, it, q, held, held_mask, conv)) {
+                    active = false;
+                    flags = conv ? 1 : 0;
+                }
             }
-        }
+        } while (lanes_on(active) > QUADS);
     }
     auto output = [&](bool ends, unsigned pr, bool conv, const float (&xe)[3], const float (&Je)[9], int ite, int ne, int ke, int pe) {
         int pos = -1;

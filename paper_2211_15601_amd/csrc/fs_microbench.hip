@@ -4,6 +4,8 @@
 // same gathers from LDS.  Not part of the articulation path itself.
 #include "../../include/fastsnarf_bench.h"
 
+#include "fs_field.hpp"
+
 #include <hip/hip_runtime.h>
 
 namespace {
@@ -79,6 +81,18 @@ __global__ __launch_bounds__(256) void mb_fma(int iters, float *__restrict__ sin
     if (r == 123.456f) sink[threadIdx.x] = r;
 }
 
+// 2^20 threads, 4096 floats each
+__global__ __launch_bounds__(256) void mb_recip(unsigned long long *__restrict__ differ)
+{
+    const unsigned first = (blockIdx.x * 256u + threadIdx.x) * 4096u;
+    unsigned n = 0;
+    for (unsigned i = 0; i < 4096u; ++i) {
+        const float a = __uint_as_float(first + i), r = fs::recip(a);
+        if (fs::is_normal(r) && __float_as_uint(r) != __float_as_uint(1.0f / a)) ++n;
+    }
+    if (n) atomicAdd(differ, (unsigned long long)n);
+}
+
 template <class F>
 bool time_ms(F launch, float *ms)
 {
@@ -140,6 +154,12 @@ extern "C" fs_status fs_microbench(int32_t which, int64_t array_bytes, double *r
         const int fi = 2048;
         ok = time_ms([&] { mb_fma<<<256 * 16, 256>>>(fi, reinterpret_cast<float *>(sink)); }, &ms);
         if (ok) *result = (double)(256 * 16) * 256 * fi * 128 * 2 / (ms * 1e-3);       // flop per second
+    } else if (which == FS_MB_RECIP) {
+        unsigned long long *differ = reinterpret_cast<unsigned long long *>(sink), n = 0;
+        ok = hipMemset(differ, 0, sizeof n) == hipSuccess;
+        if (ok) mb_recip<<<4096, 256>>>(differ);
+        ok = ok && hipGetLastError() == hipSuccess && hipMemcpy(&n, differ, sizeof n, hipMemcpyDeviceToHost) == hipSuccess;
+        if (ok) *result = (double)n;
     } else {
         st = FS_E_ARG;
     }
