@@ -267,6 +267,7 @@ constexpr size_t FS_LDS_GRID_MAX = 60 * 1024;
 // ... by one block of 12 waves per CU: the CU's 160 KiB less the 12 KiB of parked requests of those waves
 constexpr int FS_LDS_BIG_WAVES = 12;
 constexpr size_t FS_LDS_GRID_MAX_BIG = 148 * 1024;
+constexpr size_t L2_BYTES = 4u << 20;       // of an XCD
 
 // the counts of converged lanes per grid cell that a solve with slots keeps
 fs_status need_solve_counts(fs_ctx *c, int ncell)
@@ -404,7 +405,7 @@ fs_status fs_create(const fs_grid_desc *desc, const fs_params *params, void *hip
             }
             per_cu = 1;
         } else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_solve<true, true>, 256, gb <= FS_LDS_GRID_MAX ? gb : 0) != hipSuccess || per_cu < 1) per_cu = 1;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_ws, k_solve_ws<true, true, FS_WS_CONSUMERS, false>, 64 * (FS_WS_CONSUMERS + 1), 0) != hipSuccess || per_cu_ws < 1) per_cu_ws = 2;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_ws, k_solve_ws<true, true, FS_WS_CONSUMERS, true>, 64 * (FS_WS_CONSUMERS + 1), 0) != hipSuccess || per_cu_ws < 1) per_cu_ws = 2;
         c->occ_ws_blocks_per_cu = per_cu_ws;
         int per_cu_vx = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_vx, k_solve_ws<true, true, FS_VX_CONSUMERS, false>, 64 * (FS_VX_CONSUMERS + 1), 0) != hipSuccess || per_cu_vx < 1) per_cu_vx = 2;
@@ -616,12 +617,16 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const bool lds = (ctx->lds_grid && grid_bytes <= FS_LDS_GRID_MAX) || lds_big;
     // Launch shape.  Grid in LDS (k_solve): latency / ALU bound, every wave the registers allow, refill at 32 idle
     // lanes.  Grid read through the caches (k_solve_ws, bound by the vector-memory path): blocks of one producer and
-    // several consumers, 2 blocks per CU (measured: more waves that compute Eq. (8) only thrash the L1).
+    // several consumers, two or three per CU.
     const bool voxel_list = fused && ctx->prm.init_mode == FS_INIT_VOXEL;     // the solve draws from the list of pairs that have a candidate
     // fused voxel-based candidates: the producer only looks initial states up (k_corr_init computed them once per pose)
     const bool vx = !lds && voxel_list;
     const int wpb = lds_big ? FS_LDS_BIG_WAVES : (lds ? 4 : 1);       // waves of a block that draw chunks from the cursor
-    const int auto_blocks = lds ? 3 : 2;
+    const bool bone = ctx->prm.init_mode == FS_INIT_BONE;
+    // A third block per CU hides latency on a grid that the L2 of an XCD holds, and thrashes it on a larger one.  States per bone, 200 k points, two /
+    // three blocks, kernel us: 0.4 MB grid 577 / 548, 3.0 MB 602 / 584, 4.3 MB 682 / 684, 10 MB 760 / 792, 24 MB 935 / 1032.  Candidates are
+    // slower with three (whole call on 1 M ray samples 150 / 155).
+    const int auto_blocks = lds || (bone && grid_bytes <= L2_BYTES) ? 3 : 2;
     const int want_blocks = ctx->blocks_per_cu ? (lds ? std::max(ctx->blocks_per_cu, 3) : ctx->blocks_per_cu) : auto_blocks;
     const int occ = lds ? ctx->occ_blocks_per_cu : (vx ? ctx->occ_vx_blocks_per_cu : ctx->occ_ws_blocks_per_cu);
     const int per_cu = lds_big ? 1 : std::max(1, std::min(want_blocks, occ));
@@ -629,6 +634,11 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     // more lose 3 ... 40 %); on grids beyond it at 24 (1.34 instead of 1.37 ms on the 8-pose batch; 48: 1.38)
     S.refill_min = ctx->refill_min ? ctx->refill_min : (lds ? 32 : (grid_bytes > (32u << 20) ? 24 : 8));
     S.prefetch = grid_bytes > (32u << 20);
+    // Eighths of the chunks dealt out without asking the cursor.  Whole calls, us, with 0 / 4 / 6 / 7: one state per bone on 64x64x16 nodes, 200 k
+    // points 732 / 709 / 723 / 739, 65 k points 411 / 397 / 399 / 406, 20 k points on 45x39x11 209 / 203 / 201 / 201; candidates, 2 M ray samples
+    // 303 / 292 / 286 / 286.  On grids beyond the L2 all blocks should read the same stretch of the points: 8 poses of 128x128x32 nodes
+    // 2438 / 2447 / 2460 / 2488.
+    S.dealt = S.prefetch ? 0 : (bone ? 4 : 6);
     const int blocks = (int)std::min<long long>(grid1d(chunks, wpb), (long long)per_cu * ctx->n_cus);
     InitP I;
     I.mode = ctx->prm.init_mode;

@@ -696,6 +696,7 @@ struct SolveP {
     int ki;              // kernels of small batches: initial states per wave (pair_of)
     int spin_limit;      // producer / consumer kernel: polls of a work queue before a wave gives up
     int xcd_ranges;      // producer / consumer kernel: the list is cut into 8 ranges, one per XCD, each with its own cursor
+    int dealt;           // eighths of the chunks that are dealt out without the cursor (Chunks)
     int prefetch;        // producer / consumer kernel: consumers ask for the next cell's records at the end of a pass
 };
 
@@ -980,6 +981,41 @@ __device__ __forceinline__ CellGroup group_request(bool want, int cell, int lane
     return g;
 }
 __device__ __forceinline__ int group_position(const CellGroup &g) { return __shfl(g.base, g.leader) + g.rank; }
+
+// Chunks of work for one of the waves that draw them.  The first S.dealt eighths are dealt out in rounds, chunk w + i * drawers to
+// drawer w; the cursor, which starts behind one round, hands out the rest: it serves one drawer after the other, 9 ns each, and every drawer
+// waits for its answer.
+struct Chunks {
+    long long round, shared, own;
+};
+__device__ __forceinline__ Chunks first_chunk(const SolveP &S, long long total, int drawer, int drawers, long long &next, long long &c1)
+{
+    Chunks c;
+    c.round = (long long)drawers * S.chunk;
+    c.shared = max(c.round, total / c.round * S.dealt / 8 * c.round);
+    c.own = next = (long long)drawer * S.chunk;
+    c1 = min(total, next + S.chunk);
+    return c;
+}
+// false: there is none left (wave-wide call)
+__device__ __forceinline__ bool next_chunk(Chunks &c, const SolveP &S, long long total, unsigned *__restrict__ cursor, int lane,
+                                           long long &next, long long &c1)
+{
+    c.own += c.round;
+    if (c.own < c.shared) {
+        next = c.own;
+    } else {
+        unsigned b = 0;
+        if (lane == 0) b = atomicAdd(cursor + CUR_ALL, (unsigned)S.chunk);
+        next = c.shared - c.round + (long long)(unsigned)__builtin_amdgcn_readfirstlane((int)b);
+        if (next >= total) {
+            next = c1;
+            return false;
+        }
+    }
+    c1 = min(total, next + S.chunk);
+    return true;
+}
 
 // The parked requests of one wave: entry i = {cell, pair}, one per SIMD lane.  Lanes of one point that reach
 // the same root are neighbours in the wave and finish within a few passes of each other, so many entries name
@@ -1273,10 +1309,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
     // with a list only the pairs list[0 .. *list_len) ({point, cell << 3 | k}) are solved
     const long long total = list ? (long long)*list_len : S.total;
     const int lane = threadIdx.x & 63;
-    // wave-uniform: the wave's current chunk is [next, c1).  The first chunk of wave w is chunk w (the cursor
-    // starts behind these): 2048 waves asking one counter at once would wait 9 ns each, one after the other.
-    long long next = (long long)__builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6)) * S.chunk;
-    long long c1 = min(total, next + S.chunk);
+    // wave-uniform: the wave's current chunk is [next, c1)
+    long long next, c1;
+    Chunks chunks = first_chunk(S, total, __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6)), (int)gridDim.x * NW, next, c1);
     bool exhausted = false;          // wave-uniform: the global cursor has run past the end
     const long long N = S.N;
 
@@ -1297,17 +1332,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
         // hand out pairs until fewer than refill_min lanes are idle: a pair whose initial state is
         // invalid is answered on the spot and its lane asks again
         while (!exhausted && nidle >= S.refill_min) {
-            if (next >= c1) {
-                unsigned b = 0;
-                if (lane == 0) b = atomicAdd(cursor + CUR_ALL, (unsigned)S.chunk);
-                b = (unsigned)__builtin_amdgcn_readfirstlane((int)b);
-                if ((long long)b >= total) {
-                    exhausted = true;
-                } else {
-                    next = b;
-                    c1 = min(total, (long long)b + S.chunk);
-                }
-            }
+            if (next >= c1) exhausted = !next_chunk(chunks, S, total, cursor, lane, next, c1);
             if (!exhausted) {
                 const int rank = __popcll(idle & ((1ull << lane) - 1ull));
                 const long long pq = next + rank;
@@ -1475,11 +1500,11 @@ __device__ __forceinline__ void lds_store_release(int *p, int v)
 // ---- result records of k_solve_ws leave through LDS ---------------------------------------------------------------
 // A lane that finishes does not store its 64-byte record itself (four 16-byte stores to an address of its own: four
 // vector-memory instructions in nearly every pass of the wave, each of which reaches memory as a partial write of a
-// 32-byte sector).  The wave parks finished records in LDS, OUT_PEND per wave, together with the grid cell of the
-// converged ones; when OUT_SEND have gathered it asks for their positions in their cells' lists (one atomic per cell
+// 32-byte sector).  The wave parks finished records in LDS, OUT_PEND per wave, together with the place of the
+// converged ones; when OUT_PEND - 15 have gathered it asks for their positions in their cells' lists (one atomic per cell
 // and round of 64, as flush_slots does), puts each position into its record, and writes the records out with four
 // consecutive lanes per record: every record reaches memory once, whole, as 64 contiguous bytes.
-constexpr int OUT_PEND = 128, OUT_SEND = 112;
+template <int OUT_PEND>
 struct OutQ {
     float4 rec[OUT_PEND][4];
     int place[OUT_PEND];      // where in the transform grids the cell of a converged lane that wants a position begins, else -1
@@ -1494,24 +1519,25 @@ __device__ __forceinline__ int cell_at(const GridP &G, int ncell, int place)
     return (int)(p * (unsigned)ncell + (c - ix) * (unsigned)(G.nz - 1) + v - c * (unsigned)G.nz);
 }
 
-__device__ __forceinline__ void out_flush(const GridP &G, OutQ &q, int npend, int lane, int *__restrict__ cell_count, int ncell,
+template <int OUT_PEND>
+__device__ __forceinline__ void out_flush(const GridP &G, OutQ<OUT_PEND> &q, int npend, int lane, int *__restrict__ cell_count, int ncell,
                                           float4 *__restrict__ rec)
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the LDS writes of the wave's other lanes
     __builtin_amdgcn_wave_barrier();
     if (cell_count) {
-        // two rounds of 64 entries; the atomics of both are on their way before either answer is used
-        bool valid[2];
-        CellGroup g[2];
+        // rounds of 64 entries; the atomics of all are on their way before an answer is used
+        bool valid[OUT_PEND / 64];
+        CellGroup g[OUT_PEND / 64];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < OUT_PEND / 64; ++b) {
             const int at = 64 * b + lane < npend ? q.place[64 * b + lane] : -1;
             valid[b] = at >= 0;
             const int c = valid[b] ? cell_at(G, ncell, at) : -1;
             g[b] = group_request(valid[b], c, lane, cell_count);
         }
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < OUT_PEND / 64; ++b) {
             const int at = group_position(g[b]);
             if (valid[b]) reinterpret_cast<int *>(&q.rec[64 * b + lane][1])[0] = at;
         }
@@ -1524,8 +1550,9 @@ __device__ __forceinline__ void out_flush(const GridP &G, OutQ &q, int npend, in
 }
 
 // park the record of every lane with `want` (wave-wide call); place < 0: no position wanted
+template <int OUT_PEND>
 __device__ __forceinline__ void out_park(const GridP &G, bool want, const float x[3], const float J[9], int flags, int place, int pair,
-                                         OutQ &q, int &npend, int lane, int *__restrict__ cell_count, int ncell, float4 *__restrict__ rec)
+                                         OutQ<OUT_PEND> &q, int &npend, int lane, int *__restrict__ cell_count, int ncell, float4 *__restrict__ rec)
 {
     const unsigned long long m = __ballot(want);
     if (m) {
@@ -1544,7 +1571,7 @@ __device__ __forceinline__ void out_park(const GridP &G, bool want, const float 
         }
         npend += __popcll(m);
     }
-    if (npend >= OUT_SEND) {
+    if (npend >= OUT_PEND - 16) {
         out_flush(G, q, npend, lane, cell_count, ncell, rec);
         npend = 0;
     }
@@ -1660,8 +1687,67 @@ __device__ __forceinline__ bool lane_step(const GridP &G, const SolveP &S, const
     return finish_step(S, dx, gn, g, J, it, conv);
 }
 
+// Jacobian (and field) of a fresh pair from the corners in `need` (zeros in place of the others), the lower four of the cell first,
+// then the upper four: the arithmetic of jacobian_from_corners, but with all eight records in registers the producer, not the
+// consumers, would decide how many waves a SIMD holds (176 registers without this, 160).  Returns whether an entry of the blend or
+// of the Jacobian is an exact zero.
+__device__ __forceinline__ bool prepare_jacobian(const float *__restrict__ Tcell, const GridP &G, const Cell &c, int need, const float (&x)[3],
+                                                 float (&d)[3], float (&J)[9])
+{
+    float om[8], T[12], dc[8][3];
+    corner_weights(c, om);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        float q[4][12];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+#pragma unroll
+            for (int e = 0; e < 12; ++e) q[k][e] = 0.0f;
+            if ((need >> (4 * h + k)) & 1) load12(Tcell + corner_off(G, 4 * h + k), q[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+#pragma unroll
+            for (int e = 0; e < 12; ++e) T[e] = h + k == 0 ? om[0] * q[0][e] : FS_FMA(om[4 * h + k], q[k][e], T[e]);
+            apply12(q[k], x, dc[4 * h + k]);
+        }
+        // nothing is moved across: the sums of the lower corners are made before the upper ones are asked for
+#pragma unroll
+        for (int e = 0; e < 12; ++e) asm volatile("" : "+v"(T[e]));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(dc[4 * h + k][0]), "+v"(dc[4 * h + k][1]), "+v"(dc[4 * h + k][2]) : : "memory");
+    }
+    apply12(T, x, d);
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) J[r * 3 + j] = T[r * 4 + j];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) add_weight_derivative(G, c, k, dc[k], J);
+    float m = __builtin_fabsf(T[0]);
+#pragma unroll
+    for (int e = 1; e < 12; ++e) m = __builtin_fminf(m, __builtin_fabsf(T[e]));
+#pragma unroll
+    for (int e = 0; e < 9; ++e) m = __builtin_fminf(m, __builtin_fabsf(J[e]));
+    return m == 0.0f;
+}
+
+// Pair number i of a batch that is handed out in tiles of TILE_PTS points, in a tile state after state: eight consecutive SIMD lanes
+// are the same state of eight points, a batch of 64 eight states of them.  Neighbours in one state read and write consecutive addresses;
+// states of one point often reach the same root and share its records and its atomic.  (Kernel us with all states of a point side by side / tiles of
+// 8 / 16 / 64 points: 200 k points 711 / 684 / 687 / 685, 20 k points on 45x39x11 nodes 142 / 135 / 135 / 140, 65 k points with positions
+// 313 / 313 / 317 / 339.)
+constexpr unsigned TILE_PTS = 8;
+__device__ __forceinline__ void tile_pair(unsigned i, unsigned N, unsigned K, int &n, int &k)
+{
+    const unsigned t = i / (TILE_PTS * K), r = i - t * (TILE_PTS * K), pts = min(TILE_PTS, N - t * TILE_PTS);     // the last tile may be short
+    const unsigned kk = pts == TILE_PTS ? r / TILE_PTS : r / pts;
+    k = (int)kk;
+    n = (int)(t * TILE_PTS + r - kk * pts);
+}
+
 template <bool FUSED, bool WITH_J, int NCONS, bool SKIP>
-__global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, SolveP S, InitP I, const float *__restrict__ T,
+__global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(GridP G, SolveP S, InitP I, const float *__restrict__ T,
                                                const float *__restrict__ xq, const int32_t *__restrict__ pose,
                                                const float *__restrict__ x0, const float *__restrict__ J0,
                                                const uint8_t *__restrict__ valid0, float4 *__restrict__ rec,
@@ -1672,7 +1758,8 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
 {
     __shared__ float s_ring[NCONS][ST_FIELDS][WS_RING];
     __shared__ int s_tail[NCONS], s_head[NCONS], s_done;
-    __shared__ OutQ s_out[WITH_J ? NCONS + 1 : 1];      // records on their way out, per wave (only full records are parked)
+    constexpr int OUT_PEND = SKIP ? 64 : 128;        // 64: 50 KiB of LDS, so that a CU holds three blocks
+    __shared__ OutQ<OUT_PEND> s_out[WITH_J ? NCONS + 1 : 1];      // records on their way out, per wave (only full records are parked)
     if (threadIdx.x < NCONS) {
         s_tail[threadIdx.x] = 0;
         s_head[threadIdx.x] = 0;
@@ -1684,7 +1771,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
     const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const long long N = S.N;
     int npend = 0;                   // wave-uniform: entries of the wave's s_out in use
-    OutQ &outq = s_out[WITH_J ? wib : 0];
+    OutQ<OUT_PEND> &outq = s_out[WITH_J ? wib : 0];
     const int stride = (int)G.V * 12;          // of the poses' grids; P of them are below 2^31
 
     if (wib == NCONS) {
@@ -1704,13 +1791,11 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
         const int home = (int)(blockIdx.x & (N_XCD - 1));
         const long long per = ((total + (long long)N_XCD * S.chunk - 1) / ((long long)N_XCD * S.chunk)) * S.chunk;
         long long next, c1;
+        Chunks chunks = first_chunk(S, total, (int)blockIdx.x, (int)gridDim.x, next, c1);
         if (ranges) {
             const long long r1 = min(total, (home + 1) * per);
             next = home * per + (long long)(blockIdx.x >> 3) * S.chunk;
             c1 = min(r1, next + S.chunk);
-        } else {
-            next = (long long)blockIdx.x * S.chunk;
-            c1 = min(total, next + S.chunk);
         }
         int alive = 0;                    // ranges home, home + 1, ... home + alive - 1 are known to be used up
         int tails[NCONS];
@@ -1738,12 +1823,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                     }
                     if (!got) break;
                 } else {
-                    unsigned b = 0;
-                    if (lane == 0) b = atomicAdd(cursor + CUR_ALL, (unsigned)S.chunk);
-                    b = (unsigned)__builtin_amdgcn_readfirstlane((int)b);
-                    if ((long long)b >= total) break;
-                    next = b;
-                    c1 = min(total, (long long)b + S.chunk);
+                    if (!next_chunk(chunks, S, total, cursor, lane, next, c1)) break;
                 }
             }
             const long long pq = next + lane;
@@ -1761,9 +1841,8 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                     nn = e.x;
                     nk = e.y & 7;
                     gcell = e.y >> 3;
-                } else if (S.point_major) {   // consecutive SIMD lanes: the K initial states of one point
-                    nn = (int)(upq / (unsigned)S.K);
-                    nk = (int)(upq - (unsigned)nn * (unsigned)S.K);
+                } else if (S.point_major) {
+                    tile_pair(upq, (unsigned)N, (unsigned)S.K, nn, nk);
                 } else {                      // consecutive SIMD lanes: consecutive points, same initial state
                     nk = (int)(upq / (unsigned)N);
                     nn = (int)(upq - (unsigned)nk * (unsigned)N);
@@ -1787,33 +1866,15 @@ __global__ __launch_bounds__(64 * (NCONS + 1), 2) void k_solve_ws(GridP G, Solve
                             nx[r] = FS_FMA(bi[r * 3 + 0], y[0], FS_FMA(bi[r * 3 + 1], y[1], bi[r * 3 + 2] * y[2]));
                         const Cell c0 = locate(G, nx);
                         base0 = c0.base;
-                        float qn[8][12];
                         // corner records of weight zero contribute nothing to the Jacobian either (the derivative of
                         // their weight vanishes along the clamped axis by definition and carries the zero factor
                         // along the others): fetch the rest, zeros in their place, and if an entry of the blend
                         // or of the Jacobian comes out as an exact zero, do it again with all eight
                         const bool near = __builtin_fabsf(nx[0]) < SKIP_MAX && __builtin_fabsf(nx[1]) < SKIP_MAX && __builtin_fabsf(nx[2]) < SKIP_MAX;
-                        const int need = prod_skip && near ? corners_needed(c0) : 0xFF;
-#pragma unroll
-                        for (int c = 0; c < 8; ++c) {
-#pragma unroll
-                            for (int e = 0; e < 12; ++e) qn[c][e] = 0.0f;
-                        }
-                        load_corners(Tn + c0.base, G, need, qn);
+                        int need = prod_skip && near ? corners_needed(c0) : 0xFF;
                         float Jac[9];
-                        jacobian_from_corners(G, c0, qn, nx, d, Jac);
-                        if (need != 0xFF) {
-                            float d2[3];
-                            bool z = blend_apply_z(c0, qn, nx, d2);      // the same blend as inside the Jacobian
-                            float m = __builtin_fabsf(Jac[0]);
-#pragma unroll
-                            for (int e = 1; e < 9; ++e) m = __builtin_fminf(m, __builtin_fabsf(Jac[e]));
-                            z = z || m == 0.0f;
-                            if (z) {
-                                load_corners(Tn + c0.base, G, 0xFF & ~need, qn);
-                                jacobian_from_corners(G, c0, qn, nx, d, Jac);
-                            }
-                        }
+                        if (prepare_jacobian(Tn + c0.base, G, c0, need, nx, d, Jac) && need != 0xFF)
+                            (void)prepare_jacobian(Tn + c0.base, G, c0, 0xFF, nx, d, Jac);
                         ok = inv3(Jac, nJ);
                         if (!ok) {
 #pragma unroll
