@@ -1687,36 +1687,43 @@ __device__ __forceinline__ bool lane_step(const GridP &G, const SolveP &S, const
     return finish_step(S, dx, gn, g, J, it, conv);
 }
 
-// Jacobian (and field) of a fresh pair from the corners in `need` (zeros in place of the others), the lower four of the cell first,
-// then the upper four: the arithmetic of jacobian_from_corners, but with all eight records in registers the producer, not the
-// consumers, would decide how many waves a SIMD holds (176 registers without this, 160).  Returns whether an entry of the blend or
-// of the Jacobian is an exact zero.
+// Jacobian (and field) of a fresh pair from the corners in `need` (zeros in place of the others): the arithmetic of
+// jacobian_from_corners, but the corners are fetched in two halves, the z-pairs of one x, y side and then of the other: with all eight
+// records in registers the producer, not the consumers, would decide how many waves a SIMD holds (176 registers, now 160).  Returns whether an
+// entry of the blend or of the Jacobian is an exact zero.
 __device__ __forceinline__ bool prepare_jacobian(const float *__restrict__ Tcell, const GridP &G, const Cell &c, int need, const float (&x)[3],
                                                  float (&d)[3], float (&J)[9])
 {
-    float om[8], T[12], dc[8][3];
+    float om[8], T[12], dc[8][3], q[2][4][12];          // q[h]: corners 2h, 2h + 4, 2h + 1, 2h + 5
     corner_weights(c, om);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        float q[4][12];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int i = 0; i < 4; ++i) {
+            const int k = 2 * h + (i >> 1) + 4 * (i & 1);
 #pragma unroll
-            for (int e = 0; e < 12; ++e) q[k][e] = 0.0f;
-            if ((need >> (4 * h + k)) & 1) load12(Tcell + corner_off(G, 4 * h + k), q[k]);
+            for (int e = 0; e < 12; ++e) q[h][i][e] = 0.0f;
+            if ((need >> k) & 1) load12(Tcell + corner_off(G, k), q[h][i]);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int i = 0; i < 4; ++i) apply12(q[h][i], x, dc[2 * h + (i >> 1) + 4 * (i & 1)]);
 #pragma unroll
-            for (int e = 0; e < 12; ++e) T[e] = h + k == 0 ? om[0] * q[0][e] : FS_FMA(om[4 * h + k], q[k][e], T[e]);
-            apply12(q[k], x, dc[4 * h + k]);
-        }
-        // nothing is moved across: the sums of the lower corners are made before the upper ones are asked for
+        for (int i = 0; i < 4; i += 2)
+#pragma unroll
+            for (int e = 0; e < 12; ++e) T[e] = h + i == 0 ? om[0] * q[0][0][e] : FS_FMA(om[2 * h + (i >> 1)], q[h][i][e], T[e]);
+        // nothing is moved across: the lower corners of this half have been added when the other half is asked for
 #pragma unroll
         for (int e = 0; e < 12; ++e) asm volatile("" : "+v"(T[e]));
 #pragma unroll
-        for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(dc[4 * h + k][0]), "+v"(dc[4 * h + k][1]), "+v"(dc[4 * h + k][2]) : : "memory");
+        for (int i = 0; i < 4; ++i) {
+            const int k = 2 * h + (i >> 1) + 4 * (i & 1);
+            asm volatile("" : "+v"(dc[k][0]), "+v"(dc[k][1]), "+v"(dc[k][2]) : : "memory");
+        }
     }
+#pragma unroll
+    for (int k = 4; k < 8; ++k)
+#pragma unroll
+        for (int e = 0; e < 12; ++e) T[e] = FS_FMA(om[k], q[(k - 4) >> 1][((k & 1) << 1) + 1][e], T[e]);
     apply12(T, x, d);
 #pragma unroll
     for (int r = 0; r < 3; ++r)
