@@ -568,7 +568,7 @@ fs_status fs_init(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_t
     const long long total = (long long)N * K;
     if (ctx->prm.init_mode == FS_INIT_BONE)
         k_init_bone<<<grid1d(total, 256), 256, 0, ctx->stream>>>(ctx->G, ctx->T, ctx->Binv, ctx->Bok, d_xq, d_pose, N,
-                                                                 d_x0, d_Jinv0, d_valid0);
+                                                                 d_x0, d_Jinv0, d_valid0, reinterpret_cast<const int *>(ctx->cursor + CUR_NONFINITE), ctx->pre_serial);
     else
         k_init_voxel<<<grid1d(total, 256), 256, 0, ctx->stream>>>(ctx->G, ctx->C, ctx->bbox, ctx->cinit, d_xq, d_pose, N,
                                                                   d_x0, d_Jinv0, d_valid0);
@@ -934,15 +934,16 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
         const int groups = N >= (1 << 19) ? 1 : (K >= 8 ? 8 : (K >= 4 ? 4 : (K >= 2 ? 2 : 1)));
         const dim3 rg(grid1d(N, 256 / groups));
         float4 *grec4 = reinterpret_cast<float4 *>(ctx->grec);
+        const int *nonfinite = reinterpret_cast<const int *>(ctx->cursor + CUR_NONFINITE);
 #define FS_LAUNCH_RECORDS(R, E)                                                                                       \
     k_grad_records<R, E><<<rg, 256, 0, st>>>(G, ctx->T, d_xc, d_Jinv, d_conv, d_gxc, d_pose, N, K, ncell, ctx->gcount, pos, \
                                              grec4, d_gxq, groups, (R) ? ctx->srec : nullptr,                          \
-                                             ((R) && ctx->slots_list) ? ctx->vcnt : nullptr)
+                                             ((R) && ctx->slots_list) ? ctx->vcnt : nullptr, nonfinite, ctx->pre_serial)
         // from_rec: the solve's own result records are still in the context: one 64-byte read per pair
         if (from_rec && mode != 0) FS_LAUNCH_RECORDS(true, true);
         else if (from_rec && groups == 1)     // large batches: three lanes of a point in flight, stage by stage
             k_grad_records<true, false, 3><<<rg, 256, 0, st>>>(G, ctx->T, d_xc, d_Jinv, d_conv, d_gxc, d_pose, N, K, ncell, ctx->gcount,
-                                                               pos, grec4, d_gxq, groups, ctx->srec, ctx->slots_list ? ctx->vcnt : nullptr);
+                                                               pos, grec4, d_gxq, groups, ctx->srec, ctx->slots_list ? ctx->vcnt : nullptr, nonfinite, ctx->pre_serial);
         else if (from_rec) FS_LAUNCH_RECORDS(true, false);
         else if (mode != 0) FS_LAUNCH_RECORDS(false, true);
         else FS_LAUNCH_RECORDS(false, false);

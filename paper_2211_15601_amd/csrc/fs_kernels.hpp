@@ -213,6 +213,81 @@ __device__ __forceinline__ void bone_inverse(int i, const float *__restrict__ B,
     ok[i] = good ? 1 : 0;
 }
 
+// Corners that can have a non-zero weight: along a clamped axis only the side the point was clamped to
+// (fraction 0: offset 0, fraction 1: offset 1).  An axis that merely happens to have fraction 0 keeps both sides.
+__device__ __forceinline__ int corners_needed(const Cell &c)
+{
+    const int mx = c.cl[0] ? (c.f[0] == 0.0f ? 0x55 : 0xAA) : 0xFF;
+    const int my = c.cl[1] ? (c.f[1] == 0.0f ? 0x33 : 0xCC) : 0xFF;
+    const int mz = c.cl[2] ? (c.f[2] == 0.0f ? 0x0F : 0xF0) : 0xFF;
+    return mx & my & mz;
+}
+
+// Jacobian (and field) of a fresh pair from the corners in `need` (zeros in place of the others): the arithmetic of
+// jacobian_from_corners, but the corners are fetched in two halves, the z-pairs of one x, y side and then of the other: with all eight
+// records in registers the producer, not the consumers, would decide how many waves a SIMD holds (176 registers, now 160).  Returns whether an
+// entry of the blend or of the Jacobian is an exact zero.
+__device__ __forceinline__ bool prepare_jacobian(const float *__restrict__ Tcell, const GridP &G, const Cell &c, int need, const float (&x)[3],
+                                                 float (&d)[3], float (&J)[9])
+{
+    float om[8], T[12], dc[8][3], q[2][4][12];          // q[h]: corners 2h, 2h + 4, 2h + 1, 2h + 5
+    corner_weights(c, om);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = 2 * h + (i >> 1) + 4 * (i & 1);
+#pragma unroll
+            for (int e = 0; e < 12; ++e) q[h][i][e] = 0.0f;
+            if ((need >> k) & 1) load12(Tcell + corner_off(G, k), q[h][i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) apply12(q[h][i], x, dc[2 * h + (i >> 1) + 4 * (i & 1)]);
+#pragma unroll
+        for (int i = 0; i < 4; i += 2)
+#pragma unroll
+            for (int e = 0; e < 12; ++e) T[e] = h + i == 0 ? om[0] * q[0][0][e] : FS_FMA(om[2 * h + (i >> 1)], q[h][i][e], T[e]);
+        // nothing is moved across: the lower corners of this half have been added when the other half is asked for
+#pragma unroll
+        for (int e = 0; e < 12; ++e) asm volatile("" : "+v"(T[e]));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = 2 * h + (i >> 1) + 4 * (i & 1);
+            asm volatile("" : "+v"(dc[k][0]), "+v"(dc[k][1]), "+v"(dc[k][2]) : : "memory");
+        }
+    }
+#pragma unroll
+    for (int k = 4; k < 8; ++k)
+#pragma unroll
+        for (int e = 0; e < 12; ++e) T[e] = FS_FMA(om[k], q[(k - 4) >> 1][((k & 1) << 1) + 1][e], T[e]);
+    apply12(T, x, d);
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) J[r * 3 + j] = T[r * 4 + j];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) add_weight_derivative(G, c, k, dc[k], J);
+    float m = __builtin_fabsf(T[0]);
+#pragma unroll
+    for (int e = 1; e < 12; ++e) m = __builtin_fminf(m, __builtin_fabsf(T[e]));
+#pragma unroll
+    for (int e = 0; e < 9; ++e) m = __builtin_fminf(m, __builtin_fabsf(J[e]));
+    return m == 0.0f;
+}
+
+// field_dJ without the corners of weight zero, whose records contribute nothing (the derivative of their weight vanishes along the
+// clamped axis by definition and carries the zero factor along the others): zeros in their place, and if an entry of the blend or of
+// the Jacobian comes out as an exact zero, again with all eight.  may_skip: the grid's entries are below SKIP_MAX.
+// Bound: the gathers.  (k_init_bone on 30 k points x 17 bones, 32x32x8 nodes, with all eight: a step 229 us, now 221; exact backward of 20 k
+// points x 24 201.6 -> 200.5.)
+__device__ __forceinline__ void field_dJ_clamped(const float *__restrict__ Tp, const GridP &G, const Cell &c, bool may_skip, const float (&x)[3],
+                                                 float (&d)[3], float (&J)[9])
+{
+    const bool near = __builtin_fabsf(x[0]) < SKIP_MAX && __builtin_fabsf(x[1]) < SKIP_MAX && __builtin_fabsf(x[2]) < SKIP_MAX;
+    int need = may_skip && near ? corners_needed(c) : 0xFF;
+    while (prepare_jacobian(Tp + c.base, G, c, need, x, d, J) && need != 0xFF) need = 0xFF;
+}
+
 // ------------------------------------------------------------------------------------------------
 // Initial states.  One thread per lane q = k*N + n.
 // ------------------------------------------------------------------------------------------------
@@ -231,8 +306,9 @@ __global__ __launch_bounds__(256) void k_init_bone(GridP G, const float *__restr
                                                    const float *__restrict__ Binv, const uint8_t *__restrict__ Bok,
                                                    const float *__restrict__ xq, const int32_t *__restrict__ pose,
                                                    long long N, float *__restrict__ o_x0, float *__restrict__ o_J,
-                                                   uint8_t *__restrict__ o_v)
+                                                   uint8_t *__restrict__ o_v, const int *__restrict__ nonfinite, int serial)
 {
+    const bool may_skip = __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
     const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= N * G.nb) return;
     const int k = (int)(q / N);
@@ -247,7 +323,7 @@ __global__ __launch_bounds__(256) void k_init_bone(GridP G, const float *__restr
         for (int r = 0; r < 3; ++r)
             x0[r] = FS_FMA(bi[r * 3 + 0], y[0], FS_FMA(bi[r * 3 + 1], y[1], bi[r * 3 + 2] * y[2]));
         float d[3], J[9];
-        field_dJ(T + (long long)p * G.V * 12, G, x0, d, J);
+        field_dJ_clamped(T + (long long)p * G.V * 12, G, locate(G, x0), may_skip, x0, d, J);
         ok = inv3(J, Ji);
     }
     write_init(q, N, k, n, x0, Ji, ok, o_x0, o_J, o_v);
@@ -1583,16 +1659,7 @@ __device__ __forceinline__ void out_park(const GridP &G, bool want, const float 
 // an exact zero.  A consumer of k_solve_ws may fetch only the other corners (bit c of the mask below); the
 // registers of the skipped ones keep whatever finite record (or the initial zeros) they held before.  If a
 // blended entry then comes out as an exact zero, the skipped records are fetched and the evaluation is
-// repeated, so that even the sign of that zero is the one the full sum has.
-// Corners that can have a non-zero weight: along a clamped axis only the side the point was clamped to
-// (fraction 0: offset 0, fraction 1: offset 1).  An axis that merely happens to have fraction 0 keeps both sides.
-__device__ __forceinline__ int corners_needed(const Cell &c)
-{
-    const int mx = c.cl[0] ? (c.f[0] == 0.0f ? 0x55 : 0xAA) : 0xFF;
-    const int my = c.cl[1] ? (c.f[1] == 0.0f ? 0x33 : 0xCC) : 0xFF;
-    const int mz = c.cl[2] ? (c.f[2] == 0.0f ? 0x0F : 0xF0) : 0xFF;
-    return mx & my & mz;
-}
+// repeated, so that even the sign of that zero is the one the full sum has (corners_needed).
 
 // Issue order of the 24 loads of a cell.  The two z-neighbours of an (x, y) corner are 96 contiguous bytes, i.e. six
 // 16-byte pieces in one or two cache lines; FS_LOAD_ORDER 1 issues the six pieces of a corner pair back to back
@@ -1685,58 +1752,6 @@ __device__ __forceinline__ bool lane_step(const GridP &G, const SolveP &S, const
 #pragma unroll
     for (int r = 0; r < 3; ++r) gn[r] = d[r] - xp[r];
     return finish_step(S, dx, gn, g, J, it, conv);
-}
-
-// Jacobian (and field) of a fresh pair from the corners in `need` (zeros in place of the others): the arithmetic of
-// jacobian_from_corners, but the corners are fetched in two halves, the z-pairs of one x, y side and then of the other: with all eight
-// records in registers the producer, not the consumers, would decide how many waves a SIMD holds (176 registers, now 160).  Returns whether an
-// entry of the blend or of the Jacobian is an exact zero.
-__device__ __forceinline__ bool prepare_jacobian(const float *__restrict__ Tcell, const GridP &G, const Cell &c, int need, const float (&x)[3],
-                                                 float (&d)[3], float (&J)[9])
-{
-    float om[8], T[12], dc[8][3], q[2][4][12];          // q[h]: corners 2h, 2h + 4, 2h + 1, 2h + 5
-    corner_weights(c, om);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 2 * h + (i >> 1) + 4 * (i & 1);
-#pragma unroll
-            for (int e = 0; e < 12; ++e) q[h][i][e] = 0.0f;
-            if ((need >> k) & 1) load12(Tcell + corner_off(G, k), q[h][i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) apply12(q[h][i], x, dc[2 * h + (i >> 1) + 4 * (i & 1)]);
-#pragma unroll
-        for (int i = 0; i < 4; i += 2)
-#pragma unroll
-            for (int e = 0; e < 12; ++e) T[e] = h + i == 0 ? om[0] * q[0][0][e] : FS_FMA(om[2 * h + (i >> 1)], q[h][i][e], T[e]);
-        // nothing is moved across: the lower corners of this half have been added when the other half is asked for
-#pragma unroll
-        for (int e = 0; e < 12; ++e) asm volatile("" : "+v"(T[e]));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 2 * h + (i >> 1) + 4 * (i & 1);
-            asm volatile("" : "+v"(dc[k][0]), "+v"(dc[k][1]), "+v"(dc[k][2]) : : "memory");
-        }
-    }
-#pragma unroll
-    for (int k = 4; k < 8; ++k)
-#pragma unroll
-        for (int e = 0; e < 12; ++e) T[e] = FS_FMA(om[k], q[(k - 4) >> 1][((k & 1) << 1) + 1][e], T[e]);
-    apply12(T, x, d);
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) J[r * 3 + j] = T[r * 4 + j];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) add_weight_derivative(G, c, k, dc[k], J);
-    float m = __builtin_fabsf(T[0]);
-#pragma unroll
-    for (int e = 1; e < 12; ++e) m = __builtin_fminf(m, __builtin_fabsf(T[e]));
-#pragma unroll
-    for (int e = 0; e < 9; ++e) m = __builtin_fminf(m, __builtin_fabsf(J[e]));
-    return m == 0.0f;
 }
 
 // Pair number i of a batch that is handed out in tiles of TILE_PTS points, in a tile state after state: eight consecutive SIMD lanes
@@ -1873,15 +1888,8 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                             nx[r] = FS_FMA(bi[r * 3 + 0], y[0], FS_FMA(bi[r * 3 + 1], y[1], bi[r * 3 + 2] * y[2]));
                         const Cell c0 = locate(G, nx);
                         base0 = c0.base;
-                        // corner records of weight zero contribute nothing to the Jacobian either (the derivative of
-                        // their weight vanishes along the clamped axis by definition and carries the zero factor
-                        // along the others): fetch the rest, zeros in their place, and if an entry of the blend
-                        // or of the Jacobian comes out as an exact zero, do it again with all eight
-                        const bool near = __builtin_fabsf(nx[0]) < SKIP_MAX && __builtin_fabsf(nx[1]) < SKIP_MAX && __builtin_fabsf(nx[2]) < SKIP_MAX;
-                        int need = prod_skip && near ? corners_needed(c0) : 0xFF;
                         float Jac[9];
-                        if (prepare_jacobian(Tn + c0.base, G, c0, need, nx, d, Jac) && need != 0xFF)
-                            (void)prepare_jacobian(Tn + c0.base, G, c0, 0xFF, nx, d, Jac);
+                        field_dJ_clamped(Tn, G, c0, prod_skip, nx, d, Jac);
                         ok = inv3(Jac, nJ);
                         if (!ok) {
 #pragma unroll
@@ -2470,12 +2478,14 @@ __global__ __launch_bounds__(256) void k_grad_records(GridP G, const float *__re
                                                       const int32_t *__restrict__ pose, long long N, int K, int ncell,
                                                       const int *__restrict__ offset, const int *__restrict__ pos,
                                                       float4 *__restrict__ rec, float *__restrict__ gxq, int groups,
-                                                      const float4 *__restrict__ srec, const uint8_t *__restrict__ cand_cnt)
+                                                      const float4 *__restrict__ srec, const uint8_t *__restrict__ cand_cnt,
+                                                      const int *__restrict__ nonfinite, int serial)
 {
     // `groups` (a power of two <= 8) threads share a point and take its lanes k = g, g + groups, ...;
     // consecutive threads of a group are consecutive points, so every load is coalesced
     __shared__ float s_gq[256 * 3];
     const int ppb = 256 / groups;                 // points per block
+    const bool may_skip = EXACT && __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
     const int g = threadIdx.x / ppb, i = threadIdx.x - g * ppb;
     const long long n = (long long)blockIdx.x * ppb + i;
     float gq[3] = {0.0f, 0.0f, 0.0f};
@@ -2565,9 +2575,10 @@ __global__ __launch_bounds__(256) void k_grad_records(GridP G, const float *__re
 #pragma unroll
             for (int r = 0; r < 3; ++r) gx[r] = gxc[((long long)k * 3 + r) * N + n];
             bool ok = true;
+            const Cell c = locate(G, x);
             if (EXACT) {
                 float d[3], J[9];
-                field_dJ(T + (long long)p * G.V * 12, G, x, d, J);
+                field_dJ_clamped(T + (long long)p * G.V * 12, G, c, may_skip, x, d, J);
                 ok = inv3(J, M);
             }
             float lam[3] = {0.0f, 0.0f, 0.0f};
@@ -2578,7 +2589,6 @@ __global__ __launch_bounds__(256) void k_grad_records(GridP G, const float *__re
                     gq[r] -= lam[r];
                 }
             }
-            const Cell c = locate(G, x);
             const int cl = p * ncell + cell_linear(G, c);
             const long long slot = (long long)offset[cl] + pq;
             // positions that do not belong to these roots (a caller mixing arrays of different solves)
