@@ -1147,15 +1147,22 @@ __device__ __forceinline__ void park_slots(bool want_slot, int slot_cell, int pa
     }
 }
 
+// 1 / den for the lanes of the wave that are here
+__device__ __forceinline__ float reciprocal(float den)
+{
+    float rinv = recip(den);
+    if (__builtin_expect(__any(!is_normal(rinv)), 0)) {
+        asm volatile("");                // a branch: the division is not to be computed in every step
+        rinv = 1.0f / den;
+    }
+    return rinv;
+}
+
 // Rank-one update of J~ (good Broyden, inverse form) with u = dx - J~ dg, v = dx^T J~, den = v dg; none where den is 0 or not finite.
 __device__ __forceinline__ void rank_one(float (&J)[9], const float (&u)[3], const float (&v)[3], float den)
 {
     if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
-        float rinv = recip(den);
-        if (__builtin_expect(__any(!is_normal(rinv)), 0)) {
-            asm volatile("");                // a branch: the division is not to be computed in every step
-            rinv = 1.0f / den;
-        }
+        const float rinv = reciprocal(den);
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
             const float sc = u[r] * rinv;
@@ -1178,7 +1185,7 @@ __device__ __forceinline__ void advance(const float (&J)[9], const float (&g)[3]
 // What follows once the field's residual gn at the new x is known: the update of J~ and the test.  True: the pair has ended.
 // A step begins with advance() rather than ending with it, so that x and J~ have one place each and the test has no branch: with the next
 // step computed in a branch after the test, and loops that end at their head, the compiler copied the state to other registers and back
-// in every pass (a pass of k_solve_once 311 vector instructions, now 233; of a quad 155, now 145).
+// in every pass (a pass of k_solve_once 311 vector instructions, now 233).
 __device__ __forceinline__ bool finish_step(const SolveP &S, const float (&dx)[3], const float (&gn)[3], float (&g)[3], float (&J)[9],
                                             int &it, bool &conv)
 {
@@ -1203,8 +1210,8 @@ __device__ __forceinline__ bool finish_step(const SolveP &S, const float (&dx)[3
 // A pair whose trajectory is long is bound by the latency of a step: a chain of cell lookup, 8 corner records, blend,
 // rank-one update.  With one lane per pair a step costs the wave some 320 vector instructions and 24 gathered loads
 // whoever else is active.  Here the four lanes of a quad work on one pair: lane r = 0, 1, 2 looks up axis r, fetches row r
-// of every corner record (8 loads of 16 bytes; the three lanes read 48 contiguous bytes) and blends that row; the rest of
-// the state is kept by all four lanes alike and costs what it costs one lane.  Lane 3 repeats lane 2.  The operations
+// of every corner record (8 loads of 16 bytes; the three lanes read 48 contiguous bytes) and blends that row, and
+// computes what belongs to row r of the update (QuadState).  Lane 3 repeats lane 2.  The operations
 // on every number, and their order, are those of one lane per pair, so the results are the same bits.
 template <int R>
 __device__ __forceinline__ float quad_get(float v)      // the value of lane R of the quad
@@ -1235,14 +1242,14 @@ __device__ __forceinline__ QuadAxis quad_axis(const GridP &G)
     return A;
 }
 
-// the cell of x, every lane of the quad holding the whole x: base and fractions (ci and cl are not set)
-__device__ __forceinline__ Cell quad_locate(const QuadAxis &A, const float x[3])
+// the cell of x from its coordinate along the lane's axis: base and fractions (ci and cl are not set)
+__device__ __forceinline__ Cell quad_locate(const QuadAxis &A, float xr)
 {
     Cell c;
     int i0;
     float f;
     bool cl;
-    locate_axis(pick3(A.row, x[0], x[1], x[2]), A.lo, A.inv_h, A.m, A.n, i0, f, cl);
+    locate_axis(xr, A.lo, A.inv_h, A.m, A.n, i0, f, cl);
     const int b = i0 * A.stride;
     c.base = quad_get<0>(b) + quad_get<1>(b) + quad_get<2>(b);
     c.f[0] = quad_get<0>(f);
@@ -1278,24 +1285,77 @@ __device__ __forceinline__ void quad_blend(const float (&om)[8], const float (&q
         for (int e = 0; e < 4; ++e) T[e] = FS_FMA(om[k], q[k][e], T[e]);
 }
 
-// One Broyden step of the pair of every active quad.  x, g, J: its state, xpr: x' along the lane's axis, it: steps taken;
-// q, held: the lane's row of the corner records and the base of the cell they belong to (-1: none).  True: the pair has ended.
-__device__ __forceinline__ bool quad_step(const GridP &G, const SolveP &S, const QuadAxis &A, const float *__restrict__ Tp, float xpr,
-                                          float (&x)[3], float (&g)[3], float (&J)[9], int &it, float (&q)[8][4], int &held, bool &conv)
+// The state of a quad's pair: x along the lane's axis, g whole, the lane's row and column of J~.  What is one number per row (dx, u, v) is
+// computed by its lane and fetched by the others; every number by the operations of finish_step.  (All of J~ and x in every lane:
+// 145 instead of 128 vector instructions per step; 37 points of 24 states, up to 50 steps: the call 41.1 us, now 38.4.)
+struct QuadState {
+    float x, g[3], row[3], col[3];
+};
+__device__ __forceinline__ QuadState quad_state(int row, const float (&x)[3], const float (&g)[3], const float (&J)[9])
 {
-    float dx[3];
-    advance(J, g, x, dx);
-    const Cell cell = quad_locate(A, x);
+    QuadState q;
+    q.x = pick3(row, x[0], x[1], x[2]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        q.g[c] = g[c];
+        q.row[c] = pick3(row, J[c], J[3 + c], J[6 + c]);
+        q.col[c] = pick3(row, J[3 * c], J[3 * c + 1], J[3 * c + 2]);
+    }
+    return q;
+}
+// the whole x and J~ in every lane
+__device__ __forceinline__ void quad_unpack(const QuadState &q, float (&x)[3], float (&J)[9])
+{
+    x[0] = quad_get<0>(q.x);
+    x[1] = quad_get<1>(q.x);
+    x[2] = quad_get<2>(q.x);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        J[c] = quad_get<0>(q.row[c]);
+        J[3 + c] = quad_get<1>(q.row[c]);
+        J[6 + c] = quad_get<2>(q.row[c]);
+    }
+}
+
+// One Broyden step of the pair of every active quad.  xpr: x' along the lane's axis, it: steps taken; q, held: the lane's row of the
+// corner records and the base of the cell they belong to (-1: none).  True: the pair has ended.
+__device__ __forceinline__ bool quad_step(const GridP &G, const SolveP &S, const QuadAxis &A, const float *__restrict__ Tp, float xpr,
+                                          QuadState &s, int &it, float (&q)[8][4], int &held, bool &conv)
+{
+    const float dxr = -FS_FMA(s.row[2], s.g[2], FS_FMA(s.row[1], s.g[1], s.row[0] * s.g[0]));
+    s.x = s.x + dxr;
+    const Cell cell = quad_locate(A, s.x);
     if (cell.base != held) {
         quad_load(Tp + cell.base, G, A.row, q);
         held = cell.base;
     }
+    const float x[3] = {quad_get<0>(s.x), quad_get<1>(s.x), quad_get<2>(s.x)};
+    const float vr = FS_FMA(quad_get<2>(dxr), s.col[2], FS_FMA(quad_get<1>(dxr), s.col[1], quad_get<0>(dxr) * s.col[0]));
+    const float v[3] = {quad_get<0>(vr), quad_get<1>(vr), quad_get<2>(vr)};
     float om[8], T[4];
     corner_weights(cell, om);
     quad_blend(om, q, T);
     const float gr = quad_apply(T, x) - xpr;
     const float gn[3] = {quad_get<0>(gr), quad_get<1>(gr), quad_get<2>(gr)};
-    return finish_step(S, dx, gn, g, J, it, conv);
+    float dg[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) dg[r] = gn[r] - s.g[r];
+    const float ur = dxr - FS_FMA(s.row[2], dg[2], FS_FMA(s.row[1], dg[1], s.row[0] * dg[0]));
+    const float den = FS_FMA(v[2], dg[2], FS_FMA(v[1], dg[1], v[0] * dg[0]));
+    if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
+        const float sc = ur * reciprocal(den);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s.row[c] = FS_FMA(sc, v[c], s.row[c]);
+        s.col[0] = FS_FMA(quad_get<0>(sc), vr, s.col[0]);
+        s.col[1] = FS_FMA(quad_get<1>(sc), vr, s.col[1]);
+        s.col[2] = FS_FMA(quad_get<2>(sc), vr, s.col[2]);
+    }
+    ++it;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) s.g[r] = gn[r];
+    const float r2 = FS_FMA(gn[2], gn[2], FS_FMA(gn[1], gn[1], gn[0] * gn[0]));
+    conv = r2 < S.tol2;
+    return conv || !(r2 < S.div2) || it >= S.max_iters;
 }
 
 // A wave whose last QUADS pairs (or fewer) are all that is left for it hands them from single lanes to quads: quad j
@@ -1341,11 +1401,13 @@ __device__ __forceinline__ void quad_tail(const GridP &G, const SolveP &S, const
     pz = __shfl(pz, src);
     const float *Tp = T + (long long)pz * G.V * 12;
     bool conv = false;
+    QuadState state = quad_state(A.row, x, g, J);
     if (on) {
         float q[8][4];
         int held = -1;
-        while (!quad_step(G, S, A, Tp, xpr, x, g, J, it, q, held, conv)) {}
+        while (!quad_step(G, S, A, Tp, xpr, state, it, q, held, conv)) {}
     }
+    quad_unpack(state, x, J);
     emit(on && (lane & 3) == 0, conv, x, J, it, n, k, pz);
 }
 
@@ -2216,7 +2278,7 @@ __global__ __launch_bounds__(LDS ? 1024 : 256) void k_solve_quad(GridP G, SolveP
         for (int e = 0; e < 9; ++e) J[e] = J0[((long long)k * 9 + e) * N + n];
         ok = live && valid0[pair] != 0;
         if (ok) {
-            const Cell c = quad_locate(A, x);
+            const Cell c = quad_locate(A, pick3(row, x[0], x[1], x[2]));
             float q[8][4], om[8], Tr[4];
             quad_load(Tp + c.base, G, row, q);
             corner_weights(c, om);
@@ -2236,7 +2298,9 @@ __global__ __launch_bounds__(LDS ? 1024 : 256) void k_solve_quad(GridP G, SolveP
         if (!(conv || !(r2 < S.div2) || 0 >= S.max_iters)) {
             float q[8][4];
             int held = -1;
-            while (!quad_step(G, S, A, Tp, xpr, x, g, J, it, q, held, conv)) {}
+            QuadState state = quad_state(row, x, g, J);
+            while (!quad_step(G, S, A, Tp, xpr, state, it, q, held, conv)) {}
+            quad_unpack(state, x, J);
         }
     }
     int pos = -1;
