@@ -1642,10 +1642,12 @@ __device__ __forceinline__ void lds_store_release(int *p, int v)
 // converged ones; when OUT_PEND - 15 have gathered it asks for their positions in their cells' lists (one atomic per cell
 // and round of 64, as flush_slots does), puts each position into its record, and writes the records out with four
 // consecutive lanes per record: every record reaches memory once, whole, as 64 contiguous bytes.
-template <int OUT_PEND>
+// Without J~ a record is 16 bytes; those of eight neighbouring points in one state are one line.  (Stored by each lane as it finished: 200 k points
+// of 24 states 705 us, now 682.)
+template <int OUT_PEND, bool WITH_J>
 struct OutQ {
-    float4 rec[OUT_PEND][4];
-    int place[OUT_PEND];      // where in the transform grids the cell of a converged lane that wants a position begins, else -1
+    float4 rec[OUT_PEND][WITH_J ? 4 : 1];
+    int place[WITH_J ? OUT_PEND : 1];      // where in the transform grids the cell of a converged lane that wants a position begins, else -1
     int pair[OUT_PEND];
 };
 
@@ -1657,13 +1659,13 @@ __device__ __forceinline__ int cell_at(const GridP &G, int ncell, int place)
     return (int)(p * (unsigned)ncell + (c - ix) * (unsigned)(G.nz - 1) + v - c * (unsigned)G.nz);
 }
 
-template <int OUT_PEND>
-__device__ __forceinline__ void out_flush(const GridP &G, OutQ<OUT_PEND> &q, int npend, int lane, int *__restrict__ cell_count, int ncell,
+template <int OUT_PEND, bool WITH_J>
+__device__ __forceinline__ void out_flush(const GridP &G, OutQ<OUT_PEND, WITH_J> &q, int npend, int lane, int *__restrict__ cell_count, int ncell,
                                           float4 *__restrict__ rec)
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the LDS writes of the wave's other lanes
     __builtin_amdgcn_wave_barrier();
-    if (cell_count) {
+    if (WITH_J && cell_count) {
         // rounds of 64 entries; the atomics of all are on their way before an answer is used
         bool valid[OUT_PEND / 64];
         CellGroup g[OUT_PEND / 64];
@@ -1677,20 +1679,21 @@ __device__ __forceinline__ void out_flush(const GridP &G, OutQ<OUT_PEND> &q, int
 #pragma unroll
         for (int b = 0; b < OUT_PEND / 64; ++b) {
             const int at = group_position(g[b]);
-            if (valid[b]) reinterpret_cast<int *>(&q.rec[64 * b + lane][1])[0] = at;
+            if (valid[b]) reinterpret_cast<int *>(&q.rec[64 * b + lane][WITH_J ? 1 : 0])[0] = at;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
-    for (int i = lane; i < npend * 4; i += 64) rec[(long long)q.pair[i >> 2] * 4 + (i & 3)] = q.rec[i >> 2][i & 3];
+    constexpr int Q = WITH_J ? 4 : 1;          // float4 per record
+    for (int i = lane; i < npend * Q; i += 64) rec[(long long)q.pair[i / Q] * Q + i % Q] = q.rec[i / Q][i % Q];
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // before the entries are overwritten
     __builtin_amdgcn_wave_barrier();
 }
 
 // park the record of every lane with `want` (wave-wide call); place < 0: no position wanted
-template <int OUT_PEND>
+template <int OUT_PEND, bool WITH_J>
 __device__ __forceinline__ void out_park(const GridP &G, bool want, const float x[3], const float J[9], int flags, int place, int pair,
-                                         OutQ<OUT_PEND> &q, int &npend, int lane, int *__restrict__ cell_count, int ncell, float4 *__restrict__ rec)
+                                         OutQ<OUT_PEND, WITH_J> &q, int &npend, int lane, int *__restrict__ cell_count, int ncell, float4 *__restrict__ rec)
 {
     const unsigned long long m = __ballot(want);
     if (m) {
@@ -1701,11 +1704,13 @@ __device__ __forceinline__ void out_park(const GridP &G, bool want, const float 
         if (want) {
             const int at = npend + __popcll(m & ((1ull << lane) - 1ull));
             q.rec[at][0] = make_float4(x[0], x[1], x[2], __int_as_float(flags));
-            q.rec[at][1] = make_float4(__int_as_float(-1), J[0], J[1], J[2]);
-            q.rec[at][2] = make_float4(J[3], J[4], J[5], J[6]);
-            q.rec[at][3] = make_float4(J[7], J[8], 0.0f, 0.0f);
-            q.place[at] = place;
             q.pair[at] = pair;
+            if constexpr (WITH_J) {
+                q.rec[at][1] = make_float4(__int_as_float(-1), J[0], J[1], J[2]);
+                q.rec[at][2] = make_float4(J[3], J[4], J[5], J[6]);
+                q.rec[at][3] = make_float4(J[7], J[8], 0.0f, 0.0f);
+                q.place[at] = place;
+            }
         }
         npend += __popcll(m);
     }
@@ -1843,7 +1848,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
     __shared__ float s_ring[NCONS][ST_FIELDS][WS_RING];
     __shared__ int s_tail[NCONS], s_head[NCONS], s_done;
     constexpr int OUT_PEND = SKIP ? 64 : 128;        // 64: 50 KiB of LDS, so that a CU holds three blocks
-    __shared__ OutQ<OUT_PEND> s_out[WITH_J ? NCONS + 1 : 1];      // records on their way out, per wave (only full records are parked)
+    __shared__ OutQ<OUT_PEND, WITH_J> s_out[NCONS + 1];      // records on their way out, per wave (only full records are parked)
     if (threadIdx.x < NCONS) {
         s_tail[threadIdx.x] = 0;
         s_head[threadIdx.x] = 0;
@@ -1855,7 +1860,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
     const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const long long N = S.N;
     int npend = 0;                   // wave-uniform: entries of the wave's s_out in use
-    OutQ<OUT_PEND> &outq = s_out[WITH_J ? wib : 0];
+    OutQ<OUT_PEND, WITH_J> &outq = s_out[wib];
     const int stride = (int)G.V * 12;          // of the poses' grids; P of them are below 2^31
 
     if (wib == NCONS) {
@@ -1993,21 +1998,14 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                     const float r2 = FS_FMA(ng[2], ng[2], FS_FMA(ng[1], ng[1], ng[0] * ng[0]));
                     const bool conv = r2 < S.tol2;
                     if (conv || !(r2 < S.div2) || 0 >= S.max_iters) {
-                        if (WITH_J) {
-                            want_out = true;
-                            out_flags = conv ? 1 : 0;
-                            if (cell_count && conv) out_place = np * stride + base0;
-                        } else {
-                            write_record<false>(rec, pair, nx, nJ, conv ? 1 : 0);
-                        }
+                        want_out = true;
+                        out_flags = conv ? 1 : 0;
+                        if (cell_count && conv) out_place = np * stride + base0;
                     } else {
                         keep = true;
                     }
                 }
-                if (!ok && !norec) {
-                    if (WITH_J) want_out = true;         // out_flags = 0, no position
-                    else write_record<false>(rec, pair, nx, nJ, 0);
-                }
+                if (!ok && !norec) want_out = true;         // out_flags = 0, no position
             }
             const unsigned long long km = __ballot(keep);
             const int nkeep = __popcll(km);
@@ -2051,10 +2049,10 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                 for (int c = 0; c < NCONS; ++c) if (c == best) tails[c] = tl;
                 if (lane == 0) lds_store_release(&s_tail[best], tl);
             }
-            if (WITH_J) out_park(G, want_out, nx, nJ, out_flags, out_place, pair, outq, npend, lane, cell_count, ncell, rec);
+            out_park(G, want_out, nx, nJ, out_flags, out_place, pair, outq, npend, lane, cell_count, ncell, rec);
         }
         if (lost && lane == 0) *give_up = 1;
-        if (WITH_J && npend > 0) out_flush(G, outq, npend, lane, cell_count, ncell, rec);
+        if (npend > 0) out_flush(G, outq, npend, lane, cell_count, ncell, rec);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         if (lane == 0) lds_store_release(&s_done, 1);
         return;
@@ -2065,13 +2063,9 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
     // what becomes of a pair that has ended in a quad (wave-wide call; `ends` in one lane of the quad)
     auto emit = [&](bool ends, bool conv, const float (&xe)[3], const float (&Je)[9], int ite, int ne, int ke, int pe) {
         const int flags = (conv ? 1 : 0) | (ite << 8), pair = (int)((long long)ke * N + ne);
-        if (WITH_J) {
-            int place = -1;
-            if (ends && cell_count && conv) place = pe * stride + locate(G, xe).base;
-            out_park(G, ends, xe, Je, flags, place, pair, outq, npend, lane, cell_count, ncell, rec);
-        } else if (ends) {
-            write_record<false>(rec, pair, xe, Je, flags);
-        }
+        int place = -1;
+        if (WITH_J && ends && cell_count && conv) place = pe * stride + locate(G, xe).base;
+        out_park(G, ends, xe, Je, flags, place, pair, outq, npend, lane, cell_count, ncell, rec);
     };
     bool active = false;
     int n = 0, k = 0, it = 0, pz = 0, head = 0;
@@ -2133,13 +2127,9 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
         if (active) {
             bool conv;
             if (lane_step<SKIP>(G, S, Tp, may_skip, xp, x, g, J, it, q, held, held_mask, conv)) {
-                if (WITH_J) {
-                    want_out = true;
-                    out_flags = (conv ? 1 : 0) | (it << 8);
-                    if (cell_count && conv) out_place = pz * stride + held;
-                } else {
-                    write_record<false>(rec, (long long)k * N + n, x, J, (conv ? 1 : 0) | (it << 8));
-                }
+                want_out = true;
+                out_flags = (conv ? 1 : 0) | (it << 8);
+                if (cell_count && conv) out_place = pz * stride + held;
                 active = false;
             } else if (!SKIP && S.prefetch) {
                 // the corner records the next pass will need are asked for now: they travel while this pass parks
@@ -2155,12 +2145,12 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                 }
             }
         }
-        if (WITH_J) out_park(G, want_out, x, J, out_flags, out_place, (int)((long long)k * N + n), outq, npend, lane, cell_count, ncell, rec);
+        out_park(G, want_out, x, J, out_flags, out_place, (int)((long long)k * N + n), outq, npend, lane, cell_count, ncell, rec);
         nidle = 64 - lanes_on(active);
     } while (!(fin && 64 - nidle <= QUADS));
     // the wave's last pairs, four lanes each
     quad_tail(G, S, T, active, lane, xp, x, g, J, it, n, k, pz, emit);
-    if (WITH_J && npend > 0) out_flush(G, outq, npend, lane, cell_count, ncell, rec);
+    if (npend > 0) out_flush(G, outq, npend, lane, cell_count, ncell, rec);
 }
 
 // Which pairs a wave of the kernels for small batches takes: `per` pairs (64, or 16 quads), as a tile of ki initial states
