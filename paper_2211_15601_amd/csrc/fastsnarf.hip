@@ -281,15 +281,15 @@ fs_status need_solve_counts(fs_ctx *c, int ncell)
 // Kernels of the solve by the size of a batch (pairs = K * N; all three give the same bits).  What bounds a small batch is
 // max_iters times the latency of a step, and a step is half as long with four lanes per pair (0.5 to 0.6 instead of 1.0 to 1.2 us);
 // what bounds a large one is instruction issue and the vector cache, where one lane per pair and refilled waves win.
-// Measured, kernel us, k_solve_quad / k_solve_once / k_solve_ws, 24 states per point on a 64x64x16 grid: 12 k pairs
-// 43 / 52 / 69; 48 k 47 / 49 / 74; 98 k 77 / 57 / 81; 192 k 111 / 78 / 93; 288 k 148 / 124 / 115.  The lines are where
+// Measured, solve and dedupe, us, k_solve_quad / k_solve_once / k_solve_ws, 24 states per point on a 64x64x16 grid: 24 k pairs 49 / 54 / 58;
+// 48 k 54 / 55 / 62; 98 k 78 / 58 / 69; 197 k 103 / 79 / 88; 240 k 116 / 100 / 94; 288 k 126 / 110 / 102.  The lines are where
 // the chip is full: three quad waves per SIMD; all pairs of k_solve_once resident at once (3 waves per SIMD of 64).
 // With voxel-based candidates the share of pairs that have one is not known here (rays 1/7, scans 6/10), k_solve_ws needs
-// its list of them first and most quads of a sparse batch end at once: rays, 74 k pairs 26 (quad) / 33 (once), 180 k 33 / 35;
-// scans, 74 k 43 / 33, 180 k 65 / 44.  The upper line there, 4.5 waves per SIMD of which 3 are resident, is a compromise: whole calls,
-// solve and dedupe, k_solve_once / k_solve_ws, on 32x32x8, 64x64x16 and 128x128x32 nodes: rays, 198 k pairs 33 / 50, 34 / 56, 43 / 67,
-// 295 k 33 / 50, 37 / 57, 45 / 71; scans, 198 k 57 / 64, 58 / 68, 75 / 80, 246 k 59 / 65, 69 / 71, 85 / 84, 295 k 58 / 67, 77 / 72, 93 / 87.
-// Scans on large grids would gain 7 % from a line at 210 k to 270 k pairs, rays would lose 35 %.
+// its list of them first and most quads of a sparse batch end at once: rays, 72 k pairs 29 (quad) / 32 (once), 192 k 34 / 35;
+// scans, 72 k 37 / 37, 192 k 56 / 39.  The upper line there, 4.5 waves per SIMD of which 3 are resident, is a compromise, k_solve_once / k_solve_ws
+// on 64x64x16 and 128x128x32 nodes: rays, 192 k pairs 35 / 71, 42 / 81, 294 k 39 / 71, 47 / 90, 600 k 48 / 77, 64 / 100; scans, 192 k 39 / 50, 53 / 61,
+// 294 k 60 / 57, 78 / 69, 600 k 89 / 70, 120 / 89.
+// Scans would gain 6 to 12 % from a line at 210 k to 270 k pairs, rays would lose 45 %.
 enum { SOLVE_QUAD, SOLVE_ONCE, SOLVE_LARGE };
 int solve_kind(const fs_ctx *c, long long pairs, bool candidates)
 {
