@@ -608,7 +608,6 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     S.tol2 = ctx->prm.tol * ctx->prm.tol;
     S.div2 = ctx->prm.div_thresh * ctx->prm.div_thresh;
     S.K = K;
-    S.point_major = ctx->point_major;
     S.chunk = ctx->chunk;
     S.spin_limit = ctx->spin_limit;
     const long long chunks = (S.total + S.chunk - 1) / S.chunk;
@@ -631,9 +630,13 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const int occ = lds ? ctx->occ_blocks_per_cu : (vx ? ctx->occ_vx_blocks_per_cu : ctx->occ_ws_blocks_per_cu);
     const int per_cu = lds_big ? 1 : std::max(1, std::min(want_blocks, occ));
     // consumers of k_solve_ws refill from their queue at 8 idle lanes (8 ... 24: within 1 % on grids the L2 holds; 32 and
-    // more lose 3 ... 40 %); on grids beyond it at 24 (1.34 instead of 1.37 ms on the 8-pose batch; 48: 1.38)
-    S.refill_min = ctx->refill_min ? ctx->refill_min : (lds ? 32 : (grid_bytes > (32u << 20) ? 24 : 8));
+    // more lose 3 ... 40 %); with candidates on grids beyond it at 24 (1.34 instead of 1.37 ms on the 8-pose batch; 48: 1.38)
+    S.refill_min = ctx->refill_min ? ctx->refill_min : (lds ? 32 : (grid_bytes > (32u << 20) && !bone ? 24 : 8));
     S.prefetch = grid_bytes > (32u << 20);
+    // Tiles of points (tile_pair), but with positions on a grid beyond the L2 all states of a point side by side: there lanes share an atomic
+    // only with the same point's (steps, us, tiles / side by side: 120 k points in two poses of 128x128x32 nodes 1072 / 996, 60 k in one 532 / 510,
+    // 60 k in eight of 64x64x16 500 / 490).
+    S.point_major = !ctx->point_major ? 0 : (d_slot && grid_bytes > L2_BYTES ? 2 : 1);
     // Eighths of the chunks dealt out without asking the cursor.  Whole calls, us, with 0 / 4 / 6 / 7: one state per bone on 64x64x16 nodes, 200 k
     // points 732 / 709 / 723 / 739, 65 k points 411 / 397 / 399 / 406, 20 k points on 45x39x11 209 / 203 / 201 / 201; candidates, 2 M ray samples
     // 303 / 292 / 286 / 286.  On grids beyond the L2 all blocks should read the same stretch of the points: 8 poses of 128x128x32 nodes

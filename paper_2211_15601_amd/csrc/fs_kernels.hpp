@@ -768,7 +768,7 @@ struct SolveP {
     int max_iters;
     float tol2, div2;
     int K;
-    int point_major;     // order in which pairs are handed out
+    int point_major;     // order in which pairs are handed out: 0 state by state, 1 (k_solve_ws) in tiles of points, 2 point by point
     int ki;              // kernels of small batches: initial states per wave (pair_of)
     int spin_limit;      // producer / consumer kernel: polls of a work queue before a wave gives up
     int xcd_ranges;      // producer / consumer kernel: the list is cut into 8 ranges, one per XCD, each with its own cursor
@@ -1930,8 +1930,11 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                     nn = e.x;
                     nk = e.y & 7;
                     gcell = e.y >> 3;
-                } else if (S.point_major) {
+                } else if (S.point_major == 1) {
                     tile_pair(upq, (unsigned)N, (unsigned)S.K, nn, nk);
+                } else if (S.point_major) {   // consecutive SIMD lanes: the K initial states of one point
+                    nn = (int)(upq / (unsigned)S.K);
+                    nk = (int)(upq - (unsigned)nn * (unsigned)S.K);
                 } else {                      // consecutive SIMD lanes: consecutive points, same initial state
                     nk = (int)(upq / (unsigned)N);
                     nn = (int)(upq - (unsigned)nk * (unsigned)N);
