@@ -70,7 +70,7 @@ struct fs_ctx {
     int sort_list;     // order the list of (point, candidate) pairs by place (large voxel-mode batches)
     int xcd_ranges;    // with an ordered list: one range of it, and one cursor, per XCD
     int spin_limit;    // polls for room in its consumers' queues before the producer wave of a solve block gives up
-    int pre_serial;    // number of the last fs_precompute; cursor[CUR_NONFINITE] == pre_serial: that grid has an entry that is not finite or not below SKIP_MAX
+    int pre_serial;    // number of the last fs_precompute (may_skip_corners)
     int *gave_up;      // pinned host word, mapped into the device: a wave that gave up sets it
     int *gave_up_dev;  // the device's address of it
     // optional timing of the Broyden kernel alone (events on the context's stream)
@@ -528,7 +528,7 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
     const bool wide = (long long)vblocks * ((G.P + 3) / 4) >= 4ll * ctx->n_cus;
 #define FS_LAUNCH_PRE(NP)                                                                                              \
     k_precompute<NP><<<(vblocks + N_XCD - 1) / N_XCD * N_XCD * ((G.P + (NP) - 1) / (NP)), 256, 0, st>>>(               \
-        G, d_W, d_B, ctx->T, ctx->Bdev, ctx->Binv, ctx->Bok, reinterpret_cast<int *>(ctx->cursor + CUR_NONFINITE),     \
+        G, d_W, d_B, ctx->T, ctx->Bdev, ctx->Binv, ctx->Bok, reinterpret_cast<int *>(ctx->cursor + CUR_GRID),          \
         ctx->pre_serial, voxel ? ctx->Y : nullptr, ctx->bb_ord, ctx->count, ncp, vblocks, (G.P + (NP) - 1) / (NP))
     if (wide) FS_LAUNCH_PRE(4);
     else FS_LAUNCH_PRE(1);
@@ -568,7 +568,7 @@ fs_status fs_init(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_t
     const long long total = (long long)N * K;
     if (ctx->prm.init_mode == FS_INIT_BONE)
         k_init_bone<<<grid1d(total, 256), 256, 0, ctx->stream>>>(ctx->G, ctx->T, ctx->Binv, ctx->Bok, d_xq, d_pose, N,
-                                                                 d_x0, d_Jinv0, d_valid0, reinterpret_cast<const int *>(ctx->cursor + CUR_NONFINITE), ctx->pre_serial);
+                                                                 d_x0, d_Jinv0, d_valid0, reinterpret_cast<const int *>(ctx->cursor + CUR_GRID));
     else
         k_init_voxel<<<grid1d(total, 256), 256, 0, ctx->stream>>>(ctx->G, ctx->C, ctx->bbox, ctx->cinit, d_xq, d_pose, N,
                                                                   d_x0, d_Jinv0, d_valid0);
@@ -704,7 +704,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         const bool staged = lds && small_in_lds(ctx, grid_bytes, per_block);
         const int threads = staged ? WAVE * per_block : 256;
         const dim3 qg(grid1d(waves * 64, threads));
-        const int *nonfinite = reinterpret_cast<const int *>(ctx->cursor + CUR_NONFINITE);
+        const int *state = reinterpret_cast<const int *>(ctx->cursor + CUR_GRID);
 #define FS_LAUNCH_QUAD(IM, L)                                                                                          \
     do {                                                                                                               \
         if (quad)                                                                                                      \
@@ -714,7 +714,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         else                                                                                                           \
             k_solve_once<IM, L><<<qg, threads, (L) ? grid_bytes : 0, st>>>(                                            \
                 ctx->G, S, I, ctx->T, d_xq, d_pose, d_x0, d_Jinv0, d_valid0, d_xc, d_conv, d_Jinv, d_iters, d_slot,    \
-                d_slot ? ctx->srec : nullptr, counts, ncell, nonfinite, ctx->pre_serial);                              \
+                d_slot ? ctx->srec : nullptr, counts, ncell, state);                                                   \
     } while (0)
         const int im = !fused ? 2 : (voxel_list ? 1 : 0);
         if (staged) {
@@ -826,7 +826,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
 #define FS_LAUNCH_SOLVE(F, J, NC, Z)                                                                                   \
     k_solve_ws<F, J, NC, Z><<<dim3(blocks), dim3((NC + 1) * WAVE), 0, st>>>(                                           \
         ctx->G, S, I, ctx->T, d_xq, d_pose, d_x0, d_Jinv0, d_valid0, ctx->srec, ctx->cursor, list, list_len, cell_count,  \
-        ncell, ctx->gave_up_dev, reinterpret_cast<const int *>(ctx->cursor + CUR_NONFINITE), ctx->pre_serial)
+        ncell, ctx->gave_up_dev, reinterpret_cast<const int *>(ctx->cursor + CUR_GRID))
         // Z = true: contexts with one state per bone.  Many of those lanes start outside the box (51 % of the
         // evaluations on the SMPL-scale scene have a clamped coordinate): the consumers skip the corner records of
         // weight zero (kernel -8 %).  Z = false: voxel-based candidates, which start inside it, where the bookkeeping
@@ -937,16 +937,16 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
         const int groups = N >= (1 << 19) ? 1 : (K >= 8 ? 8 : (K >= 4 ? 4 : (K >= 2 ? 2 : 1)));
         const dim3 rg(grid1d(N, 256 / groups));
         float4 *grec4 = reinterpret_cast<float4 *>(ctx->grec);
-        const int *nonfinite = reinterpret_cast<const int *>(ctx->cursor + CUR_NONFINITE);
+        const int *state = reinterpret_cast<const int *>(ctx->cursor + CUR_GRID);
 #define FS_LAUNCH_RECORDS(R, E)                                                                                       \
     k_grad_records<R, E><<<rg, 256, 0, st>>>(G, ctx->T, d_xc, d_Jinv, d_conv, d_gxc, d_pose, N, K, ncell, ctx->gcount, pos, \
                                              grec4, d_gxq, groups, (R) ? ctx->srec : nullptr,                          \
-                                             ((R) && ctx->slots_list) ? ctx->vcnt : nullptr, nonfinite, ctx->pre_serial)
+                                             ((R) && ctx->slots_list) ? ctx->vcnt : nullptr, state)
         // from_rec: the solve's own result records are still in the context: one 64-byte read per pair
         if (from_rec && mode != 0) FS_LAUNCH_RECORDS(true, true);
         else if (from_rec && groups == 1)     // large batches: three lanes of a point in flight, stage by stage
             k_grad_records<true, false, 3><<<rg, 256, 0, st>>>(G, ctx->T, d_xc, d_Jinv, d_conv, d_gxc, d_pose, N, K, ncell, ctx->gcount,
-                                                               pos, grec4, d_gxq, groups, ctx->srec, ctx->slots_list ? ctx->vcnt : nullptr, nonfinite, ctx->pre_serial);
+                                                               pos, grec4, d_gxq, groups, ctx->srec, ctx->slots_list ? ctx->vcnt : nullptr, state);
         else if (from_rec) FS_LAUNCH_RECORDS(true, false);
         else if (mode != 0) FS_LAUNCH_RECORDS(false, true);
         else FS_LAUNCH_RECORDS(false, false);

@@ -23,6 +23,17 @@ constexpr int FS_MAX_CORR_K_DEV = 8;
 // number of lanes of the wave with `on`, as a scalar (the compiler compares a 64-bit population count on the vector unit)
 __device__ __forceinline__ int lanes_on(bool on) { return __builtin_amdgcn_readfirstlane(__popcll(__ballot(on))); }
 
+// Two words about the grid that stands, both written by k_precompute: the number of the call that made it, and the number of the last call
+// whose grid had an entry that is not finite or not below SKIP_MAX.  Where they are equal, records of weight zero are not skipped.
+// Both are on the device because a recorded graph keeps the numbers it was recorded with, whatever calls came between its
+// replays: a replay of a recorded fs_precompute writes its own number, and whoever reads asks about the grid that is there.  (A recorded call
+// that has once made such a grid is taken to make one at every later replay: right, and slower.)
+enum { GRID_NUMBER = 0, GRID_REFUSED = 1 };
+__device__ __forceinline__ bool may_skip_corners(const int *__restrict__ state)
+{
+    return __builtin_amdgcn_readfirstlane(state[GRID_NUMBER]) != __builtin_amdgcn_readfirstlane(state[GRID_REFUSED]);
+}
+
 // ------------------------------------------------------------------------------------------------
 // Pre-computed LBS (Eq. (13)): one thread per node, all poses.  The bone transforms are read with
 // wave-uniform addresses, i.e. through the scalar cache into SGPR operands of the multiply-adds.
@@ -99,7 +110,7 @@ template <int NP>
 __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__restrict__ W,
                                                     const float *__restrict__ B, float *__restrict__ T,
                                                     float *__restrict__ Bcopy, float *__restrict__ Binv,
-                                                    uint8_t *__restrict__ Bok, int *__restrict__ nonfinite,
+                                                    uint8_t *__restrict__ Bok, int *__restrict__ state,
                                                     int serial, float *__restrict__ Y, unsigned *__restrict__ bb_part,
                                                     int *__restrict__ ccount, int ncount, int vblocks, int groups)
 {
@@ -107,14 +118,13 @@ __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__rest
     // after the other, so that its L2 has the weights
     const int t = (int)blockIdx.x / N_XCD, bt = t / groups, group = t - bt * groups, blk = bt * N_XCD + (int)blockIdx.x % N_XCD;
     if (blk >= vblocks) return;
-    // *nonfinite = serial (the number of this call) tells the solve that this grid holds an entry that is not
-    // finite, or too large: a record with weight zero may then not be skipped (SKIP_MAX)
     __shared__ __attribute__((aligned(16))) float s_tiles[4][64 * 12];
     __shared__ unsigned s_ext[NP][4][6];
     const int wib = threadIdx.x >> 6;
     float *s_tile = s_tiles[wib];
     const long long v = (long long)blk * blockDim.x + threadIdx.x, v0 = v - (threadIdx.x & 63);   // v0: the wave's first node
     if (group == 0) {
+        if (v == 0) state[GRID_NUMBER] = serial;
         for (long long i = v; i < (long long)G.P * G.nb; i += (long long)vblocks * blockDim.x)
             bone_inverse((int)i, B, Bcopy, Binv, Bok);
         if (Y)
@@ -171,7 +181,7 @@ __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__rest
                 float big = 0.0f;
 #pragma unroll
                 for (int e = 0; e < 12; ++e) big = __builtin_fmaxf(big, __builtin_fabsf(acc[q][e]) < SKIP_MAX ? 0.0f : 1.0f);
-                if (big != 0.0f) *nonfinite = serial;
+                if (big != 0.0f) state[GRID_REFUSED] = serial;
             }
             wave_store_rows<12>(T + ((long long)(p0 + q) * G.V + v0) * 12, acc[q], nrows, s_tile);
             if (Y) {
@@ -306,9 +316,9 @@ __global__ __launch_bounds__(256) void k_init_bone(GridP G, const float *__restr
                                                    const float *__restrict__ Binv, const uint8_t *__restrict__ Bok,
                                                    const float *__restrict__ xq, const int32_t *__restrict__ pose,
                                                    long long N, float *__restrict__ o_x0, float *__restrict__ o_J,
-                                                   uint8_t *__restrict__ o_v, const int *__restrict__ nonfinite, int serial)
+                                                   uint8_t *__restrict__ o_v, const int *__restrict__ state)
 {
-    const bool may_skip = __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
+    const bool may_skip = may_skip_corners(state);
     const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= N * G.nb) return;
     const int k = (int)(q / N);
@@ -817,11 +827,10 @@ __device__ __forceinline__ void read_record_J(const float4 *__restrict__ r, floa
     J[0] = b.y; J[1] = b.z; J[2] = b.w; J[3] = c.x; J[4] = c.y; J[5] = c.z; J[6] = c.w; J[7] = d.x; J[8] = d.y;
 }
 
-// Words of the context's cursor array: CUR_ALL is the work cursor of the solve kernels; CUR_NONFINITE holds the serial
-// number of the last fs_precompute whose grid had an entry that is not finite or not below SKIP_MAX.
+// Words of the context's cursor array: CUR_ALL is the work cursor of the solve kernels; CUR_GRID: two words about the grid (GRID_NUMBER).
 // CUR_XCD + j (j = 0 .. 7): the cursor of the j-th eighth of an ordered pair list, relative to the start of that eighth.
 // CUR_LIST: length of the list of pairs that have a candidate (k_voxel_list).
-constexpr int CUR_ALL = 0, CUR_LIST = 1, CUR_NONFINITE = 2, CUR_XCD = 4, CUR_WORDS = 12;
+constexpr int CUR_ALL = 0, CUR_LIST = 1, CUR_GRID = 2, CUR_XCD = 4, CUR_WORDS = 12;
 
 // The blocks of the solve kernel own their first chunk without asking: the shared cursor starts behind `nblocks`
 // chunks, the cursor of range j behind one chunk for every block b with b mod 8 = j.
@@ -1843,7 +1852,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                                                unsigned *__restrict__ cursor, const int2 *__restrict__ list,
                                                const int *__restrict__ list_len, int *__restrict__ cell_count,
                                                int ncell, int *__restrict__ give_up,
-                                               const int *__restrict__ nonfinite, int serial)
+                                               const int *__restrict__ state)
 {
     __shared__ float s_ring[NCONS][ST_FIELDS][WS_RING];
     __shared__ int s_tail[NCONS], s_head[NCONS], s_done;
@@ -1891,7 +1900,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
 #pragma unroll
         for (int c = 0; c < NCONS; ++c) tails[c] = 0;
         bool lost = false;
-        const bool prod_skip = SKIP && __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
+        const bool prod_skip = SKIP && may_skip_corners(state);
         while (!lost) {
             if (next >= c1) {
                 if (ranges) {
@@ -2079,7 +2088,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
     int held = -1;                   // base of the cell whose corners q holds (-1: none)
     int held_mask = 0;               // SKIP: which of them
     // SKIP needs a grid of entries below SKIP_MAX (k_precompute says if this one is not)
-    const bool may_skip = SKIP && __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
+    const bool may_skip = SKIP && may_skip_corners(state);
     if (SKIP) {
 #pragma unroll
         for (int c = 0; c < 8; ++c)
@@ -2339,7 +2348,7 @@ __global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(Gri
                                                uint8_t *__restrict__ o_conv, float *__restrict__ o_J,
                                                uint8_t *__restrict__ o_it, int32_t *__restrict__ o_slot,
                                                float4 *__restrict__ rec, int *__restrict__ cell_count, int ncell,
-                                               const int *__restrict__ nonfinite, int serial)
+                                               const int *__restrict__ state)
 {
     extern __shared__ float4 s_grid[];
     if (LDS) {
@@ -2422,7 +2431,7 @@ __global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(Gri
         flags = conv ? 1 : 0;
         active = !(conv || !(r2 < S.div2) || 0 >= S.max_iters);
     }
-    const bool may_skip = SKIP && __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
+    const bool may_skip = SKIP && may_skip_corners(state);
     // the test stands at the loop's end: at its head the compiler moves the whole state to other registers and back in every pass
     if (lanes_on(active) > QUADS) {
         do {
@@ -2536,13 +2545,13 @@ __global__ __launch_bounds__(256) void k_grad_records(GridP G, const float *__re
                                                       const int *__restrict__ offset, const int *__restrict__ pos,
                                                       float4 *__restrict__ rec, float *__restrict__ gxq, int groups,
                                                       const float4 *__restrict__ srec, const uint8_t *__restrict__ cand_cnt,
-                                                      const int *__restrict__ nonfinite, int serial)
+                                                      const int *__restrict__ state)
 {
     // `groups` (a power of two <= 8) threads share a point and take its lanes k = g, g + groups, ...;
     // consecutive threads of a group are consecutive points, so every load is coalesced
     __shared__ float s_gq[256 * 3];
     const int ppb = 256 / groups;                 // points per block
-    const bool may_skip = EXACT && __builtin_amdgcn_readfirstlane(*nonfinite) != serial;
+    const bool may_skip = EXACT && may_skip_corners(state);
     const int g = threadIdx.x / ppb, i = threadIdx.x - g * ppb;
     const long long n = (long long)blockIdx.x * ppb + i;
     float gq[3] = {0.0f, 0.0f, 0.0f};
