@@ -938,18 +938,29 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
         const dim3 rg(grid1d(N, 256 / groups));
         float4 *grec4 = reinterpret_cast<float4 *>(ctx->grec);
         const int *state = reinterpret_cast<const int *>(ctx->cursor + CUR_GRID);
-#define FS_LAUNCH_RECORDS(R, E)                                                                                       \
-    k_grad_records<R, E><<<rg, 256, 0, st>>>(G, ctx->T, d_xc, d_Jinv, d_conv, d_gxc, d_pose, N, K, ncell, ctx->gcount, pos, \
-                                             grec4, d_gxq, groups, (R) ? ctx->srec : nullptr,                          \
-                                             ((R) && ctx->slots_list) ? ctx->vcnt : nullptr, state)
+#define FS_LAUNCH_RECORDS(R, ...)                                                                                     \
+    k_grad_records<R, __VA_ARGS__><<<rg, 256, 0, st>>>(G, ctx->T, d_xc, d_Jinv, d_conv, d_gxc, d_pose, N, K, ncell, ctx->gcount, pos, \
+                                                       grec4, d_gxq, groups, (R) ? ctx->srec : nullptr,               \
+                                                       ((R) && ctx->slots_list) ? ctx->vcnt : nullptr, state)
+#define FS_LAUNCH_EXACT(J)                                                                                            \
+    do {                                                                                                              \
+        if (from_rec) FS_LAUNCH_RECORDS(true, J);                                                                     \
+        else FS_LAUNCH_RECORDS(false, J);                                                                             \
+    } while (0)
         // from_rec: the solve's own result records are still in the context: one 64-byte read per pair
-        if (from_rec && mode != 0) FS_LAUNCH_RECORDS(true, true);
-        else if (from_rec && groups == 1)     // large batches: three lanes of a point in flight, stage by stage
-            k_grad_records<true, false, 3><<<rg, 256, 0, st>>>(G, ctx->T, d_xc, d_Jinv, d_conv, d_gxc, d_pose, N, K, ncell, ctx->gcount,
-                                                               pos, grec4, d_gxq, groups, ctx->srec, ctx->slots_list ? ctx->vcnt : nullptr, state);
-        else if (from_rec) FS_LAUNCH_RECORDS(true, false);
-        else if (mode != 0) FS_LAUNCH_RECORDS(false, true);
-        else FS_LAUNCH_RECORDS(false, false);
+        // The exact Jacobian: many roots of bone states lie beyond the box, where half the corners or more are left out; candidates' roots
+        // seldom do.  For those, on a grid that the L2 holds waves in flight count most, and beyond it that the two z-neighbours of
+        // a corner, one or two cache lines, are asked for together.  fs_grad, us, all corners / halves / without weight zero: bones, 65 k points 135 / 130 /
+        // 123, 200 k points on 128x128x32 nodes 502 / 469 / 437; candidates on 64x64x16 nodes, 0.5 M ray samples 54 / 57 / 66, 2 M 106 / 113 / 144, 0.5 M points of scans
+        // 99 / 94 / 106; 2 M ray samples on 84x84x21 (7 MB) 170 / 171 / 202, on 128x128x32 288 / 278 / 305, 1 M of scans 457 / 398 / 380.
+        if (mode == 0) {
+            if (from_rec && groups == 1) FS_LAUNCH_RECORDS(true, JAC_BROYDEN, 3);     // large batches: three lanes of a point in flight, stage by stage
+            else if (from_rec) FS_LAUNCH_RECORDS(true, JAC_BROYDEN);
+            else FS_LAUNCH_RECORDS(false, JAC_BROYDEN);
+        } else if (ctx->prm.init_mode == FS_INIT_BONE) FS_LAUNCH_EXACT(JAC_CLAMPED);
+        else if ((size_t)G.P * G.V * 48 > L2_BYTES) FS_LAUNCH_EXACT(JAC_HALVES);
+        else FS_LAUNCH_EXACT(JAC_CELL);
+#undef FS_LAUNCH_EXACT
 #undef FS_LAUNCH_RECORDS
     }
     if (N > 0) k_grad_pieces<<<grid1d((long long)lanes, PIECE_R), 64 * PIECE_WAVES, 0, st>>>(G, ncp, ctx->gcount, ctx->grec);

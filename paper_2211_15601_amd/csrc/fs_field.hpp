@@ -175,6 +175,15 @@ __device__ __forceinline__ void jacobian_from_corners(const GridP &G, const Cell
     }
 }
 
+__device__ __forceinline__ void field_dJ(const float *__restrict__ Tp, const GridP &G, const float x[3], float d[3], float J[9])
+{
+    const Cell c = locate(G, x);
+    float q[8][12];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) load12(Tp + c.base + corner_off(G, k), q[k]);
+    jacobian_from_corners(G, c, q, x, d, J);
+}
+
 // 1 / a from the reciprocal instruction and one Newton step: the bits of the division wherever the result is a normal
 // number, which is for the caller to test (every float compared: fs_microbench kind FS_MB_RECIP).
 __device__ __forceinline__ float recip(float a)

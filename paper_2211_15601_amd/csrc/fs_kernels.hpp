@@ -288,8 +288,8 @@ __device__ __forceinline__ bool prepare_jacobian(const float *__restrict__ Tcell
 // field_dJ without the corners of weight zero, whose records contribute nothing (the derivative of their weight vanishes along the
 // clamped axis by definition and carries the zero factor along the others): zeros in their place, and if an entry of the blend or of
 // the Jacobian comes out as an exact zero, again with all eight.  may_skip: the grid's entries are below SKIP_MAX.
-// Bound: the gathers.  (k_init_bone on 30 k points x 17 bones, 32x32x8 nodes, with all eight: a step 229 us, now 221; exact backward of 20 k
-// points x 24 201.6 -> 200.5.)
+// Bound: the gathers.  (fs_init, us, all eight / these: 30 k points x 17 bones on 32x32x8 nodes 27 / 20, 65 k x 24 on 64x64x16 85 / 50, 20 k x 24 on
+// 128x128x32 48 / 32.)
 __device__ __forceinline__ void field_dJ_clamped(const float *__restrict__ Tp, const GridP &G, const Cell &c, bool may_skip, const float (&x)[3],
                                                  float (&d)[3], float (&J)[9])
 {
@@ -2532,13 +2532,15 @@ constexpr int GREC = 8;           // floats per record
 // FROM_REC: roots, masks, J~ and positions are taken from the result records the last solve left in the
 // context (one contiguous 64-byte record per pair) instead of the caller's arrays; when that solve drew its
 // pairs from the candidate list, only the first cand_cnt[n] lanes of point n have a record.
-// EXACT: lambda from the inverse of the exact Jacobian at x* (mode != 0) instead of J~; a kernel of its own so that
-// the J~ path does not carry the registers of a field evaluation (117 -> what the compiler reports now).
+// JAC: lambda from J~, or (mode != 0) from the inverse of the exact Jacobian at x*, in one of three forms with the same bits; kernels of
+// their own so that the J~ path does not carry the registers of a field evaluation.  The forms: all corners at once (112 and 120 registers, four
+// waves per SIMD), in two halves of z-pairs (152 and 164, three), in halves and without corners of weight zero (171 and 182, two).
 // REC_DEPTH (with FROM_REC and the J~ gradient only): lanes of a point in flight together, see below; 1 = one by one.
 // Measured: depth 3 takes k_grad_records from 425 to 376 us on the 8-pose batch (one thread per point) and from 41 to
 // 52 us on the SMPL-scale batch (8 threads per point, 5 instead of 8 waves per SIMD), hence a choice per launch.
-template <bool FROM_REC, bool EXACT, int REC_DEPTH = 1>
-__global__ __launch_bounds__(256) void k_grad_records(GridP G, const float *__restrict__ T,
+enum { JAC_BROYDEN, JAC_CELL, JAC_HALVES, JAC_CLAMPED };
+template <bool FROM_REC, int JAC, int REC_DEPTH = 1>
+__global__ __launch_bounds__(256, JAC == JAC_CELL ? 4 : 1) void k_grad_records(GridP G, const float *__restrict__ T,
                                                       const float *__restrict__ xc, const float *__restrict__ Jinv,
                                                       const uint8_t *__restrict__ conv, const float *__restrict__ gxc,
                                                       const int32_t *__restrict__ pose, long long N, int K, int ncell,
@@ -2551,7 +2553,8 @@ __global__ __launch_bounds__(256) void k_grad_records(GridP G, const float *__re
     // consecutive threads of a group are consecutive points, so every load is coalesced
     __shared__ float s_gq[256 * 3];
     const int ppb = 256 / groups;                 // points per block
-    const bool may_skip = EXACT && may_skip_corners(state);
+    constexpr bool EXACT = JAC != JAC_BROYDEN;
+    const bool may_skip = JAC == JAC_CLAMPED && may_skip_corners(state);
     const int g = threadIdx.x / ppb, i = threadIdx.x - g * ppb;
     const long long n = (long long)blockIdx.x * ppb + i;
     float gq[3] = {0.0f, 0.0f, 0.0f};
@@ -2641,10 +2644,16 @@ __global__ __launch_bounds__(256) void k_grad_records(GridP G, const float *__re
 #pragma unroll
             for (int r = 0; r < 3; ++r) gx[r] = gxc[((long long)k * 3 + r) * N + n];
             bool ok = true;
-            const Cell c = locate(G, x);
             if (EXACT) {
                 float d[3], J[9];
-                field_dJ_clamped(T + (long long)p * G.V * 12, G, c, may_skip, x, d, J);
+                const float *Tp = T + (long long)p * G.V * 12;
+                if constexpr (JAC == JAC_CELL) {
+                    field_dJ(Tp, G, x, d, J);
+                } else {
+                    const Cell c = locate(G, x);
+                    if constexpr (JAC == JAC_HALVES) (void)prepare_jacobian(Tp + c.base, G, c, 0xFF, x, d, J);
+                    else field_dJ_clamped(Tp, G, c, may_skip, x, d, J);
+                }
                 ok = inv3(J, M);
             }
             float lam[3] = {0.0f, 0.0f, 0.0f};
@@ -2655,6 +2664,7 @@ __global__ __launch_bounds__(256) void k_grad_records(GridP G, const float *__re
                     gq[r] -= lam[r];
                 }
             }
+            const Cell c = locate(G, x);
             const int cl = p * ncell + cell_linear(G, c);
             const long long slot = (long long)offset[cl] + pq;
             // positions that do not belong to these roots (a caller mixing arrays of different solves)

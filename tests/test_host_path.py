@@ -1,5 +1,6 @@
 """Host code of the library on a stub runtime (host_path.py): what it launches and what it answers when memory runs out."""
 import host_path
+import test_gpu_exact_backward as exact
 import test_gpu_large_kernels as large
 
 
@@ -164,4 +165,19 @@ h = ctx((16, 16, 4), init=VOXEL)
 assert precompute(h) == OK
 assert kernels(h, 100, 3, pose=None) in small and kernels(h, 100, 3, pose=None, xq=5) == ["k_solve", "k_solve_unpack"]
 L.fs_destroy(h)
+""", tmp_path)
+
+
+def test_exact_backward_takes_the_form_its_test_is_meant_for(tmp_path):
+    host_path.run(f"""
+p = Params(1e-5, 10.0, 50, 0, 1, 6, 5, 4, 3)
+for dims, voxel, P, n, form in {exact.CASES!r}:
+    p.init, K = (VOXEL, 3) if voxel else (BONE, 8)
+    h = ctx(dims, nb=8, P=P, init=p.init)
+    assert L.fs_set_params(h, ctypes.byref(p)) == OK and precompute(h) == OK and solve(h, n, K, slot=True) == OK
+    for slot in (True, False):
+        launched()
+        assert grad(h, n, K, slot=slot) == OK
+        assert f"k_grad_records<{{str(slot).lower()}},{{form}},1>" in [x.replace(" ", "") for x in names()], (dims, voxel, slot)
+    L.fs_destroy(h)
 """, tmp_path)
