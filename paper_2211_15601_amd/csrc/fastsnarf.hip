@@ -633,10 +633,17 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     // more lose 3 ... 40 %); with candidates on grids beyond it at 24 (1.34 instead of 1.37 ms on the 8-pose batch; 48: 1.38)
     S.refill_min = ctx->refill_min ? ctx->refill_min : (lds ? 32 : (grid_bytes > (32u << 20) && !bone ? 24 : 8));
     S.prefetch = grid_bytes > (32u << 20);
-    // Tiles of points (tile_pair), but with positions on a grid beyond the L2 all states of a point side by side: there lanes share an atomic
-    // only with the same point's (steps, us, tiles / side by side: 120 k points in two poses of 128x128x32 nodes 1072 / 996, 60 k in one 532 / 510,
-    // 60 k in eight of 64x64x16 500 / 490).
-    S.point_major = !ctx->point_major ? 0 : (d_slot && grid_bytes > L2_BYTES ? 2 : 1);
+    // Order of the pairs: tiles of points (tile_pair) or all states of a point side by side.  On a grid beyond the L2 neighbouring lanes should read
+    // one point's surroundings: in tiles the lines fetched for a point are gone when its next states come.  That counts once many pairs meet
+    // a large grid; small batches gain more from the tiles' outputs, given states are read whole lines at a time in tiles, and with positions
+    // lanes share an atomic only with the same point's.  Whole calls, us, tiles / side by side, 24 states per point but where stated:
+    //   roots only  9.3 MB grid, 20 k points 153 / 159, 60 k 308 / 304, 200 k 838 / 803;  24 MB 20 k 183 / 187, 60 k 374 / 359, 200 k 1050 / 945, 60 k of 64
+    //               states 1122 / 900;  4.5 MB 60 k 284 / 290, 200 k 762 / 756;  25 MB in 8 poses, points in any order, 14 k 128 / 149, 200 k 1220 / 1088
+    //   positions   120 k points in two poses of 24 MB 1072 / 996;  24 MB 20 k 287 / 288, 60 k 563 / 542, 200 k 1490 / 1370
+    //   given       24 MB 20 k 353 / 376, 200 k 2049 / 2174
+    // The line of the first is pairs times bytes of the grid = 1.5e13 (60 k points of 24 states: 10 MB).
+    const bool beyond = grid_bytes > L2_BYTES;
+    S.point_major = !ctx->point_major ? 0 : (beyond && (d_slot || (fused && (double)S.total * (double)grid_bytes > 1.5e13)) ? 2 : 1);
     // Eighths of the chunks dealt out without asking the cursor.  Whole calls, us, with 0 / 4 / 6 / 7: one state per bone on 64x64x16 nodes, 200 k
     // points 732 / 709 / 723 / 739, 65 k points 411 / 397 / 399 / 406, 20 k points on 45x39x11 209 / 203 / 201 / 201; candidates, 2 M ray samples
     // 303 / 292 / 286 / 286.  On grids beyond the L2 all blocks should read the same stretch of the points: 8 poses of 128x128x32 nodes

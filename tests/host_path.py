@@ -37,9 +37,17 @@ class Params(ctypes.Structure):
     _fields_ = [("tol", ctypes.c_float), ("div", ctypes.c_float)] + [(n, ctypes.c_int32) for n in ("iters", "init", "grad", "cx", "cy", "cz", "ck")]
 
 
+class SolveP(ctypes.Structure):
+    """what a solve kernel with queues is told (fs_kernels.hpp)"""
+    _fields_ = [(n, ctypes.c_int64) for n in ("N", "total")] + [(n, ctypes.c_int32) for n in ("chunk", "refill_min", "max_iters")] + \
+               [(n, ctypes.c_float) for n in ("tol2", "div2")] + \
+               [(n, ctypes.c_int32) for n in ("K", "point_major", "ki", "spin_limit", "xcd_ranges", "dealt", "prefetch")]
+
+
 if "FS_HOST_STUB" in os.environ:
     S = ctypes.CDLL(os.environ["FS_HOST_STUB"], mode=ctypes.RTLD_GLOBAL)
     S.stub_launch.restype = ctypes.c_char_p
+    S.stub_solve_params.restype = ctypes.c_void_p
     L = ctypes.CDLL(LIB)
     L.fs_last_error.restype = ctypes.c_char_p
 
@@ -82,6 +90,14 @@ def launched():
         out.append((m.group(1), tuple(shape[:3]), tuple(shape[3:6]), shape[6]))
     S.stub_clear_launches()
     return out
+
+
+def solve_params():
+    """of the one solve kernel with queues launched since the last call"""
+    at = [S.stub_solve_params(i) for i in range(S.stub_launches())]
+    (p,) = [SolveP.from_buffer_copy(ctypes.string_at(a, 64)) for a in at if any(ctypes.string_at(a, 64))]
+    S.stub_clear_launches()
+    return p
 
 
 def names():

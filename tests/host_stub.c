@@ -12,7 +12,7 @@
 
 static struct { const void *host; const char *name; } names[MAX_NAMES];
 static int n_names;
-static struct { const char *name; unsigned grid[3], block[3]; size_t shared; } launches[MAX_LAUNCHES];
+static struct { const char *name; unsigned grid[3], block[3]; size_t shared; char solve[64]; } launches[MAX_LAUNCHES];
 static int n_launches;
 static struct { char *at; size_t bytes; } blocks[MAX_BLOCKS];
 static int n_blocks, bad_frees, fail_in = -1, fail_launch_in = -1, memsets, n_cus = 256, occupancy = 3;
@@ -35,6 +35,8 @@ const char *stub_launch(int i, unsigned *shape)        /* shape: grid x, y, z, b
     shape[6] = (unsigned)launches[i].shared;
     return launches[i].name;
 }
+
+const void *stub_solve_params(int i) { return launches[i].solve; }      /* the SolveP (64 bytes) that a solve kernel was given */
 
 /* ---- the runtime ---- */
 hipError_t hipMalloc(void **p, size_t n)
@@ -119,12 +121,14 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hi
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t shared, hipStream_t stream)
 {
     int i;
-    (void)args; (void)stream;
+    (void)stream;
     if (fail_launch_in >= 0 && fail_launch_in-- == 0) return last_error = hipErrorLaunchFailure;
     if (n_launches == MAX_LAUNCHES) abort();
     launches[n_launches].name = "?";
     for (i = 0; i < n_names; ++i)
         if (names[i].host == f) launches[n_launches].name = names[i].name;
+    memset(launches[n_launches].solve, 0, 64);
+    if (strstr(launches[n_launches].name, "k_solve_ws") || strstr(launches[n_launches].name, "k_solveI")) memcpy(launches[n_launches].solve, args[1], 64);
     launches[n_launches].grid[0] = grid.x; launches[n_launches].grid[1] = grid.y; launches[n_launches].grid[2] = grid.z;
     launches[n_launches].block[0] = block.x; launches[n_launches].block[1] = block.y; launches[n_launches].block[2] = block.z;
     launches[n_launches++].shared = shared;

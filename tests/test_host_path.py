@@ -1,6 +1,7 @@
 """Host code of the library on a stub runtime (host_path.py): what it launches and what it answers when memory runs out."""
 import host_path
 import test_gpu_exact_backward as exact
+import test_gpu_large_grids as large_grids
 import test_gpu_large_kernels as large
 
 
@@ -179,5 +180,29 @@ for dims, voxel, P, n, form in {exact.CASES!r}:
         launched()
         assert grad(h, n, K, slot=slot) == OK
         assert f"k_grad_records<{{str(slot).lower()}},{{form}},1>" in [x.replace(" ", "") for x in names()], (dims, voxel, slot)
+    L.fs_destroy(h)
+""", tmp_path)
+
+
+def test_pairs_on_grids_beyond_the_l2_are_handed_out_point_by_point(tmp_path):
+    # In tiles of eight points the lines fetched for a point are gone when its next states come: a large batch on a large grid
+    # (200 k points of 24 states on 128x128x32 nodes, 64 states, poses in any order) took 5 to 20 % longer.
+    host_path.run(f"""
+TILES, BY_POINT = 1, 2
+def order(h, n, K, **kw):
+    S.stub_clear_launches()
+    assert solve(h, n, K, **kw) == OK
+    return solve_params().point_major
+
+for dims, P, nb, n, roots_only, positions in {large_grids.CASES!r}:
+    h = ctx(dims, nb=nb, P=P)
+    assert precompute(h) == OK
+    assert (order(h, n, nb), order(h, n, nb, slot=True)) == (roots_only, positions), dims
+    assert order(h, n, nb, fused=False, J=True) == TILES
+    L.fs_destroy(h)
+for dims, P, nb, n, expected in (((64, 64, 16), 1, 24, 1000000, TILES), ((128, 128, 32), 1, 24, 19000, TILES), ((128, 128, 32), 1, 24, 200000, BY_POINT),
+                                 ((64, 64, 16), 8, 24, 60000, BY_POINT), ((61, 47, 13), 4, 24, 40003, TILES), ((80, 80, 20), 1, 64, 60000, BY_POINT)):
+    h = ctx(dims, nb=nb, P=P)
+    assert precompute(h) == OK and order(h, n, nb) == expected, (dims, n)
     L.fs_destroy(h)
 """, tmp_path)
