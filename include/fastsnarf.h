@@ -86,14 +86,15 @@ fs_status fs_set_params(fs_ctx *ctx, const fs_params *params);
 
 /* Launch-shape knobs of the solve kernel for large batches; results never depend on them.  (Small batches, of up to 768 pairs
  * per compute unit, or 1152 where the kernel looks voxel-based candidates up, run in kernels that have no queue and ask
- * lds_grid only.)  chunk = lanes a wave draws
- * from the work cursor at a time (8..4096; every draw is one atomic on a single counter, which serves about
- * 1e8 of them per second, so small chunks make the counter the bottleneck), refill_min = idle SIMD lanes that trigger a refill
- * (1..64; until it is set: 8, 24 for grids of more than 32 MiB, 32 for a grid held in LDS),
- * blocks_per_cu = resident 256-thread blocks per compute unit (capped by what the occupancy
- * query reports; until it is set the library takes 2, or 3 where it holds the grid in LDS); for these a value of 0
- * keeps the current setting.  point_major = 1: consecutive SIMD
- * lanes take the K initial states of one point, 0: consecutive points with the same initial state,
+ * lds_grid only.)  chunk = pairs that a wave takes from the batch at a time (8..4096).  Up to three quarters of the chunks are dealt out in
+ * rounds; each of the others is one atomic on a single counter, which serves about 1e8 of them per second, so small chunks make the
+ * counter the bottleneck.  refill_min = idle SIMD lanes that trigger a refill (1..64; until it is set: 32 for a grid held in LDS, 24 for
+ * voxel-based candidates on grids of more than 32 MiB, else 8), blocks_per_cu = resident 256-thread blocks per compute unit (capped by what the
+ * occupancy query reports; until it is set the library takes 3 where it holds the grid in LDS or the context has one state per bone and a
+ * grid of at most 4 MiB, else 2); for these a value of 0 keeps the current setting.  point_major: which pairs consecutive SIMD lanes take, 1: the
+ * K initial states of one point, 0: consecutive points with the same initial state; until it is set the library chooses, by batch and
+ * grid, between 1 and tiles of eight points, state by state.  (Where the kernel looks voxel-based candidates up, the order is that of
+ * fs_set_list_order.)
  * -1: keep.  lds_grid = 1: transform grids of at most 148 KiB (all poses; blocks of 4 waves up to 60 KiB, above that one block of 12 waves per CU) are copied into LDS by every
  * block of the solve and read from there (small batches: where a block has the waves for it), 0: always read through the caches, -1: keep. */
 fs_status fs_set_tuning(fs_ctx *ctx, int32_t chunk, int32_t refill_min, int32_t blocks_per_cu, int32_t point_major,

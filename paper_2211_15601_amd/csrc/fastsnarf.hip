@@ -412,7 +412,7 @@ fs_status fs_create(const fs_grid_desc *desc, const fs_params *params, void *hip
         c->occ_vx_blocks_per_cu = per_cu_vx;
         c->spin_limit = 1 << 22;   /* x about 0.2 us per poll */
         c->blocks_per_cu = 0;      /* 0: chosen per call */
-        c->point_major = 1;
+        c->point_major = -1;       /* -1: chosen per call */
         c->lds_grid = 1;
         c->sort_list = 0;
         c->xcd_ranges = 0;
@@ -643,7 +643,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     //   given       24 MB 20 k 353 / 376, 200 k 2049 / 2174
     // The line of the first is pairs times bytes of the grid = 1.5e13 (60 k points of 24 states: 10 MB).
     const bool beyond = grid_bytes > L2_BYTES;
-    S.point_major = !ctx->point_major ? 0 : (beyond && (d_slot || (fused && (double)S.total * (double)grid_bytes > 1.5e13)) ? 2 : 1);
+    S.point_major = ctx->point_major >= 0 ? 2 * ctx->point_major : (beyond && (d_slot || (fused && (double)S.total * (double)grid_bytes > 1.5e13)) ? 2 : 1);
     // Eighths of the chunks dealt out without asking the cursor.  Whole calls, us, with 0 / 4 / 6 / 7: one state per bone on 64x64x16 nodes, 200 k
     // points 732 / 709 / 723 / 739, 65 k points 411 / 397 / 399 / 406, 20 k points on 45x39x11 209 / 203 / 201 / 201; candidates, 2 M ray samples
     // 303 / 292 / 286 / 286.  On grids beyond the L2 all blocks should read the same stretch of the points: 8 poses of 128x128x32 nodes

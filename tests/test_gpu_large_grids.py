@@ -34,8 +34,13 @@ def test_bone_states_on_large_grids(gpu_lib, dims, P, nb, n, roots_only, positio
     np.testing.assert_array_equal(out[2].view(np.uint32), ref[2].view(np.uint32))
     slot = run.slot.cpu().numpy()
     assert ((slot >= 0) == (ref[1] == 1)).all()
-    # the positions are a place for every root: the sums with and without them agree
     gxc = w.upstream_grads()
-    for name, a, b in zip(("gW", "gB", "gxq"), run.grad(out[0], None, out[1], gxc, slot=run.slot), run.grad(out[0], out[2], out[1], gxc)):
+    with_positions = run.grad(out[0], None, out[1], gxc, slot=run.slot)
+    for point_major in (1, 0):           # on request, whatever the library would choose
+        run.ctx.set_tuning(point_major=point_major)
+        for a, b in zip(run.solve(fused=True), ref):
+            np.testing.assert_array_equal(a.view(np.uint8), b.view(np.uint8))
+    # the positions are a place for every root: the sums with and without them agree
+    for name, a, b in zip(("gW", "gB", "gxq"), with_positions, run.grad(out[0], out[2], out[1], gxc)):
         gu.assert_grad_close(name, a, b, f"{dims} P={P}")
     run.ctx.close()

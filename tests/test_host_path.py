@@ -206,3 +206,24 @@ for dims, P, nb, n, expected in (((64, 64, 16), 1, 24, 1000000, TILES), ((128, 1
     assert precompute(h) == OK and order(h, n, nb) == expected, (dims, n)
     L.fs_destroy(h)
 """, tmp_path)
+
+
+def test_an_order_that_is_asked_for_is_taken(tmp_path):
+    host_path.run("""
+def order(h, n, K, **kw):
+    S.stub_clear_launches()
+    assert solve(h, n, K, **kw) == OK
+    return solve_params().point_major
+
+calls = [dict(), dict(slot=True), dict(fused=False, J=True)]
+for dims, n in (((16, 16, 4), 20000), ((64, 64, 16), 20000), ((128, 128, 32), 20000), ((128, 128, 32), 200000)):
+    h = ctx(dims)
+    assert precompute(h) == OK
+    chosen = [order(h, n, 24, **kw) for kw in calls]
+    assert set(chosen) <= {1, 2}
+    assert L.fs_set_tuning(h, 0, 0, 0, 1, -1) == OK and [order(h, n, 24, **kw) for kw in calls] == [2, 2, 2]       # all states of a point
+    assert L.fs_set_tuning(h, 0, 0, 0, 0, -1) == OK and [order(h, n, 24, **kw) for kw in calls] == [0, 0, 0]
+    assert L.fs_set_tuning(h, 128, 0, 0, -1, -1) == OK and order(h, n, 24) == 0
+    assert L.fs_set_tuning(h, 0, 0, 0, 2, -1) == E_ARG and L.fs_set_tuning(h, 0, 0, 0, -2, -1) == E_ARG
+    L.fs_destroy(h)
+""", tmp_path)
