@@ -608,6 +608,8 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     S.tol2 = ctx->prm.tol * ctx->prm.tol;
     S.div2 = ctx->prm.div_thresh * ctx->prm.div_thresh;
     S.K = K;
+    S.mag_N = div_magic((unsigned)N);
+    S.mag_K = div_magic((unsigned)K);
     S.chunk = ctx->chunk;
     S.spin_limit = ctx->spin_limit;
     const long long chunks = (S.total + S.chunk - 1) / S.chunk;

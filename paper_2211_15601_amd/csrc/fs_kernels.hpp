@@ -784,6 +784,7 @@ struct SolveP {
     int xcd_ranges;      // producer / consumer kernel: the list is cut into 8 ranges, one per XCD, each with its own cursor
     int dealt;           // eighths of the chunks that are dealt out without the cursor (Chunks)
     int prefetch;        // producer / consumer kernel: consumers ask for the next cell's records at the end of a pass
+    unsigned mag_N, mag_K;      // div_magic of N and K
 };
 
 // What the fused variant needs to compute initial states itself (same arithmetic as k_init_*).
@@ -1835,10 +1836,13 @@ __device__ __forceinline__ bool lane_step(const GridP &G, const SolveP &S, const
 // states of one point often reach the same root and share its records and its atomic.  (Kernel us with all states of a point side by side / tiles of
 // 8 / 16 / 64 points: 200 k points 711 / 684 / 687 / 685, 20 k points on 45x39x11 nodes 142 / 135 / 135 / 140, 65 k points with positions
 // 313 / 313 / 317 / 339.)
+// Quotients by div_by: the reciprocals that a division in plain C makes of S.K, S.N and the tile's size stay in vector registers
+// through the producer's loop, and with one state per bone three of them were spilled.
 constexpr unsigned TILE_PTS = 8;
-__device__ __forceinline__ void tile_pair(unsigned i, unsigned N, unsigned K, int &n, int &k)
+__device__ __forceinline__ void tile_pair(const SolveP &S, unsigned i, int &n, int &k)
 {
-    const unsigned t = i / (TILE_PTS * K), r = i - t * (TILE_PTS * K), pts = min(TILE_PTS, N - t * TILE_PTS);     // the last tile may be short
+    const unsigned N = (unsigned)S.N, K = (unsigned)S.K;
+    const unsigned t = div_by(i, K, S.mag_K) / TILE_PTS, r = i - t * (TILE_PTS * K), pts = min(TILE_PTS, N - t * TILE_PTS);     // the last tile may be short
     const unsigned kk = pts == TILE_PTS ? r / TILE_PTS : r / pts;
     k = (int)kk;
     n = (int)(t * TILE_PTS + r - kk * pts);
@@ -1940,12 +1944,12 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                     nk = e.y & 7;
                     gcell = e.y >> 3;
                 } else if (S.point_major == 1) {
-                    tile_pair(upq, (unsigned)N, (unsigned)S.K, nn, nk);
+                    tile_pair(S, upq, nn, nk);
                 } else if (S.point_major) {   // consecutive SIMD lanes: the K initial states of one point
-                    nn = (int)(upq / (unsigned)S.K);
+                    nn = (int)div_by(upq, (unsigned)S.K, S.mag_K);
                     nk = (int)(upq - (unsigned)nn * (unsigned)S.K);
                 } else {                      // consecutive SIMD lanes: consecutive points, same initial state
-                    nk = (int)(upq / (unsigned)N);
+                    nk = (int)div_by(upq, (unsigned)N, S.mag_N);
                     nn = (int)(upq - (unsigned)nk * (unsigned)N);
                 }
                 np = pose_of(pose, nn, G.P);
