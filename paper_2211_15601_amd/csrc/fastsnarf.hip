@@ -646,11 +646,14 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     // The line of the first is pairs times bytes of the grid = 1.5e13 (60 k points of 24 states: 10 MB).
     const bool beyond = grid_bytes > L2_BYTES;
     S.point_major = ctx->point_major >= 0 ? 2 * ctx->point_major : (beyond && (d_slot || (fused && (double)S.total * (double)grid_bytes > 1.5e13)) ? 2 : 1);
-    // Eighths of the chunks dealt out without asking the cursor.  Whole calls, us, with 0 / 4 / 6 / 7: one state per bone on 64x64x16 nodes, 200 k
-    // points 732 / 709 / 723 / 739, 65 k points 411 / 397 / 399 / 406, 20 k points on 45x39x11 209 / 203 / 201 / 201; candidates, 2 M ray samples
-    // 303 / 292 / 286 / 286.  On grids beyond the L2 all blocks should read the same stretch of the points: 8 poses of 128x128x32 nodes
-    // 2438 / 2447 / 2460 / 2488.
-    S.dealt = S.prefetch ? 0 : (bone ? 4 : 6);
+    // Eighths of the chunks dealt out without asking the cursor.  Whole calls, us, with 0 / 4 / 6 / 7:
+    //   one state per bone, read through the caches: 64x64x16 nodes, 200 k points 732 / 709 / 723 / 739, 65 k 411 / 397 / 399 / 406, 20 k on 45x39x11 209 / 203 /
+    //   201 / 201;  24 MB, 0 and 4 alone, 200 k 942 / 945, 60 k 358 / 356
+    //   grid in LDS, 0 / 4 / 6: 34 KiB, 20 k 119 / 119 / 119, 60 k 221 / 221 / 203, 200 k 543 / 478 / 448;  135 KiB, 60 k 219 / 220 / 204
+    //   candidates: 64x64x16 nodes, 2 M ray samples 303 / 292 / 286 / 286;  0 / 4 / 6: 11 MB, 2 M ray samples 296 / 281 / 275, 1 M of scans 323 / 297 / 289, 25 MB in
+    //   8 poses 339 / 333 / 335;  given states, 0.3 M ray samples 248 / 233 / 224
+    // On grids beyond 32 MiB all blocks should read the same stretch of the points: 8 poses of 128x128x32 nodes 2438 / 2447 / 2460 / 2488.
+    S.dealt = S.prefetch ? 0 : (bone && !lds ? 4 : 6);
     const int blocks = (int)std::min<long long>(grid1d(chunks, wpb), (long long)per_cu * ctx->n_cus);
     InitP I;
     I.mode = ctx->prm.init_mode;

@@ -227,3 +227,20 @@ for dims, n in (((16, 16, 4), 20000), ((64, 64, 16), 20000), ((128, 128, 32), 20
     assert L.fs_set_tuning(h, 0, 0, 0, 2, -1) == E_ARG and L.fs_set_tuning(h, 0, 0, 0, -2, -1) == E_ARG
     L.fs_destroy(h)
 """, tmp_path)
+
+
+def test_share_of_the_chunks_that_is_dealt_out(tmp_path):
+    host_path.run("""
+def dealt(h, n, K, **kw):
+    S.stub_clear_launches()
+    assert solve(h, n, K, **kw) == OK
+    return solve_params().dealt
+
+for dims, P, init, expected in (((16, 16, 4), 1, BONE, 6), ((13, 15, 16), 1, BONE, 6), ((13, 15, 17), 1, BONE, 4), ((128, 128, 32), 1, BONE, 4), ((128, 128, 32), 2, BONE, 0),
+                                ((16, 16, 4), 1, VOXEL, 6), ((64, 64, 16), 1, VOXEL, 6), ((128, 128, 32), 1, VOXEL, 6), ((128, 128, 32), 2, VOXEL, 0)):
+    h, K = ctx(dims, P=P, init=init), 24 if init == BONE else 3
+    assert precompute(h) == OK
+    for kw in (dict(), dict(slot=True), dict(fused=False, J=True)):
+        assert dealt(h, 400000 // K + 100000 * (init == VOXEL), K, **kw) == expected, (dims, P, init, kw)
+    L.fs_destroy(h)
+""", tmp_path)
