@@ -625,8 +625,8 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const int wpb = lds_big ? FS_LDS_BIG_WAVES : (lds ? 4 : 1);       // waves of a block that draw chunks from the cursor
     const bool bone = ctx->prm.init_mode == FS_INIT_BONE;
     // A third block per CU hides latency on a grid that the L2 of an XCD holds, and thrashes it on a larger one.  States per bone, 200 k points, two /
-    // three blocks, kernel us: 0.4 MB grid 577 / 548, 3.0 MB 602 / 584, 4.3 MB 682 / 684, 10 MB 760 / 792, 24 MB 935 / 1032.  Candidates are
-    // slower with three (whole call on 1 M ray samples 150 / 155).
+    // three blocks, kernel us: 0.4 MB grid 577 / 548, 3.0 MB 602 / 584, 4.3 MB 682 / 684, 10 MB 760 / 792, 24 MB 935 / 1032.  Candidates without J~ are
+    // slower with three (whole call on 1 M ray samples 150 / 155); with J~ their queues of 128 records (69 KiB of LDS) leave room for two.
     const int auto_blocks = lds || (bone && grid_bytes <= L2_BYTES) ? 3 : 2;
     const int want_blocks = ctx->blocks_per_cu ? (lds ? std::max(ctx->blocks_per_cu, 3) : ctx->blocks_per_cu) : auto_blocks;
     const int occ = lds ? ctx->occ_blocks_per_cu : (vx ? ctx->occ_vx_blocks_per_cu : ctx->occ_ws_blocks_per_cu);

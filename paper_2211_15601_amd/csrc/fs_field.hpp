@@ -43,8 +43,8 @@ struct Cell {
 
 __device__ __forceinline__ void locate_axis(float x, float lo, float inv_h, float m, int n, int &i0, float &f, bool &cl)
 {
-    // the median of (u, 0, m) is both clamps in one instruction, NaN to 0 included (where the product underflows to -0, it may be 0: a weight 0
-    // of either sign)
+    // the median of (u, 0, m) is both clamps in one instruction, NaN to 0 included (where u is -0, from x = -0 on a face at 0 or a product
+    // that underflows, it may be 0: a weight 0 of either sign)
     const float u = (x - lo) * inv_h, in = __builtin_amdgcn_fmed3f(u, 0.0f, m);
     cl = !(u == in);                    // also true for NaN
     const int i = (int)__builtin_floorf(in);

@@ -235,8 +235,8 @@ __device__ __forceinline__ int corners_needed(const Cell &c)
 
 // Jacobian (and field) of a fresh pair from the corners in `need` (zeros in place of the others): the arithmetic of
 // jacobian_from_corners, but the corners are fetched in two halves, the z-pairs of one x, y side and then of the other: with all eight
-// records in registers the producer, not the consumers, would decide how many waves a SIMD holds (176 registers, now 160).  Returns whether an
-// entry of the blend or of the Jacobian is an exact zero.
+// records in registers the producer of k_solve_ws, not its consumers, would decide how many waves a SIMD holds (197 registers with J~ and 179
+// without, where three waves leave 168 to each).  Returns whether an entry of the blend or of the Jacobian is an exact zero.
 __device__ __forceinline__ bool prepare_jacobian(const float *__restrict__ Tcell, const GridP &G, const Cell &c, int need, const float (&x)[3],
                                                  float (&d)[3], float (&J)[9])
 {
@@ -1649,7 +1649,7 @@ __device__ __forceinline__ void lds_store_release(int *p, int v)
 // A lane that finishes does not store its 64-byte record itself (four 16-byte stores to an address of its own: four
 // vector-memory instructions in nearly every pass of the wave, each of which reaches memory as a partial write of a
 // 32-byte sector).  The wave parks finished records in LDS, OUT_PEND per wave, together with the place of the
-// converged ones; when OUT_PEND - 15 have gathered it asks for their positions in their cells' lists (one atomic per cell
+// converged ones; when OUT_PEND - 16 have gathered it asks for their positions in their cells' lists (one atomic per cell
 // and round of 64, as flush_slots does), puts each position into its record, and writes the records out with four
 // consecutive lanes per record: every record reaches memory once, whole, as 64 contiguous bytes.
 // Without J~ a record is 16 bytes; those of eight neighbouring points in one state are one line.  (Stored by each lane as it finished: 200 k points
@@ -1792,8 +1792,8 @@ __device__ __forceinline__ bool blend_apply_z(const Cell &c, const float (&q)[8]
     return m == 0.0f;
 }
 
-// One Broyden step of one pair per lane: the step, the field at the new x, the update of J~, the test.  q, held, held_mask: the corner records the lane holds, their cell's base inside the pose's grid (-1: none) and
-// with SKIP which of them.  True: the pair has ended.
+// One Broyden step of one pair per lane: the step, the field at the new x, the update of J~, the test.  q, held, held_mask: the corner records the
+// lane holds, their cell's base inside the pose's grid (-1: none) and with SKIP which of them.  True: the pair has ended.
 template <bool SKIP>
 __device__ __forceinline__ bool lane_step(const GridP &G, const SolveP &S, const float *__restrict__ Tp, bool may_skip,
                                           const float (&xp)[3], float (&x)[3], float (&g)[3], float (&J)[9], int &it,
@@ -1861,7 +1861,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
     __shared__ float s_ring[NCONS][ST_FIELDS][WS_RING];
     __shared__ int s_tail[NCONS], s_head[NCONS], s_done;
     constexpr int OUT_PEND = SKIP ? 64 : 128;        // 64: 50 KiB of LDS, so that a CU holds three blocks
-    __shared__ OutQ<OUT_PEND, WITH_J> s_out[NCONS + 1];      // records on their way out, per wave (only full records are parked)
+    __shared__ OutQ<OUT_PEND, WITH_J> s_out[NCONS + 1];      // records on their way out, per wave
     if (threadIdx.x < NCONS) {
         s_tail[threadIdx.x] = 0;
         s_head[threadIdx.x] = 0;

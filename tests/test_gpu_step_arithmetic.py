@@ -49,7 +49,7 @@ def test_denominators_beyond_the_normal_numbers(gpu_lib, dims, n):
 
 @pytest.mark.parametrize("nb,n", [(1, ONCE + 3), (5, ONCE // 5 + 2), (17, ONCE // 17 + 9), (24, ONCE // 24 + 7)])
 def test_points_on_the_faces_and_tiles_of_pairs_that_end_short(gpu_lib, nb, n):
-    # pairs are handed out in tiles of eight points; the last tile here has 3, 6, 6 and 7
+    # pairs are handed out in tiles of eight points; the last tile here has 3, 3, 6 and 7
     s = wl.random_affine_scene(70 + nb, dims=CACHED, n_bones=nb, n_points=n, max_deg=0.0)
     x = s["x"].copy()
     B = s["B"].copy()
