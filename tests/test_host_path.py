@@ -244,3 +244,20 @@ for dims, P, init, expected in (((16, 16, 4), 1, BONE, 6), ((13, 15, 16), 1, BON
         assert dealt(h, 400000 // K + 100000 * (init == VOXEL), K, **kw) == expected, (dims, P, init, kw)
     L.fs_destroy(h)
 """, tmp_path)
+
+
+def test_settings_until_they_are_set_are_those_the_header_states(tmp_path):
+    host_path.run("""
+for dims, P, init, refill, blocks in (((16, 16, 4), 1, BONE, 32, 3), ((16, 16, 4), 1, VOXEL, 32, 3), ((64, 64, 16), 1, BONE, 8, 3), ((64, 64, 16), 1, VOXEL, 8, 2),
+                                      ((72, 72, 18), 1, BONE, 8, 2), ((128, 128, 32), 1, VOXEL, 8, 2), ((128, 128, 32), 2, BONE, 8, 2), ((128, 128, 32), 2, VOXEL, 24, 2)):
+    h, K = ctx(dims, P=P, init=init), 24 if init == BONE else 3
+    assert precompute(h) == OK
+    for kw in (dict(), dict(slot=True), dict(fused=False, J=True)):
+        S.stub_clear_launches()
+        assert solve(h, 12000000 // K, K, **kw) == OK
+        shape, at = (ctypes.c_uint * 7)(), [i for i in range(S.stub_launches()) if any(ctypes.string_at(S.stub_solve_params(i), 64))]
+        S.stub_launch(at[0], shape)
+        assert len(at) == 1 and shape[0] == blocks * 256, (dims, init, kw, shape[0])
+        assert solve_params().refill_min == refill, (dims, init, kw)
+    L.fs_destroy(h)
+""", tmp_path)
