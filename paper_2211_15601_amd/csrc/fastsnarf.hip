@@ -279,21 +279,22 @@ fs_status need_solve_counts(fs_ctx *c, int ncell)
 }
 
 // Kernels of the solve by the size of a batch (pairs = K * N; all three give the same bits).  What bounds a small batch is
-// max_iters times the latency of a step, and a step is half as long with four lanes per pair (0.5 to 0.6 instead of 1.0 to 1.2 us);
+// max_iters times the latency of a step, which is the shorter the more lanes share a pair (16 lanes 0.35 us, 4 0.5, one 1.0 to 1.2);
 // what bounds a large one is instruction issue and the vector cache, where one lane per pair and refilled waves win.
-// Measured, solve and dedupe, us, k_solve_quad / k_solve_once / k_solve_ws, 24 states per point on a 64x64x16 grid: 24 k pairs 49 / 54 / 58;
-// 48 k 54 / 55 / 62; 98 k 78 / 58 / 69; 197 k 103 / 79 / 88; 240 k 116 / 100 / 94; 288 k 126 / 110 / 102.  The lines are where
+// Measured, solve and dedupe, us, k_solve_quad / k_solve_once / k_solve_ws, 24 states per point on a 64x64x16 grid: 36 k pairs 39 / 43; 50 k 45 / 44;
+// 72 k 54 / 50; 98 k 57 / 51; 120 k 65 / 53; 192 k 84 / 65; 228 k - / 85 / 99.  The lines are where
 // the chip is full: three quad waves per SIMD; all pairs of k_solve_once resident at once (3 waves per SIMD of 64).
+// With positions a wave takes several states of a point (pair_of), those of a point without a root all run to the last step, and
+// k_solve_once keeps them in single lanes for longer; a step of training, 64x64x16, quad / once: 50 k pairs 92 / 102, 96 k 113 / 117, 156 k 133 / 133,
+// 192 k 144 / 135.  On a grid in LDS a step in single lanes is shorter: 16x16x4, 50 k pairs 78 / 73.
 // With voxel-based candidates the share of pairs that have one is not known here (rays 1/7, scans 6/10), k_solve_ws needs
-// its list of them first and most quads of a sparse batch end at once: rays, 72 k pairs 29 (quad) / 32 (once), 192 k 34 / 35;
-// scans, 72 k 37 / 37, 192 k 56 / 39.  The upper line there, 4.5 waves per SIMD of which 3 are resident, is a compromise, k_solve_once / k_solve_ws
-// on 64x64x16 and 128x128x32 nodes: rays, 192 k pairs 35 / 71, 42 / 81, 294 k 39 / 71, 47 / 90, 600 k 48 / 77, 64 / 100; scans, 192 k 39 / 50, 53 / 61,
-// 294 k 60 / 57, 78 / 69, 600 k 89 / 70, 120 / 89.
-// Scans would gain 6 to 12 % from a line at 210 k to 270 k pairs, rays would lose 45 %.
+// its list of them first and most quads of a sparse batch end at once: rays, 72 k pairs 25 (quad) / 31 (once), 150 k 27 / 33, 285 k 40 / 37;
+// scans, 72 k 38 / 35, 105 k 46 / 38, 210 k 61 / 48.  The upper line there, 4.5 waves per SIMD of which 3 are resident, is a compromise, k_solve_once / k_solve_ws
+// on 64x64x16 nodes: rays, 300 k pairs 40 / 66, 600 k 54 / 73; scans, 300 k 63 / 68, 390 k 72 / 71, 600 k 99 / 82.
 enum { SOLVE_QUAD, SOLVE_ONCE, SOLVE_LARGE };
-int solve_kind(const fs_ctx *c, long long pairs, bool candidates)
+int solve_kind(const fs_ctx *c, long long pairs, bool candidates, bool positions, bool lds)
 {
-    const long long quad = (candidates ? 320 : 192) * (long long)c->n_cus, once = (candidates ? 1152 : 768) * (long long)c->n_cus;
+    const long long quad = (candidates ? 320 : (positions && !lds ? 512 : 192)) * (long long)c->n_cus, once = (candidates ? 1152 : 768) * (long long)c->n_cus;
     return pairs <= quad ? SOLVE_QUAD : (pairs <= once ? SOLVE_ONCE : SOLVE_LARGE);
 }
 
@@ -682,7 +683,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         for (const auto &i : in)
             for (const auto &o : out) in_place = in_place || overlap(i.first, i.second, o.first, o.second);
     }
-    const int kind = sorted || in_place ? SOLVE_LARGE : solve_kind(ctx, S.total, voxel_list);
+    const int kind = sorted || in_place ? SOLVE_LARGE : solve_kind(ctx, S.total, voxel_list, d_slot != nullptr, lds);
     const bool quad = kind == SOLVE_QUAD;
     const size_t need = kind != SOLVE_LARGE ? (d_slot ? (size_t)S.total * 4 : 0) : (size_t)S.total * (with_J ? 4 : 1);
     ctx->slots_N = 0;            // from here on the records of the solve before are lost, also when this call fails
@@ -708,12 +709,24 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         hipEvent_t ev0 = nullptr, ev1 = nullptr;
         if (ctx->timing && hipEventCreate(&ev0) == hipSuccess && hipEventCreate(&ev1) == hipSuccess) (void)hipEventRecord(ev0, st);
         // grid in LDS: about one block per CU, as many waves in it as the batch gives it; else blocks of four waves
-        S.ki = d_slot && K >= 8 ? 8 : 1;
-        const int pts = (quad ? QUADS : WAVE) / S.ki;          // points per wave
-        const long long waves = ((N + pts - 1) / pts) * ((K + S.ki - 1) / S.ki);
-        const int most = quad ? 16 : FS_LDS_BIG_WAVES;
-        const int per_block = (int)std::min<long long>(most, std::max<long long>(1, (waves + ctx->n_cus - 1) / ctx->n_cus));
+        long long waves = 0;
+        int per_block = 0;
+        auto split = [&](int per) {            // into waves of `per` pairs
+            S.per = per;
+            S.ki = d_slot && K >= 8 ? std::min(8, per) : 1;
+            const int pts = per / S.ki;        // points per wave
+            waves = ((N + pts - 1) / pts) * ((K + S.ki - 1) / S.ki);
+            per_block = (int)std::min<long long>(quad ? 16 : FS_LDS_BIG_WAVES, std::max<long long>(1, (waves + ctx->n_cus - 1) / ctx->n_cus));
+        };
+        split(quad ? QUADS : WAVE);
         const bool staged = lds && small_in_lds(ctx, grid_bytes, per_block);
+        // Waves of four pairs, which take rows of 16 lanes at once: while there is one of them per SIMD, three where pairs wait for each other otherwise
+        // (candidates: most have none; positions: states of one point).  Whole calls, us, 16 pairs / 4: 24 states, roots only, 0.9 k pairs
+        // 30 / 29, 4.8 k 32 / 33, 12 k 32 / 35;  a step 2.4 k 79 / 71, 8 k 83 / 78, 12 k 66 / 62, 19 k 65 / 71;  ray samples 4.5 k 23 / 21, 13 k 22.7 / 20.6, 27 k 23.3 / 23.1,
+        // scans 9 k 29.7 / 30.4, 18 k 30 / 33.
+        // (Where the copy of the grid is dear, blocks keep the number of waves that small_in_lds was asked about.)
+        const bool many = voxel_list ? !staged : (d_slot && !(staged && lds_big));
+        if (quad && S.total <= (many ? 48ll : 16ll) * ctx->n_cus) split(HEXES);
         const int threads = staged ? WAVE * per_block : 256;
         const dim3 qg(grid1d(waves * 64, threads));
         const int *state = reinterpret_cast<const int *>(ctx->cursor + CUR_GRID);

@@ -47,7 +47,7 @@ __device__ __forceinline__ void locate_axis(float x, float lo, float inv_h, floa
     // that underflows, it may be 0: a weight 0 of either sign)
     const float u = (x - lo) * inv_h, in = __builtin_amdgcn_fmed3f(u, 0.0f, m);
     cl = !(u == in);                    // also true for NaN
-    const int i = (int)__builtin_floorf(in);
+    const int i = (int)in;              // in >= 0: its floor
     i0 = i > n - 2 ? n - 2 : i;
     f = in - (float)i0;
 }

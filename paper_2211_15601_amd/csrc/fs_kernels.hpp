@@ -785,6 +785,7 @@ struct SolveP {
     int dealt;           // eighths of the chunks that are dealt out without the cursor (Chunks)
     int prefetch;        // producer / consumer kernel: consumers ask for the next cell's records at the end of a pass
     unsigned mag_N, mag_K;      // div_magic of N and K
+    int per;             // k_solve_quad: pairs per wave, QUADS or HEXES
 };
 
 // What the fused variant needs to compute initial states itself (same arithmetic as k_init_*).
@@ -1235,37 +1236,142 @@ __device__ __forceinline__ int quad_get(int v)
 }
 __device__ __forceinline__ float pick3(int row, float a, float b, float c) { return row == 0 ? a : (row == 1 ? b : c); }
 
+// Chains of multiply-adds whose first factor comes from another lane.  The compiler gives a multiply that form and a multiply-add a
+// move of its own, hence the assembly.  A DPP operand may be read two wait states after it was written: every block begins with those, and what
+// a block returns is read by plain instructions or by another block.
+#define FS_QUAD(n) " quad_perm:[" #n "," #n "," #n "," #n "] row_mask:0xf bank_mask:0xf\n\t"
+#define FS_ROW(n) " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
+// fma(a of lane 2, b2, fma(a of lane 1, b1, a of lane 0 * b0)), lanes of the quad
+__device__ __forceinline__ float quad_dot(float a, float b0, float b1, float b2)
+{
+    float o;
+    asm("s_nop 1\n\t"
+        "v_mul_f32_dpp %0, %1, %2" FS_QUAD(0)
+        "v_fmac_f32_dpp %0, %1, %3" FS_QUAD(1)
+        "v_fmac_f32_dpp %0, %1, %4" FS_QUAD(2)
+        : "=&v"(o) : "v"(a), "v"(b0), "v"(b1), "v"(b2));
+    return o;
+}
+// a[i] = fma(s of lane i, v, a[i]), lanes of the quad
+__device__ __forceinline__ void quad_update(float s, float v, float (&a)[3])
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %3, %4" FS_QUAD(0)
+        "v_fmac_f32_dpp %1, %3, %4" FS_QUAD(1)
+        "v_fmac_f32_dpp %2, %3, %4" FS_QUAD(2)
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]) : "v"(s), "v"(v));
+}
+// a row of a transform applied to the point whose coordinates the quad's lanes hold: fma(T0, x0, fma(T1, x1, fma(T2, x2, T3)))
+__device__ __forceinline__ float quad_map(const float (&T)[4], float x)
+{
+    float o = T[3];
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %4" FS_QUAD(2)
+        "v_fmac_f32_dpp %0, %1, %3" FS_QUAD(1)
+        "v_fmac_f32_dpp %0, %1, %2" FS_QUAD(0)
+        : "+v"(o) : "v"(x), "v"(T[0]), "v"(T[1]), "v"(T[2]));
+    return o;
+}
+// quad_dot of two numbers with the same factors
+__device__ __forceinline__ void quad_dots(float a, float c, float b0, float b1, float b2, float &oa, float &oc)
+{
+    asm("s_nop 1\n\t"
+        "v_mul_f32_dpp %0, %2, %4" FS_QUAD(0)
+        "v_mul_f32_dpp %1, %3, %4" FS_QUAD(0)
+        "v_fmac_f32_dpp %0, %2, %5" FS_QUAD(1)
+        "v_fmac_f32_dpp %1, %3, %5" FS_QUAD(1)
+        "v_fmac_f32_dpp %0, %2, %6" FS_QUAD(2)
+        "v_fmac_f32_dpp %1, %3, %6" FS_QUAD(2)
+        : "=&v"(oa), "=&v"(oc) : "v"(a), "v"(c), "v"(b0), "v"(b1), "v"(b2));
+}
+// fma(-a of lane 8, b2, fma(-a of lane 4, b1, -a of lane 0 * b0)), lanes of the row
+__device__ __forceinline__ float row_dot_neg(float a, float b0, float b1, float b2)
+{
+    float o;
+    asm volatile("s_nop 1\n\t"
+        "v_mul_f32_dpp %0, -%1, %2" FS_ROW(0)
+        "v_fmac_f32_dpp %0, -%1, %3" FS_ROW(4)
+        "v_fmac_f32_dpp %0, -%1, %4" FS_ROW(8)
+        : "=&v"(o) : "v"(a), "v"(b0), "v"(b1), "v"(b2));
+    return o;
+}
+// the blend of corner_weights om (corner k in lane k of the row) and records q, one entry per lane, and the map of x by the blended
+// row that the quad holds (blend_apply)
+__device__ __forceinline__ float row_blend_apply(float om, const float (&q)[8], float x0, float x1, float x2)
+{
+    float e, d;
+    asm volatile("s_nop 1\n\t"
+        "v_mul_f32_dpp %0, %2, %3" FS_ROW(0)
+        "v_fmac_f32_dpp %0, %2, %4" FS_ROW(1)
+        "v_fmac_f32_dpp %0, %2, %5" FS_ROW(2)
+        "v_fmac_f32_dpp %0, %2, %6" FS_ROW(3)
+        "v_fmac_f32_dpp %0, %2, %7" FS_ROW(4)
+        "v_fmac_f32_dpp %0, %2, %8" FS_ROW(5)
+        "v_fmac_f32_dpp %0, %2, %9" FS_ROW(6)
+        "v_fmac_f32_dpp %0, %2, %10" FS_ROW(7)
+        "s_nop 1\n\t"
+        "v_mov_b32_dpp %1, %0" FS_QUAD(3)
+        "v_fmac_f32_dpp %1, %0, %13" FS_QUAD(2)
+        "v_fmac_f32_dpp %1, %0, %12" FS_QUAD(1)
+        "v_fmac_f32_dpp %1, %0, %11" FS_QUAD(0)
+        : "=&v"(e), "=&v"(d)
+        : "v"(om), "v"(q[0]), "v"(q[1]), "v"(q[2]), "v"(q[3]), "v"(q[4]), "v"(q[5]), "v"(q[6]), "v"(q[7]), "v"(x0), "v"(x1), "v"(x2));
+    return d;
+}
+// a[i] = fma(s of lane 4i of the row, v, a[i])
+__device__ __forceinline__ void row_update(float s, float v, float (&a)[3])
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %3, %4" FS_ROW(0)
+        "v_fmac_f32_dpp %1, %3, %4" FS_ROW(4)
+        "v_fmac_f32_dpp %2, %3, %4" FS_ROW(8)
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]) : "v"(s), "v"(v));
+}
+#undef FS_QUAD
+#undef FS_ROW
 // what a lane needs to look its axis up
 struct QuadAxis {
     float lo, inv_h, m;
     int n, stride, row;
+    float far_x, far_y;         // 1 where bit 0, 1 of the lane is clear, else 0: |far - f| is the weight of that side of an axis (quad_weights)
 };
-__device__ __forceinline__ QuadAxis quad_axis(const GridP &G)
+__device__ __forceinline__ QuadAxis quad_axis(const GridP &G, int row)
 {
     QuadAxis A;
-    A.row = min((int)(threadIdx.x & 3), 2);
-    A.lo = pick3(A.row, G.lo[0], G.lo[1], G.lo[2]);
-    A.inv_h = pick3(A.row, G.inv_h[0], G.inv_h[1], G.inv_h[2]);
-    A.m = pick3(A.row, G.m[0], G.m[1], G.m[2]);
-    A.n = A.row == 0 ? G.nx : (A.row == 1 ? G.ny : G.nz);
-    A.stride = A.row == 0 ? G.sx : (A.row == 1 ? G.sy : 12);
+    A.row = row;
+    A.lo = pick3(row, G.lo[0], G.lo[1], G.lo[2]);
+    A.inv_h = pick3(row, G.inv_h[0], G.inv_h[1], G.inv_h[2]);
+    A.m = pick3(row, G.m[0], G.m[1], G.m[2]);
+    A.n = row == 0 ? G.nx : (row == 1 ? G.ny : G.nz);
+    A.stride = row == 0 ? G.sx : (row == 1 ? G.sy : 12);
+    A.far_x = (threadIdx.x & 1) ? 0.0f : 1.0f;
+    A.far_y = (threadIdx.x & 2) ? 0.0f : 1.0f;
     return A;
 }
 
-// the cell of x from its coordinate along the lane's axis: base and fractions (ci and cl are not set)
-__device__ __forceinline__ Cell quad_locate(const QuadAxis &A, float xr)
+// base of the cell of x, and the fraction along the lane's axis, from the coordinate along that axis
+__device__ __forceinline__ int quad_place(const QuadAxis &A, float xr, float &f)
 {
-    Cell c;
     int i0;
-    float f;
     bool cl;
     locate_axis(xr, A.lo, A.inv_h, A.m, A.n, i0, f, cl);
     const int b = i0 * A.stride;
-    c.base = quad_get<0>(b) + quad_get<1>(b) + quad_get<2>(b);
-    c.f[0] = quad_get<0>(f);
-    c.f[1] = quad_get<1>(f);
-    c.f[2] = quad_get<2>(f);
-    return c;
+    return quad_get<0>(b) + quad_get<1>(b) + quad_get<2>(b);
+}
+// corner_weights from the fractions that the quad's lanes hold: lane k the product of corner k's x and y weights.  Fractions lie in [0, 1], so
+// |1 - f| and |0 - f| are the weights of an axis.
+__device__ __forceinline__ void quad_weights(const QuadAxis &A, float f, float (&om)[8])
+{
+    const float wxy = __builtin_fabsf(A.far_x - quad_get<0>(f)) * __builtin_fabsf(A.far_y - quad_get<1>(f));
+    const float z1 = quad_get<2>(f), z0 = 1.0f - z1;
+    om[0] = quad_get<0>(wxy) * z0;
+    om[1] = quad_get<1>(wxy) * z0;
+    om[2] = quad_get<2>(wxy) * z0;
+    om[3] = quad_get<3>(wxy) * z0;
+    om[4] = quad_get<0>(wxy) * z1;
+    om[5] = quad_get<1>(wxy) * z1;
+    om[6] = quad_get<2>(wxy) * z1;
+    om[7] = quad_get<3>(wxy) * z1;
 }
 
 // the lane's row of the 8 corner records
@@ -1297,7 +1403,7 @@ __device__ __forceinline__ void quad_blend(const float (&om)[8], const float (&q
 
 // The state of a quad's pair: x along the lane's axis, g whole, the lane's row and column of J~.  What is one number per row (dx, u, v) is
 // computed by its lane and fetched by the others; every number by the operations of finish_step.  (All of J~ and x in every lane:
-// 145 instead of 128 vector instructions per step; 37 points of 24 states, up to 50 steps: the call 41.1 us, now 38.4.)
+// 145 vector instructions per step; with moves between lanes as instructions of their own 128; now 113.)
 struct QuadState {
     float x, g[3], row[3], col[3];
 };
@@ -1334,31 +1440,27 @@ __device__ __forceinline__ bool quad_step(const GridP &G, const SolveP &S, const
 {
     const float dxr = -FS_FMA(s.row[2], s.g[2], FS_FMA(s.row[1], s.g[1], s.row[0] * s.g[0]));
     s.x = s.x + dxr;
-    const Cell cell = quad_locate(A, s.x);
-    if (cell.base != held) {
-        quad_load(Tp + cell.base, G, A.row, q);
-        held = cell.base;
+    float f;
+    const int base = quad_place(A, s.x, f);
+    if (base != held) {
+        quad_load(Tp + base, G, A.row, q);
+        held = base;
     }
-    const float x[3] = {quad_get<0>(s.x), quad_get<1>(s.x), quad_get<2>(s.x)};
-    const float vr = FS_FMA(quad_get<2>(dxr), s.col[2], FS_FMA(quad_get<1>(dxr), s.col[1], quad_get<0>(dxr) * s.col[0]));
-    const float v[3] = {quad_get<0>(vr), quad_get<1>(vr), quad_get<2>(vr)};
+    const float vr = quad_dot(dxr, s.col[0], s.col[1], s.col[2]);
     float om[8], T[4];
-    corner_weights(cell, om);
+    quad_weights(A, f, om);
     quad_blend(om, q, T);
-    const float gr = quad_apply(T, x) - xpr;
+    const float gr = quad_map(T, s.x) - xpr;
     const float gn[3] = {quad_get<0>(gr), quad_get<1>(gr), quad_get<2>(gr)};
     float dg[3];
 #pragma unroll
     for (int r = 0; r < 3; ++r) dg[r] = gn[r] - s.g[r];
     const float ur = dxr - FS_FMA(s.row[2], dg[2], FS_FMA(s.row[1], dg[1], s.row[0] * dg[0]));
-    const float den = FS_FMA(v[2], dg[2], FS_FMA(v[1], dg[1], v[0] * dg[0]));
+    const float den = quad_dot(vr, dg[0], dg[1], dg[2]);
     if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
         const float sc = ur * reciprocal(den);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) s.row[c] = FS_FMA(sc, v[c], s.row[c]);
-        s.col[0] = FS_FMA(quad_get<0>(sc), vr, s.col[0]);
-        s.col[1] = FS_FMA(quad_get<1>(sc), vr, s.col[1]);
-        s.col[2] = FS_FMA(quad_get<2>(sc), vr, s.col[2]);
+        quad_update(vr, sc, s.row);
+        quad_update(sc, vr, s.col);
     }
     ++it;
 #pragma unroll
@@ -1366,6 +1468,128 @@ __device__ __forceinline__ bool quad_step(const GridP &G, const SolveP &S, const
     const float r2 = FS_FMA(gn[2], gn[2], FS_FMA(gn[1], gn[1], gn[0] * gn[0]));
     conv = r2 < S.tol2;
     return conv || !(r2 < S.div2) || it >= S.max_iters;
+}
+
+// ---- sixteen SIMD lanes per pair ------------------------------------------------------------------------------------
+// The last pairs of a wave wait for one chain of instructions, each for the one before it: what a quad computes entry after entry is
+// spread over a row of 16 lanes: 82 vector instructions and 8 loads of 4 bytes per step instead of a quad's 113 and 8 of 16 bytes.  (37 points of 24
+// states, up to 50 steps: the call 37.7 -> 30.4 us; scans of 24 k points with candidates, most quads of a wave idle from the start, 57 -> 38; 8 k points of
+// 24 states by k_solve_once, whose waves end this way, 75 -> 65.)  Lane 4r + c of a row holds entry (r, c) of the blended transform (8 loads of 4 bytes; a row
+// reads the 48 bytes of a corner record) and of J~, and column c of J~; lane k the weight of corner k mod 8.  r = 3 repeats r = 2, and in J~ c = 3
+// repeats c = 2.  Numbers move between lanes as DPP operands of the multiply-adds.  Operations and their order are those of finish_step.
+template <int N>
+__device__ __forceinline__ float row_get(float v)       // the value of lane N of the row
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xf, 0xf, true));
+}
+template <int N>
+__device__ __forceinline__ int row_get(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, 0x150 + N, 0xf, 0xf, true);
+}
+constexpr int HEXES = 4;        // pairs a wave can hold this way
+
+// Steps of the pairs of at most HEXES active quads until all have ended: a row of lanes takes each, and the quads get their pairs' ends back
+// (s.x, s.row, it, conv).  Wave-wide call; xpr, s, it, pz: of the lane's quad (xpr, s.x and s.row: row A.row; s.col: its column).
+__device__ __forceinline__ void hex_run(const GridP &G, const SolveP &S, const float *__restrict__ T, bool active, int lane, int quad_row,
+                                        float xpr, QuadState &s, int &it, int pz, bool &conv)
+{
+    unsigned long long m = __ballot(active);
+    if (m == 0) return;
+    int src = 0, mine = 0;              // first lane of the quad this row takes from; the row that this lane's quad gave to
+    bool on = false;
+    for (int j = 0; m; ++j) {           // wave-uniform
+        const int b = __ffsll((long long)m) - 1;
+        m &= ~(0xfull << b);
+        if ((lane >> 4) == j) {
+            src = b;
+            on = true;
+        }
+        if ((lane >> 2) == (b >> 2)) mine = 16 * j;
+    }
+    const int r4 = (lane >> 2) & 3, c4 = lane & 3;
+    const QuadAxis A = quad_axis(G, min(r4, 2));
+    const float *Te = T + (long long)__shfl(pz, src) * G.V * 12 + A.row * 4 + c4;
+    const float hx = __shfl(xpr, src + r4);
+    float x = __shfl(s.x, src + r4), g[3], col[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        g[c] = __shfl(s.g[c], src);
+        col[c] = __shfl(s.col[c], src + c4);
+    }
+    float a = pick3(A.row, col[0], col[1], col[2]);         // J~ (r, c)
+    int hit = __shfl(it, src);
+    bool hconv = false;
+    const float far_z = (lane & 4) ? 0.0f : 1.0f;
+    if (on) {
+        float q[8];
+        int held = -1;
+        bool done;
+        do {
+            const float t = quad_dot(a, g[0], g[1], g[2]);          // -dx
+            x = x - t;
+            int i0;
+            float f;
+            bool cl;
+            locate_axis(x, A.lo, A.inv_h, A.m, A.n, i0, f, cl);
+            const int b = i0 * A.stride, base = row_get<0>(b) + row_get<4>(b) + row_get<8>(b);
+            if (base != held) {
+                const float *c = Te + base;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int k = (i >> 1) + 4 * (i & 1);        // the two z-neighbours of an (x, y) corner one after the other
+                    q[k] = c[corner_off(G, k)];
+                }
+                held = base;
+            }
+            const float om = (__builtin_fabsf(A.far_x - row_get<0>(f)) * __builtin_fabsf(A.far_y - row_get<4>(f))) * __builtin_fabsf(far_z - row_get<8>(f));
+            const float x0 = row_get<0>(x), x1 = row_get<4>(x), x2 = row_get<8>(x);
+            const float v = row_dot_neg(t, col[0], col[1], col[2]);
+            const float gr = row_blend_apply(om, q, x0, x1, x2) - hx;
+            const float gn[3] = {row_get<0>(gr), row_get<4>(gr), row_get<8>(gr)};
+            const float dg[3] = {gn[0] - g[0], gn[1] - g[1], gn[2] - g[2]};
+            float u, den;
+            quad_dots(a, v, dg[0], dg[1], dg[2], u, den);
+            u = -t - u;
+            if (den != 0.0f && __builtin_fabsf(den) < __builtin_inff()) {
+                const float sc = u * reciprocal(den);
+                a = FS_FMA(sc, v, a);
+                row_update(sc, v, col);
+            }
+            ++hit;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) g[c] = gn[c];
+            const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
+            hconv = r2 < S.tol2;
+            done = hconv || !(r2 < S.div2) || hit >= S.max_iters;
+        } while (!done);
+    }
+    const int back = mine + 4 * quad_row;
+    const float bx = __shfl(x, back), b0 = __shfl(a, back), b1 = __shfl(a, back + 1), b2 = __shfl(a, back + 2);
+    const int bi = __shfl(hit << 1 | (hconv ? 1 : 0), mine);
+    if (active) {
+        s.x = bx;
+        s.row[0] = b0;
+        s.row[1] = b1;
+        s.row[2] = b2;
+        it = bi >> 1;
+        conv = (bi & 1) != 0;
+    }
+}
+
+// Steps of the pairs of the active quads until all have ended: in quads while more than HEXES are left, then in rows (wave-wide call)
+__device__ __forceinline__ void quad_run(const GridP &G, const SolveP &S, const QuadAxis &A, const float *__restrict__ T, bool active, int lane,
+                                         float xpr, QuadState &s, int &it, int pz, bool &conv)
+{
+    if (lanes_on(active) > 4 * HEXES) {
+        const float *Tp = T + (long long)pz * G.V * 12;
+        float q[8][4];
+        int held = -1;
+        do {
+            if (active) active = !quad_step(G, S, A, Tp, xpr, s, it, q, held, conv);
+        } while (lanes_on(active) > 4 * HEXES);
+    }
+    hex_run(G, S, T, active, lane, A.row, xpr, s, it, pz, conv);
 }
 
 // A wave whose last QUADS pairs (or fewer) are all that is left for it hands them from single lanes to quads: quad j
@@ -1396,7 +1620,7 @@ __device__ __forceinline__ void quad_tail(const GridP &G, const SolveP &S, const
     if (m == 0) return;
     bool on;
     const int src = quad_source(m, lane, on);
-    const QuadAxis A = quad_axis(G);
+    const QuadAxis A = quad_axis(G, min(lane & 3, 2));
     const float xpr = pick3(A.row, __shfl(xp[0], src), __shfl(xp[1], src), __shfl(xp[2], src));
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
@@ -1409,14 +1633,9 @@ __device__ __forceinline__ void quad_tail(const GridP &G, const SolveP &S, const
     n = __shfl(n, src);
     k = __shfl(k, src);
     pz = __shfl(pz, src);
-    const float *Tp = T + (long long)pz * G.V * 12;
     bool conv = false;
     QuadState state = quad_state(A.row, x, g, J);
-    if (on) {
-        float q[8][4];
-        int held = -1;
-        while (!quad_step(G, S, A, Tp, xpr, state, it, q, held, conv)) {}
-    }
+    quad_run(G, S, A, T, on, lane, xpr, state, it, pz, conv);
     quad_unpack(state, x, J);
     emit(on && (lane & 3) == 0, conv, x, J, it, n, k, pz);
 }
@@ -2175,13 +2394,13 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
 // without a root keeps all its lanes busy to the last step, and a wave that holds 24 of those cannot go on in quads.
 // ki = 1 without positions, 8 with them (16x16x4 grid, 98 k pairs with positions: ki 1 71, 4 50, 8 45, 24 52 us; 64x64x16:
 // 72, 66, 66, 79 us).
-__device__ __forceinline__ bool pair_of(unsigned index, unsigned per, unsigned N, int K, int ki, int &n, int &k)
+__device__ __forceinline__ bool pair_of(unsigned w, unsigned i, unsigned per, unsigned N, int K, int ki, int &n, int &k)
 {
-    const unsigned pts = per / (unsigned)ki, tiles = (N + pts - 1u) / pts, w = index / per, i = index - w * per;
+    const unsigned pts = per / (unsigned)ki, tiles = (N + pts - 1u) / pts;
     const unsigned kb = w / tiles;
     k = (int)(kb * (unsigned)ki + i / pts);
     n = (int)((w - kb * tiles) * pts + i % pts);
-    const bool live = k < K && n < (int)N;
+    const bool live = i < per && k < K && n < (int)N;
     if (!live) n = k = 0;
     return live;
 }
@@ -2212,11 +2431,12 @@ __global__ __launch_bounds__(LDS ? 1024 : 256) void k_solve_quad(GridP G, SolveP
         __syncthreads();
     }
     const float *T = LDS ? reinterpret_cast<const float *>(s_grid) : Tglobal;
-    const QuadAxis A = quad_axis(G);
+    const int lane = (int)(threadIdx.x & 63);
+    const QuadAxis A = quad_axis(G, min(lane & 3, 2));
     const int row = A.row, lane3 = (int)(threadIdx.x & 3);
     const long long N = S.N;
     int n, k;
-    const bool live = pair_of((blockIdx.x * blockDim.x + threadIdx.x) >> 2, QUADS, (unsigned)S.N, S.K, S.ki, n, k);
+    const bool live = pair_of((blockIdx.x * blockDim.x + threadIdx.x) >> 6, (unsigned)lane >> 2, (unsigned)S.per, (unsigned)S.N, S.K, S.ki, n, k);
     const unsigned pair = (unsigned)k * (unsigned)N + (unsigned)n;
     const int p = pose_of(pose, n, G.P);
     const float *Tp = T + (long long)p * G.V * 12;
@@ -2284,15 +2504,14 @@ __global__ __launch_bounds__(LDS ? 1024 : 256) void k_solve_quad(GridP G, SolveP
         for (int e = 0; e < 9; ++e) J[e] = J0[((long long)k * 9 + e) * N + n];
         ok = live && valid0[pair] != 0;
         if (ok) {
-            const Cell c = quad_locate(A, pick3(row, x[0], x[1], x[2]));
-            float q[8][4], om[8], Tr[4];
-            quad_load(Tp + c.base, G, row, q);
-            corner_weights(c, om);
+            float q[8][4], om[8], Tr[4], f;
+            quad_load(Tp + quad_place(A, pick3(row, x[0], x[1], x[2]), f), G, row, q);
+            quad_weights(A, f, om);
             quad_blend(om, q, Tr);
             dr = quad_apply(Tr, x);
         }
     }
-    bool conv = false;
+    bool conv = false, active = false;
     int it = 0;
     if (ok) {
         const float gr = dr - xpr;
@@ -2301,14 +2520,11 @@ __global__ __launch_bounds__(LDS ? 1024 : 256) void k_solve_quad(GridP G, SolveP
         g[2] = quad_get<2>(gr);
         const float r2 = FS_FMA(g[2], g[2], FS_FMA(g[1], g[1], g[0] * g[0]));
         conv = r2 < S.tol2;
-        if (!(conv || !(r2 < S.div2) || 0 >= S.max_iters)) {
-            float q[8][4];
-            int held = -1;
-            QuadState state = quad_state(row, x, g, J);
-            while (!quad_step(G, S, A, Tp, xpr, state, it, q, held, conv)) {}
-            quad_unpack(state, x, J);
-        }
+        active = !(conv || !(r2 < S.div2) || 0 >= S.max_iters);
     }
+    QuadState state = quad_state(row, x, g, J);
+    quad_run(G, S, A, T, active, lane, xpr, state, it, p, conv);
+    quad_unpack(state, x, J);
     int pos = -1;
     if (cell_count) {
         const bool want = conv && lane3 == 0;
@@ -2366,7 +2582,7 @@ __global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(Gri
     const int lane = threadIdx.x & 63;
     const long long N = S.N;
     int n, k;
-    const bool live = pair_of(blockIdx.x * blockDim.x + threadIdx.x, WAVE, (unsigned)S.N, S.K, S.ki, n, k);
+    const bool live = pair_of((blockIdx.x * blockDim.x + threadIdx.x) >> 6, (unsigned)lane, WAVE, (unsigned)S.N, S.K, S.ki, n, k);
     const unsigned pair = (unsigned)k * (unsigned)N + (unsigned)n;
     const int p = pose_of(pose, n, G.P);
     const float *Tp = T + (long long)p * G.V * 12;
@@ -2514,7 +2730,7 @@ __global__ __launch_bounds__(256) void k_grad_count(GridP G, const float *__rest
                                                     int *__restrict__ pos)
 {
     int n, k;
-    const bool live = pair_of(blockIdx.x * 256u + threadIdx.x, WAVE, (unsigned)N, K, ki, n, k);
+    const bool live = pair_of((blockIdx.x * 256u + threadIdx.x) >> 6, threadIdx.x & 63u, WAVE, (unsigned)N, K, ki, n, k);
     const long long q = (long long)k * N + n;
     const bool want = live && conv[q];
     int cell = 0;

@@ -11,6 +11,7 @@ from paper_2211_15601_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 CUS = 256
+LDS, CACHED = (12, 10, 6), (20, 18, 9)
 BONE_QUAD, BONE_ONCE = 192 * CUS, 768 * CUS          # largest batches (pairs) of the two kernels, one state per bone
 VOXEL_QUAD, VOXEL_ONCE = 320 * CUS, 1152 * CUS       # ... and with voxel-based candidates
 
@@ -49,6 +50,31 @@ def test_batch_sizes_around_the_kernels_limits(gpu_lib, case):
     got = run.grad(out[0], None, out[1], gxc, slot=run.slot)
     for name, a, b in zip(("gW", "gB", "gxq"), got, want):
         gu.assert_grad_close(name, a, b, f"small batch {case}")
+
+
+@pytest.mark.parametrize("dims,nb,n,voxel", [
+    # four pairs per wave up to 16 per compute unit (roots only) or 48 (positions, candidates), then 16; states that fill no four; a single pair
+    (CACHED, 24, 16 * CUS // 24, False), (CACHED, 24, 16 * CUS // 24 + 1, False), (CACHED, 24, 48 * CUS // 24 + 1, False), (LDS, 24, 16 * CUS // 24, False),
+    (CACHED, 9, 5, False), (CACHED, 3, 7, False), (CACHED, 1, 1, False), (LDS, 11, 9, False), (CACHED, 6, 48 * CUS // 3, True), (CACHED, 6, 48 * CUS // 3 + 1, True),
+    (LDS, 6, 1, True)], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_rows_of_sixteen_lanes(gpu_lib, dims, nb, n, voxel):
+    # pairs that run to the last step, pairs that are no numbers, poses side by side: same bits as the oracle
+    s = wl.random_affine_scene(320 + nb, dims=dims, n_bones=nb, n_poses=2, n_points=n, max_deg=120.0)
+    x = s["x"].copy()
+    x[1, 3::17] = np.nan
+    x[0, 5::19] = 40.0
+    w = wl.Workload("rows", s["dims"], nb, 2, s["lo"], s["hi"], s["W"], s["B"], x, s["pose"], x, 1e-5, 10.0, 50,
+                    wl.INIT_VOXEL if voxel else wl.INIT_BONE, 3 if voxel else nb, (6, 5, 4, 3))
+    run = gu.GpuRun(w)
+    T = run.precompute()
+    with np.errstate(all="ignore"):
+        x0, J0, v0 = gu.oracle_inits(w, T)
+        ref = gu.oracle_solve(w, T, x0, J0, v0)
+    for kw in (dict(fused=True), dict(fused=True, slots=True), dict(x0=x0, J0=J0, v0=v0)):
+        out = run.solve(**kw)
+        for name, a, b in zip(("roots", "masks", "J", "iterations"), out, ref):
+            np.testing.assert_array_equal(a[~np.isnan(b)].view(np.uint8), b[~np.isnan(b)].view(np.uint8), err_msg=f"{name} {sorted(kw)}")
+            np.testing.assert_array_equal(np.isnan(a), np.isnan(b))
 
 
 @pytest.mark.parametrize("n,voxel", [(40, False), (6004, False), (5000, True), (40000, True)])
