@@ -1839,15 +1839,22 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
 // Sec. 3.1 "Custom CUDA Kernel") with the work divided between the waves of a block.  One wave (the producer) prepares
 // pairs 64 at a time, every SIMD lane busy: initial state, first evaluation of the field, first step; pairs
 // that end there (invalid state, converged or diverged at x0) it answers itself.  The other waves (the
-// consumers) only iterate: each owns a queue of prepared states {x', x, g, dx, J~, pair} in LDS, its idle
-// lanes pick states up with a few LDS reads, and its loop holds nothing but the Broyden step.  The producer
-// gives every batch to the consumer whose queue is emptiest.  Neither role ever holds the other's registers.
-// Queues: single producer, single consumer; tail is written by the producer only, head by the consumer only.
-// Every wait ends: a producer that has polled S.spin_limit times in vain for room in its consumers' queues raises
-// *give_up (host-visible) and leaves; it raises s_done on every way out, and its consumers, which wait for
-// nothing else, finish what their queues hold and leave too.
+// consumers) iterate: idle lanes take prepared states {x', x, g, J~, pair} from the block's queue in LDS, and the loop
+// holds nothing but the Broyden step.  Neither role ever holds the other's registers.
+// Start and end cost what the middle does not show, so every wave works from the first to the last: a consumer prepares its first 64 pairs itself
+// (its segment of the queue takes them from the one loop to the other), and the producer iterates when there is nothing left to prepare.
+// The queue is one for the block, so that what is left when the producer ends goes to whoever has room.  (A queue of 128 per consumer, all filled by the
+// producer: on 65 k points the consumers of a block had their first pairs after 5, 14 and 28 us, and the last of 277 us ended 75 after the producer.
+// Kernel us, that / now: 0.48 M pairs of bone states 120 / 112, 0.23 M 86 / 71, 1.6 M 277 / 277, 4.8 M 718 / 684, 0.4 M candidates of 1 M ray samples 72 / 59,
+// 40 k of 0.1 M 49 / 29, 7.9 M of eight poses 1236 / 1210.)
+// Entries are numbered as they come; one has its place modulo the queue's size.  tail: entries written (by the producer); claim: taken (by
+// exchanges among the consumers); freed: of each segment of 64, how many have been read since the start, the consumers' own pairs being the
+// first round.  The producer writes into a segment when all of the round before has been read.
+// Every wait ends: a producer that has polled S.spin_limit times in vain for room raises
+// *give_up (host-visible) and prepares no more; it raises s_done in any case, and the waves, which wait for
+// nothing else, finish what the queue holds and leave.
 // ------------------------------------------------------------------------------------------------
-constexpr int WS_RING = 128;                 // entries per queue (two batches)
+constexpr int WS_SEGMENTS = 3, WS_RING = 64 * WS_SEGMENTS;     // one segment per consumer (16 KiB)
 constexpr int FS_WS_CONSUMERS = 3;           // measured: a producer that computes Eq. (8) keeps up with three consumers, not with four
 // A producer that only looks up voxel-based candidates could serve more consumers, but more iterating waves per CU
 // only compete for the vector cache: measured on the multi-pose / training / ray batches, kernel ms with 2 blocks per
@@ -2077,15 +2084,15 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                                                int ncell, int *__restrict__ give_up,
                                                const int *__restrict__ state)
 {
-    __shared__ float s_ring[NCONS][ST_FIELDS][WS_RING];
-    __shared__ int s_tail[NCONS], s_head[NCONS], s_done;
+    __shared__ float s_ring[ST_FIELDS][WS_RING];
+    __shared__ int s_tail, s_claim, s_freed[WS_SEGMENTS], s_done;
     constexpr int OUT_PEND = SKIP ? 64 : 128;        // 64: 50 KiB of LDS, so that a CU holds three blocks
     __shared__ OutQ<OUT_PEND, WITH_J> s_out[NCONS + 1];      // records on their way out, per wave
-    if (threadIdx.x < NCONS) {
-        s_tail[threadIdx.x] = 0;
-        s_head[threadIdx.x] = 0;
+    if (threadIdx.x < WS_SEGMENTS) s_freed[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        s_tail = s_claim = WS_RING;
+        s_done = 0;
     }
-    if (threadIdx.x == 0) s_done = 0;
     __syncthreads();
     const long long total = list ? (long long)*list_len : S.total;
     const int lane = threadIdx.x & 63;
@@ -2095,8 +2102,18 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
     OutQ<OUT_PEND, WITH_J> &outq = s_out[wib];
     const int stride = (int)G.V * 12;          // of the poses' grids; P of them are below 2^31
 
-    if (wib == NCONS) {
-        // ------------------------------------------------ producer ------------------------------------------------
+    const bool producer = wib == NCONS;
+    static_assert(NCONS == WS_SEGMENTS, "a consumer's own pairs fill a segment of the queue");
+    int nown = 0;                   // of a consumer: pairs it has put into its segment itself
+    // SKIP needs a grid of entries below SKIP_MAX (k_precompute says if this one is not)
+    const bool may_skip = SKIP && may_skip_corners(state);
+    {
+        // ------------------------------------------- preparing pairs -------------------------------------------
+        // every consumer of the grid takes `own` consecutive pairs from the front; the producers' chunks are those behind
+        const bool ranges = S.xcd_ranges != 0;
+        const unsigned consumers = gridDim.x * NCONS;
+        const unsigned own = ranges ? 0u : ((unsigned)total >= 64u * consumers ? 64u : ((unsigned)total + consumers - 1u) / consumers);
+        const long long heads = min(total, (long long)own * consumers), rest = total - heads;
         // the first chunk of block b is chunk b; the shared cursor starts behind those.  (One cursor for the whole chip
         // on purpose: all XCDs then work through the same stretch of the points at the same time, and what one of them
         // brought into the memory-side cache serves the others.  With a cursor per XCD over its own eighth of the
@@ -2108,24 +2125,24 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
         // XCD's own L2 then serves 0.72 instead of 0.47 of the requests and a third of the bytes come from beyond it,
         // but the kernel is no faster (1.29 against 1.26 ms with the ordered list behind one cursor): the vector cache
         // in front of the L2 is the limit.
-        const bool ranges = S.xcd_ranges != 0;
         const int home = (int)(blockIdx.x & (N_XCD - 1));
         const long long per = ((total + (long long)N_XCD * S.chunk - 1) / ((long long)N_XCD * S.chunk)) * S.chunk;
-        long long next, c1;
-        Chunks chunks = first_chunk(S, total, (int)blockIdx.x, (int)gridDim.x, next, c1);
-        if (ranges) {
+        long long next, c1;             // of a producer: counted from the end of the consumers' own
+        Chunks chunks = first_chunk(S, rest, (int)blockIdx.x, (int)gridDim.x, next, c1);
+        if (!producer) {
+            next = min(heads, (long long)(blockIdx.x * NCONS + wib) * own);
+            c1 = min(heads, next + own);
+        } else if (ranges) {
             const long long r1 = min(total, (home + 1) * per);
             next = home * per + (long long)(blockIdx.x >> 3) * S.chunk;
             c1 = min(r1, next + S.chunk);
         }
         int alive = 0;                    // ranges home, home + 1, ... home + alive - 1 are known to be used up
-        int tails[NCONS];
-#pragma unroll
-        for (int c = 0; c < NCONS; ++c) tails[c] = 0;
+        int tail = producer ? WS_RING : 64 * wib;
         bool lost = false;
-        const bool prod_skip = SKIP && may_skip_corners(state);
         while (!lost) {
             if (next >= c1) {
+                if (!producer) break;
                 if (ranges) {
                     bool got = false;
                     while (alive < N_XCD) {
@@ -2144,17 +2161,18 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                     }
                     if (!got) break;
                 } else {
-                    if (!next_chunk(chunks, S, total, cursor, lane, next, c1)) break;
+                    if (!next_chunk(chunks, S, rest, cursor, lane, next, c1)) break;
                 }
             }
-            const long long pq = next + lane;
+            const bool mine = next + lane < c1;
+            const long long pq = (producer ? heads : 0ll) + next + lane;
             next += min(64ll, c1 - next);
             bool keep = false, want_out = false;
             int out_place = -1, out_flags = 0, pair = 0;
             int nn = 0, nk = 0, np = 0;
             float nxp[3] = {0, 0, 0}, nx[3] = {0, 0, 0}, ng[3] = {0, 0, 0};
             float nJ[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-            if (pq < c1) {
+            if (mine) {
                 const unsigned upq = (unsigned)pq;        // K * N < 2^31
                 int gcell = -1;                           // pose * ncell + correspondence cell, when the list gives it
                 if (list) {
@@ -2191,7 +2209,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                         const Cell c0 = locate(G, nx);
                         base0 = c0.base;
                         float Jac[9];
-                        field_dJ_clamped(Tn, G, c0, prod_skip, nx, d, Jac);
+                        field_dJ_clamped(Tn, G, c0, may_skip, nx, d, Jac);
                         ok = inv3(Jac, nJ);
                         if (!ok) {
 #pragma unroll
@@ -2245,56 +2263,48 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
             const unsigned long long km = __ballot(keep);
             const int nkeep = __popcll(km);
             if (nkeep > 0) {
-                // the consumer with the emptiest queue takes the batch; wait while none has room
-                int best = 0, room = -1, spins = 0;
-                while (true) {
-#pragma unroll
-                    for (int c = 0; c < NCONS; ++c) {
-                        const int r = WS_RING - (tails[c] - __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_head[c])));
-                        if (r > room) { room = r; best = c; }
-                    }
-                    if (room >= nkeep) break;
-                    room = -1;
+                // wait for room, which a consumer's segment has
+                const int seg = (tail + nkeep - 1) / 64, lap = producer ? seg / WS_SEGMENTS : 0;
+                int spins = 0;
+                while (__builtin_amdgcn_readfirstlane(lds_load_acquire(&s_freed[seg - lap * WS_SEGMENTS])) < 64 * lap) {
                     if (++spins > S.spin_limit) { lost = true; break; }
                     __builtin_amdgcn_s_sleep(8);
                 }
                 if (lost) break;
-                int tl = 0;
-#pragma unroll
-                for (int c = 0; c < NCONS; ++c) if (c == best) tl = tails[c];
                 if (keep) {
-                    const int at = (tl + __popcll(km & ((1ull << lane) - 1ull))) & (WS_RING - 1);
-                    float (&ring)[ST_FIELDS][WS_RING] = s_ring[best];
+                    const int at = (int)((unsigned)(tail + __popcll(km & ((1ull << lane) - 1ull))) % WS_RING);
 #pragma unroll
                     for (int r = 0; r < 3; ++r) {
-                        ring[ST_XP + r][at] = nxp[r];
-                        ring[ST_X + r][at] = nx[r];
-                        ring[ST_G + r][at] = ng[r];
+                        s_ring[ST_XP + r][at] = nxp[r];
+                        s_ring[ST_X + r][at] = nx[r];
+                        s_ring[ST_G + r][at] = ng[r];
                     }
 #pragma unroll
-                    for (int e = 0; e < 9; ++e) ring[ST_J + e][at] = nJ[e];
-                    ring[ST_N][at] = __int_as_float(nn);
-                    ring[ST_K][at] = __int_as_float(nk);
-                    ring[ST_P][at] = __int_as_float(np);
+                    for (int e = 0; e < 9; ++e) s_ring[ST_J + e][at] = nJ[e];
+                    s_ring[ST_N][at] = __int_as_float(nn);
+                    s_ring[ST_K][at] = __int_as_float(nk);
+                    s_ring[ST_P][at] = __int_as_float(np);
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 __builtin_amdgcn_wave_barrier();
-                tl += nkeep;
-#pragma unroll
-                for (int c = 0; c < NCONS; ++c) if (c == best) tails[c] = tl;
-                if (lane == 0) lds_store_release(&s_tail[best], tl);
+                tail += nkeep;
+                if (producer && lane == 0) lds_store_release(&s_tail, tail);
             }
             out_park(G, want_out, nx, nJ, out_flags, out_place, pair, outq, npend, lane, cell_count, ncell, rec);
+            if (!producer) {
+                nown = nkeep;
+                break;
+            }
         }
-        if (lost && lane == 0) *give_up = 1;
-        if (npend > 0) out_flush(G, outq, npend, lane, cell_count, ncell, rec);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        if (lane == 0) lds_store_release(&s_done, 1);
-        return;
+        if (producer) {
+            if (lost && lane == 0) *give_up = 1;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            if (lane == 0) lds_store_release(&s_done, 1);
+        }
     }
 
-    // ---------------------------------------------------- consumer ----------------------------------------------------
-    float (&ring)[ST_FIELDS][WS_RING] = s_ring[wib];
+    // ---------------------------------------------------- iterating ----------------------------------------------------
+    // the consumers from the beginning, the producer when there is nothing left to prepare
     // what becomes of a pair that has ended in a quad (wave-wide call; `ends` in one lane of the quad)
     auto emit = [&](bool ends, bool conv, const float (&xe)[3], const float (&Je)[9], int ite, int ne, int ke, int pe) {
         const int flags = (conv ? 1 : 0) | (ite << 8), pair = (int)((long long)ke * N + ne);
@@ -2303,15 +2313,13 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
         out_park(G, ends, xe, Je, flags, place, pair, outq, npend, lane, cell_count, ncell, rec);
     };
     bool active = false;
-    int n = 0, k = 0, it = 0, pz = 0, head = 0;
+    int n = 0, k = 0, it = 0, pz = 0;
     const float *Tp = T;
     float xp[3] = {0, 0, 0}, x[3] = {0, 0, 0}, g[3] = {0, 0, 0};
     float J[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     float q[8][12];                  // corner records of the lane's current cell, kept across iterations
     int held = -1;                   // base of the cell whose corners q holds (-1: none)
     int held_mask = 0;               // SKIP: which of them
-    // SKIP needs a grid of entries below SKIP_MAX (k_precompute says if this one is not)
-    const bool may_skip = SKIP && may_skip_corners(state);
     if (SKIP) {
 #pragma unroll
         for (int c = 0; c < 8; ++c)
@@ -2320,38 +2328,51 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
     }
     bool fin = false;                // wave-uniform: the producer has left and the queue is empty
     int nidle = 64;
+    bool head = !producer;           // the wave's own pairs come first
     do {                             // (test at the end: see k_solve_once)
         if (nidle >= S.refill_min && !fin) {
             // s_done is read before the tail: the producer raises it last
             const int d = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_done));
-            const int tail = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_tail[wib]));
-            const int avail = tail - head;
-            fin = d && avail <= nidle;
-            if (avail > 0) {
+            const int tail = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_tail));
+            int at = 64 * wib, got = nown;
+            if (!head && lane == 0) {  // entries [at, at + got) are this wave's; every failed exchange is another wave's success
+                at = __hip_atomic_load(&s_claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                do got = max(min(nidle, tail - at), 0);
+                while (got > 0 && !__hip_atomic_compare_exchange_strong(&s_claim, &at, at + got, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+            }
+            at = __builtin_amdgcn_readfirstlane(at);
+            got = __builtin_amdgcn_readfirstlane(got);
+            fin = d && !head && at + got >= tail;
+            if (got > 0 || head) {
                 const unsigned long long idle = __ballot(!active);
                 const int rank = __popcll(idle & ((1ull << lane) - 1ull));
-                if (!active && rank < avail) {
-                    const int e = (head + rank) & (WS_RING - 1);
+                if (!active && rank < got) {
+                    const int e = (int)((unsigned)(at + rank) % WS_RING);
 #pragma unroll
                     for (int r = 0; r < 3; ++r) {
-                        xp[r] = ring[ST_XP + r][e];
-                        x[r] = ring[ST_X + r][e];
-                        g[r] = ring[ST_G + r][e];
+                        xp[r] = s_ring[ST_XP + r][e];
+                        x[r] = s_ring[ST_X + r][e];
+                        g[r] = s_ring[ST_G + r][e];
                     }
 #pragma unroll
-                    for (int c = 0; c < 9; ++c) J[c] = ring[ST_J + c][e];
-                    n = __float_as_int(ring[ST_N][e]);
-                    k = __float_as_int(ring[ST_K][e]);
-                    pz = __float_as_int(ring[ST_P][e]);
-                    Tp = T + (long long)pz * G.V * 12;
+                    for (int c = 0; c < 9; ++c) J[c] = s_ring[ST_J + c][e];
+                    n = __float_as_int(s_ring[ST_N][e]);
+                    k = __float_as_int(s_ring[ST_K][e]);
+                    pz = __float_as_int(s_ring[ST_P][e]);
+                    Tp = T + (long long)pz * stride;
                     it = 0;
                     held = -1;
                     active = true;
                 }
-                head += min(nidle, avail);
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");      // the reads above are done
                 __builtin_amdgcn_wave_barrier();
-                if (lane == 0) lds_store_release(&s_head[wib], head);
+                if (lane == 0) {
+                    const int first = head ? 64 : min(got, 64 - at % 64), seg = at / 64 % WS_SEGMENTS;
+                    (void)__hip_atomic_fetch_add(&s_freed[seg], first, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (got > first)
+                        (void)__hip_atomic_fetch_add(&s_freed[seg + 1 == WS_SEGMENTS ? 0 : seg + 1], got - first, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                head = false;
             }
         }
         // a consumer waits for nothing but its own block's producer, whose waits are all bounded and which raises
