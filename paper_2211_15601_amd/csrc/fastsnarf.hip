@@ -57,6 +57,7 @@ struct fs_ctx {
     size_t srec_cap;   // float4 entries srec can hold
     u64 *look;         // look-back words of the kernels that scan in one pass, zero between kernels
     size_t look_words; // words look holds: enough for every call the context accepts
+    size_t dd_look_at; // where those of k_dedupe_one begin
     bool look_dirty;   // a launch has failed: the words may have been used and not cleared
     int *dd_sums;      // [DD_TILES] tile sums of fs_dedupe (behind the cursor's words)
     uint8_t *vcnt;     // [N] candidates per point
@@ -186,6 +187,7 @@ int scan_blocks(int n) { return grid1d(n, 1024 * scan_per_thread(n)); }
 // thousand points that a block of k_voxel_list takes
 // (kernel us for 2 / 4 / 8 thousand: 0.3 M points 9 / 10 / 16, 1 M 17 / 13 / 16, 2 M 30 / 24 / 22, 4.2 M 76 / 65 / 62)
 int list_per_thread(long long N) { return N <= (1 << 19) ? 2 : (N <= (1 << 21) ? 4 : 8); }
+constexpr int DD_ONE_BLOCKS = 1024;                       // of k_dedupe_one at most
 constexpr long long SORT_MAX_COUNTS = 1ll << 24;          // (buckets x blocks) of the sort that orders the list by place
 
 // The look-back words are made and cleared with the context, for the largest call it accepts: 8 bytes per 8192 points of
@@ -201,6 +203,8 @@ bool look_create(fs_ctx *c)
                            (long long)grid1d(N, 1024 * list_per_thread(N)), 1ll << 9});
     }
     c->look_words = (size_t)blocks + LOOK_HEAD;
+    c->dd_look_at = c->look_words + LOOK_HEAD;                  // k_dedupe_one has words of its own behind them
+    c->look_words = c->dd_look_at + LOOK_HEAD + DD_ONE_BLOCKS;
     c->look_dirty = false;
     return dev_alloc(&c->look, c->look_words) && hipMemset(c->look, 0, c->look_words * sizeof(u64)) == hipSuccess;
 }
@@ -1021,6 +1025,22 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
     return launch_status(ctx, "fs_grad");
 }
 
+// k_dedupe_one where it is the shorter; false: not launched.  At most DD_FEW lanes: for few blocks, while look-back costs less than a launch (served ray
+// samples with candidates, whole call, us, two launches / one: 37 points 15.7 / 13.4, 1024 20.7 / 18.5, 5000 22.2 / 21.2, 12 k 23.8 / 23.1, 25 k
+// 24.9 / 24.5, 60 k 33.9 / 34.5).  More than 32 lanes: the other kernels hand on 32 bits per point and read the kept lanes again (64 states: 37 points
+// 39 / 29, 3000 87 / 71, 32 k 345 / 326).  Between, two launches are as short or shorter (24 states, 37 points 29.8 / 29.8, 1500 38.9 / 41.1).
+static bool launch_dedupe_one(fs_ctx *ctx, long long N, int K, float md2, const float *d_xc, const uint8_t *d_conv, uint8_t *d_keep,
+                              int32_t *d_offsets, float *d_roots, int32_t *d_lane, long long cap)
+{
+    u64 *const look = ctx->look + ctx->dd_look_at;
+    if (K <= DD_FEW && N <= 16 * 1024)
+        k_dedupe_one<0><<<grid1d(N, 1024), 1024, 0, ctx->stream>>>(N, K, cap, md2, d_xc, d_conv, d_keep, d_offsets, d_roots, d_lane, look);
+    else if (K > 32 && N <= 128ll * DD_ONE_BLOCKS)
+        k_dedupe_one<8><<<grid1d(N, 128), 1024, 0, ctx->stream>>>(N, K, cap, md2, d_xc, d_conv, d_keep, d_offsets, d_roots, d_lane, look);
+    else return false;
+    return true;
+}
+
 // shared body of fs_dedupe and fs_dedupe_noalloc, which differ in where the tile sums live
 static fs_status dedupe_impl(fs_ctx *ctx, const char *who, int *sums, const float *d_xc, const uint8_t *d_conv, int64_t N,
                              int32_t K, float min_dist, uint8_t *d_keep, int32_t *d_offsets, float *d_roots, int32_t *d_lane,
@@ -1041,6 +1061,8 @@ static fs_status dedupe_impl(fs_ctx *ctx, const char *who, int *sums, const floa
         FS_CHECK_PTR(ctx, d_xc, false);
         FS_CHECK_PTR(ctx, d_conv, false);
         FS_CHECK_PTR(ctx, d_keep, false);
+        if (sums == ctx->dd_sums && launch_dedupe_one(ctx, N, K, min_dist * min_dist, d_xc, d_conv, d_keep, d_offsets, d_roots, d_lane, cap))
+            return launch_status(ctx, who);
         int tile = K <= DD_FEW ? 256 : 32;          // what a block takes in one pass
         while ((N + tile - 1) / tile > DD_TILES) tile *= 2;
         const int tiles = grid1d(N, tile);
@@ -1064,6 +1086,7 @@ fs_status fs_dedupe(fs_ctx *ctx, const float *d_xc, const uint8_t *d_conv, int64
 {
     if (!ctx) return FS_E_ARG;
     { fs_status gs = check_gave_up(ctx, "fs_dedupe"); if (gs != FS_OK) return gs; }
+    { fs_status ls = look_ready(ctx, "fs_dedupe"); if (ls != FS_OK) return ls; }
     return dedupe_impl(ctx, "fs_dedupe", ctx->dd_sums, d_xc, d_conv, N, K, min_dist, d_keep, d_offsets, d_roots, d_lane, cap);
 }
 

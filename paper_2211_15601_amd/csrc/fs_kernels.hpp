@@ -538,6 +538,20 @@ __device__ __forceinline__ void look_clear(u64 *__restrict__ look, int blocks)
     const long long stride = (long long)gridDim.x * gridDim.y * blockDim.x;
     for (long long i = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < LOOK_HEAD + blocks; i += stride) look[i] = 0ull;
 }
+// By a whole wave of every block of a kernel that no other follows in its call, after its look_back: the last block clears the words.  done: one word,
+// LOOK_HEAD before the ticket.
+__device__ __forceinline__ void look_finish(u64 *__restrict__ look, int blocks, int lane)
+{
+    unsigned *done = reinterpret_cast<unsigned *>(look - LOOK_HEAD);
+    int last = 0;
+    if (lane == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this block's own words have been written
+        last = (int)atomicAdd(done, 1u) == blocks - 1;
+    }
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    if (lane == 0) *done = 0u;
+    for (int i = lane; i < LOOK_HEAD + blocks; i += 64) look[i] = 0ull;
+}
 
 // sums of the block's waves (up to 16 U of them per thread group) -> exclusive prefix within the block in s_tot[0 .. n),
 // return value (first wave only): the block's sum
@@ -3575,8 +3589,35 @@ __device__ __forceinline__ void tile_sum(int mine, int *__restrict__ sums)
     if (threadIdx.x == 0) sums[blockIdx.x] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
 }
 
-// K <= DD_FEW: one thread per point, everything in registers
 constexpr int DD_FEW = 4;
+// what is kept of point n (K <= DD_FEW), by one thread with everything in registers
+__device__ __forceinline__ unsigned dedupe_point(long long N, int K, long long n, float md2, const float *__restrict__ xc,
+                                                 const uint8_t *__restrict__ conv, uint8_t *__restrict__ keep)
+{
+            bool on[DD_FEW];
+            float x[DD_FEW][3];
+#pragma unroll
+            for (int k = 0; k < DD_FEW; ++k) on[k] = k < K && conv[(long long)min(k, K - 1) * N + n] != 0;
+#pragma unroll
+            for (int k = 0; k < DD_FEW; ++k)
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    x[k][r] = 0.0f;
+                    if (on[k]) x[k][r] = xc[((long long)k * 3 + r) * N + n];
+                }
+            unsigned kept = 0u;
+#pragma unroll
+            for (int k = 0; k < DD_FEW; ++k) {
+#pragma unroll
+                for (int j = 0; j < k; ++j)
+                    if (((kept >> j) & 1u) && closer(x[k], x[j], md2)) on[k] = false;
+                kept |= (on[k] ? 1u : 0u) << k;
+            }
+#pragma unroll
+    for (int k = 0; k < DD_FEW; ++k)
+        if (k < K) keep[(long long)k * N + n] = (uint8_t)((kept >> k) & 1u);
+    return kept;
+}
 __global__ __launch_bounds__(256) void k_dedupe_few(long long N, int K, float md2, const float *__restrict__ xc,
                                                     const uint8_t *__restrict__ conv, uint8_t *__restrict__ keep,
                                                     int *__restrict__ offsets, int tile, int *__restrict__ sums)
@@ -3584,109 +3625,159 @@ __global__ __launch_bounds__(256) void k_dedupe_few(long long N, int K, float md
     const long long n0 = (long long)blockIdx.x * tile, n1 = min(N, n0 + tile);
     int mine = 0;
     for (long long n = n0 + threadIdx.x; n < n1; n += 256) {
-        bool on[DD_FEW];
-        float x[DD_FEW][3];
-#pragma unroll
-        for (int k = 0; k < DD_FEW; ++k) on[k] = k < K && conv[(long long)min(k, K - 1) * N + n] != 0;
-#pragma unroll
-        for (int k = 0; k < DD_FEW; ++k)
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                x[k][r] = 0.0f;
-                if (on[k]) x[k][r] = xc[((long long)k * 3 + r) * N + n];
-            }
-        unsigned kept = 0u;
-#pragma unroll
-        for (int k = 0; k < DD_FEW; ++k) {
-#pragma unroll
-            for (int j = 0; j < k; ++j)
-                if (((kept >> j) & 1u) && closer(x[k], x[j], md2)) on[k] = false;
-            kept |= (on[k] ? 1u : 0u) << k;
-        }
+        const unsigned kept = dedupe_point(N, K, n, md2, xc, conv, keep);
         offsets[n] = (int)kept;
         mine += __popc(kept);
-#pragma unroll
-        for (int k = 0; k < DD_FEW; ++k)
-            if (k < K) keep[(long long)k * N + n] = (uint8_t)((kept >> k) & 1u);
     }
     tile_sum(mine, sums);
 }
 
 // Eight threads per point: SIMD lane 8 g + i holds lanes k = g, 8 + g, ... (at most 8 T) of the i-th of the wave's 8 points,
-// so that all loads of a point travel together.
+// so that all loads of a point travel together.  Returns what is kept of the point, bit k for lane k (wave-wide call).
 // Bound: memory (13 bytes per lane) on large batches, two round trips and the launch on small ones.  (One thread per point
 // and lane after lane, kept roots read again for every comparison: 48 us on 200,000 points x 24 lanes, 19 us on 37; now
 // 21 and 4.5.)
+template <int T>
+__device__ __forceinline__ u64 dedupe_points(long long N, int K, long long n, bool live, float md2, const float *__restrict__ xc,
+                                             const uint8_t *__restrict__ conv, uint8_t *__restrict__ keep)
+{
+    const int lane = threadIdx.x & 63, i = lane & 7, g = lane >> 3;
+    const u64 point = 0x0101010101010101ull << i;        // the SIMD lanes of this lane's point
+    unsigned open = 0u, kept = 0u;          // bit t: lane 8 t + g of the point
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+        if (8 * t + g < K && live) open |= (conv[(long long)(8 * t + g) * N + n] != 0 ? 1u : 0u) << t;
+    float x[T][3];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            x[t][r] = 0.0f;
+            if ((open >> t) & 1u) x[t][r] = xc[((long long)(8 * t + g) * 3 + r) * N + n];
+        }
+    while (__any(open != 0u)) {
+        // the point's first open lane: slot ft of SIMD lane src
+        int ft = 0, src = lane;
+        bool found = false;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const unsigned long long m = __ballot((open >> t) & 1u) & point;
+            if (!found && m) {
+                found = true;
+                ft = t;
+                src = __ffsll((long long)m) - 1;
+            }
+        }
+        float y[3] = {x[0][0], x[0][1], x[0][2]}, c[3];
+#pragma unroll
+        for (int t = 1; t < T; ++t)
+#pragma unroll
+            for (int r = 0; r < 3; ++r) y[r] = ft == t ? x[t][r] : y[r];      // ft is the same in all lanes of the point
+#pragma unroll
+        for (int r = 0; r < 3; ++r) c[r] = __shfl(y[r], src);
+        if (found) {
+            if (lane == src) {
+                kept |= 1u << ft;
+                open &= ~(1u << ft);
+            }
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (closer(x[t], c, md2)) open &= ~(1u << t);
+        }
+    }
+    u64 mask = 0ull;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const unsigned long long m = __ballot((kept >> t) & 1u) & point;
+        // the bits of the point's 8 lanes, 8 places apart, side by side
+        mask |= (((m >> i) * 0x0102040810204080ull) >> 56) << (8 * t);
+        if (8 * t + g < K && live) keep[(long long)(8 * t + g) * N + n] = (uint8_t)((kept >> t) & 1u);
+    }
+    return mask;
+}
 template <int T>
 __global__ __launch_bounds__(256) void k_dedupe(long long N, int K, float md2, const float *__restrict__ xc,
                                                 const uint8_t *__restrict__ conv, uint8_t *__restrict__ keep,
                                                 int *__restrict__ offsets, int tile, int *__restrict__ sums)
 {
     const int lane = threadIdx.x & 63, i = lane & 7, g = lane >> 3;
-    const unsigned long long point = 0x0101010101010101ull << i;        // the SIMD lanes of this lane's point
     const long long n0 = (long long)blockIdx.x * tile, n1 = min(N, n0 + tile);
     int mine = 0;
     for (long long b = n0 + (threadIdx.x >> 6) * 8; b < n1; b += 32) {  // wave-uniform
-        const bool live = b + i < n1;
-        const long long n = live ? b + i : n1 - 1;
-        unsigned open = 0u, kept = 0u;          // bit t: lane 8 t + g of the point
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-            if (8 * t + g < K && live) open |= (conv[(long long)(8 * t + g) * N + n] != 0 ? 1u : 0u) << t;
-        float x[T][3];
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                x[t][r] = 0.0f;
-                if ((open >> t) & 1u) x[t][r] = xc[((long long)(8 * t + g) * 3 + r) * N + n];
-            }
-        while (__any(open != 0u)) {
-            // the point's first open lane: slot ft of SIMD lane src
-            int ft = 0, src = lane;
-            bool found = false;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const unsigned long long m = __ballot((open >> t) & 1u) & point;
-                if (!found && m) {
-                    found = true;
-                    ft = t;
-                    src = __ffsll((long long)m) - 1;
-                }
-            }
-            float y[3] = {x[0][0], x[0][1], x[0][2]}, c[3];
-#pragma unroll
-            for (int t = 1; t < T; ++t)
-#pragma unroll
-                for (int r = 0; r < 3; ++r) y[r] = ft == t ? x[t][r] : y[r];      // ft is the same in all lanes of the point
-#pragma unroll
-            for (int r = 0; r < 3; ++r) c[r] = __shfl(y[r], src);
-            if (found) {
-                if (lane == src) {
-                    kept |= 1u << ft;
-                    open &= ~(1u << ft);
-                }
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-                    if (closer(x[t], c, md2)) open &= ~(1u << t);
-            }
-        }
-        int count = 0;
-        unsigned mask = 0u;
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const unsigned long long m = __ballot((kept >> t) & 1u) & point;
-            count += __popcll(m);
-            // the bits of the point's 8 lanes, 8 places apart, side by side
-            if (t < 4) mask |= (unsigned)(((m >> i) * 0x0102040810204080ull) >> 56) << (8 * t);
-            if (8 * t + g < K && live) keep[(long long)(8 * t + g) * N + n] = (uint8_t)((kept >> t) & 1u);
-        }
-        if (g == 0 && live) {
-            offsets[n] = K <= 32 ? (int)mask : count;
-            mine += count;
+        const long long n = min(b + i, n1 - 1);
+        const u64 kept = dedupe_points<T>(N, K, n, b + i < n1, md2, xc, conv, keep);
+        if (g == 0 && b + i < n1) {
+            offsets[n] = K <= 32 ? (int)(unsigned)kept : __popcll(kept);
+            mine += __popcll(kept);
         }
     }
     tile_sum(mine, sums);
+}
+
+// The kept roots of point n, bits of m, from place o of the packed list on (entries from cap on are left out)
+__device__ __forceinline__ void pack_point(long long N, long long cap, long long n, u64 m, long long o, const float *__restrict__ xc,
+                                           float *__restrict__ roots, int32_t *__restrict__ lane)
+{
+    for (; m && o < cap; m &= m - 1ull, ++o) {
+        const int k = __builtin_ctzll(m);
+        if (roots) {
+            roots[o * 3 + 0] = xc[((long long)k * 3 + 0) * N + n];
+            roots[o * 3 + 1] = xc[((long long)k * 3 + 1) * N + n];
+            roots[o * 3 + 2] = xc[((long long)k * 3 + 2) * N + n];
+        }
+        if (lane) lane[o] = k;
+    }
+}
+
+// Removal and packing in one launch: a block takes 1024 points (T = 0, K <= DD_FEW) or 128 (K <= 8 T), keeps what it found of them in registers or
+// LDS, and learns by tickets and look-back (k_scan) how much the blocks before it kept.  A single block asks nobody.
+// look: the words of this kernel alone, its own last block clears them (look_finish).
+// Bound: latency of launch, loads and look-back; where it is launched, and its times, see launch_dedupe_one.
+template <int T>
+__global__ __launch_bounds__(1024) void k_dedupe_one(long long N, int K, long long cap, float md2, const float *__restrict__ xc,
+                                                     const uint8_t *__restrict__ conv, uint8_t *__restrict__ keep,
+                                                     int *__restrict__ offsets, float *__restrict__ roots, int32_t *__restrict__ lane_out,
+                                                     u64 *__restrict__ look)
+{
+    constexpr int PTS = T == 0 ? 1024 : 128;
+    __shared__ u64 s_mask[T == 0 ? 1 : PTS];
+    __shared__ int s_tot[16], s_before;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, ticket = gridDim.x > 1 ? look_ticket(look) : 0;
+    const long long n0 = (long long)ticket * PTS, n = n0 + threadIdx.x;
+    const bool mine = threadIdx.x < PTS && n < N;             // the point that this thread packs
+    u64 kept = 0ull;
+    if constexpr (T == 0) {
+        if (mine) kept = dedupe_point(N, K, n, md2, xc, conv, keep);
+    } else {
+        const int i = wid * 8 + (lane & 7);
+        const u64 m = dedupe_points<T>(N, K, min(n0 + i, N - 1), n0 + i < N, md2, xc, conv, keep);
+        if (lane < 8) s_mask[i] = m;
+        __syncthreads();
+        if (mine) kept = s_mask[threadIdx.x];
+    }
+    const int c = __popcll(kept);
+    int inc = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(inc, d);
+        if (lane >= d) inc += o;
+    }
+    if (lane == 63) s_tot[wid] = inc;
+    __syncthreads();
+    if (wid == 0) {
+        const int sum = scan_totals(s_tot, 16, lane), before = gridDim.x > 1 ? look_back(look, ticket, sum, lane) : 0;
+        if (lane == 0) {
+            s_before = before;
+            if (ticket == (int)gridDim.x - 1) offsets[N] = before + sum;
+        }
+    }
+    __syncthreads();
+    if (mine) {
+        const int o = s_before + s_tot[wid] + inc - c;
+        offsets[n] = o;
+        if (roots || lane_out) pack_point(N, cap, n, kept, o, xc, roots, lane_out);
+    }
+    if (gridDim.x > 1 && wid == 0) look_finish(look, (int)gridDim.x, lane);
 }
 
 // offsets and the packed list: roots [total][3] and lane index k, point n owns entries offsets[n] .. offsets[n+1]
@@ -3724,22 +3815,14 @@ __global__ __launch_bounds__(256) void k_dedupe_pack(long long N, int K, long lo
         if (n >= n1) continue;
         offsets[n] = at;
         if (!roots && !lane) continue;
-        long long o = at;
+        const long long o = at;
         unsigned long long m = (unsigned)info;
         if (K > 32) {
             m = 0ull;
             if (c > 0)
                 for (int k = 0; k < K; ++k) m |= (unsigned long long)(keep[(long long)k * N + n] != 0) << k;
         }
-        for (; m && o < cap; m &= m - 1ull, ++o) {
-            const int k = __builtin_ctzll(m);
-            if (roots) {
-                roots[o * 3 + 0] = xc[((long long)k * 3 + 0) * N + n];
-                roots[o * 3 + 1] = xc[((long long)k * 3 + 1) * N + n];
-                roots[o * 3 + 2] = xc[((long long)k * 3 + 2) * N + n];
-            }
-            if (lane) lane[o] = k;
-        }
+        pack_point(N, cap, n, m, o, xc, roots, lane);
     }
     if (threadIdx.x == 0 && n1 == N) offsets[N] = run;
 }
