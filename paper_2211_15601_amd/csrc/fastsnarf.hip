@@ -531,12 +531,13 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
     ++ctx->pre_serial;
     // poses per pass over the weights: see k_precompute
     const bool wide = (long long)vblocks * ((G.P + 3) / 4) >= 4ll * ctx->n_cus;
-#define FS_LAUNCH_PRE(NP)                                                                                              \
-    k_precompute<NP><<<(vblocks + N_XCD - 1) / N_XCD * N_XCD * ((G.P + (NP) - 1) / (NP)), 256, 0, st>>>(               \
+#define FS_LAUNCH_PRE(NP, FEW)                                                                                         \
+    k_precompute<NP, FEW><<<(vblocks + (FEW) + N_XCD - 1) / N_XCD * N_XCD * ((G.P + (NP) - 1) / (NP)), 256, 0, st>>>(       \
         G, d_W, d_B, ctx->T, ctx->Bdev, ctx->Binv, ctx->Bok, reinterpret_cast<int *>(ctx->cursor + CUR_GRID),          \
         ctx->pre_serial, voxel ? ctx->Y : nullptr, ctx->bb_ord, ctx->count, ncp, vblocks, (G.P + (NP) - 1) / (NP))
-    if (wide) FS_LAUNCH_PRE(4);
-    else FS_LAUNCH_PRE(1);
+    if (wide) FS_LAUNCH_PRE(4, false);
+    else if ((long long)vblocks * G.P <= 2ll * ctx->n_cus) FS_LAUNCH_PRE(1, true);
+    else FS_LAUNCH_PRE(1, false);
 #undef FS_LAUNCH_PRE
     if (voxel) {
         const CorrP &C = ctx->C;

@@ -18,7 +18,7 @@ __device__ __forceinline__ int pose_of(const int32_t *__restrict__ pose, long lo
     const int p = pose[n];
     return p < 0 ? 0 : (p >= P ? P - 1 : p);
 }
-constexpr int FS_MAX_CORR_K_DEV = 8;
+constexpr int FS_MAX_CORR_K_DEV = 8, FS_BONES_MAX = 64;
 
 // number of lanes of the wave with `on`, as a scalar (the compiler compares a 64-bit population count on the vector unit)
 __device__ __forceinline__ int lanes_on(bool on) { return __builtin_amdgcn_readfirstlane(__popcll(__ballot(on))); }
@@ -96,8 +96,7 @@ __device__ __forceinline__ unsigned wave_extent(unsigned lo, unsigned hi)
     return v;
 }
 
-// The first n_poses*n_bones threads also invert their bone's linear part for Eq. (8) and keep a copy
-// of the bone transforms for the backward.
+// n_poses*n_bones threads also invert a bone's linear part for Eq. (8) and keep a copy of the bone transforms for the backward.
 // Y (may be null; voxel-based initial states): the image y_v = T_v x_v of every node is written as well -- the
 // correspondence grid is built on those, and the transforms are in registers here anyway (a pass of its own would
 // read all of T again).  So are the extents of a block's images (bb_part[p][entry][block], ordered-integer images of the
@@ -106,7 +105,10 @@ __device__ __forceinline__ unsigned wave_extent(unsigned lo, unsigned hi)
 // NP: poses that share one pass over a node's weights.  Large grids, bound by memory: four (8-pose 128x128x32 grid: 1 -> 109 us,
 // 2 -> 86, 4 -> 87; all groups of a node on one XCD: 110 -> 87).  Grids of fewer than four blocks of 256 nodes per CU: one,
 // so that there are waves to hide the latency of weights and transforms (4 poses of 61x47x13 nodes: 4 -> 27 us, 2 -> 16, 1 -> 10).
-template <int NP>
+// FEW: no more than two blocks of one pose per CU.  A wave has no other to hide behind: the bones come from LDS and the next eight weights are on
+// their way while eight are worked in, so that it waits for memory once, not for scalar operands and weights every four bones (64x64x16 nodes: 24 bones
+// 10.2 -> 7.5 us, a frame with 64 bones 54 -> 48).  With more blocks LDS is the slower source (four poses 14.4, from LDS 15.9).
+template <int NP, bool FEW>
 __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__restrict__ W,
                                                     const float *__restrict__ B, float *__restrict__ T,
                                                     float *__restrict__ Bcopy, float *__restrict__ Binv,
@@ -117,6 +119,8 @@ __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__rest
     // block -> (nodes, group of poses): blocks go to the 8 XCDs in turn, the groups of the same nodes to the same XCD one
     // after the other, so that its L2 has the weights
     const int t = (int)blockIdx.x / N_XCD, bt = t / groups, group = t - bt * groups, blk = bt * N_XCD + (int)blockIdx.x % N_XCD;
+    if (FEW && blk == vblocks && group == 0)          // a block without nodes, which would be the last to end if it had some, inverts the bones
+        for (int i = threadIdx.x; i < G.P * G.nb; i += blockDim.x) bone_inverse(i, B, Bcopy, Binv, Bok);
     if (blk >= vblocks) return;
     __shared__ __attribute__((aligned(16))) float s_tiles[4][64 * 12];
     __shared__ unsigned s_ext[NP][4][6];
@@ -125,8 +129,9 @@ __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__rest
     const long long v = (long long)blk * blockDim.x + threadIdx.x, v0 = v - (threadIdx.x & 63);   // v0: the wave's first node
     if (group == 0) {
         if (v == 0) state[GRID_NUMBER] = serial;
-        for (long long i = v; i < (long long)G.P * G.nb; i += (long long)vblocks * blockDim.x)
-            bone_inverse((int)i, B, Bcopy, Binv, Bok);
+        if (!FEW)
+            for (long long i = v; i < (long long)G.P * G.nb; i += (long long)vblocks * blockDim.x)
+                bone_inverse((int)i, B, Bcopy, Binv, Bok);
         if (Y)
             for (long long i = v; i < ncount; i += (long long)vblocks * blockDim.x) ccount[i] = 0;
     }
@@ -143,7 +148,45 @@ __global__ __launch_bounds__(256) void k_precompute(GridP G, const float *__rest
     for (int q = 0; q < NP; ++q)
 #pragma unroll
         for (int e = 0; e < 12; ++e) acc[q][e] = 0.0f;
-    if (live) {
+    if constexpr (FEW) {
+        static_assert(NP == 1, "one pose's bones are staged");
+        __shared__ float4 s_bone[FS_BONES_MAX * 3];
+        const float4 *Bp = reinterpret_cast<const float4 *>(B + (long long)p0 * G.nb * 12);
+        for (int i = threadIdx.x; i < G.nb * 3; i += 256) s_bone[i] = Bp[i];
+        float wn[8];
+        auto weights = [&](int b0) {
+#pragma unroll
+            for (int j = 0; j < 8; j += 4) {
+                float4 w4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (vec) {
+                    if (b0 + j < G.nb) w4 = *reinterpret_cast<const float4 *>(w + b0 + j);
+                } else {
+                    if (b0 + j < G.nb) w4.x = w[b0 + j];
+                    if (b0 + j + 1 < G.nb) w4.y = w[b0 + j + 1];
+                    if (b0 + j + 2 < G.nb) w4.z = w[b0 + j + 2];
+                    if (b0 + j + 3 < G.nb) w4.w = w[b0 + j + 3];
+                }
+                wn[j] = w4.x; wn[j + 1] = w4.y; wn[j + 2] = w4.z; wn[j + 3] = w4.w;
+            }
+        };
+        weights(0);
+        __syncthreads();
+        for (int b0 = 0; b0 < G.nb; b0 += 8) {
+            float wv[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) wv[j] = wn[j];
+            weights(b0 + 8);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (b0 + j < G.nb) {
+                    const float4 r0 = s_bone[(b0 + j) * 3], r1 = s_bone[(b0 + j) * 3 + 1], r2 = s_bone[(b0 + j) * 3 + 2];
+                    const float bone[12] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w, r2.x, r2.y, r2.z, r2.w};
+#pragma unroll
+                    for (int e = 0; e < 12; ++e) acc[0][e] = b0 + j == 0 ? wv[0] * bone[e] : FS_FMA(wv[j], bone[e], acc[0][e]);
+                }
+            }
+        }
+    } else if (live) {
         for (int b0 = 0; b0 < G.nb; b0 += 4) {
             float wv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
             if (vec) {
@@ -3548,7 +3591,13 @@ __global__ __launch_bounds__(1024) void k_grad_bones_final(int nblk, int nout, c
     const int j = threadIdx.x & 15, h = threadIdx.x >> 4, p = blockIdx.y, o = blockIdx.x * 16 + j;
     float a = 0.0f;
     if (o < nout)
-        for (int b = h; b < nblk; b += 64) a += part[((long long)p * nblk + b) * nout + o];
+        for (int b0 = h; b0 < nblk; b0 += 512) {          // eight loads on their way together
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = b0 + 64 * i < nblk ? part[((long long)p * nblk + b0 + 64 * i) * nout + o] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a += v[i];
+        }
     a += __shfl_xor(a, 16);
     a += __shfl_xor(a, 32);
     if ((threadIdx.x & 63) < 16) s_sum[threadIdx.x >> 6][j] = a;
