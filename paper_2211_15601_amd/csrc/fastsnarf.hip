@@ -43,8 +43,9 @@ struct fs_ctx {
     uint8_t *ccnt;     // [P][ncell] number of candidates of a correspondence cell
     float4 *cinit;     // [P][ncell][ck][4] initial state of every candidate (k_corr_init)
     unsigned *cursor;  // work cursor of the solve kernel
-    int *gcount;       // [P*ncells + 1] per-cell lane counts, then offsets (backward)
-    int *gcount_solve; // [P*ncells + 1] per-cell counts of converged lanes written by the last fs_solve that gave slots
+    int *cells;        // [P*ncells] converged lanes per grid cell while a call counts them, zero between calls (behind the look-back words)
+    int *gplace;       // [cell_words] where the cells' records begin in the list of a backward from arrays (place_cells)
+    int *gplace_solve; // [cell_words] the same for the positions of the last fs_solve that gave them
     long long slots_N; // N of that fs_solve (0: none)
     int slots_K;
     bool slots_list;   // that solve drew its pairs from the candidate list: pairs without a candidate have no record
@@ -177,7 +178,7 @@ int grid1d(long long n, int block) { return (int)((n + block - 1) / block); }
 void free_all(fs_ctx *c)
 {
     void *ptrs[] = {c->T, c->Bdev, c->Binv, c->Bok, c->GT, c->Y, c->bb_ord, c->bbox,
-                    c->cell_of, c->count, c->offset, c->fill, c->order, c->cand, c->cursor, c->gcount, c->gcount_solve, c->gpos, c->grec, c->look, c->srec, c->gpart, c->vlist, c->cinit, c->vcnt, c->vgcell, c->vhist, c->ccnt};
+                    c->cell_of, c->count, c->offset, c->fill, c->order, c->cand, c->cursor, c->gplace, c->gplace_solve, c->gpos, c->grec, c->look, c->srec, c->gpart, c->vlist, c->cinit, c->vcnt, c->vgcell, c->vhist, c->ccnt};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -191,33 +192,41 @@ constexpr int DD_ONE_BLOCKS = 1024;                       // of k_dedupe_one at 
 constexpr long long SORT_MAX_COUNTS = 1ll << 24;          // (buckets x blocks) of the sort that orders the list by place
 
 // The look-back words are made and cleared with the context, for the largest call it accepts: 8 bytes per 8192 points of
-// K * N < 2^31, 2 MiB at most.  Growing them on demand, with a launch that clears them, breaks where the stream records a graph:
+// K * N < 2^31, 2 MiB at most.  The counts of converged lanes per cell, 4 bytes for every 48 of the transform grid, are behind them: they are zero
+// between calls as well.  Growing them on demand, with a launch that clears them, breaks where the stream records a graph:
 // the launch does not run, and calls before the graph's first replay find words of any value.
+long long all_cells(const fs_ctx *c) { return (long long)c->G.P * (c->G.nx - 1) * (c->G.ny - 1) * (c->G.nz - 1); }
 bool look_create(fs_ctx *c)
 {
-    const GridP &G = c->G;
-    long long blocks = scan_blocks(G.P * (G.nx - 1) * (G.ny - 1) * (G.nz - 1));
+    long long blocks = 0;
     if (c->prm.init_mode == FS_INIT_VOXEL) {
         const long long N = ((1ll << 31) - 1) / c->C.ck;
-        blocks = std::max({blocks, (long long)scan_blocks(G.P * c->C.ncell), (long long)scan_blocks((int)SORT_MAX_COUNTS),
+        blocks = std::max({blocks, (long long)scan_blocks(c->G.P * c->C.ncell), (long long)scan_blocks((int)SORT_MAX_COUNTS),
                            (long long)grid1d(N, 1024 * list_per_thread(N)), 1ll << 9});
     }
     c->look_words = (size_t)blocks + LOOK_HEAD;
     c->dd_look_at = c->look_words + LOOK_HEAD;                  // k_dedupe_one has words of its own behind them
     c->look_words = c->dd_look_at + LOOK_HEAD + DD_ONE_BLOCKS;
+    c->look_words += c->look_words & 1;                         // the counts are read 16 bytes at a time
+    const size_t cells_at = c->look_words;
+    c->look_words += ((size_t)all_cells(c) + 1) / 2;
     c->look_dirty = false;
-    return dev_alloc(&c->look, c->look_words) && hipMemset(c->look, 0, c->look_words * sizeof(u64)) == hipSuccess;
+    if (!dev_alloc(&c->look, c->look_words)) return false;
+    c->cells = reinterpret_cast<int *>(c->look + cells_at);
+    return hipMemset(c->look, 0, c->look_words * sizeof(u64)) == hipSuccess;
 }
 
-// Before the first launch of a call that scans: clears the words if a launch has failed since they were used.
+// Before the first launch of a call that counts on words that are zero: clears them if a launch has failed since they were used.
 fs_status look_ready(fs_ctx *c, const char *what)
 {
     if (!c->look_dirty) return FS_OK;
     if (hipStreamSynchronize(c->stream) != hipSuccess || hipMemset(c->look, 0, c->look_words * sizeof(u64)) != hipSuccess ||
         hipStreamSynchronize(nullptr) != hipSuccess)
         return launch_status(c, what);
+    k_fill_zero_i32<<<1, 64, 0, c->stream>>>(1, reinterpret_cast<int *>(c->cursor + CUR_ALL));
+    k_fill_zero_i32<<<1, 64, 0, c->stream>>>(N_XCD, reinterpret_cast<int *>(c->cursor + CUR_XCD));
     c->look_dirty = false;
-    return FS_OK;
+    return launch_status(c, what);
 }
 
 // exclusive scan of src[0..n) into a[0..n) (src == nullptr: in place) on the context's stream, a[n] = total; returns what
@@ -273,14 +282,8 @@ constexpr int FS_LDS_BIG_WAVES = 12;
 constexpr size_t FS_LDS_GRID_MAX_BIG = 148 * 1024;
 constexpr size_t L2_BYTES = 4u << 20;       // of an XCD
 
-// the counts of converged lanes per grid cell that a solve with slots keeps
-fs_status need_solve_counts(fs_ctx *c, int ncell)
-{
-    const long long ncp = (long long)c->G.P * ncell;
-    if (ncp + 1 >= (1ll << 31)) return fail(c, FS_E_SHAPE, "fs_solve: too many grid cells for d_slot");
-    if (!c->gcount_solve && !dev_alloc(&c->gcount_solve, (size_t)ncp + 1)) return fail(c, FS_E_ALLOC, "fs_solve: out of device memory");
-    return FS_OK;
-}
+// where the places of the cells go
+bool need_places(fs_ctx *c, int **p) { return *p || dev_alloc(p, (size_t)cell_words(all_cells(c))); }
 
 // Kernels of the solve by the size of a batch (pairs = K * N; all three give the same bits).  What bounds a small batch is
 // max_iters times the latency of a step, which is the shorter the more lanes share a pair (16 lanes 0.35 us, 4 0.5, one 1.0 to 1.2);
@@ -702,15 +705,11 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     }
     hipStream_t st = ctx->stream;
     const int ncell = (ctx->G.nx - 1) * (ctx->G.ny - 1) * (ctx->G.nz - 1);
+    const long long ncp = all_cells(ctx);              // P * V * 12 < 2^31
+    if (d_slot && !need_places(ctx, &ctx->gplace_solve)) return fail(ctx, FS_E_ALLOC, "fs_solve: out of device memory");
+    { fs_status ls = look_ready(ctx, "fs_solve"); if (ls != FS_OK) return ls; }
     if (kind != SOLVE_LARGE) {
-        int *counts = nullptr;
-        if (d_slot) {
-            fs_status cs = need_solve_counts(ctx, ncell);
-            if (cs != FS_OK) return cs;
-            counts = ctx->gcount_solve;
-            const long long nc = (long long)ctx->G.P * ncell + 1;
-            k_fill_zero_i32<<<(int)std::min<long long>(grid1d(nc, 256), 4096), 256, 0, st>>>(nc, counts);
-        }
+        int *counts = d_slot ? ctx->cells : nullptr;
         hipEvent_t ev0 = nullptr, ev1 = nullptr;
         if (ctx->timing && hipEventCreate(&ev0) == hipSuccess && hipEventCreate(&ev1) == hipSuccess) (void)hipEventRecord(ev0, st);
         // grid in LDS: about one block per CU, as many waves in it as the batch gives it; else blocks of four waves
@@ -740,11 +739,11 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         if (quad)                                                                                                      \
             k_solve_quad<IM, L><<<qg, threads, (L) ? grid_bytes : 0, st>>>(                                            \
                 ctx->G, S, I, ctx->T, d_xq, d_pose, d_x0, d_Jinv0, d_valid0, d_xc, d_conv, d_Jinv, d_iters, d_slot,    \
-                d_slot ? ctx->srec : nullptr, counts, ncell);                                                          \
+                d_slot ? ctx->srec : nullptr, counts, ncell, ctx->cursor + CUR_TOTAL);                                 \
         else                                                                                                           \
             k_solve_once<IM, L><<<qg, threads, (L) ? grid_bytes : 0, st>>>(                                            \
                 ctx->G, S, I, ctx->T, d_xq, d_pose, d_x0, d_Jinv0, d_valid0, d_xc, d_conv, d_Jinv, d_iters, d_slot,    \
-                d_slot ? ctx->srec : nullptr, counts, ncell, state);                                                   \
+                d_slot ? ctx->srec : nullptr, counts, ncell, state, ctx->cursor + CUR_TOTAL);                          \
     } while (0)
         const int im = !fused ? 2 : (voxel_list ? 1 : 0);
         if (staged) {
@@ -761,6 +760,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
             (void)hipEventRecord(ev1, st);
             ctx->timed->emplace_back(ev0, ev1);
         }
+        if (d_slot) k_place_cells<<<grid1d(ncp, CELL_TILE), 256, 0, st>>>((int)ncp, ctx->cells, ctx->gplace_solve, ctx->cursor + CUR_TOTAL);
         fs_status qs = launch_status(ctx, "fs_solve");
         if (qs == FS_OK && d_slot) {
             ctx->slots_N = N;
@@ -772,20 +772,9 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const int2 *list = nullptr;
     const int *list_len = nullptr;
     S.xcd_ranges = 0;
-    int *cell_count = nullptr;
-    // every wave that draws chunks (all four of a k_solve block, the producer of a k_solve_ws block) owns the
-    // chunk of its own number to begin with; the shared cursor starts behind those
-    const unsigned drawers = (unsigned)(blocks * wpb);
+    int *const cell_count = d_slot ? ctx->cells : nullptr;
     int look_blocks = 0;         // look-back words that the last kernel of this call has to clear
-    bool cleared = false;        // the counts and the cursor are cleared by the kernel that makes the list
-    if (d_slot) {
-        fs_status cs = need_solve_counts(ctx, ncell);
-        if (cs != FS_OK) return cs;
-        cell_count = ctx->gcount_solve;
-    }
-    const long long ncounts = cell_count ? (long long)ctx->G.P * ncell + 1 : 0;
     if (voxel_list) {
-        { fs_status ls = look_ready(ctx, "fs_solve"); if (ls != FS_OK) return ls; }
         const size_t need_h = (size_t)nb * sblk + 1;
         if ((size_t)N > ctx->vcap) {
             (void)hipStreamSynchronize(st);
@@ -820,7 +809,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         } else {
 #define FS_LAUNCH_LIST(U)                                                                                              \
     k_voxel_list<U><<<grid1d(N, 1024 * (U)), 1024, boxes, st>>>(ctx->G, I, N, K, d_xq, d_pose, ctx->vcnt, ctx->vlist,  \
-                                                                ctx->cursor, drawers, (unsigned)S.chunk, cell_count, ncounts, ctx->look)
+                                                                ctx->cursor, ctx->look)
             const int U = list_per_thread(N);
             look_blocks = grid1d(N, 1024 * U);
             if (U == 2) FS_LAUNCH_LIST(2);
@@ -828,11 +817,9 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
             else FS_LAUNCH_LIST(8);
 #undef FS_LAUNCH_LIST
             list_len = reinterpret_cast<const int *>(ctx->cursor + CUR_LIST);
-            cleared = true;
         }
         list = ctx->vlist;
     }
-    if (!cleared) k_fill_zero_i32<<<cell_count ? (int)std::min<long long>(grid1d(ncounts, 256), 4096) : 1, 256, 0, st>>>(ncounts, cell_count, ctx->cursor, drawers, (unsigned)S.chunk);
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (ctx->timing && hipEventCreate(&ev0) == hipSuccess && hipEventCreate(&ev1) == hipSuccess) (void)hipEventRecord(ev0, st);
     if (lds) {
@@ -879,15 +866,17 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         (void)hipEventRecord(ev1, st);
         ctx->timed->emplace_back(ev0, ev1);
     }
-    const dim3 ub(grid1d(N, 256), K);       // one thread per pair: x = point, y = initial state
-    if (with_J && voxel_list)
-        k_solve_unpack<true, true><<<ub, 256, 0, st>>>(N, S.total, ctx->vcnt, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot, ctx->look, look_blocks);
-    else if (with_J)
-        k_solve_unpack<true, false><<<ub, 256, 0, st>>>(N, S.total, nullptr, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot, ctx->look, look_blocks);
-    else if (voxel_list)
-        k_solve_unpack<false, true><<<ub, 256, 0, st>>>(N, S.total, ctx->vcnt, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot, ctx->look, look_blocks);
-    else
-        k_solve_unpack<false, false><<<ub, 256, 0, st>>>(N, S.total, nullptr, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot, ctx->look, look_blocks);
+    // one thread per pair: x = point, y = initial state; rows of blocks before those place the cells
+    const int tiles = d_slot ? grid1d(ncp, CELL_TILE) : 0, bx = grid1d(N, 256), rows = (tiles + bx - 1) / bx;
+    const dim3 ub(bx, rows + K);
+#define FS_LAUNCH_UNPACK(J, Z)                                                                                         \
+    k_solve_unpack<J, Z><<<ub, 256, 0, st>>>(N, S.total, (Z) ? ctx->vcnt : nullptr, ctx->srec, d_xc, d_conv, d_Jinv, d_iters, d_slot, ctx->look, \
+                                             look_blocks, ctx->cursor, rows, tiles, (int)ncp, ctx->cells, ctx->gplace_solve)
+    if (with_J && voxel_list) FS_LAUNCH_UNPACK(true, true);
+    else if (with_J) FS_LAUNCH_UNPACK(true, false);
+    else if (voxel_list) FS_LAUNCH_UNPACK(false, true);
+    else FS_LAUNCH_UNPACK(false, false);
+#undef FS_LAUNCH_UNPACK
     fs_status lst = launch_status(ctx, "fs_solve");
     if (lst == FS_OK && d_slot) {
         ctx->slots_N = N;
@@ -926,9 +915,8 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
     const GridP &G = ctx->G;
     const int ncell = (G.nx - 1) * (G.ny - 1) * (G.nz - 1);
     const long long ncp = (long long)G.P * ncell;
-    if (ncp + 1 >= (1ll << 31)) return fail(ctx, FS_E_SHAPE, "fs_grad: too many grid cells");
     if (!ctx->GT && !dev_alloc(&ctx->GT, (size_t)G.P * G.V * 12)) return fail(ctx, FS_E_ALLOC, "fs_grad: out of device memory");
-    if (!ctx->gcount && !dev_alloc(&ctx->gcount, (size_t)ncp + 1)) return fail(ctx, FS_E_ALLOC, "fs_grad: out of device memory");
+    if (!d_slot && !need_places(ctx, &ctx->gplace)) return fail(ctx, FS_E_ALLOC, "fs_grad: out of device memory");
     if (!ctx->gpart) {
         // 16 nodes per wave and pass, so 128 nodes are two passes of a block; no more blocks than are resident with six slots
         // (8 poses of 128x128x32 nodes, us: 512 blocks 82, 768 103, 1024 89; one pose of 65 k nodes: 256 blocks 8.6, 512 6.6)
@@ -947,21 +935,18 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
     }
     { fs_status ls = look_ready(ctx, "fs_grad"); if (ls != FS_OK) return ls; }
     hipStream_t st = ctx->stream;
-    const int *pos = ctx->gpos, *counts = nullptr;
-    if (d_slot) {
-        // the solve already counted its converged lanes per cell and gave each its slot; its counts are
-        // left as they are, so the backward can be repeated
-        pos = d_slot;
-        counts = ctx->gcount_solve;
-    } else {
-        k_fill_zero_i32<<<(int)std::min<long long>(grid1d(ncp + 1, 256), 4096), 256, 0, st>>>(ncp + 1, ctx->gcount);
+    // With d_slot the solve has counted its converged lanes per cell, given each its position and placed the cells; all of that is
+    // left as it is, so the backward can be repeated
+    const int *const pos = d_slot ? d_slot : ctx->gpos, *const places = d_slot ? ctx->gplace_solve : ctx->gplace;
+    unsigned *const records = ctx->cursor + CUR_TOTAL + (d_slot ? 0 : 1);
+    if (!d_slot) {
         if (N > 0) {
             const int ki = K >= 8 ? 8 : 1;
             const long long waves = ((N + WAVE / ki - 1) / (WAVE / ki)) * ((K + ki - 1) / ki);
-            k_grad_count<<<grid1d(waves * WAVE, 256), 256, 0, st>>>(G, d_xc, d_conv, d_pose, N, K, ki, ncell, ctx->gcount, ctx->gpos);
+            k_grad_count<<<grid1d(waves * WAVE, 256), 256, 0, st>>>(G, d_xc, d_conv, d_pose, N, K, ki, ncell, ctx->cells, ctx->gpos, records);
         }
+        k_place_cells<<<grid1d(ncp, CELL_TILE), 256, 0, st>>>((int)ncp, ctx->cells, ctx->gplace, records);
     }
-    const int look_blocks = scan_exclusive(ctx, (int)ncp, ctx->gcount, counts);
     if (N > 0) {
         // small batches: several threads share a point's lanes so that the chip has enough threads in flight
         const int groups = N >= (1 << 19) ? 1 : (K >= 8 ? 8 : (K >= 4 ? 4 : (K >= 2 ? 2 : 1)));
@@ -969,7 +954,7 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
         float4 *grec4 = reinterpret_cast<float4 *>(ctx->grec);
         const int *state = reinterpret_cast<const int *>(ctx->cursor + CUR_GRID);
 #define FS_LAUNCH_RECORDS(R, ...)                                                                                     \
-    k_grad_records<R, __VA_ARGS__><<<rg, 256, 0, st>>>(G, ctx->T, d_xc, d_Jinv, d_conv, d_gxc, d_pose, N, K, ncell, ctx->gcount, pos, \
+    k_grad_records<R, __VA_ARGS__><<<rg, 256, 0, st>>>(G, ctx->T, d_xc, d_Jinv, d_conv, d_gxc, d_pose, N, K, ncell, places, pos, \
                                                        grec4, d_gxq, groups, (R) ? ctx->srec : nullptr,               \
                                                        ((R) && ctx->slots_list) ? ctx->vcnt : nullptr, state)
 #define FS_LAUNCH_EXACT(J)                                                                                            \
@@ -993,16 +978,16 @@ fs_status fs_grad(fs_ctx *ctx, const float *d_W, const float *d_xc, const float 
 #undef FS_LAUNCH_EXACT
 #undef FS_LAUNCH_RECORDS
     }
-    if (N > 0) k_grad_pieces<<<grid1d((long long)lanes, PIECE_R), 64 * PIECE_WAVES, 0, st>>>(G, ncp, ctx->gcount, ctx->grec);
+    if (N > 0) k_grad_pieces<<<grid1d((long long)lanes, PIECE_R), 64 * PIECE_WAVES, 0, st>>>(G, records, ctx->grec);
     // crowded grids: one thread per (node, adjacent cell); sparse ones: one thread per node, which walks the 4 cells at
     // its height and hands their share for the node above to the next SIMD lane
     const long long nodes = (long long)G.P * G.V;
     if ((long long)lanes >= 8 * nodes)
-        k_grad_nodes_p<<<grid1d(nodes * 8, 256), 256, 0, st>>>(G, ncell, ctx->gcount, ctx->grec, ctx->GT);
+        k_grad_nodes_p<<<grid1d(nodes * 8, 256), 256, 0, st>>>(G, ncell, places, ctx->grec, ctx->GT);
     else
-        k_grad_nodes_z<<<grid1d(nodes, 256), 256, 0, st>>>(G, ncell, ctx->gcount, ctx->grec, ctx->GT);
+        k_grad_nodes_z<<<grid1d(nodes, 256), 256, 0, st>>>(G, ncell, places, ctx->grec, ctx->GT);
     const int nout = G.nb * 12;
-#define FS_LAUNCH_OUT_S(MT, S) k_grad_outputs<MT, S><<<ctx->gb_blocks, 256, 0, st>>>(G, d_W, ctx->GT, ctx->Bdev, d_gW, ctx->gpart, ctx->look, look_blocks)
+#define FS_LAUNCH_OUT_S(MT, S) k_grad_outputs<MT, S><<<ctx->gb_blocks, 256, 0, st>>>(G, d_W, ctx->GT, ctx->Bdev, d_gW, ctx->gpart)
 #define FS_LAUNCH_OUT(MT)                                                                                              \
     do {                                                                                                               \
         if (G.P == 1) FS_LAUNCH_OUT_S(MT, 1);                                                                          \
@@ -1077,7 +1062,7 @@ static fs_status dedupe_impl(fs_ctx *ctx, const char *who, int *sums, const floa
 #undef FS_LAUNCH_DEDUPE
         k_dedupe_pack<<<tiles, 256, 0, st>>>(N, K, cap, d_xc, d_keep, d_offsets, tile, sums, d_roots, d_lane);
     } else {
-        k_fill_zero_i32<<<1, 64, 0, st>>>(1, d_offsets, nullptr);
+        k_fill_zero_i32<<<1, 64, 0, st>>>(1, d_offsets);
     }
     return launch_status(ctx, who);
 }

@@ -889,14 +889,89 @@ __device__ __forceinline__ void read_record_J(const float4 *__restrict__ r, floa
 // Words of the context's cursor array: CUR_ALL is the work cursor of the solve kernels; CUR_GRID: two words about the grid (GRID_NUMBER).
 // CUR_XCD + j (j = 0 .. 7): the cursor of the j-th eighth of an ordered pair list, relative to the start of that eighth.
 // CUR_LIST: length of the list of pairs that have a candidate (k_voxel_list).
-constexpr int CUR_ALL = 0, CUR_LIST = 1, CUR_GRID = 2, CUR_XCD = 4, CUR_WORDS = 12;
-
-// The blocks of the solve kernel own their first chunk without asking: the shared cursor starts behind `nblocks`
-// chunks, the cursor of range j behind one chunk for every block b with b mod 8 = j.
-__device__ __forceinline__ void reset_cursors(unsigned *__restrict__ cursor, int i, unsigned nblocks, unsigned chunk)
+// CUR_TOTAL, CUR_TOTAL + 1: converged lanes of the last solve that gave positions, and of the last backward from arrays (place_cells).
+// The work cursors are zero between calls: the kernel that follows a solve kernel clears them (reset_cursors).  (A launch of its own before the solve
+// kernel: 2 to 4 us.)
+constexpr int CUR_ALL = 0, CUR_LIST = 1, CUR_GRID = 2, CUR_XCD = 4, CUR_TOTAL = 12, CUR_WORDS = 14;
+__device__ __forceinline__ void reset_cursors(unsigned *__restrict__ cursor, int i)
 {
-    if (i == 0) cursor[CUR_ALL] = nblocks * chunk;
-    if (i < N_XCD) cursor[CUR_XCD + i] = ((nblocks + (N_XCD - 1) - (unsigned)i) / N_XCD) * chunk;
+    if (i == 0) cursor[CUR_ALL] = 0u;
+    if (i < N_XCD) cursor[CUR_XCD + i] = 0u;
+}
+
+// ---- where a grid cell's records lie in the list of the backward -------------------------------------------------------
+// The counts of a solve's converged lanes (one per pose and grid cell) become places: every cell gets a stretch of the list.  The order of the stretches
+// is free, so a block takes a tile of cells, adds its sum to the total with one atomic, and needs nothing from the other blocks.  Cells of a tile follow each
+// other; place(c) is where cell c's stretch begins, place(c) + 1 holds its end, which is the next cell's begin or a word of the tile's own.
+// The counts are zero between calls: they are cleared here, on the way.
+// Bound: memory, 4 bytes read and 4 written per cell.  (Counts cleared by a launch before the solve, then an ordered scan in the backward:
+// two launches, 2 to 4 and 4.5 us on 60 k cells.)
+constexpr int CELL_TILE = 4096, CELL_STRIDE = CELL_TILE + 4;          // ends of tiles: a word, and three for alignment
+__host__ __device__ inline long long cell_words(long long ncp) { return (ncp + CELL_TILE - 1) / CELL_TILE * CELL_STRIDE; }
+__device__ __forceinline__ int place(int c) { return c + (int)((unsigned)c / CELL_TILE) * (CELL_STRIDE - CELL_TILE); }
+
+// tile `t`, by a block of 256 threads
+__device__ __forceinline__ void place_cells(int t, int ncp, int *__restrict__ counts, int *__restrict__ offset, unsigned *__restrict__ total)
+{
+    __shared__ int s_sum[16], s_base;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, c0 = t * CELL_TILE + (int)threadIdx.x * 4;
+    int4 e[4];
+    int at[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const int c = c0 + b * 1024;
+        e[b] = make_int4(0, 0, 0, 0);
+        if (c + 3 < ncp) {
+            e[b] = *reinterpret_cast<const int4 *>(counts + c);
+        } else {
+            if (c < ncp) e[b].x = counts[c];
+            if (c + 1 < ncp) e[b].y = counts[c + 1];
+            if (c + 2 < ncp) e[b].z = counts[c + 2];
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const int c = c0 + b * 1024, sum = e[b].x + e[b].y + e[b].z + e[b].w;
+        if (sum != 0) {
+            if (c + 3 < ncp) *reinterpret_cast<int4 *>(counts + c) = make_int4(0, 0, 0, 0);
+            else
+                for (int i = c; i < ncp; ++i) counts[i] = 0;
+        }
+        int inc = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(inc, d);
+            if (lane >= d) inc += o;
+        }
+        at[b] = inc - sum;
+        if (lane == 63) s_sum[b * 4 + wid] = inc;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int run = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int v = s_sum[i];
+            s_sum[i] = run;
+            run += v;
+        }
+        s_base = (int)atomicAdd(total, (unsigned)run);
+        offset[t * CELL_STRIDE + CELL_TILE] = s_base + run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        int4 o;
+        o.x = s_base + s_sum[b * 4 + wid] + at[b];
+        o.y = o.x + e[b].x;
+        o.z = o.y + e[b].y;
+        o.w = o.z + e[b].z;
+        *reinterpret_cast<int4 *>(offset + t * CELL_STRIDE + (int)threadIdx.x * 4 + b * 1024) = o;
+    }
+}
+__global__ __launch_bounds__(256) void k_place_cells(int ncp, int *__restrict__ counts, int *__restrict__ offset, unsigned *__restrict__ total)
+{
+    place_cells((int)blockIdx.x, ncp, counts, offset, total);
 }
 
 // Per pose the lower corner of the box of node images and the size of a correspondence cell (the arithmetic of cell_index)
@@ -925,22 +1000,18 @@ __device__ __forceinline__ int corr_cell(const InitP &I, const float *s_pose, in
 // pairs that have one, {point n, (pose * ncell + correspondence cell) << 3 | k}, from which the solve draws.  The
 // list is in the order of the points: parts of it in the order in which blocks arrive would mix up to two million
 // points, i.e. several poses' grids (Broyden kernel on the 8-pose batch 1447 instead of 1330 us).  A block takes 1024 U
-// consecutive points.  The counts of the solve's converged lanes (may be null) and its cursor are cleared on the way.
+// consecutive points.
 // Bound: the chain of tickets and memory (17 bytes read or written per point, 8 per pair).  (A counting pass, a scan of two launches,
 // an expanding pass and a clearing pass: 28 us on 1 M ray samples, 42 us on 2 M, 85 us on the 8-pose batch; now 13, 24 and 62.)
 template <int U>
 __global__ __launch_bounds__(1024) void k_voxel_list(GridP G, InitP I, long long N, int K, const float *__restrict__ xq,
                                                      const int32_t *__restrict__ pose, uint8_t *__restrict__ cnt8,
                                                      int2 *__restrict__ list, unsigned *__restrict__ cursor,
-                                                     unsigned nblocks, unsigned chunk, int *__restrict__ counts, long long ncounts,
                                                      u64 *__restrict__ look)
 {
     extern __shared__ float s_pose[];            // [P][6]
     __shared__ int s_tot[16 * U], s_base;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, ticket = look_ticket(look);
-    if (blockIdx.x == 0 && threadIdx.x < N_XCD) reset_cursors(cursor, (int)threadIdx.x, nblocks, chunk);
-    if (counts)
-        for (long long i = (long long)blockIdx.x * 1024 + threadIdx.x; i < ncounts; i += (long long)gridDim.x * 1024) counts[i] = 0;
     const long long n0 = (long long)ticket * (1024 * U);
     float y[U][3];
     int p[U];
@@ -1067,10 +1138,18 @@ __global__ __launch_bounds__(256) void k_solve_unpack(long long N, long long tot
                                                       const float4 *__restrict__ rec, float *__restrict__ o_x,
                                                       uint8_t *__restrict__ o_conv, float *__restrict__ o_J,
                                                       uint8_t *__restrict__ o_it, int32_t *__restrict__ o_slot,
-                                                      u64 *__restrict__ look, int look_blocks)
+                                                      u64 *__restrict__ look, int look_blocks, unsigned *__restrict__ cursor,
+                                                      int rows, int tiles, int ncp, int *__restrict__ counts, int *__restrict__ offset)
 {
     look_clear(look, look_blocks);
-    const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;      // grid: points x initial states
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < N_XCD) reset_cursors(cursor, (int)threadIdx.x);
+    // grid: points x initial states, behind `rows` rows of blocks that place the cells of the positions (place_cells; tiles = 0: none)
+    if ((int)blockIdx.y < rows) {
+        const int t = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+        if (t < tiles) place_cells(t, ncp, counts, offset, cursor + CUR_TOTAL);
+        return;
+    }
+    const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x, k = (int)blockIdx.y - rows;
     if (n >= N) return;
     const long long pq = k * N + n;
     bool have = true;
@@ -1127,7 +1206,7 @@ __device__ __forceinline__ CellGroup group_request(bool want, int cell, int lane
 __device__ __forceinline__ int group_position(const CellGroup &g) { return __shfl(g.base, g.leader) + g.rank; }
 
 // Chunks of work for one of the waves that draw them.  The first S.dealt eighths are dealt out in rounds, chunk w + i * drawers to
-// drawer w; the cursor, which starts behind one round, hands out the rest: it serves one drawer after the other, 9 ns each, and every drawer
+// drawer w; the cursor hands out the rest: it serves one drawer after the other, 9 ns each, and every drawer
 // waits for its answer.
 struct Chunks {
     long long round, shared, own;
@@ -1151,7 +1230,7 @@ __device__ __forceinline__ bool next_chunk(Chunks &c, const SolveP &S, long long
     } else {
         unsigned b = 0;
         if (lane == 0) b = atomicAdd(cursor + CUR_ALL, (unsigned)S.chunk);
-        next = c.shared - c.round + (long long)(unsigned)__builtin_amdgcn_readfirstlane((int)b);
+        next = c.shared + (long long)(unsigned)__builtin_amdgcn_readfirstlane((int)b);
         if (next >= total) {
             next = c1;
             return false;
@@ -1730,6 +1809,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
         __syncthreads();
     }
     const float *T = reinterpret_cast<const float *>(s_grid);
+    if (blockIdx.x == 0 && threadIdx.x == 0) cursor[CUR_TOTAL] = 0u;          // for place_cells, later in this call
     // with a list only the pairs list[0 .. *list_len) ({point, cell << 3 | k}) are solved
     const long long total = list ? (long long)*list_len : S.total;
     const int lane = threadIdx.x & 63;
@@ -2151,6 +2231,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
         s_done = 0;
     }
     __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) cursor[CUR_TOTAL] = 0u;          // for place_cells, later in this call
     const long long total = list ? (long long)*list_len : S.total;
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -2171,7 +2252,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
         const unsigned consumers = gridDim.x * NCONS;
         const unsigned own = ranges ? 0u : ((unsigned)total >= 64u * consumers ? 64u : ((unsigned)total + consumers - 1u) / consumers);
         const long long heads = min(total, (long long)own * consumers), rest = total - heads;
-        // the first chunk of block b is chunk b; the shared cursor starts behind those.  (One cursor for the whole chip
+        // the first chunk of block b is chunk b; the shared cursor counts what lies behind those.  (One cursor for the whole chip
         // on purpose: all XCDs then work through the same stretch of the points at the same time, and what one of them
         // brought into the memory-side cache serves the others.  With a cursor per XCD over its own eighth of the
         // points -- one pose per XCD on the multi-pose batch -- the kernel was 13 % slower: eight transform grids
@@ -2206,7 +2287,8 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                         const int j = (home + alive) & (N_XCD - 1);
                         unsigned b = 0;
                         if (lane == 0) b = atomicAdd(cursor + CUR_XCD + j, (unsigned)S.chunk);
-                        b = (unsigned)__builtin_amdgcn_readfirstlane((int)b);
+                        // the blocks of this range own its first chunks
+                        b = (unsigned)__builtin_amdgcn_readfirstlane((int)b) + ((gridDim.x + (N_XCD - 1) - (unsigned)j) / N_XCD) * (unsigned)S.chunk;
                         const long long r1 = min(total, (j + 1) * per), at = j * per + (long long)b;
                         if ((long long)b < per && at < r1) {
                             next = at;
@@ -2499,9 +2581,10 @@ __global__ __launch_bounds__(LDS ? 1024 : 256) void k_solve_quad(GridP G, SolveP
                                                const uint8_t *__restrict__ valid0, float *__restrict__ o_x,
                                                uint8_t *__restrict__ o_conv, float *__restrict__ o_J,
                                                uint8_t *__restrict__ o_it, int32_t *__restrict__ o_slot,
-                                               float4 *__restrict__ rec, int *__restrict__ cell_count, int ncell)
+                                               float4 *__restrict__ rec, int *__restrict__ cell_count, int ncell, unsigned *__restrict__ total)
 {
     extern __shared__ float4 s_grid[];
+    if (cell_count && blockIdx.x == 0 && threadIdx.x == 0) *total = 0u;          // for place_cells, later in this call
     if (LDS) {
         const int n4 = (int)((long long)G.P * G.V * 3);      // float4 per record: 3
         const float4 *src = reinterpret_cast<const float4 *>(Tglobal);
@@ -2646,9 +2729,10 @@ __global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(Gri
                                                uint8_t *__restrict__ o_conv, float *__restrict__ o_J,
                                                uint8_t *__restrict__ o_it, int32_t *__restrict__ o_slot,
                                                float4 *__restrict__ rec, int *__restrict__ cell_count, int ncell,
-                                               const int *__restrict__ state)
+                                               const int *__restrict__ state, unsigned *__restrict__ total)
 {
     extern __shared__ float4 s_grid[];
+    if (cell_count && blockIdx.x == 0 && threadIdx.x == 0) *total = 0u;          // for place_cells, later in this call
     if (LDS) {
         const int n4 = (int)((long long)G.P * G.V * 3);      // float4 per record: 3
         const float4 *src = reinterpret_cast<const float4 *>(Tglobal);
@@ -2788,14 +2872,11 @@ __global__ __launch_bounds__(LDS ? 768 : 256, LDS ? 1 : 3) void k_solve_once(Gri
 // cell of x* (pass 1 below, or the positions k_solve hands out), crowded cells are summed once per
 // corner (k_grad_pieces), and every grid node then adds what its 8 adjacent cells hold (k_grad_nodes_p).
 
-// a[0..n) = 0; `cursors` (may be null): the solve kernels' work cursor is reset on the way
-__global__ void k_fill_zero_i32(long long n, int *__restrict__ a, unsigned *__restrict__ cursors = nullptr,
-                                unsigned nblocks = 0u, unsigned chunk = 0u)
+// a[0..n) = 0
+__global__ void k_fill_zero_i32(long long n, int *__restrict__ a)
 {
-    long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long stride = (long long)gridDim.x * blockDim.x;
-    if (cursors && i < N_XCD) reset_cursors(cursors, (int)i, nblocks, chunk);
-    for (; i < n; i += stride) a[i] = 0;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) a[i] = 0;
 }
 
 // pass 1 (only when the solve did not hand out positions): one thread per lane; position of the lane
@@ -2805,8 +2886,9 @@ __global__ void k_fill_zero_i32(long long n, int *__restrict__ a, unsigned *__re
 __global__ __launch_bounds__(256) void k_grad_count(GridP G, const float *__restrict__ xc,
                                                     const uint8_t *__restrict__ conv, const int32_t *__restrict__ pose,
                                                     long long N, int K, int ki, int ncell, int *__restrict__ count,
-                                                    int *__restrict__ pos)
+                                                    int *__restrict__ pos, unsigned *__restrict__ total)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *total = 0u;          // for place_cells, the next launch
     int n, k;
     const bool live = pair_of((blockIdx.x * 256u + threadIdx.x) >> 6, threadIdx.x & 63u, WAVE, (unsigned)N, K, ki, n, k);
     const long long q = (long long)k * N + n;
@@ -2905,8 +2987,9 @@ __global__ __launch_bounds__(256, JAC == JAC_CELL ? 4 : 1) void k_grad_records(G
                     if (on[u]) {
                         const Cell c = locate(G, x);
                         cl[u] = p * ncell + cell_linear(G, c);
-                        o0[u] = offset[cl[u]];
-                        o1[u] = offset[cl[u] + 1];
+                        const int *o = offset + place(cl[u]);
+                        o0[u] = o[0];
+                        o1[u] = o[1];
                     }
                 }
 #pragma unroll
@@ -2964,10 +3047,11 @@ __global__ __launch_bounds__(256, JAC == JAC_CELL ? 4 : 1) void k_grad_records(G
             }
             const Cell c = locate(G, x);
             const int cl = p * ncell + cell_linear(G, c);
-            const long long slot = (long long)offset[cl] + pq;
+            const int *o = offset + place(cl);
+            const long long slot = (long long)o[0] + pq;
             // positions that do not belong to these roots (a caller mixing arrays of different solves)
             // must not send the store outside the cell's part of the list
-            if (pq < 0 || slot >= offset[cl + 1]) continue;
+            if (pq < 0 || slot >= o[1]) continue;
             rec[slot * 2] = make_float4(x[0], x[1], x[2], lam[0]);
             rec[slot * 2 + 1] = make_float4(lam[1], lam[2], __int_as_float(cl), 0.0f);
         }
@@ -3054,14 +3138,14 @@ constexpr int PIECE_ROW = 20;     // floats per staged record: 8 weights + 12 pr
 #endif
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(64 * PIECE_WAVES) void k_grad_pieces(GridP G, long long ncp, const int *__restrict__ offset, float *rec)
+__global__ __launch_bounds__(64 * PIECE_WAVES) void k_grad_pieces(GridP G, const unsigned *__restrict__ records, float *rec)
 {
     __shared__ float4 sm4[PIECE_R * PIECE_ROW / 4];
     __shared__ int s_cell[PIECE_R];
     float *sm = reinterpret_cast<float *>(sm4);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const long long s = (long long)blockIdx.x * PIECE_R;
-    const long long total = offset[ncp];
+    const long long total = *records;
     if (s >= total) return;
     const int e = (int)min((long long)PIECE_R, total - s);
     // each wave loads and expands its share of the range: SIMD lane l of wave w holds records
@@ -3213,7 +3297,7 @@ __global__ __launch_bounds__(256) void k_grad_nodes_p(GridP G, int ncell, const 
 #pragma unroll
     for (int e = 0; e < 12; ++e) acc[e] = 0.0f;
     const int c = adjacent_cell(G, ncell, p, ix, iy, iz, cn);
-    const int a = c < 0 ? 0 : offset[c], b = c < 0 ? 0 : offset[c + 1];
+    const int a = c < 0 ? 0 : offset[place(c)], b = c < 0 ? 0 : offset[place(c) + 1];
     if (a < b) {
         for (int j = a / PIECE_R; j <= (b - 1) / PIECE_R; ++j) {
             const int ps = max(a, j * PIECE_R), pe = min(b, (j + 1) * PIECE_R);
@@ -3350,8 +3434,8 @@ __global__ __launch_bounds__(256) void k_grad_nodes_z(GridP G, int ncell, const 
             int b = a[ab] = 0;
             if (!(cx < 0 || cy < 0 || cx > G.nx - 2 || cy > G.ny - 2)) {
                 const int c = p * ncell + (cx * (G.ny - 1) + cy) * (G.nz - 1) + iz;
-                a[ab] = offset[c];
-                b = offset[c + 1];
+                a[ab] = offset[place(c)];
+                b = offset[place(c) + 1];
             }
             small[ab] = b - a[ab] < PIECE_MIN;
             from[ab] = a[ab] - walk;
@@ -3380,7 +3464,7 @@ __global__ __launch_bounds__(256) void k_grad_nodes_z(GridP G, int ncell, const 
         }
 #pragma unroll
         for (int ab = 0; ab < 4; ++ab)
-            if (!small[ab]) grad_cell_pair<true, true>(G, rec, a[ab], offset[p * ncell + ((ix - (ab & 1)) * (G.ny - 1) + iy - (ab >> 1)) * (G.nz - 1) + iz + 1], ab, ix - (ab & 1), iy - (ab >> 1), iz, acc, up);
+            if (!small[ab]) grad_cell_pair<true, true>(G, rec, a[ab], offset[place(p * ncell + ((ix - (ab & 1)) * (G.ny - 1) + iy - (ab >> 1)) * (G.nz - 1) + iz) + 1], ab, ix - (ab & 1), iy - (ab >> 1), iz, acc, up);
     }
     // what the node below collected for this one (lane - 1 is node i - 1: the same column when iz > 0)
     const bool from_lane = lane > 0 && valid && iz > 0;
@@ -3394,7 +3478,7 @@ __global__ __launch_bounds__(256) void k_grad_nodes_z(GridP G, int ncell, const 
             const int cx = ix - (ab & 1), cy = iy - (ab >> 1);
             if (cx < 0 || cy < 0 || cx > G.nx - 2 || cy > G.ny - 2) continue;
             const int c = p * ncell + (cx * (G.ny - 1) + cy) * (G.nz - 1) + iz - 1;
-            const int a = offset[c], b = offset[c + 1];
+            const int a = offset[place(c)], b = offset[place(c) + 1];
             if (a != b) grad_cell_pair<false, true>(G, rec, a, b, ab, cx, cy, iz - 1, up, acc);
         }
     }
@@ -3421,10 +3505,8 @@ __global__ __launch_bounds__(256) void k_grad_nodes_z(GridP G, int ncell, const 
 // the way through LDS for weights and gW 146.
 template <int MT, int S>
 __global__ __launch_bounds__(256, 2) void k_grad_outputs(GridP G, const float *__restrict__ W, const float *__restrict__ GT,
-                                                         const float *__restrict__ B, float *gW, float *__restrict__ part,
-                                                         u64 *__restrict__ look, int look_blocks)
+                                                         const float *__restrict__ B, float *gW, float *__restrict__ part)
 {
-    look_clear(look, look_blocks);
     constexpr int PC = S * 4 / 3, ROW = S * 16 + 8;          // poses per pass; floats per row of the tile in LDS (padded: no bank twice)
     __shared__ float4 s_bone[S * 4][MT * 16];    // quarter x bone, zero where there is no such pose or bone
     __shared__ float4 s_tile[4][16 * ROW / 4];
