@@ -3073,18 +3073,14 @@ __global__ __launch_bounds__(256, JAC == JAC_CELL ? 4 : 1) void k_grad_records(G
 // that cell (same clamping, same subtraction), without looking the cell up again
 __device__ __forceinline__ float frac_in_cell(float x, float lo, float inv_h, float m, int i0)
 {
-    float u = (x - lo) * inv_h;
-    u = !(u >= 0.0f) ? 0.0f : (u > m ? m : u);
-    return u - (float)i0;
+    return __builtin_amdgcn_fmed3f((x - lo) * inv_h, 0.0f, m) - (float)i0;
 }
 
-// contribution of sorted record s, which lies in the cell with origin (cx, cy, cz), to the node that is that
+// contribution of a sorted record {x*, lambda}, which lies in the cell with origin (cx, cy, cz), to the node that is that
 // cell's corner (da, db, dc)
-__device__ __forceinline__ void grad_accumulate(const GridP &G, const float *__restrict__ rec, int s, int cx, int cy, int cz,
+__device__ __forceinline__ void grad_accumulate(const GridP &G, const float4 r0, const float4 r1, int cx, int cy, int cz,
                                                 int da, int db, int dc, float (&acc)[12])
 {
-    const float4 *r = reinterpret_cast<const float4 *>(rec + (long long)s * GREC);
-    const float4 r0 = r[0], r1 = r[1];
     const float x[3] = {r0.x, r0.y, r0.z};
     const float lam[3] = {r0.w, r1.x, r1.y};
     const float fx = frac_in_cell(x[0], G.lo[0], G.inv_h[0], G.m[0], cx);
@@ -3117,15 +3113,13 @@ __device__ __forceinline__ int adjacent_cell(const GridP &G, int ncell, int p, i
 // floats per piece instead of every record of a crowded cell; shorter pieces stay as records.
 constexpr int PIECE_R = 256;
 constexpr int PIECE_MIN = 96 / GREC;
-constexpr int PIECE_RPL = PIECE_R / 64;   // records per SIMD lane when a wave scans its range
-constexpr int PIECE_WAVES = 4;            // waves per range (2: the same but on sparse lists, 62.6 instead of 54.6 us on 7.7 M records)
-constexpr int PIECE_OWN = PIECE_R / PIECE_WAVES;   // records a wave loads and expands
-constexpr int PIECE_LOAD = PIECE_OWN / 64;         // ... per SIMD lane
+constexpr int PIECE_WAVES = PIECE_R / 64; // waves per range, a record per SIMD lane (2 waves, two records each: the same but on sparse lists, 62.6 instead of 54.6 us on 7.7 M records)
 
-// Bound: latency of the chain total -> records -> pieces -> sums; where pieces start is found with ballots and bit scans, not
-// with a minimum over shuffles (7.7 M records in 4 M cells 71 -> 62.6 us, 1.4 M in 60 k 34 -> 32).  Loading records before
-// the total is known saves nothing on full lists and reads unused room on others (2 M ray samples 20 -> 53 us).
-// One block of PIECE_WAVES waves per range: the waves share the loading and expanding of the records and
+// Bound: instruction issue (vector units 0.6 and matrix cores 0.25 of the busy cycles with 25 records per cell), so a pass has a comparison and a
+// select per group only where the piece may end in it, nothing is masked that nobody stores, and where pieces lie is found with scalar bit
+// operations on one ballot per wave (1.3 M records in 60 k cells, pieces of some 25: 30.1 -> 23.1 us; 0.48 M 13.3 -> 10.6).  Persistent blocks that ask
+// for the next range's records early: 37 instead of 30 us; loading records before the total is known: nothing on full lists, 20 -> 53 us on others.
+// One block of PIECE_WAVES waves per range: a thread loads and expands a record, the waves
 // take the long pieces in turn.  Every record of the range is expanded once (SIMD lane = record) into its 8 corner
 // weights omega_c and its 12 products lambda_r [x*; 1]_j, staged in LDS; the sums of a piece are then the
 // matrix product  S[c][rj] = sum_t omega_c(t) * (lambda_r [x;1]_j)(t),  an 8 x len by len x 12 contraction,
@@ -3133,68 +3127,68 @@ constexpr int PIECE_LOAD = PIECE_OWN / 64;         // ... per SIMD lane
 // Operand layout of that instruction: lane 16k+i supplies A[i][k] and B[k][i]; lane 16g+j receives
 // D[4g+q][j] in accumulator register q.
 constexpr int PIECE_ROW = 20;     // floats per staged record: 8 weights + 12 products
-#ifndef FS_PIECES_VALU
-#define FS_PIECES_VALU 0
-#endif
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(64 * PIECE_WAVES) void k_grad_pieces(GridP G, const unsigned *__restrict__ records, float *rec)
 {
-    __shared__ float4 sm4[PIECE_R * PIECE_ROW / 4];
-    __shared__ int s_cell[PIECE_R];
+    __shared__ float4 sm4[(PIECE_R + 16) * PIECE_ROW / 4 + 1];          // ... 16 rows of zeros, and the four columns read behind the last
+    __shared__ unsigned long long s_start[PIECE_WAVES];
     float *sm = reinterpret_cast<float *>(sm4);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const long long s = (long long)blockIdx.x * PIECE_R;
     const long long total = *records;
     if (s >= total) return;
     const int e = (int)min((long long)PIECE_R, total - s);
-    // each wave loads and expands its share of the range: SIMD lane l of wave w holds records
-    // PIECE_OWN * w + l, PIECE_OWN * w + 64 + l, ...
-    float4 r0[PIECE_LOAD], r1[PIECE_LOAD];
-#pragma unroll
-    for (int b = 0; b < PIECE_LOAD; ++b) {
-        const int t = PIECE_OWN * w + 64 * b + lane;
-        r0[b] = r1[b] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (t < e) {
-            const float4 *r = reinterpret_cast<const float4 *>(rec + (s + t) * GREC);
-            r0[b] = r[0];
-            r1[b] = r[1];
-        }
-        s_cell[t] = t < e ? __float_as_int(r1[b].z) : -1;
+    // thread t loads and expands record t of the range.  A piece starts where the cell differs from the one before (lane 0 reads the record of the
+    // wave before for that); the first of the range always starts one, and so does the end of the list, for what lies before it.
+    const int t = threadIdx.x;
+    float4 r0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), r1 = r0;
+    int before = -1;
+    if (t < e) {
+        const float4 *r = reinterpret_cast<const float4 *>(rec + (s + t) * GREC);
+        r0 = r[0];
+        r1 = r[1];
+        if (lane == 0 && t > 0) before = __float_as_int(r[-1].z);
+    }
+    {
+        const int cell = __float_as_int(r1.z), left = __shfl_up(cell, 1);
+        if (lane > 0) before = left;
+        const unsigned long long b = __ballot(t == e || (t < e && (t == 0 || cell != before)));
+        if (lane == 0) s_start[w] = b;
     }
     __syncthreads();
-    // Every wave finds the pieces of the whole range (same data, same result).  Bit l of start[b]: record 64 b + l starts a
-    // piece, i.e. its cell differs from the one before it (the first of the range always does).  A piece ends where the
-    // next bit is set.  many[b]: the starts of pieces with at least PIECE_MIN records.
-    unsigned long long start[PIECE_RPL], many[PIECE_RPL];
-    int len[PIECE_RPL];
+    // Every wave finds the long pieces of the whole range, with scalar instructions: a start is one if none of the next PIECE_MIN - 1 places is a
+    // start.
+    unsigned long long start[PIECE_WAVES], many[PIECE_WAVES], any_long = 0ull;
 #pragma unroll
-    for (int b = 0; b < PIECE_RPL; ++b) {
-        const int t = 64 * b + lane;
-        start[b] = __ballot(t < e && (t == 0 || s_cell[t] != s_cell[t - 1]));
+    for (int b = 0; b < PIECE_WAVES; ++b) {
+        const unsigned long long v = s_start[b];
+        start[b] = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32)) << 32 |
+                   (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
     }
-    int later = e;                       // first piece start in later batches
-    unsigned long long any_long = 0ull;
 #pragma unroll
-    for (int b = PIECE_RPL - 1; b >= 0; --b) {
-        const unsigned long long rest = (start[b] >> lane) >> 1;
-        const int end = rest ? 64 * b + lane + __ffsll((long long)rest) : later;
-        len[b] = end - (64 * b + lane);
-        many[b] = start[b] & __ballot(len[b] >= PIECE_MIN);
+    for (int b = 0; b < PIECE_WAVES; ++b) {
+        const unsigned long long after = b + 1 < PIECE_WAVES ? start[b + 1] : 1ull;         // the range ends behind its last record
+        static_assert(PIECE_MIN == 12, "the next 11 places");
+        unsigned long long lo = start[b] >> 1 | after << 63, hi = after >> 1;               // bit l: place l + 1
+        lo |= lo >> 1 | hi << 63, hi |= hi >> 1;
+        lo |= lo >> 2 | hi << 62, hi |= hi >> 2;
+        lo |= lo >> 4 | hi << 60, hi |= hi >> 4;                                            // places l + 1 .. l + 8
+        lo |= lo >> 3 | hi << 61;
+        many[b] = start[b] & ~lo;
+        if (e < 64 * (b + 1)) many[b] &= e > 64 * b ? (1ull << (e - 64 * b)) - 1ull : 0ull; // the end of the list is no piece
         any_long |= many[b];
-        if (start[b]) later = 64 * b + __ffsll((long long)start[b]) - 1;
     }
     if (!any_long) return;              // nothing to summarise here (sparse lists end here); same in every wave
     // expand the records
-#pragma unroll
-    for (int b = 0; b < PIECE_LOAD; ++b) {
-        const int t = PIECE_OWN * w + 64 * b + lane;
+    if (threadIdx.x <= 16 * PIECE_ROW / 4) sm4[PIECE_R * PIECE_ROW / 4 + threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    {
         float4 o[5];
 #pragma unroll
         for (int h = 0; h < 5; ++h) o[h] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (t < e) {
-            const float x[3] = {r0[b].x, r0[b].y, r0[b].z};
-            const float lam[3] = {r0[b].w, r1[b].x, r1[b].y};
+            const float x[3] = {r0.x, r0.y, r0.z};
+            const float lam[3] = {r0.w, r1.x, r1.y};
             const Cell cl = locate(G, x);
             float om[8];
             corner_weights(cl, om);
@@ -3207,10 +3201,10 @@ __global__ __launch_bounds__(64 * PIECE_WAVES) void k_grad_pieces(GridP G, const
         for (int h = 0; h < 5; ++h) sm4[t * (PIECE_ROW / 4) + h] = o[h];
     }
     __syncthreads();
-    const int col = lane & 15, kq = lane >> 4;
+    const int col = lane & 15, kq = lane >> 4, zero = (PIECE_R + kq) * PIECE_ROW + col;
     int turn = 0;                        // the waves take the long pieces in turn
 #pragma unroll
-    for (int i = 0; i < PIECE_RPL; ++i) {
+    for (int i = 0; i < PIECE_WAVES; ++i) {
         unsigned long long m = many[i];
         while (m) {
             const int src = __ffsll((long long)m) - 1;
@@ -3218,50 +3212,46 @@ __global__ __launch_bounds__(64 * PIECE_WAVES) void k_grad_pieces(GridP G, const
             const bool mine = turn == w;
             turn = turn + 1 == PIECE_WAVES ? 0 : turn + 1;
             if (!mine) continue;
-            const int ps = 64 * i + src, pe = ps + __builtin_amdgcn_readlane(len[i], src);
-            // four groups per pass into four accumulators: their LDS reads are in flight together and no
-            // MFMA waits for the one before it; records outside the piece enter as zeros
-#if FS_PIECES_VALU
-            // the same sums with vector FMAs, for comparison: lane (kq, col) takes rows 2 kq, 2 kq + 1 of column col
-            {
-                float a0 = 0.0f, a1 = 0.0f, b0 = 0.0f, b1 = 0.0f;
-                if (col < 12) {
-                    int t = ps;
-                    for (; t + 1 < pe; t += 2) {
-                        const float2 w0 = *reinterpret_cast<const float2 *>(sm + t * PIECE_ROW + 2 * kq);
-                        const float2 w1 = *reinterpret_cast<const float2 *>(sm + (t + 1) * PIECE_ROW + 2 * kq);
-                        const float p0 = sm[t * PIECE_ROW + 8 + col], p1 = sm[(t + 1) * PIECE_ROW + 8 + col];
-                        a0 = FS_FMA(w0.x, p0, a0); a1 = FS_FMA(w0.y, p0, a1);
-                        b0 = FS_FMA(w1.x, p1, b0); b1 = FS_FMA(w1.y, p1, b1);
-                    }
-                    if (t < pe) {
-                        const float2 w0 = *reinterpret_cast<const float2 *>(sm + t * PIECE_ROW + 2 * kq);
-                        const float p0 = sm[t * PIECE_ROW + 8 + col];
-                        a0 = FS_FMA(w0.x, p0, a0); a1 = FS_FMA(w0.y, p0, a1);
-                    }
-                    float *o = rec + (s + ps) * GREC + (2 * kq) * 12 + col;
-                    o[0] = a0 + b0;
-                    o[12] = a1 + b1;
-                }
-                continue;
-            }
-#endif
-            v4f acc4[4];
+            // it ends where the next one starts
+            const int ps = 64 * i + src;
+            const unsigned long long rest = start[i] >> src >> 1;
+            int pe = PIECE_R;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) acc4[u] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-            const int g1 = (pe - 1) >> 2;
-            for (int g = ps >> 2; g <= g1; g += 4) {
+            for (int b = PIECE_WAVES - 1; b > i; --b)
+                if (start[b]) pe = 64 * b + __ffsll((long long)start[b]) - 1;
+            if (rest) pe = ps + __ffsll((long long)rest);
+            // Four groups per pass into four accumulators: their LDS reads are in flight together and no MFMA waits for the one before it.
+            // Records behind the piece enter as rows of zeros; rows 8..15 and columns 12..15 are sums of whatever lies there, which nobody
+            // stores.  `at`: this lane's entry of the pass's first group; a group is 4 rows further.
+            v4f acc4[4];
+            int at = (ps + kq) * PIECE_ROW + col, n = pe - ps;
+            {
                 float av[4], bv[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int t = 4 * (g + u) + kq;
-                    const bool in = t >= ps && t < pe;          // pe <= PIECE_R
-                    av[u] = (in && col < 8) ? sm[t * PIECE_ROW + col] : 0.0f;
-                    bv[u] = (in && col < 12) ? sm[t * PIECE_ROW + 8 + col] : 0.0f;
+                    const float *q = sm + (4 * u + kq < n ? at : zero) + 4 * u * PIECE_ROW;
+                    av[u] = q[0];
+                    bv[u] = q[8];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc4[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u], (v4f){0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+            }
+            for (n -= 16, at += 16 * PIECE_ROW; n >= 16; n -= 16, at += 16 * PIECE_ROW) {
+                float av[4], bv[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    av[u] = sm[at + 4 * u * PIECE_ROW];
+                    bv[u] = sm[at + 4 * u * PIECE_ROW + 8];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) acc4[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u], acc4[u], 0, 0, 0);
             }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (4 * u < n) {
+                    const float *q = sm + (4 * u + kq < n ? at : zero) + 4 * u * PIECE_ROW;
+                    acc4[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[0], q[8], acc4[u], 0, 0, 0);
+                }
             const v4f acc = (acc4[0] + acc4[1]) + (acc4[2] + acc4[3]);
             if (kq < 2 && col < 12) {
                 float *o = rec + (s + ps) * GREC + (4 * kq) * 12 + col;
@@ -3272,6 +3262,13 @@ __global__ __launch_bounds__(64 * PIECE_WAVES) void k_grad_pieces(GridP G, const
             }
         }
     }
+}
+
+// v of the lane that the DPP control names, all lanes taking part
+template <int CTRL>
+__device__ __forceinline__ float lane_from(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
 }
 
 // G_T of every node from the pieces of its 8 adjacent cells, for crowded cells (k_grad_nodes_z takes the sparse ones): 8 threads
@@ -3312,16 +3309,19 @@ __global__ __launch_bounds__(256) void k_grad_nodes_p(GridP G, int ncell, const 
                     acc[4 * h + 3] += u.w;
                 }
             } else {
-                for (int s = ps; s < pe; ++s)
-                    grad_accumulate(G, rec, s, ix - (cn & 1), iy - ((cn >> 1) & 1), iz - ((cn >> 2) & 1), cn & 1, (cn >> 1) & 1,
+                for (int s = ps; s < pe; ++s) {
+                    const float4 *r = reinterpret_cast<const float4 *>(rec + (long long)s * GREC);
+                    grad_accumulate(G, r[0], r[1], ix - (cn & 1), iy - ((cn >> 1) & 1), iz - ((cn >> 2) & 1), cn & 1, (cn >> 1) & 1,
                                     (cn >> 2) & 1, acc);
+                }
             }
         }
     }
 #pragma unroll
     for (int e = 0; e < 12; ++e) {
-#pragma unroll
-        for (int d = 4; d >= 1; d >>= 1) acc[e] += __shfl_xor(acc[e], d);
+        acc[e] += lane_from<0xB1>(acc[e]);           // the neighbour of a pair, then of a quad
+        acc[e] += lane_from<0x4E>(acc[e]);
+        acc[e] += lane_from<0x141>(acc[e]);          // the other quad of eight lanes
     }
     if (cn == 0) {
         float4 *o = reinterpret_cast<float4 *>(GT + i * 12);

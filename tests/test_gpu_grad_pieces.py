@@ -1,0 +1,61 @@
+"""Sums of the pieces of the backward's record list: cells with exactly so many records that a piece is one short of the length from
+which it is summed, ends inside, at and behind a group of 4 and a pass of 16 records, and fills ranges of 256; and what is not a number in one
+cell stays with that cell's nodes."""
+import numpy as np
+import pytest
+
+import gpu_util as gu
+import oracle
+from paper_2211_15601_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = {
+    "short": [11, 12, 13, 1, 15, 16, 17, 2, 27, 28, 29, 31, 32, 33],
+    "ranges": [244, 12, 256, 255, 257, 11, 500, 513],
+    "one": [12], "one short": [11], "many of twelve": [12] * 64, "end at a range": [128, 128],
+}
+
+
+def scene(lengths, dims=(6, 7, 9), seed=3):
+    rng = np.random.default_rng(seed)
+    N = sum(lengths)
+    s = wl.random_affine_scene(61, dims=dims, n_bones=4, n_poses=1, n_points=N)
+    cells = rng.permutation((dims[0] - 1) * (dims[1] - 1) * (dims[2] - 1))[:len(lengths)]
+    cell = np.repeat(cells, lengths)[rng.permutation(N)]
+    i = np.stack([cell // (dims[2] - 1) // (dims[1] - 1), cell // (dims[2] - 1) % (dims[1] - 1), cell % (dims[2] - 1)])
+    lo, hi = np.asarray(s["lo"], np.float64), np.asarray(s["hi"], np.float64)
+    h = (hi - lo) / (np.asarray(dims) - 1)
+    xc = (lo[:, None] + (i + 0.05 + 0.9 * rng.random((3, N))) * h[:, None]).astype(np.float32)[None]
+    w = wl.Workload("pieces", s["dims"], 4, 1, s["lo"], s["hi"], s["W"], s["B"], s["x"], None, s["x"], 1e-5, 10.0, 20, wl.INIT_BONE, 4, (1, 1, 1, 1))
+    J = (np.eye(3).reshape(1, 9, 1) + 0.2 * rng.standard_normal((1, 9, N))).astype(np.float32)
+    return w, cells, cell, xc, J, np.ones((1, N), np.uint8), rng.standard_normal((1, 3, N)).astype(np.float32)
+
+
+def gradients(w, xc, J, cv, gxc):
+    run = gu.GpuRun(w)
+    run.K = 1
+    T = run.precompute()
+    return T, run.grad(xc, J, cv, gxc)
+
+
+@pytest.mark.parametrize("lengths", LENGTHS.values(), ids=LENGTHS.keys())
+def test_sums_of_pieces(gpu_lib, lengths):
+    w, _, _, xc, J, cv, gxc = scene(lengths)
+    T, got = gradients(w, xc, J, cv, gxc)
+    want = oracle.grad(w.dims, w.lo, w.hi, T, w.W, w.B, xc, J, cv, gxc, pose=None, mode=0, prec="f64")
+    for name, a, b in zip(("gW", "gB", "gxq"), got, want):
+        gu.assert_grad_close(name, a, b, str(lengths))
+
+
+def test_nan_stays_in_its_cell(gpu_lib):
+    lengths = LENGTHS["short"] + LENGTHS["ranges"]
+    w, cells, cell, xc, J, cv, gxc = scene(lengths)
+    bad = cells[3], cells[5], cells[17]                 # one record (kept as it is), a summed piece, two ranges
+    for c in bad:
+        gxc[0, :, np.flatnonzero(cell == c)[0]] = np.nan
+    T, got = gradients(w, xc, J, cv, gxc)
+    want = oracle.grad(w.dims, w.lo, w.hi, T, w.W, w.B, xc, J, cv, gxc, pose=None, mode=0, prec="f64")
+    a, b = np.asarray(got[0]).reshape(-1), np.asarray(want[0]).reshape(-1)
+    assert (np.isnan(a) == np.isnan(b)).all() and np.isnan(b).any() and not np.isnan(b).all()
+    gu.assert_grad_close("gW", a[~np.isnan(b)], b[~np.isnan(b)], "nodes of the other cells")
