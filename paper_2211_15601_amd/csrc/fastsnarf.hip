@@ -35,10 +35,10 @@ struct fs_ctx {
     float *Y;          // [P][V][3]
     unsigned *bb_ord;  // [P][6][blocks of k_precompute]: per-block extents of the node images
     float *bbox;       // [P][6]
-    int *cell_of;      // [P][V]
-    int *count, *offset;   // [P*ncell] nodes per correspondence cell; [P*ncell + 1] where its list starts
-    int *fill;         // [P][V] arrival slot of a node inside its cell
-    float4 *order;     // [P][V] the nodes sorted by correspondence cell: {image[3], node index}
+    int *head;         // [2][P*ncell] chunks of a correspondence cell, and the first of those that its table does not hold (k_corr_chunks)
+    int2 *table;       // [P*ncell][CHUNKS] place and length of a cell's chunks
+    int2 *link;        // [P][bricks][BRICK] next chunk and length, of those places where a chunk of a list starts
+    float4 *sample;    // [P][bricks][BRICK] the nodes of a brick sorted by correspondence cell: {image[3], node index}
     int32_t *cand;     // [P][ncell][ck]
     uint8_t *ccnt;     // [P][ncell] number of candidates of a correspondence cell
     float4 *cinit;     // [P][ncell][ck][4] initial state of every candidate (k_corr_init)
@@ -175,10 +175,30 @@ bool params_ok(const fs_params *p, char *why, size_t n)
 
 int grid1d(long long n, int block) { return (int)((n + block - 1) / block); }
 
+// The bricks of nodes that blocks of k_corr_chunks take: 2^lz nodes along z, 2^ly along y, the rest of BRICK along x; 8 x 8 x 16 nodes, longer along the others
+// where an axis is shorter, so that bricks have room for at most four times the nodes of a large grid (P V < 2^31 / 12: places stay below 2^31).
+struct Bricks {
+    int lz, ly, nx, ny, nz;
+    explicit Bricks(const GridP &G)
+    {
+        auto bits = [](int n) { int b = 0; while (b < 10 && 1 << b < n) ++b; return b; };
+        lz = std::min(4, bits(G.nz));
+        ly = std::min(3, bits(G.ny));
+        const int lx = std::min(10 - lz - ly, bits(G.nx));
+        ly = std::min(10 - lz - lx, std::max(ly, bits(G.ny)));
+        lz = 10 - ly - lx;
+        static_assert(BRICK == 1 << 10, "bits of a brick");
+        nx = grid1d(G.nx, 1 << lx);
+        ny = grid1d(G.ny, 1 << ly);
+        nz = grid1d(G.nz, 1 << lz);
+    }
+    size_t count() const { return (size_t)nx * ny * nz; }
+};
+
 void free_all(fs_ctx *c)
 {
     void *ptrs[] = {c->T, c->Bdev, c->Binv, c->Bok, c->GT, c->Y, c->bb_ord, c->bbox,
-                    c->cell_of, c->count, c->offset, c->fill, c->order, c->cand, c->cursor, c->gplace, c->gplace_solve, c->gpos, c->grec, c->look, c->srec, c->gpart, c->vlist, c->cinit, c->vcnt, c->vgcell, c->vhist, c->ccnt};
+                    c->head, c->table, c->link, c->sample, c->cand, c->cursor, c->gplace, c->gplace_solve, c->gpos, c->grec, c->look, c->srec, c->gpart, c->vlist, c->cinit, c->vcnt, c->vgcell, c->vhist, c->ccnt};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -436,8 +456,8 @@ fs_status fs_create(const fs_grid_desc *desc, const fs_params *params, void *hip
         C.cx = params->corr_nx; C.cy = params->corr_ny; C.cz = params->corr_nz; C.ck = params->corr_k;
         C.ncell = C.cx * C.cy * C.cz;
         ok = dev_alloc(&c->Y, P * V * 3) && dev_alloc(&c->bb_ord, P * 6 * (size_t)grid1d(V, 256)) && dev_alloc(&c->bbox, P * 6) &&
-             dev_alloc(&c->cell_of, P * V) && dev_alloc(&c->count, P * C.ncell) && dev_alloc(&c->offset, P * C.ncell + 1) && dev_alloc(&c->fill, P * V) &&
-             dev_alloc(&c->order, P * V) && dev_alloc(&c->cand, P * (size_t)C.ncell * C.ck) && dev_alloc(&c->ccnt, P * (size_t)C.ncell) &&
+             dev_alloc(&c->head, 2 * P * C.ncell) && dev_alloc(&c->table, P * C.ncell * CHUNKS) && dev_alloc(&c->link, P * Bricks(G).count() * BRICK) && dev_alloc(&c->sample, P * Bricks(G).count() * BRICK) &&
+             dev_alloc(&c->cand, P * (size_t)C.ncell * C.ck) && dev_alloc(&c->ccnt, P * (size_t)C.ncell) &&
              dev_alloc(&c->cinit, P * (size_t)C.ncell * C.ck * 4);
     }
     if (ok) ok = look_create(c) && hipStreamSynchronize(nullptr) == hipSuccess;      // cleared before the first call, whichever stream that is on
@@ -537,7 +557,7 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
 #define FS_LAUNCH_PRE(NP, FEW)                                                                                         \
     k_precompute<NP, FEW><<<(vblocks + (FEW) + N_XCD - 1) / N_XCD * N_XCD * ((G.P + (NP) - 1) / (NP)), 256, 0, st>>>(       \
         G, d_W, d_B, ctx->T, ctx->Bdev, ctx->Binv, ctx->Bok, reinterpret_cast<int *>(ctx->cursor + CUR_GRID),          \
-        ctx->pre_serial, voxel ? ctx->Y : nullptr, ctx->bb_ord, ctx->count, ncp, vblocks, (G.P + (NP) - 1) / (NP))
+        ctx->pre_serial, voxel ? ctx->Y : nullptr, ctx->bb_ord, ctx->head, 2 * ncp, vblocks, (G.P + (NP) - 1) / (NP))
     if (wide) FS_LAUNCH_PRE(4, false);
     else if ((long long)vblocks * G.P <= 2ll * ctx->n_cus) FS_LAUNCH_PRE(1, true);
     else FS_LAUNCH_PRE(1, false);
@@ -546,12 +566,10 @@ fs_status fs_precompute(fs_ctx *ctx, const float *d_W, const float *d_B)
         const CorrP &C = ctx->C;
         const bool own_box = vblocks <= EXTENT_OWN;
         if (!own_box) k_corr_bbox<<<G.P * 6, 1024, 0, st>>>(vblocks, ctx->bb_ord, ctx->bbox);
-        const int lz = G.nz > 8 ? 4 : (G.nz > 4 ? 3 : 2), nbx = grid1d(G.nx, BRICK >> (lz + 3)), nby = grid1d(G.ny, 8), nbz = grid1d(G.nz, 1 << lz);
-        k_corr_count<<<dim3(nbx * nby * nbz, G.P), BRICK, 0, st>>>(G, C, ctx->Y, ctx->bb_ord, vblocks, own_box, ctx->bbox, lz, nby, nbz,
-                                                                   ctx->cell_of, ctx->count, ctx->fill);
-        const int look_blocks = scan_exclusive(ctx, ncp, ctx->offset, ctx->count);
-        k_corr_scatter<<<dim3(vblocks, G.P), 256, 0, st>>>(G, C, ctx->Y, ctx->cell_of, ctx->offset, ctx->fill, ctx->order, ctx->look, look_blocks);
-        k_corr_select<<<dim3(grid1d(C.ncell, 4), G.P), 256, 0, st>>>(G, C, ctx->bbox, ctx->offset, ctx->order, ctx->cand, ctx->ccnt);
+        const Bricks b(G);
+        k_corr_chunks<<<dim3((unsigned)b.count(), G.P), BRICK, 0, st>>>(G, C, ctx->Y, ctx->bb_ord, vblocks, own_box, ctx->bbox, b.lz, b.ly, b.ny, b.nz,
+                                                                        ctx->head, ctx->table, ctx->link, ctx->sample);
+        k_corr_select<<<dim3(grid1d(C.ncell, 4), G.P), 256, 0, st>>>(G, C, ctx->bbox, ctx->head, ctx->table, ctx->link, ctx->sample, ctx->cand, ctx->ccnt);
         k_corr_init<<<grid1d((long long)ncp * C.ck, 256), 256, 0, st>>>(G, C, ctx->T, ctx->cand, ctx->cinit);
     }
     fs_status s = launch_status(ctx, "fs_precompute");

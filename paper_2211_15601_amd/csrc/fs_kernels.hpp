@@ -462,19 +462,24 @@ __global__ __launch_bounds__(1024) void k_corr_bbox(int nblk, const unsigned *__
     }
 }
 
-// The cell of every node's image, and the node's place in its cell's list.  Device-scope atomics are executed outside the
-// L2 and were the cost of this kernel, so a block of 1024 threads takes a brick of nodes (8 x 8 x 16; images of neighbours are
-// neighbours, a brick falls into a few dozen cells), counts per cell in an LDS hash table, and adds each cell once to its
-// counter.  (Lanes of a wave grouped by cell instead, 64 nodes along z: some 14 atomics per 64 nodes: 67 us on the
-// 8-pose grid, now 36.)
+// The nodes by the cell of their image, as lists of chunks.  A block of 1024 threads takes a brick of nodes (8 x 8 x 16; images of
+// neighbours are neighbours, a brick falls into a few dozen cells), counts per cell in an LDS hash table, and leaves the brick's nodes
+// {image[3], node index} sorted by cell in the brick's own part of `sample`: a chunk per cell, {place, length}.  The first CHUNKS of a cell are
+// entered in a table of the cell's, by one atomic on how many there are; the others make a list behind that, each put in front by an exchange.
+// head[gc]: number of chunks, head[cells + gc]: place of the list's first + 1, or 0 (both cleared by k_precompute); link[place]: {place + 1 of the next
+// or 0, length}.  Nothing is added up over blocks, so that no scan and no second pass over the nodes follows.  (Positions by an atomic per cell and
+// brick, a scan, a kernel that moves the nodes, and lists that are read once per candidate: 21 us with k_corr_select on 65 k nodes and two launches
+// more, 129 on the 8-pose grid; now 14 and 127.)
+constexpr int CHUNKS = 8;
 // own_box: the block reduces the extents itself (up to EXTENT_OWN blocks of k_precompute; block 0 of a pose keeps the box).
 constexpr int EXTENT_OWN = 512;
 constexpr int BRICK = 1024, HASH = 2 * BRICK;
-__global__ __launch_bounds__(BRICK) void k_corr_count(GridP G, CorrP C, const float *__restrict__ Y, const unsigned *__restrict__ bb_part,
-                                                      int nblk, bool own_box, float *__restrict__ bbox, int lz, int nby, int nbz,
-                                                      int *__restrict__ cell_of, int *__restrict__ count, int *__restrict__ slot)
+__global__ __launch_bounds__(BRICK) void k_corr_chunks(GridP G, CorrP C, const float *__restrict__ Y, const unsigned *__restrict__ bb_part,
+                                                       int nblk, bool own_box, float *__restrict__ bbox, int lz, int ly, int nby, int nbz,
+                                                       int *__restrict__ head, int2 *__restrict__ table, int2 *__restrict__ link,
+                                                       float4 *__restrict__ sample)
 {
-    __shared__ int s_key[HASH], s_cnt[HASH];
+    __shared__ int s_key[HASH], s_cnt[HASH], s_tot[BRICK / 64];
     __shared__ float s_box[6];
     const int p = blockIdx.y, wib = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int i = threadIdx.x; i < HASH; i += BRICK) {
@@ -489,16 +494,18 @@ __global__ __launch_bounds__(BRICK) void k_corr_count(GridP G, CorrP C, const fl
         }
     }
     __syncthreads();
-    // brick of 2^lz nodes along z, 8 along y, the rest along x
-    const int bz = (int)blockIdx.x % nbz, bt = (int)blockIdx.x / nbz, by = bt % nby, bx = bt / nby;
-    const int iz = (bz << lz) + (int)(threadIdx.x & ((1u << lz) - 1u)), iy = by * 8 + (int)((threadIdx.x >> lz) & 7u);
-    const int ix = bx * (BRICK >> (lz + 3)) + (int)(threadIdx.x >> (lz + 3));
+    // brick of 2^lz nodes along z, 2^ly along y, the rest along x
+    const int bz = (int)blockIdx.x % nbz, bt = (int)blockIdx.x / nbz, by = bt % nby, bx = bt / nby, t = (int)threadIdx.x;
+    const int iz = (bz << lz) + (t & ((1 << lz) - 1)), iy = (by << ly) + ((t >> lz) & ((1 << ly) - 1));
+    const int ix = bx * (BRICK >> (lz + ly)) + (t >> (lz + ly));
     const bool valid = ix < G.nx && iy < G.ny && iz < G.nz;
     const long long i = (long long)p * G.V + ((long long)ix * G.ny + iy) * G.nz + iz;
-    int c = -1, h = 0, rank = 0;
+    int h = 0, rank = 0;
+    float y[3] = {0.0f, 0.0f, 0.0f};
     if (valid) {
-        const float y[3] = {Y[i * 3], Y[i * 3 + 1], Y[i * 3 + 2]};
-        c = cell_index(C, s_box, y);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) y[r] = Y[i * 3 + r];
+        const int c = cell_index(C, s_box, y);
         // at most BRICK keys in a table of twice the size: the search ends
         h = (int)(((unsigned)c * 2654435761u) >> 21);
         static_assert(HASH == 1 << 11, "hash bits");
@@ -514,13 +521,32 @@ __global__ __launch_bounds__(BRICK) void k_corr_count(GridP G, CorrP C, const fl
         rank = atomicAdd(&s_cnt[h], 1);
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < HASH; t += BRICK)
-        if (s_cnt[t] > 0) s_cnt[t] = atomicAdd(count + p * C.ncell + s_key[t], s_cnt[t]);
-    __syncthreads();
-    if (valid) {
-        cell_of[i] = c;
-        slot[i] = s_cnt[h] + rank;      // a position inside the cell's list
+    // counts -> where the chunks start, two entries per thread
+    static_assert(HASH == 2 * BRICK, "entries per thread");
+    const int e0 = 2 * (int)threadIdx.x, n0 = s_cnt[e0], n1 = s_cnt[e0 + 1];
+    int inc = n0 + n1;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(inc, d);
+        if (lane >= d) inc += o;
     }
+    if (lane == 63) s_tot[wib] = inc;
+    __syncthreads();
+    int at0 = inc - n0 - n1;
+    for (int b = 0; b < wib; ++b) at0 += s_tot[b];
+    const int base = (int)(blockIdx.y * gridDim.x + blockIdx.x) * BRICK;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int n = q == 0 ? n0 : n1, at = q == 0 ? at0 : at0 + n0;
+        s_cnt[e0 + q] = at;
+        if (n > 0) {
+            const int gc = p * C.ncell + s_key[e0 + q], slot = atomicAdd(head + gc, 1);
+            if (slot < CHUNKS) table[(long long)gc * CHUNKS + slot] = make_int2(base + at, n);
+            else link[base + at] = make_int2(atomicExch(head + G.P * C.ncell + gc, base + at + 1), n);
+        }
+    }
+    __syncthreads();
+    if (valid) sample[base + s_cnt[h] + rank] = make_float4(y[0], y[1], y[2], __int_as_float((int)(i - (long long)p * G.V)));
 }
 
 // ---- prefix sums over blocks in one pass (decoupled look-back) ------------------------------------------------------
@@ -674,25 +700,6 @@ __global__ __launch_bounds__(1024) void k_scan(int n, const int *src, int *out, 
     }
 }
 
-// Every node goes to its place in its cell's list as {image[3], node index}: the selection below then reads its
-// samples as consecutive 16-byte entries.  (With a list of node indices alone every sample cost three gathered 4-byte
-// loads of its image in each of the three passes: k_corr_select 127 us on the 8-pose grid.)
-// (Up to 8192 cells scanned by every block in LDS instead of by a launch of its own: 9.6 instead of 4.8 + 4.6 us.)
-__global__ __launch_bounds__(256) void k_corr_scatter(GridP G, CorrP C, const float *__restrict__ Y,
-                                                      const int *__restrict__ cell_of, const int *__restrict__ offset,
-                                                      const int *__restrict__ slot, float4 *__restrict__ sample, u64 *__restrict__ look,
-                                                      int look_blocks)
-{
-    look_clear(look, look_blocks);
-    const long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int p = blockIdx.y;
-    if (v >= G.V) return;
-    const long long i = (long long)p * G.V + v;
-    const int c = p * C.ncell + cell_of[i];
-    const float *y = Y + i * 3;
-    sample[offset[c] + slot[i]] = make_float4(y[0], y[1], y[2], __int_as_float((int)v));
-}
-
 // smallest value of the 64 lanes; all lanes must call
 __device__ __forceinline__ u64 wave_min(u64 v)
 {
@@ -717,21 +724,34 @@ __device__ __forceinline__ u64 wave_min(u64 v)
 // One wave per cell.  Candidate j is the sample with the smallest (distance^2 of its image to the
 // cell centre, node index) among those farther than r_sep (canonical distance) from candidates
 // 0..j-1: the same set, in the same order, as visiting the samples by increasing key and accepting
-// greedily.  Bound: instruction issue, so the wave's minimum runs on DPP moves (the two halves of the key with lane
-// shuffles through the LDS, canonical positions also before any candidate: 84 us for 65,536 cells, 8.6 for 8192; now 72 and 6.6.)
-__global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const float *__restrict__ bbox, const int *__restrict__ offset,
-                                                     const float4 *__restrict__ sample, int32_t *__restrict__ cand,
+// greedily.  Of cells of up to SELECT_MAX nodes the samples' keys are held in registers: made once, and a sample that is too close to a
+// candidate is out for good.  Larger cells walk their chunks once per candidate.
+// Bound: latency (chunks -> samples) with few cells, instruction issue with many, so the places of the samples are written into LDS chunk by chunk
+// (compared in registers with where each chunk starts: 95 us for 65,536 cells, now 79), empty cells end at once, and the wave's minimum runs on DPP
+// moves (with lane shuffles through the LDS 12 us more).  16 keys per lane instead of 8: 10 instead of 6.9 us for 8192 cells.
+constexpr int SELECT_REGS = 8, SELECT_MAX = 64 * SELECT_REGS;
+__global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const float *__restrict__ bbox, const int *__restrict__ head,
+                                                     const int2 *__restrict__ table, const int2 *__restrict__ link, const float4 *__restrict__ sample, int32_t *__restrict__ cand,
                                                      uint8_t *__restrict__ ccnt)
 {
     // accepted candidates' positions, per wave: the same for all lanes and indexed by a loop counter -- in registers
     // that indexing turns into chains of selects, from LDS it is one broadcast read per candidate
     __shared__ float4 s_acc[4][FS_MAX_CORR_K_DEV];
+    __shared__ int s_from[4][SELECT_MAX];
     const int lane = threadIdx.x & 63, wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int p = blockIdx.y, c = blockIdx.x * 4 + wib;
     if (c >= C.ncell) return;
     const long long gc = (long long)p * C.ncell + c;
     const float *bb = bbox + p * 6;
-    const int beg = offset[gc], end = offset[gc + 1];
+    const int chunks = __builtin_amdgcn_readfirstlane(head[gc]), rest = __builtin_amdgcn_readfirstlane(head[G.P * C.ncell + gc]);
+    int2 entry = make_int2(0, 0);
+    if (lane < CHUNKS) entry = table[gc * CHUNKS + lane];
+    int32_t *out = cand + gc * C.ck;
+    if (chunks == 0) {
+        if (lane < C.ck) out[lane] = -1;
+        if (lane == 0) ccnt[gc] = 0;
+        return;
+    }
     const int ciz = c % C.cz, ciy = (c / C.cz) % C.cy, cix = c / (C.cz * C.cy);
     const float cs0 = (bb[3] - bb[0]) / (float)C.cx;
     const float cs1 = (bb[4] - bb[1]) / (float)C.cy;
@@ -740,40 +760,102 @@ __global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const flo
                           FS_FMA((float)ciz + 0.5f, cs2, bb[2])};
     const float rs2 = 6.25f * FS_FMA(G.h[2], G.h[2], FS_FMA(G.h[1], G.h[1], G.h[0] * G.h[0]));
     int na = 0;
-    int32_t *out = cand + gc * C.ck;
-    for (int j = 0; j < C.ck; ++j) {
-        // {distance^2 (its bits order like the number, which is not negative), node}; a distance that is no number never wins
-        u64 best = ~0ull;
-        for (int s = beg + lane; s < end; s += WAVE) {
-            const float4 sm = sample[s];
-            const int v = __float_as_int(sm.w);
-            if (na > 0) {
-                float x[3];
-                node_pos(G, v, x);
-                bool far = true;
-                for (int a = 0; a < na; ++a) {
-                    const float4 ac = s_acc[wib][a];
-                    const float ex = x[0] - ac.x, ey = x[1] - ac.y, ez = x[2] - ac.z;
-                    const float d2 = FS_FMA(ez, ez, FS_FMA(ey, ey, ex * ex));
-                    if (!(d2 > rs2)) far = false;
-                }
-                if (!far) continue;
-            }
-            const float dx = sm.x - ctr[0], dy = sm.y - ctr[1], dz = sm.z - ctr[2];
-            const float key = FS_FMA(dz, dz, FS_FMA(dy, dy, dx * dx));
-            const u64 k = (u64)__float_as_uint(key) << 32 | (unsigned)v;
-            if (key == key && k < best) best = k;
+    // {distance^2 (its bits order like the number, which is not negative), node}; a distance that is no number never wins
+    auto key_of = [&](const float4 sm) {
+        const float dx = sm.x - ctr[0], dy = sm.y - ctr[1], dz = sm.z - ctr[2];
+        const float key = FS_FMA(dz, dz, FS_FMA(dy, dy, dx * dx));
+        return key == key ? (u64)__float_as_uint(key) << 32 | (unsigned)__float_as_int(sm.w) : ~0ull;
+    };
+    auto apart = [&](const float (&x)[3], const float (&ac)[3]) {
+        const float ex = x[0] - ac[0], ey = x[1] - ac[1], ez = x[2] - ac[2];
+        return FS_FMA(ez, ez, FS_FMA(ey, ey, ex * ex)) > rs2;
+    };
+    // the chunks, until `on` wants no more
+    auto walk = [&](auto on) {
+        bool more = true;
+        for (int i = 0; i < min(chunks, CHUNKS) && more; ++i)
+            more = on(__builtin_amdgcn_readlane(entry.x, i), __builtin_amdgcn_readlane(entry.y, i));
+        for (int at = rest; at != 0 && more;) {
+            const int2 l = link[at - 1];
+            more = on(at - 1, __builtin_amdgcn_readfirstlane(l.y));
+            at = __builtin_amdgcn_readfirstlane(l.x);
         }
-        best = wave_min(best);
-        if (best == ~0ull) break;     // wave-uniform
-        const int bv = (int)(unsigned)best;
-        float xa[3];
-        node_pos(G, bv, xa);
-        if (lane == 0) s_acc[wib][na] = make_float4(xa[0], xa[1], xa[2], 0.0f);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        ++na;
-        if (lane == 0) out[j] = bv;
+    };
+    // the places of the cell's samples, one after the other
+    int n = 0;
+    walk([&](int place, int len) {
+        if (n + len <= SELECT_MAX)
+            for (int i = lane; i < len; i += WAVE) s_from[wib][n + i] = place + i;
+        n += len;
+        return n <= SELECT_MAX;
+    });
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (n <= SELECT_MAX) {
+        u64 key[SELECT_REGS];
+#pragma unroll
+        for (int r0 = 0; r0 < SELECT_REGS; r0 += 4) {
+#pragma unroll
+            for (int r = r0; r < r0 + 4; ++r) key[r] = ~0ull;
+            if (r0 * 64 < n) {
+                float4 sm[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if ((r0 + r) * 64 + lane < n) sm[r] = sample[s_from[wib][(r0 + r) * 64 + lane]];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if ((r0 + r) * 64 + lane < n) key[r0 + r] = key_of(sm[r]);
+            }
+        }
+        for (int j = 0; j < C.ck; ++j) {
+            u64 best = key[0];
+#pragma unroll
+            for (int r = 1; r < SELECT_REGS; ++r)
+                if (r * 64 < n && key[r] < best) best = key[r];
+            best = wave_min(best);
+            if (best == ~0ull) break;     // wave-uniform
+            ++na;
+            if (lane == 0) out[j] = (int)(unsigned)best;
+            if (na == C.ck) break;
+            float ac[3];
+            node_pos(G, (unsigned)best, ac);
+#pragma unroll
+            for (int r = 0; r < SELECT_REGS; ++r)
+                if (r * 64 < n && key[r] != ~0ull) {
+                    float x[3];
+                    node_pos(G, (unsigned)key[r], x);
+                    if (!apart(x, ac)) key[r] = ~0ull;
+                }
+        }
+    } else {
+        for (int j = 0; j < C.ck; ++j) {
+            u64 best = ~0ull;
+            walk([&](int place, int len) {
+                for (int s = lane; s < len; s += WAVE) {
+                    const float4 q = sample[place + s];
+                    float x[3];
+                    node_pos(G, (unsigned)__float_as_int(q.w), x);
+                    bool far = true;
+                    for (int a = 0; a < na; ++a) {
+                        const float4 ac = s_acc[wib][a];
+                        const float acc[3] = {ac.x, ac.y, ac.z};
+                        if (!apart(x, acc)) far = false;
+                    }
+                    const u64 k = key_of(q);
+                    if (far && k < best) best = k;
+                }
+                return true;
+            });
+            best = wave_min(best);
+            if (best == ~0ull) break;     // wave-uniform
+            float xa[3];
+            node_pos(G, (unsigned)best, xa);
+            if (lane == 0) s_acc[wib][na] = make_float4(xa[0], xa[1], xa[2], 0.0f);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            ++na;
+            if (lane == 0) out[j] = (int)(unsigned)best;
+        }
     }
     if (lane == 0) {
         for (int j = na; j < C.ck; ++j) out[j] = -1;
