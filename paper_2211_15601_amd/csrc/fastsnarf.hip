@@ -243,7 +243,7 @@ fs_status look_ready(fs_ctx *c, const char *what)
     if (hipStreamSynchronize(c->stream) != hipSuccess || hipMemset(c->look, 0, c->look_words * sizeof(u64)) != hipSuccess ||
         hipStreamSynchronize(nullptr) != hipSuccess)
         return launch_status(c, what);
-    k_fill_zero_i32<<<1, 64, 0, c->stream>>>(1, reinterpret_cast<int *>(c->cursor + CUR_ALL));
+    k_fill_zero_i32<<<1, 64, 0, c->stream>>>(2, reinterpret_cast<int *>(c->cursor + CUR_ALL));        // CUR_LIST as well
     k_fill_zero_i32<<<1, 64, 0, c->stream>>>(N_XCD, reinterpret_cast<int *>(c->cursor + CUR_XCD));
     c->look_dirty = false;
     return launch_status(c, what);
@@ -827,9 +827,11 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         } else {
 #define FS_LAUNCH_LIST(U)                                                                                              \
     k_voxel_list<U><<<grid1d(N, 1024 * (U)), 1024, boxes, st>>>(ctx->G, I, N, K, d_xq, d_pose, ctx->vcnt, ctx->vlist,  \
-                                                                ctx->cursor, ctx->look)
+                                                                ctx->cursor, ctx->look, ordered)
+            // k_voxel_list, us, in the points' order / in the order of the blocks: 0.3 M points of rays or scans 8.7 / 7.6, 1 M 13.4 / 10.9, 2 M 22.9 / 16.4
+            const bool ordered = grid_bytes > L2_BYTES;
             const int U = list_per_thread(N);
-            look_blocks = grid1d(N, 1024 * U);
+            look_blocks = ordered ? grid1d(N, 1024 * U) : 0;
             if (U == 2) FS_LAUNCH_LIST(2);
             else if (U == 4) FS_LAUNCH_LIST(4);
             else FS_LAUNCH_LIST(8);

@@ -972,12 +972,12 @@ __device__ __forceinline__ void read_record_J(const float4 *__restrict__ r, floa
 // CUR_XCD + j (j = 0 .. 7): the cursor of the j-th eighth of an ordered pair list, relative to the start of that eighth.
 // CUR_LIST: length of the list of pairs that have a candidate (k_voxel_list).
 // CUR_TOTAL, CUR_TOTAL + 1: converged lanes of the last solve that gave positions, and of the last backward from arrays (place_cells).
-// The work cursors are zero between calls: the kernel that follows a solve kernel clears them (reset_cursors).  (A launch of its own before the solve
+// The work cursors and CUR_LIST are zero between calls: the kernel that follows a solve kernel clears them (reset_cursors).  (A launch of its own before the solve
 // kernel: 2 to 4 us.)
 constexpr int CUR_ALL = 0, CUR_LIST = 1, CUR_GRID = 2, CUR_XCD = 4, CUR_TOTAL = 12, CUR_WORDS = 14;
 __device__ __forceinline__ void reset_cursors(unsigned *__restrict__ cursor, int i)
 {
-    if (i == 0) cursor[CUR_ALL] = 0u;
+    if (i == 0) cursor[CUR_ALL] = cursor[CUR_LIST] = 0u;
     if (i < N_XCD) cursor[CUR_XCD + i] = 0u;
 }
 
@@ -1081,19 +1081,19 @@ __device__ __forceinline__ int corr_cell(const InitP &I, const float *s_pose, in
 // Voxel-based initial states leave most lanes without a candidate (a ray sample in empty space has none): the list of the
 // pairs that have one, {point n, (pose * ncell + correspondence cell) << 3 | k}, from which the solve draws.  The
 // list is in the order of the points: parts of it in the order in which blocks arrive would mix up to two million
-// points, i.e. several poses' grids (Broyden kernel on the 8-pose batch 1447 instead of 1330 us).  A block takes 1024 U
-// consecutive points.
+// points, i.e. several poses' grids (Broyden kernel on the 8-pose batch 1447 instead of 1330 us).  Where an XCD's L2 holds all grids that does not
+// matter (ordered = false): a block takes its part of the list with one atomic and waits for no other.  A block takes 1024 U consecutive points.
 // Bound: the chain of tickets and memory (17 bytes read or written per point, 8 per pair).  (A counting pass, a scan of two launches,
 // an expanding pass and a clearing pass: 28 us on 1 M ray samples, 42 us on 2 M, 85 us on the 8-pose batch; now 13, 24 and 62.)
 template <int U>
 __global__ __launch_bounds__(1024) void k_voxel_list(GridP G, InitP I, long long N, int K, const float *__restrict__ xq,
                                                      const int32_t *__restrict__ pose, uint8_t *__restrict__ cnt8,
                                                      int2 *__restrict__ list, unsigned *__restrict__ cursor,
-                                                     u64 *__restrict__ look)
+                                                     u64 *__restrict__ look, bool ordered)
 {
     extern __shared__ float s_pose[];            // [P][6]
     __shared__ int s_tot[16 * U], s_base;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, ticket = look_ticket(look);
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, ticket = ordered ? look_ticket(look) : (int)blockIdx.x;
     const long long n0 = (long long)ticket * (1024 * U);
     float y[U][3];
     int p[U];
@@ -1133,10 +1133,10 @@ __global__ __launch_bounds__(1024) void k_voxel_list(GridP G, InitP I, long long
     __syncthreads();
     if (wid == 0) {
         const int mine = scan_totals(s_tot, 16 * U, lane);
-        const int before = look_back(look, ticket, mine, lane);
+        const int before = ordered ? look_back(look, ticket, mine, lane) : 0;
         if (lane == 0) {
-            s_base = before;
-            if (ticket == (int)gridDim.x - 1) cursor[CUR_LIST] = (unsigned)(before + mine);
+            s_base = ordered ? before : (int)atomicAdd(cursor + CUR_LIST, (unsigned)mine);
+            if (ordered && ticket == (int)gridDim.x - 1) cursor[CUR_LIST] = (unsigned)(before + mine);
         }
     }
     __syncthreads();
