@@ -1069,11 +1069,14 @@ static fs_status dedupe_impl(fs_ctx *ctx, const char *who, int *sums, const floa
         FS_CHECK_PTR(ctx, d_keep, false);
         if (sums == ctx->dd_sums && launch_dedupe_one(ctx, N, K, min_dist * min_dist, d_xc, d_conv, d_keep, d_offsets, d_roots, d_lane, cap))
             return launch_status(ctx, who);
+        const bool four = K <= DD_FEW && N >= 1 << 19;         // one point per thread / four, whole call, us: 66 k points 7.5 / 8.1, 262 k 9.1 / 9.7, 524 k 12.9 / 12.6, 1 M 24.9 / 20.5, 4.2 M 78.5 / 73.1
         int tile = K <= DD_FEW ? 256 : 32;          // what a block takes in one pass
         while ((N + tile - 1) / tile > DD_TILES) tile *= 2;
         const int tiles = grid1d(N, tile);
-#define FS_LAUNCH_DEDUPE(KERNEL) KERNEL<<<tiles, 256, 0, st>>>(N, K, min_dist * min_dist, d_xc, d_conv, d_keep, d_offsets, tile, sums)
-        if (K <= DD_FEW) FS_LAUNCH_DEDUPE(k_dedupe_few);
+        const int threads = four ? std::min(256, tile / 4) : 256;
+#define FS_LAUNCH_DEDUPE(KERNEL) KERNEL<<<tiles, threads, 0, st>>>(N, K, min_dist * min_dist, d_xc, d_conv, d_keep, d_offsets, tile, sums)
+        if (four) FS_LAUNCH_DEDUPE(k_dedupe_few<4>);
+        else if (K <= DD_FEW) FS_LAUNCH_DEDUPE(k_dedupe_few<1>);
         else if (K <= 8) FS_LAUNCH_DEDUPE(k_dedupe<1>);
         else if (K <= 16) FS_LAUNCH_DEDUPE(k_dedupe<2>);
         else if (K <= 24) FS_LAUNCH_DEDUPE(k_dedupe<3>);
