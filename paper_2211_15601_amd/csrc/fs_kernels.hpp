@@ -3182,6 +3182,18 @@ __device__ __forceinline__ void grad_accumulate(const GridP &G, const float4 r0,
     }
 }
 
+// the 12 sums of a piece for one corner
+__device__ __forceinline__ void add_sums(const float4 (&v)[3], float (&acc)[12])
+{
+#pragma unroll
+    for (int h = 0; h < 3; ++h) {
+        acc[4 * h] += v[h].x;
+        acc[4 * h + 1] += v[h].y;
+        acc[4 * h + 2] += v[h].z;
+        acc[4 * h + 3] += v[h].w;
+    }
+}
+
 __device__ __forceinline__ int adjacent_cell(const GridP &G, int ncell, int p, int ix, int iy, int iz, int cn)
 {
     const int cx = ix - (cn & 1), cy = iy - ((cn >> 1) & 1), cz = iz - ((cn >> 2) & 1);
@@ -3355,6 +3367,9 @@ __device__ __forceinline__ float lane_from(float v)
 
 // G_T of every node from the pieces of its 8 adjacent cells, for crowded cells (k_grad_nodes_z takes the sparse ones): 8 threads
 // share a node, one per adjacent cell, and add what they have in a butterfly.
+// Bound: vector instructions (0.75 of the busy cycles), then the chain of the most crowded cell (at the box's corners, 12 k records of 1.3 M), whose whole ranges
+// are therefore added four at a time (65 k points 15.7 -> 14.0 us, with the butterfly on DPP and one clamp per fraction; four sums or several records
+// asked for at a time wherever there is more than one: 18 to 19).
 // Measured on the multi-pose batch (7.7 M records over 4.2 M nodes, one thread per node: 450 us) and not adopted: a block per brick
 // of 4 x 4 x 16 nodes that first copies the records of the cells around it into LDS and gathers from there, same loops:
 // 450 .. 518 us (fewer resident threads, three barriers per block); the same with one loop over all records of a node's
@@ -3377,25 +3392,28 @@ __global__ __launch_bounds__(256) void k_grad_nodes_p(GridP G, int ncell, const 
     for (int e = 0; e < 12; ++e) acc[e] = 0.0f;
     const int c = adjacent_cell(G, ncell, p, ix, iy, iz, cn);
     const int a = c < 0 ? 0 : offset[place(c)], b = c < 0 ? 0 : offset[place(c) + 1];
-    if (a < b) {
-        for (int j = a / PIECE_R; j <= (b - 1) / PIECE_R; ++j) {
-            const int ps = max(a, j * PIECE_R), pe = min(b, (j + 1) * PIECE_R);
-            if (pe - ps >= PIECE_MIN) {
-                const float4 *q = reinterpret_cast<const float4 *>(rec + (long long)ps * GREC + cn * 12);
+    for (int ps = a, pe; ps < b; ps = pe) {
+        const float4 *q = reinterpret_cast<const float4 *>(rec + (long long)ps * GREC + cn * 12);
+        if (ps % PIECE_R == 0 && b - ps >= 4 * PIECE_R) {          // four whole ranges: their sums on the way together
+            float4 v[4][3];
 #pragma unroll
-                for (int h = 0; h < 3; ++h) {
-                    const float4 u = q[h];
-                    acc[4 * h] += u.x;
-                    acc[4 * h + 1] += u.y;
-                    acc[4 * h + 2] += u.z;
-                    acc[4 * h + 3] += u.w;
-                }
-            } else {
-                for (int s = ps; s < pe; ++s) {
-                    const float4 *r = reinterpret_cast<const float4 *>(rec + (long long)s * GREC);
-                    grad_accumulate(G, r[0], r[1], ix - (cn & 1), iy - ((cn >> 1) & 1), iz - ((cn >> 2) & 1), cn & 1, (cn >> 1) & 1,
-                                    (cn >> 2) & 1, acc);
-                }
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int h = 0; h < 3; ++h) v[u][h] = q[u * (PIECE_R * GREC / 4) + h];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add_sums(v[u], acc);
+            pe = ps + 4 * PIECE_R;
+            continue;
+        }
+        pe = min(b, (ps / PIECE_R + 1) * PIECE_R);
+        if (pe - ps >= PIECE_MIN) {
+            const float4 v[3] = {q[0], q[1], q[2]};
+            add_sums(v, acc);
+        } else {
+            for (int s = ps; s < pe; ++s) {
+                const float4 *r = reinterpret_cast<const float4 *>(rec + (long long)s * GREC);
+                grad_accumulate(G, r[0], r[1], ix - (cn & 1), iy - ((cn >> 1) & 1), iz - ((cn >> 2) & 1), cn & 1, (cn >> 1) & 1,
+                                (cn >> 2) & 1, acc);
             }
         }
     }

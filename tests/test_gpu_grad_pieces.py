@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 LENGTHS = {
     "short": [11, 12, 13, 1, 15, 16, 17, 2, 27, 28, 29, 31, 32, 33],
     "ranges": [244, 12, 256, 255, 257, 11, 500, 513],
+    "whole ranges": [1024 + 256, 3, 4096, 2047, 1023],
     "one": [12], "one short": [11], "many of twelve": [12] * 64, "end at a range": [128, 128],
 }
 
