@@ -3524,7 +3524,7 @@ __global__ __launch_bounds__(256) void k_grad_nodes_z(GridP G, int ncell, const 
         // four records per round whose loads travel together, so that a wave runs as long as the longest sum of four lists
         // among its lanes.  Bound: vector ALU (2700 instructions per wave with the 4 lists side by side, a record of
         // each per round, as long as the longest list of any lane: 282 us on 8 poses of 128x128x32 nodes with 7.7 M
-        // records, now 257).  The other cells follow one by one.
+        // records, now 226).  The other cells follow one by one.
         int a[4], from[4], upto[4];       // upto[ab]: records of the cells up to and with ab; record t of the walk is from[ab] + t
         bool small[4];
         int walk = 0;
@@ -3547,8 +3547,10 @@ __global__ __launch_bounds__(256) void k_grad_nodes_z(GridP G, int ncell, const 
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int t = j + u;
-                const int f = t >= upto[2] ? from[3] : (t >= upto[1] ? from[2] : (t >= upto[0] ? from[1] : from[0]));
-                r0[u] = r1[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                int f = from[0];
+                f = t >= upto[0] ? from[1] : f;
+                f = t >= upto[1] ? from[2] : f;
+                f = t >= upto[2] ? from[3] : f;
                 if (t < walk) {
                     const float4 *r = reinterpret_cast<const float4 *>(rec + (long long)(f + t) * GREC);
                     r0[u] = r[0];
