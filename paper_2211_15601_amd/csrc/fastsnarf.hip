@@ -221,7 +221,7 @@ bool look_create(fs_ctx *c)
     long long blocks = 0;
     if (c->prm.init_mode == FS_INIT_VOXEL) {
         const long long N = ((1ll << 31) - 1) / c->C.ck;
-        blocks = std::max({blocks, (long long)scan_blocks(c->G.P * c->C.ncell), (long long)scan_blocks((int)SORT_MAX_COUNTS),
+        blocks = std::max({blocks, (long long)scan_blocks((int)SORT_MAX_COUNTS),
                            (long long)grid1d(N, 1024 * list_per_thread(N)), 1ll << 9});
     }
     c->look_words = (size_t)blocks + LOOK_HEAD;
@@ -249,17 +249,17 @@ fs_status look_ready(fs_ctx *c, const char *what)
     return launch_status(c, what);
 }
 
-// exclusive scan of src[0..n) into a[0..n) (src == nullptr: in place) on the context's stream, a[n] = total; returns what
+// exclusive scan of a[0..n) in place on the context's stream, a[n] = total; returns what
 // the kernel after it has to clear of the look-back words
-int scan_exclusive(fs_ctx *c, int n, int *a, const int *src)
+int scan_exclusive(fs_ctx *c, int n, int *a)
 {
     if (n <= 0) {
         k_fill_zero_i32<<<1, 64, 0, c->stream>>>(1, a);
         return 0;
     }
     const int m = scan_blocks(n);
-    if (scan_per_thread(n) == 4) k_scan<4><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->look);
-    else k_scan<16><<<m, 1024, 0, c->stream>>>(n, src ? src : a, a, c->look);
+    if (scan_per_thread(n) == 4) k_scan<4><<<m, 1024, 0, c->stream>>>(n, a, a, c->look);
+    else k_scan<16><<<m, 1024, 0, c->stream>>>(n, a, a, c->look);
     return m;
 }
 
@@ -820,7 +820,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
         if (sorted) {
             k_voxel_count<<<grid1d(N, 256), 256, boxes, st>>>(ctx->G, I, N, d_xq, d_pose, ctx->vcnt, ctx->vgcell);
             k_sort_hist<<<(unsigned)sblk, 1024, nb * sizeof(int), st>>>(N, ctx->C.cz, nb, ctx->vgcell, ctx->vcnt, ctx->vhist);
-            const int scanned = scan_exclusive(ctx, (int)((long long)nb * sblk), ctx->vhist, nullptr);
+            const int scanned = scan_exclusive(ctx, (int)((long long)nb * sblk), ctx->vhist);
             k_sort_scatter<<<(unsigned)sblk, 1024, nb * sizeof(int), st>>>(N, ctx->C.cz, nb, ctx->vgcell, ctx->vcnt, ctx->vhist, ctx->vlist, ctx->look, scanned);
             list_len = ctx->vhist + (long long)nb * sblk;
             S.xcd_ranges = (!lds && ctx->xcd_ranges) ? 1 : 0;
