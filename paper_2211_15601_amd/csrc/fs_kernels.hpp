@@ -2059,18 +2059,18 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
 // pairs 64 at a time, every SIMD lane busy: initial state, first evaluation of the field, first step; pairs
 // that end there (invalid state, converged or diverged at x0) it answers itself.  The other waves (the
 // consumers) iterate: idle lanes take prepared states {x', x, g, J~, pair} from the block's queue in LDS, and the loop
-// holds nothing but the Broyden step.  Neither role ever holds the other's registers.
+// holds nothing but the Broyden step.  Neither role ever holds the other's vector registers.
 // Start and end cost what the middle does not show, so every wave works from the first to the last: a consumer prepares its first 64 pairs itself
 // (its segment of the queue takes them from the one loop to the other), and the producer iterates when there is nothing left to prepare.
 // The queue is one for the block, so that what is left when the producer ends goes to whoever has room.  (A queue of 128 per consumer, all filled by the
 // producer: on 65 k points the consumers of a block had their first pairs after 5, 14 and 28 us, and the last of 277 us ended 75 after the producer.
 // Kernel us, that / now: 0.48 M pairs of bone states 120 / 112, 0.23 M 86 / 71, 1.6 M 277 / 277, 4.8 M 718 / 684, 0.4 M candidates of 1 M ray samples 72 / 59,
 // 40 k of 0.1 M 49 / 29, 7.9 M of eight poses 1236 / 1210.)
-// Entries are numbered as they come; one has its place modulo the queue's size.  tail: entries written (by the producer); claim: taken (by
-// exchanges among the consumers); freed: of each segment of 64, how many have been read since the start, the consumers' own pairs being the
-// first round.  The producer writes into a segment when all of the round before has been read.
+// Entries are numbered as they come; one has its place modulo the queue's size.  tail: twice the entries written (by the producer), and one more when
+// nothing will be added; claim: entries taken (by exchanges among the waves that iterate); freed: of each segment of 64, how many have been read since the
+// start, the consumers' own pairs being the first round.  The producer writes into a segment when all of the round before has been read.
 // Every wait ends: a producer that has polled S.spin_limit times in vain for room raises
-// *give_up (host-visible) and prepares no more; it raises s_done in any case, and the waves, which wait for
+// *give_up (host-visible) and prepares no more; it marks the tail as final in any case, and the waves, which wait for
 // nothing else, finish what the queue holds and leave.
 // ------------------------------------------------------------------------------------------------
 constexpr int WS_SEGMENTS = 3, WS_RING = 64 * WS_SEGMENTS;     // one segment per consumer (16 KiB)
@@ -2304,13 +2304,13 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                                                const int *__restrict__ state)
 {
     __shared__ float s_ring[ST_FIELDS][WS_RING];
-    __shared__ int s_tail, s_claim, s_freed[WS_SEGMENTS], s_done;
+    __shared__ int s_tail, s_claim, s_freed[WS_SEGMENTS];
     constexpr int OUT_PEND = SKIP ? 64 : 128;        // 64: 50 KiB of LDS, so that a CU holds three blocks
     __shared__ OutQ<OUT_PEND, WITH_J> s_out[NCONS + 1];      // records on their way out, per wave
     if (threadIdx.x < WS_SEGMENTS) s_freed[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
-        s_tail = s_claim = WS_RING;
-        s_done = 0;
+        s_claim = WS_RING;
+        s_tail = 2 * WS_RING;
     }
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x == 0) cursor[CUR_TOTAL] = 0u;          // for place_cells, later in this call
@@ -2324,6 +2324,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
 
     const bool producer = wib == NCONS;
     static_assert(NCONS == WS_SEGMENTS, "a consumer's own pairs fill a segment of the queue");
+    int tail = producer ? WS_RING : 64 * wib;        // entries written
     int nown = 0;                   // of a consumer: pairs it has put into its segment itself
     // SKIP needs a grid of entries below SKIP_MAX (k_precompute says if this one is not)
     const bool may_skip = SKIP && may_skip_corners(state);
@@ -2358,7 +2359,6 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
             c1 = min(r1, next + S.chunk);
         }
         int alive = 0;                    // ranges home, home + 1, ... home + alive - 1 are known to be used up
-        int tail = producer ? WS_RING : 64 * wib;
         bool lost = false;
         while (!lost) {
             if (next >= c1) {
@@ -2492,6 +2492,13 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                     __builtin_amdgcn_s_sleep(8);
                 }
                 if (lost) break;
+                // Where pairs end after few steps the others wait for the producer: its wave goes first on its SIMD while less than a batch is left to claim
+                // (not in the first round, while the others still prepare pairs themselves).  All equal / so, whole calls, us: 0.8 M points of 5 states 472 / 414,
+                // 0.2 M of 8 196 / 182, of 24 577 / 576; 1 M ray samples 87 / 87.  From the first batch on: 0.3 M points of scans with candidates 60 / 63.
+                if (lap >= 2) {
+                    if (tail - __builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < 64) __builtin_amdgcn_s_setprio(3);
+                    else __builtin_amdgcn_s_setprio(0);
+                }
                 if (keep) {
                     const int at = (int)((unsigned)(tail + __popcll(km & ((1ull << lane) - 1ull))) % WS_RING);
 #pragma unroll
@@ -2509,7 +2516,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 __builtin_amdgcn_wave_barrier();
                 tail += nkeep;
-                if (producer && lane == 0) lds_store_release(&s_tail, tail);
+                if (producer && lane == 0) lds_store_release(&s_tail, 2 * tail);
             }
             out_park(G, want_out, nx, nJ, out_flags, out_place, pair, outq, npend, lane, cell_count, ncell, rec);
             if (!producer) {
@@ -2518,9 +2525,10 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
             }
         }
         if (producer) {
+            __builtin_amdgcn_s_setprio(0);
             if (lost && lane == 0) *give_up = 1;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            if (lane == 0) lds_store_release(&s_done, 1);
+            if (lane == 0) lds_store_release(&s_tail, 2 * tail + 1);
         }
     }
 
@@ -2552,18 +2560,19 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
     bool head = !producer;           // the wave's own pairs come first
     do {                             // (test at the end: see k_solve_once)
         if (nidle >= S.refill_min && !fin) {
-            // s_done is read before the tail: the producer raises it last
-            const int d = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_done));
-            const int tail = __builtin_amdgcn_readfirstlane(lds_load_acquire(&s_tail));
-            int at = 64 * wib, got = nown;
+            int at = 64 * wib, got = nown, tail = 0, done = 0;
             if (!head && lane == 0) {  // entries [at, at + got) are this wave's; every failed exchange is another wave's success
                 at = __hip_atomic_load(&s_claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                const int t = lds_load_acquire(&s_tail);
+                tail = t >> 1;
+                done = t & 1;
                 do got = max(min(nidle, tail - at), 0);
                 while (got > 0 && !__hip_atomic_compare_exchange_strong(&s_claim, &at, at + got, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+                done = done && at + got >= tail;
             }
             at = __builtin_amdgcn_readfirstlane(at);
             got = __builtin_amdgcn_readfirstlane(got);
-            fin = d && !head && at + got >= tail;
+            fin = __builtin_amdgcn_readfirstlane(done) != 0;
             if (got > 0 || head) {
                 const unsigned long long idle = __ballot(!active);
                 const int rank = __popcll(idle & ((1ull << lane) - 1ull));
@@ -2597,7 +2606,7 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
             }
         }
         // a consumer waits for nothing but its own block's producer, whose waits are all bounded and which raises
-        // s_done on every way out: this loop ends when the producer has
+        // marks the tail as final on every way out: this loop ends when the producer has
         if (!__any(active) && !fin) __builtin_amdgcn_s_sleep(8);
         bool want_out = false;
         int out_place = -1, out_flags = 0;

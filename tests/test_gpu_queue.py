@@ -37,6 +37,22 @@ def test_batches_around_what_the_consumers_prepare(gpu_lib, pairs):
             assert ((slot.cpu().numpy() >= 0) == (ref[1] == 1)).all()
 
 
+@pytest.mark.parametrize("laps", [2, 4])
+def test_queue_used_several_times_over(gpu_lib, laps):
+    # a round of the queue is 192 entries per block; few steps per pair, so that the producers' waves change their priority as the queue runs empty
+    n = (OWN + laps * 192 * BLOCKS) // NB
+    s = wl.random_affine_scene(414, dims=DIMS, n_bones=NB, n_points=n)
+    w = wl.Workload("laps", s["dims"], NB, 1, s["lo"], s["hi"], s["W"], s["B"], s["x"], s["pose"], s["x"], 1e-5, 10.0, 50, wl.INIT_BONE, NB, (6, 5, 4, 3))
+    run = gu.GpuRun(w)
+    T = run.precompute()
+    ref = gu.oracle_solve(w, T, *gu.oracle_inits(w, T))
+    for kw in (dict(want_J=False), dict(slots=True)):
+        out = run.solve(fused=True, **kw)
+        for name, a, b in zip(("roots", "masks", "J", "iterations"), out, ref):
+            if a is not None:
+                np.testing.assert_array_equal(a.view(np.uint8), b.view(np.uint8), err_msg=f"{name} {sorted(kw)}")
+
+
 @pytest.mark.parametrize("some", [0, 1, 700, 33000])
 def test_lists_that_leave_waves_without_a_pair(gpu_lib, some):
     corr, n = (24, 24, 12, 3), 294912 // 3 + 1                      # just above the batches that need no list
