@@ -2558,6 +2558,12 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
     bool fin = false;                // wave-uniform: the producer has left and the queue is empty
     int nidle = 64;
     bool head = !producer;           // the wave's own pairs come first
+    // Given states are read, not computed: where they are candidates, some four in ten end at once and the others soon, and waves that share out every
+    // part of a batch as it comes all run with few lanes.  On large batches a wave therefore claims all that it has lanes for, or nothing yet.
+    // Parts / whole, whole calls, us: candidates of 1 M points of scans 382 / 350, 0.5 M in four poses 196 / 184, 2 M ray samples 560 / 554; 0.11 M, 640 pairs per
+    // block, 59 / 61; 24 states of 65 k points 307 either way.  (A wave that waits leaves the rest to the others, and the queue is never short of it: the
+    // producer waits for room only where more than 64 entries are unclaimed.)
+    const bool whole = !FUSED && total >= 2048ll * gridDim.x;
     do {                             // (test at the end: see k_solve_once)
         if (nidle >= S.refill_min && !fin) {
             int at = 64 * wib, got = nown, tail = 0, done = 0;
@@ -2566,8 +2572,10 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
                 const int t = lds_load_acquire(&s_tail);
                 tail = t >> 1;
                 done = t & 1;
-                do got = max(min(nidle, tail - at), 0);
-                while (got > 0 && !__hip_atomic_compare_exchange_strong(&s_claim, &at, at + got, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+                do {
+                    got = max(min(nidle, tail - at), 0);
+                    if (whole && !done && got < nidle) got = 0;
+                } while (got > 0 && !__hip_atomic_compare_exchange_strong(&s_claim, &at, at + got, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
                 done = done && at + got >= tail;
             }
             at = __builtin_amdgcn_readfirstlane(at);

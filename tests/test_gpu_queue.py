@@ -77,3 +77,27 @@ def test_lists_that_leave_waves_without_a_pair(gpu_lib, some):
         for name, a, b in zip(("roots", "masks", "J", "iterations"), out, ref):
             if a is not None:
                 np.testing.assert_array_equal(a.view(np.uint8), b.view(np.uint8), err_msg=f"{name} {sorted(kw)}")
+
+
+@pytest.mark.parametrize("init,n", [(wl.INIT_VOXEL, 349525), (wl.INIT_VOXEL, 349526), (wl.INIT_BONE, 196607), (wl.INIT_BONE, 196608)])
+def test_given_states_claimed_whole(gpu_lib, init, n):
+    # around 2048 pairs per block (two blocks per compute unit with candidates, else three), where waves begin to claim all that they have lanes for
+    # or nothing: the bits of the solve that makes the same states itself, and whose waves take what there is
+    K = NB if init == wl.INIT_BONE else 3
+    s = wl.random_affine_scene(413, dims=DIMS, n_bones=NB, n_points=n)
+    w = wl.Workload("given", s["dims"], NB, 1, s["lo"], s["hi"], s["W"], s["B"], s["x"], s["pose"], s["x"], 1e-5, 10.0, 50, init, K, (6, 5, 4, 3))
+    run = gu.GpuRun(w)
+    run.precompute()
+    new = lambda *shape, dtype=torch.float32: torch.full(shape, 99, dtype=dtype, device=gu.DEV)
+    outs = []
+    for given in (False, True):
+        x0, J0, v0 = new(K, 3, n), new(K, 9, n), new(K, n, dtype=torch.uint8)
+        xc, J, cv, it = new(K, 3, n), new(K, 9, n), new(K, n, dtype=torch.uint8), new(K, n, dtype=torch.uint8)
+        if given:
+            run.ctx.init(run.xq, None, n, x0, J0, v0)
+        run.ctx.solve(run.xq, None, n, K, *((x0, J0, v0) if given else (None, None, None)), xc, cv, J, it)
+        torch.cuda.synchronize()
+        outs.append((xc, cv, J, it))
+    for name, a, b in zip(("roots", "masks", "J", "iterations"), *outs):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+    assert outs[0][1].float().mean() > 0.2
