@@ -724,8 +724,8 @@ __device__ __forceinline__ u64 wave_min(u64 v)
 // One wave per cell.  Candidate j is the sample with the smallest (distance^2 of its image to the
 // cell centre, node index) among those farther than r_sep (canonical distance) from candidates
 // 0..j-1: the same set, in the same order, as visiting the samples by increasing key and accepting
-// greedily.  Of cells of up to SELECT_MAX nodes the samples' keys are held in registers: made once, and a sample that is too close to a
-// candidate is out for good.  Larger cells walk their chunks once per candidate.
+// greedily.  The keys of a cell's first SELECT_MAX samples are held in registers: made once, and a sample that is too close to a
+// candidate is out for good.  Those behind them are read once per candidate.
 // Bound: latency (chunks -> samples) with few cells, instruction issue with many, so the places of the samples are written into LDS chunk by chunk
 // (compared in registers with where each chunk starts: 95 us for 65,536 cells, now 79), empty cells end at once, and the wave's minimum runs on DPP
 // moves (with lane shuffles through the LDS 12 us more).  16 keys per lane instead of 8: 10 instead of 6.9 us for 8192 cells.
@@ -828,21 +828,53 @@ __global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const flo
                 }
         }
     } else {
+        // Crowded cell: the first SELECT_MAX samples as above, those behind them, the chunks from number `from` on and of that one what lies behind `skip`, once per
+        // candidate.  Bound: latency of the chain of chunks and samples.  (fs_precompute on 64x64x16 nodes, us, with everything read once per candidate, a sample per
+        // lane at a time: 4x4x2 cells of 8 candidates 536, now 298; 16x16x4 cells 73, now 44; eight poses of 128x128x32 nodes, 8x8x8 cells of 3 467, now 324.)
+        int from = 0, skip = 0;
+        n = 0;
+        walk([&](int place, int len) {
+            skip = min(len, SELECT_MAX - n);
+            for (int i = lane; i < skip; i += WAVE) s_from[wib][n + i] = place + i;
+            n += skip;
+            if (skip < len) return false;
+            ++from;
+            return true;
+        });
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        u64 key[SELECT_REGS];
+#pragma unroll
+        for (int r = 0; r < SELECT_REGS; ++r) key[r] = key_of(sample[s_from[wib][r * 64 + lane]]);
         for (int j = 0; j < C.ck; ++j) {
-            u64 best = ~0ull;
+            u64 best = key[0];
+#pragma unroll
+            for (int r = 1; r < SELECT_REGS; ++r)
+                if (key[r] < best) best = key[r];
+            int seen = 0;
             walk([&](int place, int len) {
-                for (int s = lane; s < len; s += WAVE) {
-                    const float4 q = sample[place + s];
-                    float x[3];
-                    node_pos(G, (unsigned)__float_as_int(q.w), x);
-                    bool far = true;
-                    for (int a = 0; a < na; ++a) {
-                        const float4 ac = s_acc[wib][a];
-                        const float acc[3] = {ac.x, ac.y, ac.z};
-                        if (!apart(x, acc)) far = false;
+                const int first = seen < from ? len : (seen == from ? skip : 0);
+                ++seen;
+                for (int s0 = first + lane; s0 < len; s0 += 4 * WAVE) {        // four samples on their way together
+                    float4 q[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (s0 + u * WAVE < len) q[u] = sample[place + s0 + u * WAVE];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const u64 k = s0 + u * WAVE < len ? key_of(q[u]) : ~0ull;
+                        if (k < best) {
+                            float x[3];
+                            node_pos(G, (unsigned)k, x);
+                            bool far = true;
+                            for (int a = 0; a < na; ++a) {
+                                const float4 ac = s_acc[wib][a];
+                                const float acc[3] = {ac.x, ac.y, ac.z};
+                                if (!apart(x, acc)) far = false;
+                            }
+                            if (far) best = k;
+                        }
                     }
-                    const u64 k = key_of(q);
-                    if (far && k < best) best = k;
                 }
                 return true;
             });
@@ -855,6 +887,13 @@ __global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const flo
             __builtin_amdgcn_wave_barrier();
             ++na;
             if (lane == 0) out[j] = (int)(unsigned)best;
+#pragma unroll
+            for (int r = 0; r < SELECT_REGS; ++r)
+                if (key[r] != ~0ull) {
+                    float x[3];
+                    node_pos(G, (unsigned)key[r], x);
+                    if (!apart(x, xa)) key[r] = ~0ull;
+                }
         }
     }
     if (lane == 0) {

@@ -33,3 +33,12 @@ def test_candidates_equal_the_oracle(gpu_lib, dims, P, corr):
     np.testing.assert_array_equal(bbox.view(np.uint32).ravel(), obox.view(np.uint32).ravel())
     np.testing.assert_array_equal(cand.ravel(), ocand.ravel())
     assert (cand >= 0).any()
+
+
+@pytest.mark.parametrize("dims,P,corr", [
+    ((2, 2, 129), 1, (1, 1, 1, 8)),                                         # 516 nodes: four behind those that are kept
+    ((20, 20, 5), 2, (1, 1, 1, 8)), ((13, 11, 17), 1, (2, 2, 1, 8)),        # the limit inside a chunk that is not the first
+    ((24, 24, 24), 1, (2, 1, 1, 8)),                                        # most behind it, in the table and in the list
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_cells_that_do_not_fit_the_registers(gpu_lib, dims, P, corr):
+    test_candidates_equal_the_oracle(gpu_lib, dims, P, corr)
