@@ -71,7 +71,7 @@ struct fs_ctx {
     bool lds_big;      // the grid is larger than 60 KiB and fits the LDS of a CU as one block of 12 waves
     int sort_list;     // order the list of (point, candidate) pairs by place (large voxel-mode batches)
     int xcd_ranges;    // with an ordered list: one range of it, and one cursor, per XCD
-    int spin_limit;    // polls for room in its consumers' queues before the producer wave of a solve block gives up
+    int spin_limit;    // polls for room in the block's queue before the producer wave of a solve block gives up
     int pre_serial;    // number of the last fs_precompute (may_skip_corners)
     int *gave_up;      // pinned host word, mapped into the device: a wave that gave up sets it
     int *gave_up_dev;  // the device's address of it
@@ -249,17 +249,13 @@ fs_status look_ready(fs_ctx *c, const char *what)
     return launch_status(c, what);
 }
 
-// exclusive scan of a[0..n) in place on the context's stream, a[n] = total; returns what
+// exclusive scan of a[0..n), n > 0, in place on the context's stream, a[n] = total; returns what
 // the kernel after it has to clear of the look-back words
 int scan_exclusive(fs_ctx *c, int n, int *a)
 {
-    if (n <= 0) {
-        k_fill_zero_i32<<<1, 64, 0, c->stream>>>(1, a);
-        return 0;
-    }
     const int m = scan_blocks(n);
-    if (scan_per_thread(n) == 4) k_scan<4><<<m, 1024, 0, c->stream>>>(n, a, a, c->look);
-    else k_scan<16><<<m, 1024, 0, c->stream>>>(n, a, a, c->look);
+    if (scan_per_thread(n) == 4) k_scan<4><<<m, 1024, 0, c->stream>>>(n, a, c->look);
+    else k_scan<16><<<m, 1024, 0, c->stream>>>(n, a, c->look);
     return m;
 }
 
@@ -308,16 +304,18 @@ bool need_places(fs_ctx *c, int **p) { return *p || dev_alloc(p, (size_t)cell_wo
 // Kernels of the solve by the size of a batch (pairs = K * N; all three give the same bits).  What bounds a small batch is
 // max_iters times the latency of a step, which is the shorter the more lanes share a pair (16 lanes 0.35 us, 4 0.5, one 1.0 to 1.2);
 // what bounds a large one is instruction issue and the vector cache, where one lane per pair and refilled waves win.
-// Measured, solve and dedupe, us, k_solve_quad / k_solve_once / k_solve_ws, 24 states per point on a 64x64x16 grid: 36 k pairs 39 / 43; 50 k 45 / 44;
-// 72 k 54 / 50; 98 k 57 / 51; 120 k 65 / 53; 192 k 84 / 65; 228 k - / 85 / 99.  The lines are where
-// the chip is full: three quad waves per SIMD; all pairs of k_solve_once resident at once (3 waves per SIMD of 64).
+// Measured, us, k_solve_quad / k_solve_once / k_solve_ws (k_solve where the grid is in LDS).  Solve and dedupe, 24 states per point, 64x64x16 nodes: 24 k pairs 35 / 42 / 46; 48 k 40 / 42 /
+// 51; 72 k 48 / 49 / 59; 120 k 62 / 51 / 68; 156 k 72 / 61 / 75; 192 k 80 / 63 / 71; 228 k 89 / 83 / 75; 288 k 103 / 90 / 84; 128x128x32 nodes: 98 k 62 / 63 / 66; 192 k 94 / 86 / 77.  The lines
+// are where the chip is full: three quad waves per SIMD; all pairs of k_solve_once resident at once (3 waves per SIMD of 64).
 // With positions a wave takes several states of a point (pair_of), those of a point without a root all run to the last step, and
-// k_solve_once keeps them in single lanes for longer; a step of training, 64x64x16, quad / once: 50 k pairs 92 / 102, 96 k 113 / 117, 156 k 133 / 133,
-// 192 k 144 / 135.  On a grid in LDS a step in single lanes is shorter: 16x16x4, 50 k pairs 78 / 73.
+// k_solve_once keeps them in single lanes for longer; a step of training, 64x64x16: 48 k pairs 84 / 90 / 95, 98 k 102 / 104 / 109, 156 k 118 / 118 / 127,
+// 192 k 128 / 124 / 124, 228 k 140 / 143 / 132.  On a grid in LDS a step in single lanes is shorter: 16x16x4, 48 k pairs 66 / 70 / 97, 98 k 87 / 76 / 108, 192 k 114 / 89 / 121, 228 k
+// 128 / 120 / 128.
 // With voxel-based candidates the share of pairs that have one is not known here (rays 1/7, scans 6/10), k_solve_ws needs
-// its list of them first and most quads of a sparse batch end at once: rays, 72 k pairs 25 (quad) / 31 (once), 150 k 27 / 33, 285 k 40 / 37;
-// scans, 72 k 38 / 35, 105 k 46 / 38, 210 k 61 / 48.  The upper line there, 4.5 waves per SIMD of which 3 are resident, is a compromise, k_solve_once / k_solve_ws
-// on 64x64x16 nodes: rays, 300 k pairs 40 / 66, 600 k 54 / 73; scans, 300 k 63 / 68, 390 k 72 / 71, 600 k 99 / 82.
+// its list of them first and most quads of a sparse batch end at once.  Solve and dedupe, 64x64x16: rays, 74 k pairs 27 / 32 / 41, 150 k 29 / 34 / 43, 285 k 36 / 38 / 53, 390 k 42 / 40 / 56, 600 k
+// 54 / 48 / 61, 900 k 72 / 60 / 66; scans, 30 k 24 / 27 / 37, 74 k 31 / 27 / 42, 150 k 41 / 33 / 46, 285 k 56 / 47 / 50, 390 k 68 / 55 / 54, 600 k 92 / 75 / 59; 128x128x32: rays, 285 k 45 / 46 / 64, 600 k
+// 61 / 63 / 75; scans, 150 k 48 / 46 / 54, 285 k 68 / 68 / 60.  Both lines are compromises between the two: the upper one, 4.5 waves per SIMD of which 3 are resident, where scans begin to
+// lose more than rays gain.
 enum { SOLVE_QUAD, SOLVE_ONCE, SOLVE_LARGE };
 int solve_kind(const fs_ctx *c, long long pairs, bool candidates, bool positions, bool lds)
 {
@@ -651,9 +649,14 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
     const bool vx = !lds && voxel_list;
     const int wpb = lds_big ? FS_LDS_BIG_WAVES : (lds ? 4 : 1);       // waves of a block that draw chunks from the cursor
     const bool bone = ctx->prm.init_mode == FS_INIT_BONE;
-    // A third block per CU hides latency on a grid that the L2 of an XCD holds, and thrashes it on a larger one.  States per bone, 200 k points, two /
-    // three blocks, kernel us: 0.4 MB grid 577 / 548, 3.0 MB 602 / 584, 4.3 MB 682 / 684, 10 MB 760 / 792, 24 MB 935 / 1032.  Candidates without J~ are
-    // slower with three (whole call on 1 M ray samples 150 / 155); with J~ their queues of 128 records (69 KiB of LDS) leave room for two.
+    // A third block per CU hides latency, and misses the L2 more often.  fs_solve, us, two / three blocks:
+    //   states per bone, 24, 12 k / 40 k / 200 k points: 3 MB grid, 200 k 634 / 580, with positions 838 / 713;  4.5 MB 76 / 75, 165 / 160, 673 / 616, with positions 97 / 97, 199 / 181, 814 / 706;  10.6 MB 81 / 81, 175 / 174,
+    //   707 / 672, with positions 102 / 102, 206 / 191, 845 / 752;  13.5 MB 82 / 84, 182 / 183, 725 / 704;  21 MB 87 / 86, 192 / 197, 766 / 785;  24 MB 200 k 785 / 821;  7 MB in 4
+    //   poses 88 / 88, 190 / 191, 773 / 712;  25 MB in 8 97 / 100, 214 / 218, 835 / 797
+    //   candidates, 1 M points, roots only: 3 MB rays 87 / 90, scans 124 / 130;  7 MB 104 / 114, 173 / 181;  25 MB 132 / 137, 228 / 239;  with positions 3 MB 99 / 99, 166 / 156;  7 MB 117 / 125,
+    //   220 / 209;  25 MB 149 / 149, 284 / 282;  25 MB in 8 poses, 4.2 M points 1378 / 1427;  0.1 M of scans, 3 MB, 44 / 48, with positions 53 / 56
+    // Two is what fs_set_tuning promises for candidates, which gain in one form and lose in the others, and beyond 4 MiB, where three lost before the waves of a block shared one
+    // queue; with this kernel large batches lose from some 16 MB on only.
     const int auto_blocks = lds || (bone && grid_bytes <= L2_BYTES) ? 3 : 2;
     const int want_blocks = ctx->blocks_per_cu ? (lds ? std::max(ctx->blocks_per_cu, 3) : ctx->blocks_per_cu) : auto_blocks;
     const int occ = lds ? ctx->occ_blocks_per_cu : (vx ? ctx->occ_vx_blocks_per_cu : ctx->occ_ws_blocks_per_cu);

@@ -641,11 +641,11 @@ __device__ __forceinline__ int scan_totals(int *s_tot, int n, int lane)
     return run;
 }
 
-// Exclusive prefix sum of src[0..n) into out (may be src), out[n] = total; src and out 16-byte aligned.  PER (a multiple of 4) entries per
+// Exclusive prefix sum of a[0..n) in place, a[n] = total; a 16-byte aligned.  PER (a multiple of 4) entries per
 // thread, 1024 threads.  Bound: memory, and the launch.  (Tile sums and a second pass over the tiles, two launches: 21 us
 // on 4.2 M entries, 9 us on 65 k; now 13 and 5.)
 template <int PER>
-__global__ __launch_bounds__(1024) void k_scan(int n, const int *src, int *out, u64 *__restrict__ look)
+__global__ __launch_bounds__(1024) void k_scan(int n, int *__restrict__ a, u64 *__restrict__ look)
 {
     __shared__ int s_tot[16 * (PER / 4)], s_before;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -657,11 +657,11 @@ __global__ __launch_bounds__(1024) void k_scan(int n, const int *src, int *out, 
     for (int b = 0; b < PER / 4; ++b) {
         const long long i = base + b * 4096;
         e[b] = make_int4(0, 0, 0, 0);
-        if (i + 3 < n) e[b] = *reinterpret_cast<const int4 *>(src + i);
+        if (i + 3 < n) e[b] = *reinterpret_cast<const int4 *>(a + i);
         else if (i < n) {
-            e[b].x = src[i];
-            if (i + 1 < n) e[b].y = src[i + 1];
-            if (i + 2 < n) e[b].z = src[i + 2];
+            e[b].x = a[i];
+            if (i + 1 < n) e[b].y = a[i + 1];
+            if (i + 2 < n) e[b].z = a[i + 2];
         }
         sum[b] = e[b].x + e[b].y + e[b].z + e[b].w;
         int inc = sum[b];
@@ -679,7 +679,7 @@ __global__ __launch_bounds__(1024) void k_scan(int n, const int *src, int *out, 
         const int before = look_back(look, t, mine, lane);
         if (lane == 0) {
             s_before = before;
-            if (t == (int)gridDim.x - 1) out[n] = before + mine;
+            if (t == (int)gridDim.x - 1) a[n] = before + mine;
         }
     }
     __syncthreads();
@@ -691,11 +691,11 @@ __global__ __launch_bounds__(1024) void k_scan(int n, const int *src, int *out, 
         o.y = o.x + e[b].x;
         o.z = o.y + e[b].y;
         o.w = o.z + e[b].z;
-        if (i + 3 < n) *reinterpret_cast<int4 *>(out + i) = o;
+        if (i + 3 < n) *reinterpret_cast<int4 *>(a + i) = o;
         else if (i < n) {
-            out[i] = o.x;
-            if (i + 1 < n) out[i + 1] = o.y;
-            if (i + 2 < n) out[i + 2] = o.z;
+            a[i] = o.x;
+            if (i + 1 < n) a[i + 1] = o.y;
+            if (i + 2 < n) a[i + 2] = o.z;
         }
     }
 }
@@ -1118,10 +1118,10 @@ __device__ __forceinline__ int corr_cell(const InitP &I, const float *s_pose, in
 }
 
 // Voxel-based initial states leave most lanes without a candidate (a ray sample in empty space has none): the list of the
-// pairs that have one, {point n, (pose * ncell + correspondence cell) << 3 | k}, from which the solve draws.  The
-// list is in the order of the points: parts of it in the order in which blocks arrive would mix up to two million
+// pairs that have one, {point n, (pose * ncell + correspondence cell) << 3 | k}, from which the solve draws.  A block takes 1024 U consecutive points, whose
+// pairs follow each other.  ordered: so do the blocks' parts, in the order of the points; parts in the order in which blocks arrive would mix up to two million
 // points, i.e. several poses' grids (Broyden kernel on the 8-pose batch 1447 instead of 1330 us).  Where an XCD's L2 holds all grids that does not
-// matter (ordered = false): a block takes its part of the list with one atomic and waits for no other.  A block takes 1024 U consecutive points.
+// matter (ordered = false): a block takes its part of the list with one atomic and waits for no other.
 // Bound: the chain of tickets and memory (17 bytes read or written per point, 8 per pair).  (A counting pass, a scan of two launches,
 // an expanding pass and a clearing pass: 28 us on 1 M ray samples, 42 us on 2 M, 85 us on the 8-pose batch; now 13, 24 and 62.)
 template <int U>
@@ -2344,7 +2344,9 @@ __global__ __launch_bounds__(64 * (NCONS + 1), SKIP ? 3 : 2) void k_solve_ws(Gri
 {
     __shared__ float s_ring[ST_FIELDS][WS_RING];
     __shared__ int s_tail, s_claim, s_freed[WS_SEGMENTS];
-    constexpr int OUT_PEND = SKIP ? 64 : 128;        // 64: 50 KiB of LDS, so that a CU holds three blocks
+    // One state per bone: 64 and 128 take the same time (fs_solve with positions, us, 64 / 128: 20 k points 111 / 112, 65 k 257 / 254, 200 k 706 / 700; 24 MB 137 / 137, 324 / 321, 895 / 884), in 34
+    // instead of 52 KiB of LDS
+    constexpr int OUT_PEND = SKIP ? 64 : 128;
     __shared__ OutQ<OUT_PEND, WITH_J> s_out[NCONS + 1];      // records on their way out, per wave
     if (threadIdx.x < WS_SEGMENTS) s_freed[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
