@@ -39,8 +39,10 @@ BYTES_EVAL = 384     # ... = 8 x 48 bytes gathered per field evaluation
 PEAK_FP32_TFLOPS = 157.3            # published fp32 vector peak (needs packed fp32 instructions)
 PEAK_FP32_UNPACKED_TFLOPS = 78.6    # 256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2.4 GHz: one FMA per lane per clock
 PEAK_HBM_BPS = 8.0e12
-# pairs per CU up to which the kernels without queues run: (states per bone or given, voxel-based candidates looked up inside)
+# pairs per CU up to which the kernels without queues run: (states per bone or given, voxel-based candidates looked up inside); QUAD_MAX_SLOTS: with positions on a
+# grid that is not held in LDS
 QUAD_MAX, ONCE_MAX = (192, 320), (768, 1152)
+QUAD_MAX_SLOTS = (512, 320)
 LDS_GRID_MAX = 148 * 1024           # transform grids (all poses) up to this size are held in LDS by k_solve
 
 
@@ -87,7 +89,8 @@ class Case:
         self.grid_bytes = int(w.n_poses * w.dims[0] * w.dims[1] * w.dims[2] * 48)
         per_cu = N * K / torch.cuda.get_device_properties(dev).multi_processor_count
         kind = 1 if w.init_mode == 1 and not args.unfused else 0
-        self.kernel = ("k_solve_quad" if per_cu <= QUAD_MAX[kind] else "k_solve_once" if per_cu <= ONCE_MAX[kind]
+        quad_max = QUAD_MAX_SLOTS if self.slot is not None and self.grid_bytes > LDS_GRID_MAX else QUAD_MAX
+        self.kernel = ("k_solve_quad" if per_cu <= quad_max[kind] else "k_solve_once" if per_cu <= ONCE_MAX[kind]
                        else "k_solve" if self.grid_bytes <= LDS_GRID_MAX else "k_solve_ws")
 
     def step(self, marks=None):

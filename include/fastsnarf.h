@@ -73,8 +73,10 @@ typedef struct {
 } fs_params;
 
 /* Create a context on the current HIP device.  `hip_stream` is a hipStream_t (NULL = the
- * default stream).  Allocates the library-owned grids (n_poses * V * 48 bytes and smaller) and
- * one word of pinned host memory.  On failure *out is NULL. */
+ * default stream).  Allocates the library-owned grids and one word of pinned host memory.  Per pose: 48 bytes per
+ * node, 4 per grid cell; with FS_INIT_VOXEL 12 more per node, 24 per place in the bricks of 1024 nodes that cover the
+ * grid (one place per node where the axes are long, up to four where they are short or odd, more on grids of fewer
+ * than some 4000 nodes), 73 per correspondence cell and 68 per candidate.  On failure *out is NULL. */
 fs_status fs_create(const fs_grid_desc *desc, const fs_params *params, void *hip_stream, fs_ctx **out);
 
 /* Free everything the context owns.  Synchronises the stream first.  NULL is allowed. */
@@ -113,14 +115,15 @@ fs_status fs_set_tuning(fs_ctx *ctx, int32_t chunk, int32_t refill_min, int32_t 
  * step from 2.77 to 2.79 ms.)  Hence the default. */
 fs_status fs_set_list_order(fs_ctx *ctx, int32_t by_place);
 
-/* The waves of a block of the solve kernel hand work to each other through queues in LDS (one wave prepares
- * initial states, the others iterate).  The preparing wave's wait for room in those queues is bounded: when it has
- * polled `polls` times in vain (about 0.2 us each; default 2^22) it gives up and leaves, and the iterating waves,
- * which wait for nothing but that wave, finish what they hold and leave too, so the kernel always ends.
+/* The waves of a block of the solve kernel hand work to each other through a queue in LDS (one wave prepares
+ * initial states, the others iterate).  The preparing wave's wait for room in that queue is bounded: when it has
+ * polled `polls` times in vain (about 0.2 us each; default 2^22) it gives up and prepares no more, and all waves,
+ * which wait for nothing else, finish what the queue holds and leave, so the kernel always ends.
  * The call during which that happened returns FS_OK (nothing is synchronised), its results are incomplete,
  * and every later call on the context that uses the device returns FS_E_DEVICE: destroy the context.  No healthy run
  * comes near the default; the limit exists for tests of this path (polls = 0: the preparing wave gives up the first
- * time it finds every queue full).  polls >= 0. */
+ * time it finds no room, which may be at its first batch: the queue is opened by the iterating waves, as they take out the pairs they begin with).
+ * polls >= 0. */
 fs_status fs_set_spin_limit(fs_ctx *ctx, int32_t polls);
 
 /* Pre-compute linear blend skinning on the grid nodes, Eq. (13) / Sec. 3.1 "Pre-computing
@@ -155,8 +158,8 @@ fs_status fs_init(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_t
  *   Outputs may lie over inputs (a solve in place).
  *   d_slot [K][N] (may be NULL): bookkeeping for fs_grad.  The kernel counts its converged lanes per
  *   grid cell of x* as they finish and writes each lane's arrival position in its cell (-1 where
- *   conv == 0); the counts, and the solve's result records (roots, masks, J~), stay in the context
- *   until the next fs_solve.  The positions depend on the order in which lanes finish, so they differ
+ *   conv == 0); where each cell's lanes go in the backward's list, and the solve's result records (roots, masks, J~), stay in
+ *   the context until the next fs_solve.  The positions depend on the order in which lanes finish, so they differ
  *   from run to run; any run's set is a valid input of fs_grad.  With d_slot, d_Jinv may be NULL:
  *   J~ is then not written out at all and fs_grad takes it from the context. */
 fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_t N, int32_t K,
@@ -170,7 +173,7 @@ fs_status fs_solve(fs_ctx *ctx, const float *d_xq, const int32_t *d_pose, int64_
  *        d_W as given to fs_precompute
  *        d_slot: NULL, or the array the last fs_solve on this context wrote (same N, K, and d_xc,
  *        d_conv, d_pose as that call left them; FS_E_STATE otherwise where it can be told).  The
- *        pass that sorts the lanes by grid cell then reuses the solve's counts instead of counting
+ *        pass that sorts the lanes by grid cell then uses the places the solve made of its counts instead of counting
  *        again, and roots, masks and J~ are read from the result records that solve left in the
  *        context (one contiguous record per pair) rather than from d_xc / d_conv / d_Jinv; d_Jinv may
  *        then be NULL for FS_GRAD_BROYDEN_J too.  The sums are the same up to the order of the fp32

@@ -458,10 +458,10 @@ def test_single_point_and_tiny_grid(lib, lds_grid):
 
 
 def test_wave_that_gives_up_is_reported(lib):
-    # the producer wave's wait for room in its consumers' queues is bounded; with the bound at zero it leaves the first
-    # time it finds every queue full (made certain here: 48 batches per block, and consumers that take new pairs
-    # only once all their lanes are idle): the kernel still ends, that call returns FS_OK (nothing is
-    # synchronised), and every later call that uses the device reports it
+    # the producer wave's wait for room in its block's queue is bounded; with the bound at zero it prepares no more the first
+    # time it finds none.  Made certain here: behind the 64 pairs that every consumer prepares itself come 1856 per block, 29
+    # batches for a queue of three, and waves take new pairs only once all their lanes are idle, after up to 50 steps.
+    # The kernel still ends, that call returns FS_OK (nothing is synchronised), and every later call that uses the device reports it
     w = wl.make_config(2, n_points=65536, dims=(32, 32, 8))
     run = gu.GpuRun(w)
     ctx = run.ctx
