@@ -469,7 +469,7 @@ __global__ __launch_bounds__(1024) void k_corr_bbox(int nblk, const unsigned *__
 // head[gc]: number of chunks, head[cells + gc]: place of the list's first + 1, or 0 (both cleared by k_precompute); link[place]: {place + 1 of the next
 // or 0, length}.  Nothing is added up over blocks, so that no scan and no second pass over the nodes follows.  (Positions by an atomic per cell and
 // brick, a scan, a kernel that moves the nodes, and lists that are read once per candidate: 21 us with k_corr_select on 65 k nodes and two launches
-// more, 129 on the 8-pose grid; now 14 and 127.)
+// more, 129 on the 8-pose grid; now 14 and 113.)
 constexpr int CHUNKS = 8;
 // own_box: the block reduces the extents itself (up to EXTENT_OWN blocks of k_precompute; block 0 of a pose keeps the box).
 constexpr int EXTENT_OWN = 512;
@@ -727,7 +727,7 @@ __device__ __forceinline__ u64 wave_min(u64 v)
 // greedily.  The keys of a cell's first SELECT_MAX samples are held in registers: made once, and a sample that is too close to a
 // candidate is out for good.  Those behind them are read once per candidate.
 // Bound: latency (chunks -> samples) with few cells, instruction issue with many, so the places of the samples are written into LDS chunk by chunk
-// (compared in registers with where each chunk starts: 95 us for 65,536 cells, now 79), empty cells end at once, and the wave's minimum runs on DPP
+// (compared in registers with where each chunk starts: 95 us for 65,536 cells instead of 79; now, with crowded cells apart, 64), empty cells end at once, and the wave's minimum runs on DPP
 // moves (with lane shuffles through the LDS 12 us more).  16 keys per lane instead of 8: 10 instead of 6.9 us for 8192 cells.
 constexpr int SELECT_REGS = 8, SELECT_MAX = 64 * SELECT_REGS;
 __global__ __launch_bounds__(256) void k_corr_select(GridP G, CorrP C, const float *__restrict__ bbox, const int *__restrict__ head,
@@ -2103,8 +2103,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void k_solve(GridP G, Sol
 // (its segment of the queue takes them from the one loop to the other), and the producer iterates when there is nothing left to prepare.
 // The queue is one for the block, so that what is left when the producer ends goes to whoever has room.  (A queue of 128 per consumer, all filled by the
 // producer: on 65 k points the consumers of a block had their first pairs after 5, 14 and 28 us, and the last of 277 us ended 75 after the producer.
-// Kernel us, that / now: 0.48 M pairs of bone states 120 / 112, 0.23 M 86 / 71, 1.6 M 277 / 277, 4.8 M 718 / 684, 0.4 M candidates of 1 M ray samples 72 / 59,
-// 40 k of 0.1 M 49 / 29, 7.9 M of eight poses 1236 / 1210.)
+// Whole fs_solve, us, that, and quads for a wave's last pairs / now: 0.29 M pairs of bone states 91 / 73, 0.48 M 108 / 97, 1.6 M 233 / 217, 4.8 M 591 / 576, with positions 699 / 706; candidates of
+// 0.3 M ray samples 75 / 56, of 1 M 98 / 87, of 4.2 M points in eight poses 1118 / 1098, with positions 1317 / 1322; 8 candidates of 16x16x4 cells, 0.5 M points of scans 203 / 208, whose lanes have
+// fewer neighbours in a wave.  A longer queue, 256 to 384 entries: within 1 %.)
 // Entries are numbered as they come; one has its place modulo the queue's size.  tail: twice the entries written (by the producer), and one more when
 // nothing will be added; claim: entries taken (by exchanges among the waves that iterate); freed: of each segment of 64, how many have been read since the
 // start, the consumers' own pairs being the first round.  The producer writes into a segment when all of the round before has been read.
